@@ -865,6 +865,12 @@ void Engine::build_iteration_schedules(const std::vector<char>* active) {
   crow.cone_cap = kConeBlocksPerCheckRange;
   crow.build(row0, check_block(row0), active);
   ccol.build(col0, check_block(col0), active);
+  // 32 values per candidate and range of the multisection passes: row ranges
+  // with cone blocks are cut finer there than in the trial passes, so their
+  // number is crow's own
+  const size_t need_c = (size_t)std::max(ccol.nblk, 1) * 2 * 32 * 8, need_r = (size_t)std::max(crow.nblk, 1) * 2 * 32 * 8;
+  if (rec_probe_c.bytes < need_c) rec_probe_c.alloc(need_c);
+  if (rec_probe_r.bytes < need_r) rec_probe_r.alloc(need_r);
 }
 
 void Engine::build_schedule() {
@@ -895,8 +901,6 @@ void Engine::build_schedule() {
   rec_lam.alloc((size_t)nc * 3 * 8);
   rec_cand_c.alloc((size_t)vc * 16 * 8);
   rec_cand_r.alloc((size_t)vr * 14 * 8);
-  rec_probe_c.alloc((size_t)vc * 2 * 32 * 8);
-  rec_probe_r.alloc((size_t)vr * 2 * 32 * 8);
   rec_nc.alloc((size_t)vc * 3 * 8);
   rec_nr.alloc((size_t)vr * 3 * 8);
   rec_nm.alloc((size_t)std::max(trow.nblk, 1) * 8);
