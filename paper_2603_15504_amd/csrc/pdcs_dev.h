@@ -116,8 +116,8 @@ struct RowBlocks {
 // kBandSlotBits | slot, where slot < kBandSlots names the LDS accumulator it
 // adds into: slots below the band's row count are the rows themselves, higher
 // slots are extra accumulators of rows that repeat within one group of kWave
-// consecutive entries (no two entries of such a group share a slot), and the
-// last slot is the sink of the padding.  A workgroup runs kBandWaves waves, each
+// consecutive entries (no two entries of such a group share a slot), and slot
+// BandTiles::slots - 1 is the sink of the padding.  A workgroup runs kBandWaves waves, each
 // on one band-tile of the same window index.  In a batch every instance has its
 // own bands and windows; an instance with fewer windows than the batch's
 // largest count has empty tiles (zero partial sums) for the missing ones.
@@ -127,6 +127,7 @@ constexpr int kBandSlotBits = 14;
 constexpr int kBandColBits = 32 - kBandSlotBits;
 constexpr int kBandWaves = 2;
 constexpr int kBandUnroll = 16;
+constexpr int kTileRound = 256 * kBandWaves;  // band-tiles that give every CU one workgroup
 struct BandTiles {
   const int32_t* group;      // per workgroup slot group, per wave: band-tile or -1
   const int32_t* slot;       // launch slot -> group (-1: idle); slot s runs on XCD s % 8
@@ -144,6 +145,7 @@ struct BandTiles {
   const uint32_t* pk;        // packed entries
   int32_t nslot;             // launch slots (workgroups)
   int32_t P;                 // windows
+  int32_t slots;             // LDS accumulators per wave: the most a tile uses, and the sink
 };
 
 // Schedule of an elementwise pass: contiguous element ranges per workgroup.

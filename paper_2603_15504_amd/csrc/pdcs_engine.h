@@ -119,7 +119,7 @@ struct BandSchedule {
 // the CSR order (-1 for padding), so the scaled values can be filled in.
 struct BandSet {
   int P = 1;
-  int ntile = 0, nslot = 0;
+  int ntile = 0, nslot = 0, slots = 1;
   int64_t R = 0, nent = 0;
   DBuf group, slot, start, row0, nrows, used, tinst, col0, panel, run_start, run_row, run_ext, ext, pk, src;
   DBuf val32, val64, part32, part64, part64b;

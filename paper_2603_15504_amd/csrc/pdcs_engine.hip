@@ -466,7 +466,7 @@ bool build_band_tile(int64_t r0, int64_t r1, int p, int64_t c0, int64_t c1, int6
   }
   const size_t q = (size_t)kBandUnroll * kWave;
   while ((out.pk.size() - base) % q) {
-    out.pk.push_back((uint32_t)(kBandSlots - 1));
+    out.pk.push_back(0u);  // padding: gets the layout's sink slot once that is known
     out.src.push_back(-1);
   }
   for (int r = 0; r < nr; ++r) {
@@ -530,18 +530,27 @@ void BandSet::build(const std::vector<int64_t>& r0s, const std::vector<int64_t>&
       const double per_row = rows_b > 0 ? (double)nnz_b / (double)rows_b / (double)Pb[b] : 1.0;
       while (rbb > 256 && (double)rbb * per_row > (double)bs.entry_cap) rbb /= 2;
     }
-    // Band boundaries with about equal entries (the count of rbb-row bands,
-    // each at most rbb rows): with heavy-tailed row lengths, fixed heights
-    // leave some bands far heavier than others, and the heaviest sets the time.
+    // Band boundaries with about equal entries: with heavy-tailed row lengths,
+    // fixed heights leave some bands far heavier than others, and the heaviest
+    // sets the time.  A single problem whose tiles fill at least half of the
+    // chip gets whole rounds of it (kTileRound waves): with the count the
+    // heights alone give, the last round is nearly empty or CUs stay idle.  (G x
+    // and G^T y, both directions, FP32 / FP64: m = 2.5e5, n = 5e5, power-law
+    // rows, nnz = 1.35e7: 110 / 152 us before, 95 / 115 with 512 tiles;
+    // m = 2e5, n = 5e5, nnz = 5e6: 51 / 66 before, 49 / 64; twice as many
+    // tiles: 51 / 66, half as many: 70 / 85.)
     std::vector<std::pair<int64_t, int64_t>> cuts;
     {
       const int64_t ra = r0s[b], re = r0s[b + 1];
-      const int64_t nbands = (re - ra + rbb - 1) / rbb;
-      const double target = nbands > 0 ? (double)((int64_t)ptr[re] - ptr[ra]) / (double)nbands : 0.0;
+      const int64_t e0 = ptr[ra], ne = (int64_t)ptr[re] - e0;
+      int64_t nbands = (re - ra + rbb - 1) / rbb;
+      if (NB == 1 && nbands * P >= kTileRound / 2) nbands = (nbands * P + kTileRound - 1) / kTileRound * kTileRound / P;
+      nbands = std::min<int64_t>(nbands, re - ra);
       int64_t r = ra;
-      while (r < re) {
+      for (int64_t q = 1; r < re; ++q) {
+        const int64_t want = q < nbands ? e0 + (int64_t)((double)ne * (double)q / (double)nbands) : e0 + ne;
         int64_t e = r + 1;
-        while (e < re && e - r < rbb && (double)((int64_t)ptr[e + 1] - ptr[r]) <= target) ++e;
+        while (e < re && e - r < bs.rows && (q >= nbands || (int64_t)ptr[e + 1] <= want)) ++e;
         cuts.push_back({r, e});
         r = e;
       }
@@ -579,6 +588,12 @@ void BandSet::build(const std::vector<int64_t>& r0s, const std::vector<int64_t>&
   if (bb.pk.size() >= (size_t)INT32_MAX) throw Error(PDCS_ERR_SIZE, "band tiles exceed 2^31 entries");
   ntile = (int)bands.size() * P;
   nent = (int64_t)bb.pk.size();
+  slots = 1;
+  for (int32_t q : bb.used) slots = std::max(slots, q + 1);
+  const uint32_t sink = (uint32_t)(slots - 1);
+  for (int64_t e = 0; e < nent; ++e)
+    if (bb.src[e] < 0) bb.pk[e] = sink;
+  HIP_OK(band_raise_lds_limit());
   // workgroups: kBandWaves consecutive bands of one window; windows routed to
   // XCDs (slot s runs on XCD s % 8), window p to the XCDs x with x % P == p
   const int nb = (int)bands.size();
@@ -642,6 +657,7 @@ void BandSet::build(const std::vector<int64_t>& r0s, const std::vector<int64_t>&
   nslot = (int)sl.size();
   // every index the kernel reads, checked before anything reaches the device
   auto fail = [](const char* what) { throw Error(PDCS_ERR_STATE, std::string("band layout check: ") + what); };
+  if (slots > kBandSlots) fail("slots");
   if ((int)bb.start.size() != ntile + 1 || (int)bb.run_start.size() != ntile + 1 || (int)bb.used.size() != ntile)
     fail("tile tables");
   if (bb.run_ext.size() != bb.run_row.size() + 1 || bb.src.size() != bb.pk.size()) fail("run tables");
@@ -654,7 +670,7 @@ void BandSet::build(const std::vector<int64_t>& r0s, const std::vector<int64_t>&
     if (e1 < e0 || (e1 - e0) % ((int64_t)kBandUnroll * kWave)) fail("tile padding");
     if (bb.nrows[t] < 0 || bb.nrows[t] > kBandRows || (int64_t)bb.row0[t] + bb.nrows[t] > R) fail("tile rows");
     if (bb.panel[t] < 0 || bb.panel[t] >= P || bb.col0[t] < 0) fail("tile window");
-    if (bb.used[t] < bb.nrows[t] || bb.used[t] > kBandSlots - 1) fail("tile slots");
+    if (bb.used[t] < bb.nrows[t] || bb.used[t] > slots - 1) fail("tile slots");
     const int ti = bb.tinst[t];
     if (ti < 0 || ti >= NB || bb.row0[t] < r0s[ti] || (int64_t)bb.row0[t] + bb.nrows[t] > r0s[ti + 1]) fail("tile instance");
     if (bb.start[t + 1] > bb.start[t] && (bb.col0[t] < g0s[ti] || bb.col0[t] >= g0s[ti + 1])) fail("tile window instance");
@@ -662,7 +678,7 @@ void BandSet::build(const std::vector<int64_t>& r0s, const std::vector<int64_t>&
     for (int64_t e = e0; e < e1; ++e) {
       const uint32_t slot_e = bb.pk[e] & ((1u << kBandSlotBits) - 1u);
       const int64_t col = (int64_t)bb.col0[t] + (bb.pk[e] >> kBandSlotBits);
-      if ((slot_e >= (uint32_t)bb.used[t] && slot_e != (uint32_t)(kBandSlots - 1)) || col >= g0s[ti + 1]) fail("entry");
+      if ((slot_e >= (uint32_t)bb.used[t] && slot_e != sink) || col >= g0s[ti + 1]) fail("entry");
       if (bb.src[e] >= 0 && (bb.src[e] >= ptr[R] || idx[bb.src[e]] != col)) fail("entry source");
     }
     for (int32_t r = bb.run_start[t]; r < bb.run_start[t + 1]; ++r) {
@@ -696,6 +712,7 @@ void BandSet::build(const std::vector<int64_t>& r0s, const std::vector<int64_t>&
 void BandSet::reset() {
   P = 1;
   ntile = nslot = 0;
+  slots = 1;
   R = nent = 0;
   band_rows = 0;
   for (DBuf* d : {&group, &slot, &start, &row0, &nrows, &used, &tinst, &col0, &panel, &run_start, &run_row, &run_ext,
@@ -721,6 +738,7 @@ BandTiles BandSet::view() const {
   b.pk = pk.as<uint32_t>();
   b.nslot = nslot;
   b.P = P;
+  b.slots = slots;
   return b;
 }
 

@@ -585,6 +585,12 @@ __global__ __launch_bounds__(kBlock) void k_dual(RowBlocks rb, MatPtrs<TM> A, It
 // the result does not depend on scheduling.  The entry stream is software
 // pipelined: packed entries and values are loaded two iterations ahead and the
 // gathers one iteration ahead of the accumulation.  Output: part[panel * R + r].
+// What bounds it: the L2's rate of gathered sectors (m = 2e5, n = 5e5, nnz = 5e6:
+// 5e6 sectors of 64 B in 22 us, 14.5 TB/s; more waves per CU, with shorter bands
+// or bands shared by several waves, bring more distinct sectors and no time, and
+// staging x through LDS moves as many bytes through the same L2), and on the
+// largest problems the stream of entries.  The LDS of a launch holds what its
+// tallest tile uses, so that workgroups of short bands share a CU.
 // ---------------------------------------------------------------------------
 // Instances a check or evaluation pass works on.
 // kModeRay: the infeasibility rays of a check, FP64 vectors whatever the
@@ -691,7 +697,8 @@ __global__ __launch_bounds__(kBandWaves * kWave) void k_band_spmv(BandTiles bt, 
                                                                   const T* __restrict__ x, T* __restrict__ part,
                                                                   int64_t R, const Inst* __restrict__ inst,
                                                                   int prec, int need_acc) {
-  __shared__ T acc[kBandWaves * kBandSlots];
+  extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
+  T* acc = reinterpret_cast<T*>(dyn);
   const int g = bt.slot[blockIdx.x];
   if (g < 0) return;
   const int w = threadIdx.x / kWave;
@@ -701,7 +708,7 @@ __global__ __launch_bounds__(kBandWaves * kWave) void k_band_spmv(BandTiles bt, 
     const Inst& I = inst[bt.tinst[t]];
     if (I.status != kActive || I.precision != prec || (need_acc && I.last_acc == 0)) return;
   }
-  band_tile_product<T, T, T>(bt, t, acc + w * kBandSlots, val, x, part, R);
+  band_tile_product<T, T, T>(bt, t, acc + w * bt.slots, val, x, part, R);
 }
 
 // Check / evaluation products with FP64 values of vectors in the iterate
@@ -712,7 +719,8 @@ __global__ __launch_bounds__(kBandWaves * kWave) void k_band_cand(BandTiles bt, 
                                                                   double* __restrict__ part, int64_t R,
                                                                   const Inst* __restrict__ inst, int prec, int mode,
                                                                   int which) {
-  __shared__ double acc[kBandWaves * kBandSlots];
+  extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
+  double* acc = reinterpret_cast<double*>(dyn);
   const int g = bt.slot[blockIdx.x];
   if (g < 0) return;
   const int w = threadIdx.x / kWave;
@@ -721,7 +729,7 @@ __global__ __launch_bounds__(kBandWaves * kWave) void k_band_cand(BandTiles bt, 
   const Inst& I = inst[bt.tinst[t]];
   if (!mode_selects(I, mode) || !prec_selects(I, mode, prec)) return;
   if (which == 1 && mode == kModeCheck && I.use_avg == 0) return;
-  band_tile_product<double, TX, double>(bt, t, acc + w * kBandSlots, val, x, part, R);
+  band_tile_product<double, TX, double>(bt, t, acc + w * bt.slots, val, x, part, R);
 }
 
 // Window sums of the check / evaluation products, per instance.
@@ -2721,13 +2729,40 @@ const double* band_val<double>(const KernelCtx& k, int which) {
   return which ? k.bvalT64 : k.bval64;
 }
 
+// Launches of the band-tile kernels, with the LDS of the layout's accumulators.
+template <typename T>
+static void launch_band_spmv(const BandTiles& bt, const T* val, const T* x, T* part, int64_t R, const Inst* inst, int prec,
+                             int need_acc, hipStream_t s) {
+  if (bt.nslot > 0)
+    k_band_spmv<T><<<grid1(bt.nslot), kBandWaves * kWave, (size_t)kBandWaves * bt.slots * sizeof(T), s>>>(
+        bt, val, x, part, R, inst, prec, need_acc);
+}
+
+template <typename TX>
+static void launch_band_cand(const BandTiles& bt, const double* val, const TX* x, double* part, int64_t R,
+                             const Inst* inst, int prec, int mode, int which, hipStream_t s) {
+  if (bt.nslot > 0)
+    k_band_cand<TX><<<grid1(bt.nslot), kBandWaves * kWave, (size_t)kBandWaves * bt.slots * 8, s>>>(
+        bt, val, x, part, R, inst, prec, mode, which);
+}
+
+// Lets the band-tile kernels ask for up to kBandSlots FP64 accumulators per
+// wave on the current device.
+hipError_t band_raise_lds_limit() {
+  const void* const fns[] = {reinterpret_cast<const void*>(&k_band_spmv<float>), reinterpret_cast<const void*>(&k_band_spmv<double>),
+                             reinterpret_cast<const void*>(&k_band_cand<float>), reinterpret_cast<const void*>(&k_band_cand<double>)};
+  for (const void* f : fns) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kBandWaves * kBandSlots * 8);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 template <typename T>
 static void launch_dual_t(const KernelCtx& k, hipStream_t s, int prec, const IterPtrs<T>& it,
                           const DataPtrs<T>& d, const MatPtrs<T>& A, T* part) {
   if (k.use_band) {
-    if (k.band1.nslot > 0)
-      k_band_spmv<T><<<grid1(k.band1.nslot), kBandWaves * kWave, 0, s>>>(k.band1, band_val<T>(k, 0), it.xh, part,
-                                                                         k.M, k.inst, prec, 0);
+    launch_band_spmv<T>(k.band1, band_val<T>(k, 0), it.xh, part, k.M, k.inst, prec, 0, s);
   } else if (k.brow.nblk > 0) {
     k_dual<T, T><<<grid1(k.brow.nblk), kBlock, 0, s>>>(k.brow, A, it, d, k.inst, prec, k.rec_dual);
   }
@@ -2745,9 +2780,7 @@ template <typename T>
 static void launch_lam_t(const KernelCtx& k, hipStream_t s, int prec, const IterPtrs<T>& it,
                          const DataPtrs<T>& d, const MatPtrs<T>& AT, T* part) {
   if (k.use_band) {
-    if (k.band2.nslot > 0)
-      k_band_spmv<T><<<grid1(k.band2.nslot), kBandWaves * kWave, 0, s>>>(k.band2, band_val<T>(k, 1), it.yh, part,
-                                                                         k.N, k.inst, prec, 1);
+    launch_band_spmv<T>(k.band2, band_val<T>(k, 1), it.yh, part, k.N, k.inst, prec, 1, s);
     if (k.vcol.nblk > 0)
       k_lam_epi<T><<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, part, k.band2.P, k.N, it, d, k.inst, prec,
                                                           k.rec_lam_epi);
@@ -2842,23 +2875,13 @@ static void launch_cand_t(const KernelCtx& k, hipStream_t s, int prec, const Ite
                           const T* x0, const T* x1, const T* y0, const T* y1, int mode) {
   if (k.use_band) {
     // band tiles with FP64 values: one pass per vector, then the window sums
-    if (k.band1.nslot > 0) {
-      k_band_cand<T><<<grid1(k.band1.nslot), kBandWaves * kWave, 0, s>>>(k.band1, k.bval64, x0, k.bpart64, k.M,
-                                                                         k.inst, prec, mode, 0);
-      if (x1)
-        k_band_cand<T><<<grid1(k.band1.nslot), kBandWaves * kWave, 0, s>>>(k.band1, k.bval64, x1, k.bpart64b, k.M,
-                                                                           k.inst, prec, mode, 1);
-    }
+    launch_band_cand<T>(k.band1, k.bval64, x0, k.bpart64, k.M, k.inst, prec, mode, 0, s);
+    if (x1) launch_band_cand<T>(k.band1, k.bval64, x1, k.bpart64b, k.M, k.inst, prec, mode, 1, s);
     if (k.vrow.nblk > 0)
       k_band_combine2<<<grid1(k.vrow.nblk), kBlock, 0, s>>>(k.vrow, k.band1.P, k.M, k.bpart64,
                                                              x1 ? k.bpart64b : nullptr, k.cgx0, k.cgx1, k.inst, mode);
-    if (k.band2.nslot > 0) {
-      k_band_cand<T><<<grid1(k.band2.nslot), kBandWaves * kWave, 0, s>>>(k.band2, k.bvalT64, y0, k.bpartT64, k.N,
-                                                                         k.inst, prec, mode, 0);
-      if (y1)
-        k_band_cand<T><<<grid1(k.band2.nslot), kBandWaves * kWave, 0, s>>>(k.band2, k.bvalT64, y1, k.bpartT64b,
-                                                                           k.N, k.inst, prec, mode, 1);
-    }
+    launch_band_cand<T>(k.band2, k.bvalT64, y0, k.bpartT64, k.N, k.inst, prec, mode, 0, s);
+    if (y1) launch_band_cand<T>(k.band2, k.bvalT64, y1, k.bpartT64b, k.N, k.inst, prec, mode, 1, s);
     if (k.vcol.nblk > 0)
       k_band_combine2<<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, k.band2.P, k.N, k.bpartT64,
                                                              y1 ? k.bpartT64b : nullptr, k.cgty0, k.cgty1, k.inst,
@@ -2914,16 +2937,12 @@ static void launch_restart_t(const KernelCtx& k, hipStream_t s, int prec, const 
 // has an unbounded column.
 static void launch_ray_products(const KernelCtx& k, hipStream_t s) {
   if (k.use_band) {
-    if (k.band2.nslot > 0)
-      k_band_cand<double><<<grid1(k.band2.nslot), kBandWaves * kWave, 0, s>>>(k.band2, k.bvalT64, k.ry, k.bpartT64,
-                                                                              k.N, k.inst, kFP64, kModeRay, 0);
+    launch_band_cand<double>(k.band2, k.bvalT64, k.ry, k.bpartT64, k.N, k.inst, kFP64, kModeRay, 0, s);
     if (k.vcol.nblk > 0)
       k_band_combine2<<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, k.band2.P, k.N, k.bpartT64, nullptr, k.rgty,
                                                              nullptr, k.inst, kModeRay);
     if (k.ray_x) {
-      if (k.band1.nslot > 0)
-        k_band_cand<double><<<grid1(k.band1.nslot), kBandWaves * kWave, 0, s>>>(k.band1, k.bval64, k.rx, k.bpart64,
-                                                                                k.M, k.inst, kFP64, kModeRay, 0);
+      launch_band_cand<double>(k.band1, k.bval64, k.rx, k.bpart64, k.M, k.inst, kFP64, kModeRay, 0, s);
       if (k.vrow.nblk > 0)
         k_band_combine2<<<grid1(k.vrow.nblk), kBlock, 0, s>>>(k.vrow, k.band1.P, k.M, k.bpart64, nullptr, k.rgx,
                                                                nullptr, k.inst, kModeRay);
@@ -3131,12 +3150,10 @@ void launch_band_plain(const BandTiles& bt, int prec, const void* val, const voi
   if (bt.nslot <= 0 || R <= 0) return;
   const dim3 g((unsigned)((R + 255) / 256));
   if (prec == kFP64) {
-    k_band_spmv<double><<<grid1(bt.nslot), kBandWaves * kWave, 0, s>>>(bt, (const double*)val, (const double*)in,
-                                                                       (double*)part, R, nullptr, kFP64, 0);
+    launch_band_spmv<double>(bt, (const double*)val, (const double*)in, (double*)part, R, nullptr, kFP64, 0, s);
     k_band_sum<double><<<g, 256, 0, s>>>((const double*)part, bt.P, R, (double*)out);
   } else {
-    k_band_spmv<float><<<grid1(bt.nslot), kBandWaves * kWave, 0, s>>>(bt, (const float*)val, (const float*)in,
-                                                                      (float*)part, R, nullptr, kFP32, 0);
+    launch_band_spmv<float>(bt, (const float*)val, (const float*)in, (float*)part, R, nullptr, kFP32, 0, s);
     k_band_sum<float><<<g, 256, 0, s>>>((const float*)part, bt.P, R, (float*)out);
   }
 }

@@ -136,6 +136,9 @@ struct SetupCtx {
   float *bval32, *bvalT32;
 };
 
+// raises the dynamic-LDS limit of the band-tile kernels on the current device
+hipError_t band_raise_lds_limit();
+
 void launch_setup(const KernelCtx& k, const SetupCtx& su, hipStream_t s, int mask);
 void launch_trial(const KernelCtx& k, hipStream_t s, int mask);
 // K trials of every instance, one workgroup per instance (k.wg_trials layouts)
