@@ -125,9 +125,13 @@ constexpr int kBandRows = 8192;
 constexpr int kBandSlots = 9216;
 constexpr int kBandSlotBits = 14;
 constexpr int kBandColBits = 32 - kBandSlotBits;
-constexpr int kBandWaves = 2;
+// (One wave, one band-tile per workgroup: tiles then spread evenly over the CUs,
+// where pairs left some CUs two workgroups to do and others one.  m = 2.5e5,
+// n = 5e5, power-law rows, nnz = 1.35e7, 540 tiles, G x and G^T y: FP32 110 us in
+// pairs, 99 alone, FP64 153 and 130; m = 2e5, n = 5e5: 51 / 66 either way; a trial
+// of 48 LPs in FP64: 108 and 99 us.)
+constexpr int kBandWaves = 1;
 constexpr int kBandUnroll = 16;
-constexpr int kTileRound = 256 * kBandWaves;  // band-tiles that give every CU one workgroup
 struct BandTiles {
   const int32_t* group;      // per workgroup slot group, per wave: band-tile or -1
   const int32_t* slot;       // launch slot -> group (-1: idle); slot s runs on XCD s % 8

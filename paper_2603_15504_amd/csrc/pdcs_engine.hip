@@ -530,27 +530,18 @@ void BandSet::build(const std::vector<int64_t>& r0s, const std::vector<int64_t>&
       const double per_row = rows_b > 0 ? (double)nnz_b / (double)rows_b / (double)Pb[b] : 1.0;
       while (rbb > 256 && (double)rbb * per_row > (double)bs.entry_cap) rbb /= 2;
     }
-    // Band boundaries with about equal entries: with heavy-tailed row lengths,
-    // fixed heights leave some bands far heavier than others, and the heaviest
-    // sets the time.  A single problem whose tiles fill at least half of the
-    // chip gets whole rounds of it (kTileRound waves): with the count the
-    // heights alone give, the last round is nearly empty or CUs stay idle.  (G x
-    // and G^T y, both directions, FP32 / FP64: m = 2.5e5, n = 5e5, power-law
-    // rows, nnz = 1.35e7: 110 / 152 us before, 95 / 115 with 512 tiles;
-    // m = 2e5, n = 5e5, nnz = 5e6: 51 / 66 before, 49 / 64; twice as many
-    // tiles: 51 / 66, half as many: 70 / 85.)
+    // Band boundaries with about equal entries (the count of rbb-row bands,
+    // each at most rbb rows): with heavy-tailed row lengths, fixed heights
+    // leave some bands far heavier than others, and the heaviest sets the time.
     std::vector<std::pair<int64_t, int64_t>> cuts;
     {
       const int64_t ra = r0s[b], re = r0s[b + 1];
-      const int64_t e0 = ptr[ra], ne = (int64_t)ptr[re] - e0;
-      int64_t nbands = (re - ra + rbb - 1) / rbb;
-      if (NB == 1 && nbands * P >= kTileRound / 2) nbands = (nbands * P + kTileRound - 1) / kTileRound * kTileRound / P;
-      nbands = std::min<int64_t>(nbands, re - ra);
+      const int64_t nbands = (re - ra + rbb - 1) / rbb;
+      const double target = nbands > 0 ? (double)((int64_t)ptr[re] - ptr[ra]) / (double)nbands : 0.0;
       int64_t r = ra;
-      for (int64_t q = 1; r < re; ++q) {
-        const int64_t want = q < nbands ? e0 + (int64_t)((double)ne * (double)q / (double)nbands) : e0 + ne;
+      while (r < re) {
         int64_t e = r + 1;
-        while (e < re && e - r < bs.rows && (q >= nbands || (int64_t)ptr[e + 1] <= want)) ++e;
+        while (e < re && e - r < rbb && (double)((int64_t)ptr[e + 1] - ptr[r]) <= target) ++e;
         cuts.push_back({r, e});
         r = e;
       }

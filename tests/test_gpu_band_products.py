@@ -1,6 +1,6 @@
-"""Band tiles cut by equal entries in whole rounds of the chip: products at the
-sizes around the rule (fewer tiles than half a round, just past it, several
-windows, power-law rows) against the host's FP64 product."""
+"""Products of the band layout at tile counts below, at and past a round of the
+chip, with several windows and with power-law rows (launches whose LDS follows
+the tallest tile), against the host's FP64 product."""
 import numpy as np
 import pytest
 
@@ -29,7 +29,7 @@ CASES = {
 
 
 @pytest.mark.parametrize("name", list(CASES))
-def test_products_around_the_tile_count_rule(name):
+def test_products_over_tile_counts(name):
     c = dict(CASES[name])
     rng = np.random.default_rng(17)
     if c.pop("zipf", False):
