@@ -382,20 +382,50 @@ __device__ __forceinline__ double row_dot_stream(const int32_t* __restrict__ col
   return s;
 }
 
-// Products of one row block with NV gathered vectors, reduced per row; fn(r, s)
+// Products of entries [0, n) of a row block with NV vectors into LDS, n <= 256 U:
+// every index and value is requested before the first gather, and every gather
+// before the first product (entries past the end repeat the last one, whose LDS
+// slots past n nobody reads).
+template <int U, int NV, typename TM, typename TV>
+__device__ __forceinline__ void stage_products(int n, const int32_t* __restrict__ idx, const TM* __restrict__ val,
+                                               const TV* const (&xs)[NV], double* lds) {
+  const int tid = threadIdx.x;
+  int c[U];
+  TM v[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int i = min(u * kBlock + tid, n - 1);
+    c[u] = __builtin_nontemporal_load(idx + i);
+    v[u] = __builtin_nontemporal_load(val + i);
+  }
+  TV g[NV][U];
+#pragma unroll
+  for (int k = 0; k < NV; ++k)
+#pragma unroll
+    for (int u = 0; u < U; ++u) g[k][u] = xs[k][c[u]];
+#pragma unroll
+  for (int k = 0; k < NV; ++k)
+#pragma unroll
+    for (int u = 0; u < U; ++u) lds[k * kRowBlockCap + u * kBlock + tid] = (double)v[u] * (double)g[k][u];
+}
+
+// Products of one row block with NV gathered vectors, reduced per row; fn(r, s, d)
 // is called exactly once per row r of the block, by one thread, with s[k] the
-// row's dot product with xs[k] (FP64 accumulation).  lds: NV * kRowBlockCap
+// row's dot product with xs[k] (FP64 accumulation) and d what pre(r) returned:
+// pre loads what the row's epilogue needs, and is called before the products are
+// formed, so that those loads are in flight with them.  lds: NV * kRowBlockCap
 // doubles plus kWavesPerBlock * NV doubles.  Every thread of the workgroup must
 // call this (it synchronizes).
-template <int NV, typename TM, typename TV, class Fn>
+template <int NV, typename TM, typename TV, class Pre, class Fn>
 __device__ __forceinline__ void block_rows(int r0, int r1, const int32_t* __restrict__ ptr,
                                            const int32_t* __restrict__ idx, const TM* __restrict__ val,
-                                           const TV* const (&xs)[NV], double* lds, Fn&& fn) {
+                                           const TV* const (&xs)[NV], double* lds, Pre&& pre, Fn&& fn) {
   const int tid = threadIdx.x;
   const int R = r1 - r0;
   const int q0 = ptr[r0], q1 = ptr[r1];
   if (R == 1) {
     // one row of any length: register accumulation, unrolled streaming loads
+    const auto d = pre(r0);
     double s[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) s[k] = 0.0;
@@ -434,61 +464,58 @@ __device__ __forceinline__ void block_rows(int r0, int r1, const int32_t* __rest
         t[k] = 0.0;
         for (int w = 0; w < kWavesPerBlock; ++w) t[k] += red[w * NV + k];
       }
-      fn(r0, t);
+      fn(r0, t, d);
     }
     return;
   }
   // several rows, at most kRowBlockCap nonzeros: stage the products in LDS
   const int n = q1 - q0;
-  for (int i0 = 0; i0 < n; i0 += 4 * kBlock) {
-    int c[4];
-    double v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = i0 + u * kBlock + tid;
-      c[u] = i < n ? __builtin_nontemporal_load(idx + q0 + i) : 0;
-      v[u] = i < n ? (double)__builtin_nontemporal_load(val + q0 + i) : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = i0 + u * kBlock + tid;
-      if (i < n) {
-#pragma unroll
-        for (int k = 0; k < NV; ++k) lds[k * kRowBlockCap + i] = v[u] * (double)xs[k][c[u]];
-      }
-    }
-  }
-  __syncthreads();
   if (R <= kBlock) {
     int T = 64;
     while (T > 1 && T * R > kBlock) T >>= 1;
-    const int g = tid / T, li = tid & (T - 1);
+    const int g = min(tid / T, R - 1), li = tid & (T - 1);
     const int r = r0 + g;
+    const int a = ptr[r] - q0, e = ptr[r + 1] - q0;
+    const auto d = pre(r);
+    if (n > 4 * kBlock) stage_products<8, NV>(n, idx + q0, val + q0, xs, lds);
+    else if (n > 0) stage_products<4, NV>(n, idx + q0, val + q0, xs, lds);
+    __syncthreads();
     double s[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) s[k] = 0.0;
-    if (g < R) {
-      const int a = ptr[r] - q0, e = ptr[r + 1] - q0;
-      for (int i = a + li; i < e; i += T)
+    for (int i = a + li; i < e; i += T)
 #pragma unroll
-        for (int k = 0; k < NV; ++k) s[k] += lds[k * kRowBlockCap + i];
-    }
+      for (int k = 0; k < NV; ++k) s[k] += lds[k * kRowBlockCap + i];
 #pragma unroll
     for (int k = 0; k < NV; ++k)
       for (int off = T >> 1; off > 0; off >>= 1) s[k] += __shfl_xor(s[k], off, kWave);
-    if (li == 0 && g < R) fn(r, s);
+    if (li == 0 && tid / T < R) fn(r, s, d);
   } else {
+    if (n > 4 * kBlock) stage_products<8, NV>(n, idx + q0, val + q0, xs, lds);
+    else if (n > 0) stage_products<4, NV>(n, idx + q0, val + q0, xs, lds);
+    __syncthreads();
     for (int r = r0 + tid; r < r1; r += kBlock) {
       const int a = ptr[r] - q0, e = ptr[r + 1] - q0;
+      const auto d = pre(r);
       double s[NV];
 #pragma unroll
       for (int k = 0; k < NV; ++k) s[k] = 0.0;
       for (int i = a; i < e; ++i)
 #pragma unroll
         for (int k = 0; k < NV; ++k) s[k] += lds[k * kRowBlockCap + i];
-      fn(r, s);
+      fn(r, s, d);
     }
   }
+}
+
+// block_rows with no epilogue data: fn(r, s).
+struct NoRow {};
+template <int NV, typename TM, typename TV, class Fn>
+__device__ __forceinline__ void block_rows(int r0, int r1, const int32_t* __restrict__ ptr,
+                                           const int32_t* __restrict__ idx, const TM* __restrict__ val,
+                                           const TV* const (&xs)[NV], double* lds, Fn&& fn) {
+  block_rows<NV>(r0, r1, ptr, idx, val, xs, lds, [](int) { return NoRow{}; },
+                 [&](int r, const double* s, const NoRow&) { fn(r, s); });
 }
 
 // Sum over the L-lane groups of a wavefront (L a power of two <= 64).

@@ -432,7 +432,11 @@ __global__ __launch_bounds__(kBlock) void k_proj_cone(int cone, int dim, const d
 // K3: primal step over the columns of the instance.
 // The five passes of a trial are device functions of the workgroup's range or
 // instance, so that k_trials_wg can run them back to back inside one workgroup.
-template <typename T>
+// They are bound by the latency of their loads: each takes U elements per thread
+// at a time and requests all of their operands before the first is used
+// (elements past the end repeat the last one and are not stored).
+constexpr int kElems = 4;  // elements per thread of the passes over global memory
+template <typename T, int U>
 __device__ __forceinline__ void primal_body(int b, const Ranges& R, const IterPtrs<T>& it, const DataPtrs<T>& d,
                                             Inst* inst, int prec, double* rec) {
   __shared__ double lds[kWavesPerBlock * 2];
@@ -444,24 +448,37 @@ __device__ __forceinline__ void primal_body(int b, const Ranges& R, const IterPt
   const double tau = I.eta / I.omega;
   double acc[2] = {0.0, 0.0};
   const int j1 = R.blk_end[b];
-  for (int j = R.blk_start[b] + (int)threadIdx.x; j < j1; j += kBlock) {
-    double x = (double)it.x[j];
-    double gty = (double)it.gty[j];
-    if (commit) {
-      const double xh = (double)it.xh[j];
-      const double gh = (double)it.gtyh[j];
-      x = (double)(T)(ca * ((1.0 + beta) * xh - beta * x) + cb * (double)it.xa[j]);
-      gty = (double)(T)(ca * ((1.0 + beta) * gh - beta * gty) + cb * (double)it.gtya[j]);
-      it.x[j] = (T)x;
-      it.gty[j] = (T)gty;
-      if (avg) it.sx[j] = (T)((double)it.sx[j] + etak * xh);
+  for (int j0 = R.blk_start[b] + (int)threadIdx.x; j0 < j1; j0 += U * kBlock) {
+    T x[U], g[U], xh[U], gh[U], xa[U], ga[U], sx[U], c[U], lo[U], hi[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = min(j0 + u * kBlock, j1 - 1);
+      x[u] = it.x[j], g[u] = it.gty[j], c[u] = d.c[j], lo[u] = d.l[j], hi[u] = d.u[j];
+      if (commit) xh[u] = it.xh[j], gh[u] = it.gtyh[j], xa[u] = it.xa[j], ga[u] = it.gtya[j];
+      if (commit && avg) sx[u] = it.sx[j];
     }
-    const double c = (double)d.c[j];
-    const double xn = (double)(T)clampd(x - tau * (c - gty), (double)d.l[j], (double)d.u[j]);
-    it.xh[j] = (T)xn;
-    const double dx = xn - x;
-    acc[0] += dx * dx;
-    acc[1] += c * xn;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + u * kBlock;
+      if (j >= j1) break;
+      double xv = (double)x[u];
+      double gty = (double)g[u];
+      if (commit) {
+        const double xhv = (double)xh[u];
+        const double ghv = (double)gh[u];
+        xv = (double)(T)(ca * ((1.0 + beta) * xhv - beta * xv) + cb * (double)xa[u]);
+        gty = (double)(T)(ca * ((1.0 + beta) * ghv - beta * gty) + cb * (double)ga[u]);
+        it.x[j] = (T)xv;
+        it.gty[j] = (T)gty;
+        if (avg) it.sx[j] = (T)((double)sx[u] + etak * xhv);
+      }
+      const double cv = (double)c[u];
+      const double xn = (double)(T)clampd(xv - tau * (cv - gty), (double)lo[u], (double)hi[u]);
+      it.xh[j] = (T)xn;
+      const double dx = xn - xv;
+      acc[0] += dx * dx;
+      acc[1] += cv * xn;
+    }
   }
   block_sum_store<2>(acc, lds, rec + (size_t)b * 2);
 }
@@ -470,11 +487,15 @@ template <typename T>
 __global__ __launch_bounds__(kBlock) void k_primal(Ranges R, IterPtrs<T> it, DataPtrs<T> d,
                                                    Inst* __restrict__ inst, int prec,
                                                    double* __restrict__ rec) {
-  primal_body<T>(blockIdx.x, R, it, d, inst, prec, rec);
+  primal_body<T, kElems>(blockIdx.x, R, it, d, inst, prec, rec);
 }
 
 // K1: CSR SpMV G x_hat with the fused dual step.  Record: ||dy||^2,
 // dy^T G dx, ||(G x_hat - h) - Proj_Kd*(.)||^2, h^T y_hat.
+template <typename T>
+struct DualRow {  // a row's operands
+  T y, gx, yh, gh, ya, ga, sy, h;
+};
 template <typename T>
 struct DualEpilogue {
   IterPtrs<T> it;
@@ -482,19 +503,26 @@ struct DualEpilogue {
   bool commit, avg;
   double ca, cb, beta, etak, sigma;
   int mz_end, soc_start;
-  __device__ __forceinline__ void operator()(int r, double s, double (&acc)[4]) const {
-    double y = (double)it.y[r];
-    double gx = (double)it.gx[r];
+  __device__ __forceinline__ DualRow<T> load(int r) const {
+    DualRow<T> o;
+    o.y = it.y[r], o.gx = it.gx[r], o.h = d.h[r];
+    if (commit) o.yh = it.yh[r], o.gh = it.gxh[r], o.ya = it.ya[r], o.ga = it.gxa[r];
+    if (commit && avg) o.sy = it.sy[r];
+    return o;
+  }
+  __device__ __forceinline__ void operator()(int r, double s, const DualRow<T>& o, double (&acc)[4]) const {
+    double y = (double)o.y;
+    double gx = (double)o.gx;
     if (commit) {
-      const double yh = (double)it.yh[r];
-      const double gh = (double)it.gxh[r];
-      y = (double)(T)(ca * ((1.0 + beta) * yh - beta * y) + cb * (double)it.ya[r]);
-      gx = (double)(T)(ca * ((1.0 + beta) * gh - beta * gx) + cb * (double)it.gxa[r]);
+      const double yh = (double)o.yh;
+      const double gh = (double)o.gh;
+      y = (double)(T)(ca * ((1.0 + beta) * yh - beta * y) + cb * (double)o.ya);
+      gx = (double)(T)(ca * ((1.0 + beta) * gh - beta * gx) + cb * (double)o.ga);
       it.y[r] = (T)y;
       it.gx[r] = (T)gx;
-      if (avg) it.sy[r] = (T)((double)it.sy[r] + etak * yh);
+      if (avg) it.sy[r] = (T)((double)o.sy + etak * yh);
     }
-    const double hv = (double)d.h[r];
+    const double hv = (double)o.h;
     const double gxn = (double)(T)s;
     const double v = y + sigma * (hv - 2.0 * gxn + gx);
     if (r >= soc_start) {  // cone block row: projected with its block afterwards
@@ -535,12 +563,21 @@ __device__ __forceinline__ DualEpilogue<T> make_dual_epilogue(const Inst& I, con
 }
 
 template <typename T>
-__device__ __forceinline__ void lam_epilogue(int j, double s, const IterPtrs<T>& it, const DataPtrs<T>& d,
+struct LamCol {  // a column's operands
+  T c, l, u;
+};
+template <typename T>
+__device__ __forceinline__ LamCol<T> lam_load(int j, const DataPtrs<T>& d) {
+  return LamCol<T>{d.c[j], d.l[j], d.u[j]};
+}
+
+template <typename T>
+__device__ __forceinline__ void lam_epilogue(int j, double s, const IterPtrs<T>& it, const LamCol<T>& o,
                                              double (&acc)[3]) {
   const double g = (double)(T)s;
   it.gtyh[j] = (T)g;
-  const double lam = (double)d.c[j] - g;
-  const double lo = (double)d.l[j], hi = (double)d.u[j];
+  const double lam = (double)o.c - g;
+  const double lo = (double)o.l, hi = (double)o.u;
   const bool lf = isfinite(lo), uf = isfinite(hi);
   double res;
   if (!lf && !uf) res = lam;
@@ -562,7 +599,8 @@ __device__ __forceinline__ void dual_body(int b, const RowBlocks& rb, const MatP
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   const T* const xs[1] = {it.xh};
   block_rows<1>(rb.blk_row0[b], rb.blk_row1[b], A.ptr, A.idx, A.val, xs, lds,
-                [&](int r, const double* s) { epi(r, s[0], acc); });
+                [&](int r) { return epi.load(r); },
+                [&](int r, const double* s, const DualRow<T>& o) { epi(r, s[0], o, acc); });
   __syncthreads();
   block_sum_store<4>(acc, lds, rec + (size_t)b * 4);
 }
@@ -775,6 +813,32 @@ __global__ void k_band_vals(const int32_t* __restrict__ src, int64_t n, const do
   o32[e] = (float)v;
 }
 
+// s[u] += the P window partial sums of element e0 + u kBlock (the last one, end - 1,
+// in place of those past it), in window order; two windows' loads in flight.
+template <typename T, int U>
+__device__ __forceinline__ void window_sums(const T* __restrict__ part, int P, int64_t M, int e0, int end,
+                                            double (&s)[U]) {
+  int p = 0;
+  for (; p + 2 <= P; p += 2) {
+    T v[2][U];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[k][u] = part[(size_t)(p + k) * M + min(e0 + u * kBlock, end - 1)];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int u = 0; u < U; ++u) s[u] += (double)v[k][u];
+  }
+  if (p < P) {
+    T v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = part[(size_t)p * M + min(e0 + u * kBlock, end - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) s[u] += (double)v[u];
+  }
+}
+
 // K1b: combine the P partial sums of G x_hat per row, then the dual step
 // (same epilogue and record as k_dual).
 template <typename T>
@@ -789,10 +853,18 @@ __global__ __launch_bounds__(kBlock) void k_dual_epi(Ranges R, const T* __restri
   const DualEpilogue<T> epi = make_dual_epilogue(I, it, d);
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   const int r1 = R.blk_end[b];
-  for (int r = R.blk_start[b] + (int)threadIdx.x; r < r1; r += kBlock) {
-    double s = 0.0;
-    for (int p = 0; p < P; ++p) s += (double)part[(size_t)p * M + r];
-    epi(r, s, acc);
+  for (int q0 = R.blk_start[b] + (int)threadIdx.x; q0 < r1; q0 += kElems * kBlock) {
+    DualRow<T> o[kElems];
+    double s[kElems];
+#pragma unroll
+    for (int u = 0; u < kElems; ++u) {
+      o[u] = epi.load(min(q0 + u * kBlock, r1 - 1));
+      s[u] = 0.0;
+    }
+    window_sums<T, kElems>(part, P, M, q0, r1, s);
+#pragma unroll
+    for (int u = 0; u < kElems; ++u)
+      if (q0 + u * kBlock < r1) epi(q0 + u * kBlock, s[u], o[u], acc);
   }
   if (R.blk_soc0 && R.blk_soc1[b] > R.blk_soc0[b]) {
     __syncthreads();  // the blocks' unprojected values and committed iterates are in memory
@@ -845,10 +917,18 @@ __global__ __launch_bounds__(kBlock) void k_lam_epi(Ranges R, const T* __restric
   if (I.status != kActive || I.precision != prec || I.last_acc == 0) return;
   double acc[3] = {0.0, 0.0, 0.0};
   const int j1 = R.blk_end[b];
-  for (int j = R.blk_start[b] + (int)threadIdx.x; j < j1; j += kBlock) {
-    double s = 0.0;
-    for (int p = 0; p < P; ++p) s += (double)part[(size_t)p * N + j];
-    lam_epilogue<T>(j, s, it, d, acc);
+  for (int q0 = R.blk_start[b] + (int)threadIdx.x; q0 < j1; q0 += kElems * kBlock) {
+    LamCol<T> o[kElems];
+    double s[kElems];
+#pragma unroll
+    for (int u = 0; u < kElems; ++u) {
+      o[u] = lam_load<T>(min(q0 + u * kBlock, j1 - 1), d);
+      s[u] = 0.0;
+    }
+    window_sums<T, kElems>(part, P, N, q0, j1, s);
+#pragma unroll
+    for (int u = 0; u < kElems; ++u)
+      if (q0 + u * kBlock < j1) lam_epilogue<T>(q0 + u * kBlock, s[u], it, o[u], acc);
   }
   block_sum_store<3>(acc, lds, rec + (size_t)b * 3);
 }
@@ -944,7 +1024,8 @@ __device__ __forceinline__ void lam_body(int b, const RowBlocks& rb, const MatPt
   double acc[3] = {0.0, 0.0, 0.0};
   const T* const ys[1] = {it.yh};
   block_rows<1>(rb.blk_row0[b], rb.blk_row1[b], AT.ptr, AT.idx, AT.val, ys, lds,
-                [&](int j, const double* s) { lam_epilogue<T>(j, s[0], it, d, acc); });
+                [&](int j) { return lam_load<T>(j, d); },
+                [&](int j, const double* s, const LamCol<T>& o) { lam_epilogue<T>(j, s[0], it, o, acc); });
   __syncthreads();
   block_sum_store<3>(acc, lds, rec + (size_t)b * 3);
 }
@@ -1030,7 +1111,7 @@ __global__ __launch_bounds__(kBlock) void k_trials_wg(Ranges vcol, RowBlocks bro
       const Inst& I = inst[iid];
       if (I.status != kActive || I.precision != prec) break;
     }
-    for (int b = p0; b < p1; ++b) primal_body<T>(b, vcol, it, d, inst, prec, rec_p);
+    for (int b = p0; b < p1; ++b) primal_body<T, kElems>(b, vcol, it, d, inst, prec, rec_p);
     __syncthreads();
     for (int b = d0; b < d1; ++b) dual_body<T, T>(b, brow, A, it, d, inst, prec, rec_d);
     __syncthreads();
@@ -1078,8 +1159,9 @@ __device__ __forceinline__ void dual_rows_lds(int r0, int r1, const MatPtrs<T>& 
   const DualEpilogue<T> epi = make_dual_epilogue(I, it, d);
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   for (int r = r0 + (int)threadIdx.x; r < r1; r += kBlock) {
+    const DualRow<T> o = epi.load(r);
     const double s = row_dot_seq(A.ptr[r], A.ptr[r + 1], A.idx, A.val, it.xh);
-    epi(r, s, acc);
+    epi(r, s, o, acc);
   }
   block_sum_store<4>(acc, lds, rec);
 }
@@ -1091,8 +1173,9 @@ __device__ __forceinline__ void lam_rows_lds(int c0, int c1, const MatPtrs<T>& A
   if (I.status != kActive || I.last_acc == 0) return;
   double acc[3] = {0.0, 0.0, 0.0};
   for (int j = c0 + (int)threadIdx.x; j < c1; j += kBlock) {
+    const LamCol<T> o = lam_load<T>(j, d);
     const double s = row_dot_seq(AT.ptr[j], AT.ptr[j + 1], AT.idx, AT.val, it.yh);
-    lam_epilogue<T>(j, s, it, d, acc);
+    lam_epilogue<T>(j, s, it, o, acc);
   }
   block_sum_store<3>(acc, lds, rec);
 }
@@ -1242,7 +1325,7 @@ __global__ __launch_bounds__(kBlock) void k_trials_lds(Ranges vcol, RowBlocks br
   for (int s = 0; s < K; ++s) {
     if (Ish.status != kActive || Ish.precision != prec) break;
     if (rowwise) {
-      primal_body<T>(0, l1, li, ld, li_inst, prec, recp);
+      primal_body<T, 2>(0, l1, li, ld, li_inst, prec, recp);
       __syncthreads();
       dual_rows_lds<T>(r0, r0 + m, LA, li, ld, Ish, recd);
       __syncthreads();
@@ -1252,7 +1335,7 @@ __global__ __launch_bounds__(kBlock) void k_trials_lds(Ranges vcol, RowBlocks br
       __syncthreads();
       fin_beta_body(iid, one - iid, recl, li_inst);
     } else {
-      for (int b = p0; b < p0 + np; ++b) primal_body<T>(b, lv, li, ld, li_inst, prec, rp_);
+      for (int b = p0; b < p0 + np; ++b) primal_body<T, 2>(b, lv, li, ld, li_inst, prec, rp_);
       __syncthreads();
       for (int b = d0; b < d0 + nd; ++b) dual_body<T, T>(b, lr, LA, li, ld, li_inst, prec, rd_);
       __syncthreads();
