@@ -334,6 +334,43 @@ __device__ __forceinline__ void reduce_records(const double* rec, int b0, int b1
   __syncthreads();
 }
 
+// reduce_records in two halves, for a workgroup that has other loads to issue in
+// between, over at most kFoldRecords records of sums.  records_load: this thread's
+// share.  records_store: the waves' sums into lds (kWavesPerBlock * NV doubles);
+// after a barrier, records_total adds them (any thread).  The same order, and the
+// same bits, as reduce_records.
+constexpr int kFoldRecords = 2 * kBlock;
+template <int NV>
+__device__ __forceinline__ void records_load(const double* __restrict__ rec, int b0, int b1, double (&v)[NV]) {
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] = 0.0;
+  if (b1 <= b0) return;
+  const int k0 = b0 + (int)threadIdx.x, k1 = k0 + kBlock;
+  double a[NV], b[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) a[i] = rec[(size_t)min(k0, b1 - 1) * NV + i];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) b[i] = rec[(size_t)min(k1, b1 - 1) * NV + i];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] = (k0 < b1 ? a[i] : 0.0) + (k1 < b1 ? b[i] : 0.0);
+}
+template <int NV>
+__device__ __forceinline__ void records_store(const double (&v)[NV], double* lds) {
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const double s = wave_sum(v[i]);
+    if ((threadIdx.x & (kWave - 1)) == 0) lds[threadIdx.x / kWave * NV + i] = s;
+  }
+}
+template <int NV>
+__device__ __forceinline__ void records_total(const double* lds, double (&v)[NV]) {
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    v[i] = lds[i];
+    for (int w = 1; w < kWavesPerBlock; ++w) v[i] += lds[w * NV + i];
+  }
+}
+
 // Row-dot over a CSR row segment by a group of L lanes (lane li of the group),
 // FP64 accumulation, loads unrolled by 4 to keep several gathers in flight.
 template <typename TM, typename TV>
@@ -386,9 +423,10 @@ __device__ __forceinline__ double row_dot_stream(const int32_t* __restrict__ col
 // every index and value is requested before the first gather, and every gather
 // before the first product (entries past the end repeat the last one, whose LDS
 // slots past n nobody reads).
-template <int U, int NV, typename TM, typename TV>
+// early() runs while the gathers are in flight.
+template <int U, int NV, typename TM, typename TV, class Early>
 __device__ __forceinline__ void stage_products(int n, const int32_t* __restrict__ idx, const TM* __restrict__ val,
-                                               const TV* const (&xs)[NV], double* lds) {
+                                               const TV* const (&xs)[NV], double* lds, Early&& early) {
   const int tid = threadIdx.x;
   int c[U];
   TM v[U];
@@ -403,6 +441,7 @@ __device__ __forceinline__ void stage_products(int n, const int32_t* __restrict_
   for (int k = 0; k < NV; ++k)
 #pragma unroll
     for (int u = 0; u < U; ++u) g[k][u] = xs[k][c[u]];
+  early();
 #pragma unroll
   for (int k = 0; k < NV; ++k)
 #pragma unroll
@@ -413,19 +452,22 @@ __device__ __forceinline__ void stage_products(int n, const int32_t* __restrict_
 // is called exactly once per row r of the block, by one thread, with s[k] the
 // row's dot product with xs[k] (FP64 accumulation) and d what pre(r) returned:
 // pre loads what the row's epilogue needs, and is called before the products are
-// formed, so that those loads are in flight with them.  lds: NV * kRowBlockCap
-// doubles plus kWavesPerBlock * NV doubles.  Every thread of the workgroup must
-// call this (it synchronizes).
-template <int NV, typename TM, typename TV, class Pre, class Fn>
+// formed, so that those loads are in flight with them.  early() is called once by
+// every thread with the gathers in flight, mid() (which may synchronize) once they
+// are done and before the first fn.  lds:
+// NV * kRowBlockCap doubles plus kWavesPerBlock * NV doubles.  Every thread of
+// the workgroup must call this (it synchronizes).
+template <int NV, typename TM, typename TV, class Pre, class Early, class Mid, class Fn>
 __device__ __forceinline__ void block_rows(int r0, int r1, const int32_t* __restrict__ ptr,
                                            const int32_t* __restrict__ idx, const TM* __restrict__ val,
-                                           const TV* const (&xs)[NV], double* lds, Pre&& pre, Fn&& fn) {
+                                           const TV* const (&xs)[NV], double* lds, Pre&& pre, Early&& early, Mid&& mid, Fn&& fn) {
   const int tid = threadIdx.x;
   const int R = r1 - r0;
   const int q0 = ptr[r0], q1 = ptr[r1];
   if (R == 1) {
     // one row of any length: register accumulation, unrolled streaming loads
     const auto d = pre(r0);
+    early();
     double s[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) s[k] = 0.0;
@@ -456,6 +498,7 @@ __device__ __forceinline__ void block_rows(int r0, int r1, const int32_t* __rest
       const double w = wave_sum(s[k]);
       if (lane == 0) red[wave * NV + k] = w;
     }
+    mid();
     __syncthreads();
     if (tid == 0) {
       double t[NV];
@@ -477,8 +520,10 @@ __device__ __forceinline__ void block_rows(int r0, int r1, const int32_t* __rest
     const int r = r0 + g;
     const int a = ptr[r] - q0, e = ptr[r + 1] - q0;
     const auto d = pre(r);
-    if (n > 4 * kBlock) stage_products<8, NV>(n, idx + q0, val + q0, xs, lds);
-    else if (n > 0) stage_products<4, NV>(n, idx + q0, val + q0, xs, lds);
+    if (n > 4 * kBlock) stage_products<8, NV>(n, idx + q0, val + q0, xs, lds, early);
+    else if (n > 0) stage_products<4, NV>(n, idx + q0, val + q0, xs, lds, early);
+    else early();
+    mid();
     __syncthreads();
     double s[NV];
 #pragma unroll
@@ -491,8 +536,10 @@ __device__ __forceinline__ void block_rows(int r0, int r1, const int32_t* __rest
       for (int off = T >> 1; off > 0; off >>= 1) s[k] += __shfl_xor(s[k], off, kWave);
     if (li == 0 && tid / T < R) fn(r, s, d);
   } else {
-    if (n > 4 * kBlock) stage_products<8, NV>(n, idx + q0, val + q0, xs, lds);
-    else if (n > 0) stage_products<4, NV>(n, idx + q0, val + q0, xs, lds);
+    if (n > 4 * kBlock) stage_products<8, NV>(n, idx + q0, val + q0, xs, lds, early);
+    else if (n > 0) stage_products<4, NV>(n, idx + q0, val + q0, xs, lds, early);
+    else early();
+    mid();
     __syncthreads();
     for (int r = r0 + tid; r < r1; r += kBlock) {
       const int a = ptr[r] - q0, e = ptr[r + 1] - q0;
@@ -506,6 +553,13 @@ __device__ __forceinline__ void block_rows(int r0, int r1, const int32_t* __rest
       fn(r, s, d);
     }
   }
+}
+
+template <int NV, typename TM, typename TV, class Pre, class Fn>
+__device__ __forceinline__ void block_rows(int r0, int r1, const int32_t* __restrict__ ptr,
+                                           const int32_t* __restrict__ idx, const TM* __restrict__ val,
+                                           const TV* const (&xs)[NV], double* lds, Pre&& pre, Fn&& fn) {
+  block_rows<NV>(r0, r1, ptr, idx, val, xs, lds, pre, [] {}, [] {}, fn);
 }
 
 // block_rows with no epilogue data: fn(r, s).

@@ -172,7 +172,7 @@ struct Engine {
   DBuf D1, D2, cgx0, cgx1, cgty0, cgty1, xout, yout, lamout, stat_r, stat_c;
   DBuf rec_primal, rec_dual, rec_lam, rec_cand_c, rec_cand_r, rec_probe_c, rec_probe_r;
   DBuf rec_nc, rec_nr, rec_nm;
-  DBuf d_inst, d_summary, warm_x, warm_y, d_trace;
+  DBuf d_inst, d_inst2, d_summary, warm_x, warm_y, d_trace;
   DBuf d_row0i, d_col0i, warm_ptr, d_flag;       // instance offsets, device warm-start pointer table
   DBuf xs0, ys0, rx, ry, rgx, rgty;              // infeasibility rays (FP64)
   bool any_unbounded = false;                    // some column has an infinite bound
@@ -211,6 +211,7 @@ struct Engine {
   void build_iteration_schedules(const std::vector<char>* active);
   void clear_graphs();
   void ensure_iter(int prec);
+  bool fold_trials(bool band) const;
   KernelCtx ctx(int probe_passes) const;
   void enqueue_chunk(const KernelCtx& k, int mask, int64_t K, bool timed);
   void harvest_events();

@@ -805,6 +805,7 @@ Engine::Engine(const std::vector<const HostProblem*>& probs) {
   h32.alloc((size_t)M * 4);
   for (DBuf* bf : {&c32, &l32, &u32}) bf->alloc((size_t)N * 4);
   d_inst.alloc(sizeof(Inst) * (size_t)std::max(B, 1));
+  d_inst2.alloc(sizeof(Inst) * (size_t)std::max(B, 1));
   d_summary.alloc(16);
   {
     std::vector<int32_t> r0i(row0.begin(), row0.end()), c0i(col0.begin(), col0.end());
@@ -950,6 +951,24 @@ void Engine::ensure_iter(int prec) {
   if (prec == kFP64 && !it64.ready) it64.alloc(N, M);
 }
 
+// Whether the trials' finalizers are folded into the passes that follow them.
+// Every workgroup of a pass then reads the records of its instance (rec doubles),
+// which pays while that is little: a finalizer launch takes 4 to 5 us and the gap
+// before it, reading 4 KB of records from L2 under a pass's own loads about 1 us.
+// The line: at most kFoldRecords records of a kind per instance (one round of the
+// reduction) and 64 MB of them read by all workgroups of a pass (about 5 us of L2).
+bool Engine::fold_trials(bool band) const {
+  const std::vector<int32_t>&p = vcol.h_iblk0, &d = band ? vrow.h_iblk0 : brow.h_iblk0,
+                            &l = band ? vcol.h_iblk0 : bcol.h_iblk0;
+  int64_t bytes = 0;
+  for (int b = 0; b < B; ++b) {
+    const int64_t np = p[b + 1] - p[b], nd = d[b + 1] - d[b], nl = l[b + 1] - l[b];
+    if (np > kFoldRecords || nd > kFoldRecords || nl > kFoldRecords) return false;
+    bytes += nl * (2 * np + 4 * nd) * 8 + np * 3 * nl * 8;
+  }
+  return bytes <= ((int64_t)64 << 20);
+}
+
 KernelCtx Engine::ctx(int probe_passes) const {
   KernelCtx k{};
   k.nb = B;
@@ -964,6 +983,7 @@ KernelCtx Engine::ctx(int probe_passes) const {
   k.crow = crow.view();
   k.ccol = ccol.view();
   k.inst = d_inst.as<Inst>();
+  k.inst2 = d_inst2.as<Inst>();
   k.it32 = it32.p;
   k.it64 = it64.p;
   k.d32 = DataPtrs<float>{c32.as<float>(), l32.as<float>(), u32.as<float>(), h32.as<float>()};
@@ -1004,6 +1024,7 @@ KernelCtx Engine::ctx(int probe_passes) const {
   k.rgx = rgx.as<double>();
   k.rgty = rgty.as<double>();
   k.use_band = use_band && !band_suspended ? 1 : 0;
+  k.fold = fold_trials(k.use_band != 0) ? 1 : 0;
   if (k.use_band) {
     k.band1 = band1.view();
     k.band2 = band2.view();
@@ -1055,6 +1076,12 @@ static int64_t check_period(const pdcs_options& o) {
 void Engine::enqueue_chunk(const KernelCtx& k, int mask, int64_t K, bool timed) {
   if (k.wg_trials && !k.use_band && !timed) {  // timed runs keep the per-pass launches
     launch_trials_wg(k, stream, mask, (int)K);
+    launch_check(k, stream, mask);
+    launch_summary(k, stream, d_summary.as<int32_t>());
+    return;
+  }
+  if (k.fold && !timed) {
+    launch_trials_fold(k, stream, mask, (int)K);
     launch_check(k, stream, mask);
     launch_summary(k, stream, d_summary.as<int32_t>());
     return;

@@ -429,6 +429,249 @@ __global__ __launch_bounds__(kBlock) void k_proj_cone(int cone, int dim, const d
 // Iteration kernels
 // ===========================================================================
 
+// F1: line-search decision of Function 2 for an active instance, from the sums of
+// the primal records (p) and the dual records (q); one thread.
+// pf: when non-null, pf[0] = (kbar + 1)^-0.3 and pf[1] = (kbar + 1)^-0.6 for the
+// kbar this trial reaches, computed beforehand by an otherwise idle thread
+__device__ __forceinline__ void fin_ls_apply(Inst& I, const double (&p)[2], const double (&q)[4], const double* pf,
+                                             bool traced) {
+  I.pending = 0;
+  I.check_due = 0;
+  I.kbar += 1;
+  if (I.precision == kFP64) I.fp64_iters += 1;
+  const double dx2 = p[0], dy2 = q[0], dydg = q[1];
+  const double omega = I.omega, eta = I.eta;
+  const double num = 0.5 * (omega * dx2 + dy2 / omega);
+  const double den = fabs(dydg);
+  const double etabar = den > 0.0 ? num / den : (double)INFINITY;
+  const double kb1 = (double)I.kbar + 1.0;
+  const double p3 = pf ? pf[0] : pow(kb1, -0.3), p6 = pf ? pf[1] : pow(kb1, -0.6);
+  const double eta_next = fmin((1.0 - p3) * etabar, (1.0 + p6) * eta);
+  const bool bad = !isfinite(num) || isnan(etabar) || isnan(q[2]) || isnan(q[3]) || isnan(p[1]) ||
+                   !(eta_next > 0.0) || !isfinite(eta_next);
+  if (traced && I.trace && I.kbar <= I.trace_cap) {
+    double* tr = I.trace + (I.kbar - 1) * kTraceStride;
+    tr[0] = (double)I.kbar;
+    tr[1] = eta;
+    tr[2] = etabar;
+    tr[3] = dx2;
+    tr[4] = dy2;
+    tr[5] = dydg;
+    tr[6] = eta < etabar ? 1.0 : 0.0;
+    tr[7] = eta_next;
+    for (int f = 8; f < kTraceStride; ++f) tr[f] = NAN;
+    tr[9] = (double)I.k;
+    if (bad) {  // the failing trial's reductions, for diagnosis
+      tr[10] = p[1];
+      tr[11] = q[3];
+      tr[14] = q[2];
+    }
+  }
+  if (bad) {
+    I.status = kDone;
+    I.exit_code = 8;
+    I.last_acc = 0;
+    return;
+  }
+  if (eta < etabar) {
+    I.last_acc = 1;
+    I.eta_k = eta;
+    I.eta_hat = eta_next;
+    I.accepted += 1;
+    I.dx2 = dx2;
+    I.dy2 = dy2;
+    I.dydgdx = dydg;
+    I.errp2 = q[2];
+    I.hy = q[3];
+    I.cx = p[1];
+  } else {
+    I.last_acc = 0;
+    if (I.kbar >= I.max_iter) {
+      I.status = kDone;
+      I.exit_code = 1;
+    }
+  }
+  I.eta = eta_next;
+}
+
+// One workgroup per instance.
+__device__ __forceinline__ void fin_ls_body(int iid, const int32_t* iblk_p, const double* rec_p,
+                                            const int32_t* iblk_d, const double* rec_d, Inst* inst,
+                                            const double* pf = nullptr) {
+  __shared__ double lds[kWavesPerBlock * 4];
+  Inst& I = inst[iid];
+  if (I.status != kActive) return;
+  double p[2], q[4];
+  reduce_records<2, 2>(rec_p, iblk_p[iid], iblk_p[iid + 1], lds, p);
+  reduce_records<4, 4>(rec_d, iblk_d[iid], iblk_d[iid + 1], lds, q);
+  if (threadIdx.x != 0) return;
+  fin_ls_apply(I, p, q, pf, true);
+}
+
+// F2: reflection parameter at z_hat (eq. adaptive_reflection with the relative
+// errors of eq. tolerance-2), then schedule the Halpern commit.
+// For an active instance whose trial was accepted, from the sums of the dual-slack
+// records; one thread.
+__device__ __forceinline__ void fin_beta_apply(Inst& I, const double (&q)[3], bool traced) {
+  const double errp = sqrt(I.errp2), errd = sqrt(q[0]);
+  const double pobj = I.cx;
+  const double dobj = I.hy + q[1] - q[2];
+  const double gap = fabs(pobj - dobj);
+  const double rp = errp / (1.0 + I.h1);
+  const double rd = errd / (1.0 + I.c1);
+  const double rg = gap / (1.0 + fabs(pobj) + fabs(dobj));
+  const double me = fmax(rp, fmax(rd, rg));
+  if (isnan(me) || isnan(rp) || isnan(rd) || isnan(rg)) {
+    I.status = kDone;
+    I.exit_code = 8;
+    return;
+  }
+  const double beta = me > 0.0 ? clampd(-0.1 * log10(me) + 0.2, 0.0, 1.0) : 1.0;
+  if (traced && I.trace && I.kbar <= I.trace_cap) {
+    double* tr = I.trace + (I.kbar - 1) * kTraceStride;
+    tr[8] = beta;
+    tr[10] = I.cx;
+    tr[11] = I.hy;
+    tr[12] = q[1];
+    tr[13] = q[2];
+    tr[14] = I.errp2;
+    tr[15] = q[0];
+  }
+  const double k = (double)I.k;
+  I.beta = beta;
+  I.ca = (k + 1.0) / (k + 2.0);
+  I.cb = 1.0 / (k + 2.0);
+  I.pending = 1;
+  I.sum_eta += I.eta_k;
+  I.k += 1;
+  I.check_due = (I.kbar % I.check_every) == 0 ? 1 : 0;
+  if (!I.check_due && I.kbar >= I.max_iter) {
+    I.status = kDone;
+    I.exit_code = 1;
+  }
+}
+
+// One workgroup per instance.
+__device__ __forceinline__ void fin_beta_body(int iid, const int32_t* iblk_l, const double* rec_l, Inst* inst) {
+  __shared__ double lds[kWavesPerBlock * 3];
+  Inst& I = inst[iid];
+  if (I.status != kActive || I.last_acc == 0) return;
+  double q[3];
+  reduce_records<3, 3>(rec_l, iblk_l[iid], iblk_l[iid + 1], lds, q);
+  if (threadIdx.x != 0) return;
+  fin_beta_apply(I, q, true);
+}
+
+// Finalizers folded into the passes that follow them.  Where an instance has few
+// records, every workgroup of the dual-slack pass reduces them and takes the
+// line-search decision by itself, and every workgroup of the next primal pass the
+// reflection parameter, instead of waiting for a kernel of one workgroup per
+// instance; all of them compute the same bits.  The instance record alternates
+// between two arrays: the dual-slack pass reads `inst` and its first workgroup of
+// an instance writes the record after the decision to `inst2`, the primal pass
+// reads `inst2` and its first workgroup writes `inst`, so that no workgroup reads
+// what another one of its launch writes.  Ahead of the folded step, the pass has
+// requested its own operands.
+constexpr int kInstWords = (int)(sizeof(Inst) / 8);
+static_assert(sizeof(Inst) % 8 == 0 && kInstWords <= kBlock, "an instance record is copied with one word per thread");
+
+struct FoldIn {  // the instance's records of the two passes before (dual slack: of the one before)
+  const int32_t *iblk_a, *iblk_b;
+  const double *rec_a, *rec_b;
+  const Inst* in;
+  Inst* out;
+};
+
+__device__ __forceinline__ void inst_copy_in(Inst* S, const Inst* in) {
+  if ((int)threadIdx.x < kInstWords)
+    reinterpret_cast<uint64_t*>(S)[threadIdx.x] = reinterpret_cast<const uint64_t*>(in)[threadIdx.x];
+}
+__device__ __forceinline__ void inst_copy_out(Inst* out, const Inst* S) {
+  if ((int)threadIdx.x < kInstWords)
+    reinterpret_cast<uint64_t*>(out)[threadIdx.x] = reinterpret_cast<const uint64_t*>(S)[threadIdx.x];
+}
+
+// The line-search decision, in the dual-slack pass.  load() before the pass's own
+// loads, decide() (every thread) after them; then S is the instance's record.
+struct FoldLds {
+  double a[kWavesPerBlock * 2], b[kWavesPerBlock * 4], pf[2];
+};
+struct FoldLs {
+  double p[2], q[4];
+  int64_t kbar;
+  __device__ __forceinline__ void load(const FoldIn& f, int iid, Inst* S) {
+    inst_copy_in(S, f.in + iid);
+    records_load<2>(f.rec_a, f.iblk_a[iid], f.iblk_a[iid + 1], p);
+    records_load<4>(f.rec_b, f.iblk_b[iid], f.iblk_b[iid + 1], q);
+    kbar = f.in[iid].kbar;
+  }
+  // The waves' sums and, in the workgroup that writes the record, the line-search
+  // powers (two lanes of the last wave): work for the time the pass's loads take.
+  __device__ __forceinline__ void early(FoldLds& L, bool first) const {
+    if (first && threadIdx.x >= kBlock - 2) {
+      const int e = kBlock - 1 - (int)threadIdx.x;
+      L.pf[e] = pow((double)kbar + 2.0, e ? -0.6 : -0.3);
+    }
+    records_store<2>(p, L.a);
+    records_store<4>(q, L.b);
+  }
+  __device__ __forceinline__ void decide(const FoldIn& f, FoldLds& L, int iid, Inst* S, int prec, bool first) const {
+    __syncthreads();
+    if (threadIdx.x == 0 && S->status == kActive && S->precision == prec) {
+      double ps[2], qs[4];
+      records_total<2>(L.a, ps);
+      records_total<4>(L.b, qs);
+      // (the others only need to know whether the trial is accepted: any factors in (0, 1) do)
+      const double f2[2] = {first ? L.pf[0] : 0.5, first ? L.pf[1] : 0.5};
+      fin_ls_apply(*S, ps, qs, f2, first);
+    }
+    __syncthreads();
+    if (first) inst_copy_out(f.out + iid, S);
+  }
+};
+
+// The reflection parameter, in the primal pass of the next trial.
+struct FoldBeta {
+  double q[3];
+  __device__ __forceinline__ void load(const FoldIn& f, int iid, Inst* S) {
+    inst_copy_in(S, f.in + iid);
+    records_load<3>(f.rec_a, f.iblk_a[iid], f.iblk_a[iid + 1], q);
+  }
+  __device__ __forceinline__ void decide(const FoldIn& f, int iid, Inst* S, int prec, bool first) {
+    __shared__ double lq[kWavesPerBlock * 3];
+    records_store<3>(q, lq);
+    __syncthreads();
+    const bool mine = S->precision == prec;
+    if (threadIdx.x == 0 && S->status == kActive && S->last_acc != 0 && mine) {
+      double qs[3];
+      records_total<3>(lq, qs);
+      fin_beta_apply(*S, qs, first);
+    }
+    __syncthreads();
+    if (first && mine) inst_copy_out(f.out + iid, S);
+  }
+};
+
+// The last reflection parameter of a chunk: from inst2 back to inst.
+__global__ __launch_bounds__(kBlock) void k_fold_end(FoldIn f) {
+  __shared__ Inst S;
+  __shared__ double lq[kWavesPerBlock * 3];
+  const int iid = blockIdx.x;
+  if (f.out[iid].status != kActive) return;  // its record stayed there
+  double q[3];
+  inst_copy_in(&S, f.in + iid);
+  records_load<3>(f.rec_a, f.iblk_a[iid], f.iblk_a[iid + 1], q);
+  records_store<3>(q, lq);
+  __syncthreads();
+  if (threadIdx.x == 0 && S.status == kActive && S.last_acc != 0) {
+    double qs[3];
+    records_total<3>(lq, qs);
+    fin_beta_apply(S, qs, true);
+  }
+  __syncthreads();
+  inst_copy_out(f.out + iid, &S);
+}
+
 // K3: primal step over the columns of the instance.
 // The five passes of a trial are device functions of the workgroup's range or
 // instance, so that k_trials_wg can run them back to back inside one workgroup.
@@ -437,26 +680,23 @@ __global__ __launch_bounds__(kBlock) void k_proj_cone(int cone, int dim, const d
 // (elements past the end repeat the last one and are not stored).
 constexpr int kElems = 4;  // elements per thread of the passes over global memory
 template <typename T, int U>
-__device__ __forceinline__ void primal_body(int b, const Ranges& R, const IterPtrs<T>& it, const DataPtrs<T>& d,
-                                            Inst* inst, int prec, double* rec) {
-  __shared__ double lds[kWavesPerBlock * 2];
-  const Inst& I = inst[R.blk_inst[b]];
-  if (I.status != kActive || I.precision != prec) return;
-  const bool commit = I.pending != 0;
-  const bool avg = I.use_avg != 0;
-  const double ca = I.ca, cb = I.cb, beta = I.beta, etak = I.eta_k;
-  const double tau = I.eta / I.omega;
-  double acc[2] = {0.0, 0.0};
-  const int j1 = R.blk_end[b];
-  for (int j0 = R.blk_start[b] + (int)threadIdx.x; j0 < j1; j0 += U * kBlock) {
-    T x[U], g[U], xh[U], gh[U], xa[U], ga[U], sx[U], c[U], lo[U], hi[U];
+struct PrimalElems {
+  T x[U], g[U], xh[U], gh[U], xa[U], ga[U], sx[U], c[U], lo[U], hi[U];
+  __device__ __forceinline__ void load(const IterPtrs<T>& it, const DataPtrs<T>& d, int j0, int j1, bool commit,
+                                       bool avg) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int j = min(j0 + u * kBlock, j1 - 1);
       x[u] = it.x[j], g[u] = it.gty[j], c[u] = d.c[j], lo[u] = d.l[j], hi[u] = d.u[j];
       if (commit) xh[u] = it.xh[j], gh[u] = it.gtyh[j], xa[u] = it.xa[j], ga[u] = it.gtya[j];
-      if (commit && avg) sx[u] = it.sx[j];
+      if (avg) sx[u] = it.sx[j];
     }
+  }
+  __device__ __forceinline__ void step(const IterPtrs<T>& it, const Inst& I, int j0, int j1, double (&acc)[2]) const {
+    const bool commit = I.pending != 0;
+    const bool avg = I.use_avg != 0;
+    const double ca = I.ca, cb = I.cb, beta = I.beta, etak = I.eta_k;
+    const double tau = I.eta / I.omega;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int j = j0 + u * kBlock;
@@ -479,6 +719,48 @@ __device__ __forceinline__ void primal_body(int b, const Ranges& R, const IterPt
       acc[0] += dx * dx;
       acc[1] += cv * xn;
     }
+  }
+};
+
+template <typename T, int U>
+__device__ __forceinline__ void primal_body(int b, const Ranges& R, const IterPtrs<T>& it, const DataPtrs<T>& d,
+                                            Inst* inst, int prec, double* rec) {
+  __shared__ double lds[kWavesPerBlock * 2];
+  const Inst& I = inst[R.blk_inst[b]];
+  if (I.status != kActive || I.precision != prec) return;
+  const bool commit = I.pending != 0, avg = commit && I.use_avg != 0;
+  double acc[2] = {0.0, 0.0};
+  const int j1 = R.blk_end[b];
+  for (int j0 = R.blk_start[b] + (int)threadIdx.x; j0 < j1; j0 += U * kBlock) {
+    PrimalElems<T, U> e;
+    e.load(it, d, j0, j1, commit, avg);
+    e.step(it, I, j0, j1, acc);
+  }
+  block_sum_store<2>(acc, lds, rec + (size_t)b * 2);
+}
+
+// The primal pass of every trial but the first of a chunk, with the reflection
+// parameter of the trial before folded in.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_primal_fold(Ranges R, IterPtrs<T> it, DataPtrs<T> d, FoldIn f, int prec,
+                                                        double* __restrict__ rec) {
+  __shared__ double lds[kWavesPerBlock * 2];
+  __shared__ Inst S;
+  const int b = blockIdx.x, iid = R.blk_inst[b];
+  const int j1 = R.blk_end[b];
+  int j0 = R.blk_start[b] + (int)threadIdx.x;
+  FoldBeta fold;
+  fold.load(f, iid, &S);
+  PrimalElems<T, kElems> e;
+  e.load(it, d, min(j0, j1 - 1), j1, true, true);
+  fold.decide(f, iid, &S, prec, b == R.inst_blk0[iid]);
+  if (S.status != kActive || S.precision != prec) return;
+  const bool commit = S.pending != 0, avg = commit && S.use_avg != 0;
+  double acc[2] = {0.0, 0.0};
+  if (j0 < j1) e.step(it, S, j0, j1, acc);
+  for (j0 += kElems * kBlock; j0 < j1; j0 += kElems * kBlock) {
+    e.load(it, d, j0, j1, commit, avg);
+    e.step(it, S, j0, j1, acc);
   }
   block_sum_store<2>(acc, lds, rec + (size_t)b * 2);
 }
@@ -933,78 +1215,6 @@ __global__ __launch_bounds__(kBlock) void k_lam_epi(Ranges R, const T* __restric
   block_sum_store<3>(acc, lds, rec + (size_t)b * 3);
 }
 
-// F1: line-search decision of Function 2, one workgroup per instance.
-// pf: when non-null, pf[0] = (kbar + 1)^-0.3 and pf[1] = (kbar + 1)^-0.6 for the
-// kbar this trial reaches, computed beforehand by an otherwise idle thread
-__device__ __forceinline__ void fin_ls_body(int iid, const int32_t* iblk_p, const double* rec_p,
-                                            const int32_t* iblk_d, const double* rec_d, Inst* inst,
-                                            const double* pf = nullptr) {
-  __shared__ double lds[kWavesPerBlock * 4];
-  Inst& I = inst[iid];
-  if (I.status != kActive) return;
-  double p[2], q[4];
-  reduce_records<2, 2>(rec_p, iblk_p[iid], iblk_p[iid + 1], lds, p);
-  reduce_records<4, 4>(rec_d, iblk_d[iid], iblk_d[iid + 1], lds, q);
-  if (threadIdx.x != 0) return;
-  I.pending = 0;
-  I.check_due = 0;
-  I.kbar += 1;
-  if (I.precision == kFP64) I.fp64_iters += 1;
-  const double dx2 = p[0], dy2 = q[0], dydg = q[1];
-  const double omega = I.omega, eta = I.eta;
-  const double num = 0.5 * (omega * dx2 + dy2 / omega);
-  const double den = fabs(dydg);
-  const double etabar = den > 0.0 ? num / den : (double)INFINITY;
-  const double kb1 = (double)I.kbar + 1.0;
-  const double p3 = pf ? pf[0] : pow(kb1, -0.3), p6 = pf ? pf[1] : pow(kb1, -0.6);
-  const double eta_next = fmin((1.0 - p3) * etabar, (1.0 + p6) * eta);
-  const bool bad = !isfinite(num) || isnan(etabar) || isnan(q[2]) || isnan(q[3]) || isnan(p[1]) ||
-                   !(eta_next > 0.0) || !isfinite(eta_next);
-  if (I.trace && I.kbar <= I.trace_cap) {
-    double* tr = I.trace + (I.kbar - 1) * kTraceStride;
-    tr[0] = (double)I.kbar;
-    tr[1] = eta;
-    tr[2] = etabar;
-    tr[3] = dx2;
-    tr[4] = dy2;
-    tr[5] = dydg;
-    tr[6] = eta < etabar ? 1.0 : 0.0;
-    tr[7] = eta_next;
-    for (int f = 8; f < kTraceStride; ++f) tr[f] = NAN;
-    tr[9] = (double)I.k;
-    if (bad) {  // the failing trial's reductions, for diagnosis
-      tr[10] = p[1];
-      tr[11] = q[3];
-      tr[14] = q[2];
-    }
-  }
-  if (bad) {
-    I.status = kDone;
-    I.exit_code = 8;
-    I.last_acc = 0;
-    return;
-  }
-  if (eta < etabar) {
-    I.last_acc = 1;
-    I.eta_k = eta;
-    I.eta_hat = eta_next;
-    I.accepted += 1;
-    I.dx2 = dx2;
-    I.dy2 = dy2;
-    I.dydgdx = dydg;
-    I.errp2 = q[2];
-    I.hy = q[3];
-    I.cx = p[1];
-  } else {
-    I.last_acc = 0;
-    if (I.kbar >= I.max_iter) {
-      I.status = kDone;
-      I.exit_code = 1;
-    }
-  }
-  I.eta = eta_next;
-}
-
 __global__ __launch_bounds__(kBlock) void k_fin_ls(const int32_t* __restrict__ iblk_p,
                                                    const double* __restrict__ rec_p,
                                                    const int32_t* __restrict__ iblk_d,
@@ -1037,57 +1247,77 @@ __global__ __launch_bounds__(kBlock) void k_lam(RowBlocks rb, MatPtrs<TM> AT, It
   lam_body<T, TM>(blockIdx.x, rb, AT, it, d, inst, prec, rec);
 }
 
-// F2: reflection parameter at z_hat (eq. adaptive_reflection with the relative
-// errors of eq. tolerance-2), then schedule the Halpern commit.
-__device__ __forceinline__ void fin_beta_body(int iid, const int32_t* iblk_l, const double* rec_l, Inst* inst) {
-  __shared__ double lds[kWavesPerBlock * 3];
-  Inst& I = inst[iid];
-  if (I.status != kActive || I.last_acc == 0) return;
-  double q[3];
-  reduce_records<3, 3>(rec_l, iblk_l[iid], iblk_l[iid + 1], lds, q);
-  if (threadIdx.x != 0) return;
-  const double errp = sqrt(I.errp2), errd = sqrt(q[0]);
-  const double pobj = I.cx;
-  const double dobj = I.hy + q[1] - q[2];
-  const double gap = fabs(pobj - dobj);
-  const double rp = errp / (1.0 + I.h1);
-  const double rd = errd / (1.0 + I.c1);
-  const double rg = gap / (1.0 + fabs(pobj) + fabs(dobj));
-  const double me = fmax(rp, fmax(rd, rg));
-  if (isnan(me) || isnan(rp) || isnan(rd) || isnan(rg)) {
-    I.status = kDone;
-    I.exit_code = 8;
-    return;
-  }
-  const double beta = me > 0.0 ? clampd(-0.1 * log10(me) + 0.2, 0.0, 1.0) : 1.0;
-  if (I.trace && I.kbar <= I.trace_cap) {
-    double* tr = I.trace + (I.kbar - 1) * kTraceStride;
-    tr[8] = beta;
-    tr[10] = I.cx;
-    tr[11] = I.hy;
-    tr[12] = q[1];
-    tr[13] = q[2];
-    tr[14] = I.errp2;
-    tr[15] = q[0];
-  }
-  const double k = (double)I.k;
-  I.beta = beta;
-  I.ca = (k + 1.0) / (k + 2.0);
-  I.cb = 1.0 / (k + 2.0);
-  I.pending = 1;
-  I.sum_eta += I.eta_k;
-  I.k += 1;
-  I.check_due = (I.kbar % I.check_every) == 0 ? 1 : 0;
-  if (!I.check_due && I.kbar >= I.max_iter) {
-    I.status = kDone;
-    I.exit_code = 1;
-  }
-}
-
 __global__ __launch_bounds__(kBlock) void k_fin_beta(const int32_t* __restrict__ iblk_l,
                                                      const double* __restrict__ rec_l,
                                                      Inst* __restrict__ inst) {
   fin_beta_body(blockIdx.x, iblk_l, rec_l, inst);
+}
+
+// k_lam with the line-search decision folded in.
+template <typename T, typename TM>
+__global__ __launch_bounds__(kBlock) void k_lam_fold(RowBlocks rb, MatPtrs<TM> AT, IterPtrs<T> it, DataPtrs<T> d,
+                                                     FoldIn f, int prec, double* __restrict__ rec) {
+  __shared__ double lds[kRowBlockCap + kWavesPerBlock * 3];
+  __shared__ Inst S;
+  const int b = blockIdx.x, iid = rb.blk_inst[b];
+  __shared__ FoldLds L;
+  const bool first = b == rb.inst_blk0[iid];
+  FoldLs fold;
+  fold.load(f, iid, &S);
+  double acc[3] = {0.0, 0.0, 0.0};
+  bool live = false;
+  const T* const ys[1] = {it.yh};
+  block_rows<1>(rb.blk_row0[b], rb.blk_row1[b], AT.ptr, AT.idx, AT.val, ys, lds,
+                [&](int j) { return lam_load<T>(j, d); },
+                [&] { fold.early(L, first); },
+                [&] {
+                  fold.decide(f, L, iid, &S, prec, first);
+                  live = S.status == kActive && S.precision == prec && S.last_acc != 0;
+                },
+                [&](int j, const double* s, const LamCol<T>& o) {
+                  if (live) lam_epilogue<T>(j, s[0], it, o, acc);
+                });
+  if (!live) return;
+  __syncthreads();
+  block_sum_store<3>(acc, lds, rec + (size_t)b * 3);
+}
+
+// k_lam_epi with the line-search decision folded in.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_lam_epi_fold(Ranges R, const T* __restrict__ part, int P, int64_t N,
+                                                         IterPtrs<T> it, DataPtrs<T> d, FoldIn f, int prec,
+                                                         double* __restrict__ rec) {
+  __shared__ double lds[kWavesPerBlock * 3];
+  __shared__ Inst S;
+  const int b = blockIdx.x, iid = R.blk_inst[b];
+  __shared__ FoldLds L;
+  const bool first = b == R.inst_blk0[iid];
+  FoldLs fold;
+  fold.load(f, iid, &S);
+  double acc[3] = {0.0, 0.0, 0.0};
+  const int j1 = R.blk_end[b];
+  bool decided = false;
+  for (int e0 = R.blk_start[b]; e0 < j1; e0 += kElems * kBlock) {
+    const int q0 = e0 + (int)threadIdx.x;
+    LamCol<T> o[kElems];
+    double s[kElems];
+#pragma unroll
+    for (int u = 0; u < kElems; ++u) {
+      o[u] = lam_load<T>(min(q0 + u * kBlock, j1 - 1), d);
+      s[u] = 0.0;
+    }
+    if (!decided) fold.early(L, first);
+    window_sums<T, kElems>(part, P, N, q0, j1, s);
+    if (!decided) {
+      fold.decide(f, L, iid, &S, prec, first);
+      if (S.status != kActive || S.precision != prec || S.last_acc == 0) return;
+      decided = true;
+    }
+#pragma unroll
+    for (int u = 0; u < kElems; ++u)
+      if (q0 + u * kBlock < j1) lam_epilogue<T>(q0 + u * kBlock, s[u], it, o[u], acc);
+  }
+  block_sum_store<3>(acc, lds, rec + (size_t)b * 3);
 }
 
 // A chunk of K trials of one instance per workgroup (small instances, row
@@ -2897,6 +3127,50 @@ void launch_trial_part(const KernelCtx& k, hipStream_t s, int mask, int part) {
                                              split ? k.rec_lam_epi : k.rec_lam, k.inst);
 }
 
+// K trials with the finalizers folded into the passes (k.fold): the instance
+// records alternate between inst and inst2 and are back in inst at the end.
+template <typename T>
+static void launch_primal_fold_t(const KernelCtx& k, hipStream_t s, int prec, const IterPtrs<T>& it,
+                                 const DataPtrs<T>& d, const FoldIn& f) {
+  if (k.vcol.nblk > 0) k_primal_fold<T><<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, it, d, f, prec, k.rec_primal);
+}
+
+template <typename T>
+static void launch_lam_fold_t(const KernelCtx& k, hipStream_t s, int prec, const IterPtrs<T>& it, const DataPtrs<T>& d,
+                              const MatPtrs<T>& AT, T* part, const FoldIn& f) {
+  if (k.use_band) {
+    // (whether the trial is accepted is not known yet: the product runs either way)
+    launch_band_spmv<T>(k.band2, band_val<T>(k, 1), it.yh, part, k.N, k.inst, prec, 0, s);
+    if (k.vcol.nblk > 0)
+      k_lam_epi_fold<T><<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, part, k.band2.P, k.N, it, d, f, prec,
+                                                               k.rec_lam_epi);
+  } else if (k.bcol.nblk > 0) {
+    k_lam_fold<T, T><<<grid1(k.bcol.nblk), kBlock, 0, s>>>(k.bcol, AT, it, d, f, prec, k.rec_lam);
+  }
+}
+
+void launch_trials_fold(const KernelCtx& k, hipStream_t s, int mask, int K) {
+  const bool split = k.use_band != 0;
+  const FoldIn ls{k.vcol.inst_blk0, split ? k.vrow.inst_blk0 : k.brow.inst_blk0, k.rec_primal,
+                  split ? k.rec_dual_epi : k.rec_dual, k.inst, k.inst2};
+  const FoldIn beta{split ? k.vcol.inst_blk0 : k.bcol.inst_blk0, nullptr, split ? k.rec_lam_epi : k.rec_lam, nullptr,
+                    k.inst2, k.inst};
+  for (int t = 0; t < K; ++t) {
+    if (t == 0) {
+      launch_trial_part(k, s, mask, 0);
+    } else {
+      if (mask & 1) launch_primal_fold_t<float>(k, s, kFP32, k.it32, k.d32, beta);
+      if (mask & 2) launch_primal_fold_t<double>(k, s, kFP64, k.it64, k.d64, beta);
+    }
+    launch_trial_part(k, s, mask, 1);
+    if (mask & 1) launch_dual_epi_t<float>(k, s, kFP32, k.it32, k.d32, k.bpart32);
+    if (mask & 2) launch_dual_epi_t<double>(k, s, kFP64, k.it64, k.d64, k.bpart64);
+    if (mask & 1) launch_lam_fold_t<float>(k, s, kFP32, k.it32, k.d32, k.AT32, k.bpartT32, ls);
+    if (mask & 2) launch_lam_fold_t<double>(k, s, kFP64, k.it64, k.d64, k.AT64, k.bpartT64, ls);
+  }
+  if (K > 0) k_fold_end<<<grid1(k.nb), kBlock, 0, s>>>(beta);
+}
+
 // Dynamic LDS the LDS-resident chunk kernel can take: the device's LDS per
 // workgroup less the kernel's static LDS; the first call per precision also
 // raises the kernel's dynamic-LDS limit to that size.
@@ -2945,12 +3219,6 @@ void launch_trials_wg(const KernelCtx& k, hipStream_t s, int mask, int K) {
       k_trials_wg<double><<<k.nb, kBlock, 0, s>>>(k.vcol, k.brow, k.bcol, k.A64, k.AT64, k.it64, k.d64, k.inst, kFP64,
                                                   k.rec_primal, k.rec_dual, k.rec_lam, K);
   }
-}
-
-void launch_trial(const KernelCtx& k, hipStream_t s, int mask) {
-  launch_trial_part(k, s, mask, 0);
-  launch_trial_part(k, s, mask, 1);
-  launch_trial_part(k, s, mask, 2);
 }
 
 template <typename T>

@@ -80,7 +80,7 @@ struct KernelCtx {
   RowBlocks brow, bcol;  // the same structures in row blocks (iteration passes)
   Ranges vrow, vcol;  // elementwise passes over rows and columns
   Ranges crow, ccol;  // the multisection passes: kCheckCoarsen times larger blocks
-  Inst* inst;
+  Inst *inst, *inst2;  // inst2: the other copy of the records, for launch_trials_fold
   IterPtrs<float> it32;
   IterPtrs<double> it64;
   DataPtrs<float> d32;
@@ -112,6 +112,7 @@ struct KernelCtx {
   // k_trials_lds with this many bytes of dynamic LDS when nonzero
   int wg_trials;
   int lds_trials32, lds_trials64;
+  int fold;         // trials run by launch_trials_fold
   int lds_rowwise;  // every row of G and of G^T has at most kLdsRowMax entries: row-wise passes
 
   // the K1 (K2) product is split into partial sums plus an epilogue pass
@@ -140,7 +141,8 @@ struct SetupCtx {
 hipError_t band_raise_lds_limit();
 
 void launch_setup(const KernelCtx& k, const SetupCtx& su, hipStream_t s, int mask);
-void launch_trial(const KernelCtx& k, hipStream_t s, int mask);
+// K trials of every instance, the finalizers folded into the passes (k.fold)
+void launch_trials_fold(const KernelCtx& k, hipStream_t s, int mask, int K);
 // K trials of every instance, one workgroup per instance (k.wg_trials layouts)
 void launch_trials_wg(const KernelCtx& k, hipStream_t s, int mask, int K);
 // LDS left for the instance data of the LDS-resident chunk kernel (bytes)
