@@ -419,7 +419,7 @@ int  pdcs_batch_solve_device(pdcs_batch b, const pdcs_options* opts, const void*
  * among those timed. */
 int  pdcs_batch_autotune(pdcs_batch b, double time_budget_ms);
 /* Current schedule: iter_max (row-group iterations per wavefront tile),
- * block_nnz (nonzeros per workgroup), vec_per_block (elements per workgroup). */
+ * block_nnz (recorded; a workgroup's row block holds up to 2048 nonzeros), vec_per_block (elements per workgroup). */
 int  pdcs_batch_schedule(pdcs_batch b, int64_t* iter_max, int64_t* block_nnz,
                          int64_t* vec_per_block);
 int  pdcs_batch_set_schedule(pdcs_batch b, int64_t iter_max, int64_t block_nnz,

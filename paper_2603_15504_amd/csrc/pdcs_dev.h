@@ -84,18 +84,6 @@ constexpr int kTrendChecks = 3;  // consecutive checks the low-accuracy infeasib
 constexpr int kTraceStride = 16;  // kbar, eta, eta_bar, dx2, dy2, dy^T G dx, accepted, eta', beta, k,
                                   // then for accepted trials: c^T x_hat, h^T y_hat, sum l lam+, sum u lam-, err_p^2, err_d^2
 
-// Schedule of a CSR-like pass: wavefront tiles grouped into workgroup ranges.
-struct Tiles {
-  const int32_t* tile_row0;    // first row of the tile
-  const int32_t* tile_row1;    // one past the last row
-  const int32_t* tile_lg;      // log2(lanes per row)
-  const int32_t* blk_tile0;    // per workgroup: first tile
-  const int32_t* blk_tile1;    // per workgroup: one past the last tile
-  const int32_t* blk_inst;     // per workgroup: instance
-  const int32_t* inst_blk0;    // per instance: first workgroup (B+1 entries)
-  int32_t nblk;
-};
-
 // Row-block schedule of a CSR-like pass (one workgroup per block): either a
 // single row of any length, or several consecutive rows holding at most
 // kRowBlockCap nonzeros, which are staged as products in LDS.
@@ -371,54 +359,6 @@ __device__ __forceinline__ void records_total(const double* lds, double (&v)[NV]
   }
 }
 
-// Row-dot over a CSR row segment by a group of L lanes (lane li of the group),
-// FP64 accumulation, loads unrolled by 4 to keep several gathers in flight.
-template <typename TM, typename TV>
-__device__ __forceinline__ double row_dot(const int32_t* __restrict__ col, const TM* __restrict__ val,
-                                          const TV* __restrict__ x, int p0, int p1, int li, int L) {
-  double s = 0.0;
-  int p = p0 + li;
-  for (; p + 3 * L < p1; p += 4 * L) {
-    const int c0 = col[p], c1 = col[p + L], c2 = col[p + 2 * L], c3 = col[p + 3 * L];
-    const double v0 = (double)val[p], v1 = (double)val[p + L], v2 = (double)val[p + 2 * L],
-                 v3 = (double)val[p + 3 * L];
-    const double x0 = (double)x[c0], x1 = (double)x[c1], x2 = (double)x[c2], x3 = (double)x[c3];
-    s += v0 * x0;
-    s += v1 * x1;
-    s += v2 * x2;
-    s += v3 * x3;
-  }
-  for (; p < p1; p += L) s += (double)val[p] * (double)x[col[p]];
-  return s;
-}
-
-// As row_dot, but the matrix stream (indices and values, read once per pass)
-// uses non-temporal loads so that it does not evict the gathered vector from L2.
-template <typename TM, typename TV>
-__device__ __forceinline__ double row_dot_stream(const int32_t* __restrict__ col, const TM* __restrict__ val,
-                                                 const TV* __restrict__ x, int p0, int p1, int li, int L) {
-  double s = 0.0;
-  int p = p0 + li;
-  for (; p + 3 * L < p1; p += 4 * L) {
-    const int c0 = __builtin_nontemporal_load(col + p);
-    const int c1 = __builtin_nontemporal_load(col + p + L);
-    const int c2 = __builtin_nontemporal_load(col + p + 2 * L);
-    const int c3 = __builtin_nontemporal_load(col + p + 3 * L);
-    const double v0 = (double)__builtin_nontemporal_load(val + p);
-    const double v1 = (double)__builtin_nontemporal_load(val + p + L);
-    const double v2 = (double)__builtin_nontemporal_load(val + p + 2 * L);
-    const double v3 = (double)__builtin_nontemporal_load(val + p + 3 * L);
-    const double x0 = (double)x[c0], x1 = (double)x[c1], x2 = (double)x[c2], x3 = (double)x[c3];
-    s += v0 * x0;
-    s += v1 * x1;
-    s += v2 * x2;
-    s += v3 * x3;
-  }
-  for (; p < p1; p += L)
-    s += (double)__builtin_nontemporal_load(val + p) * (double)x[__builtin_nontemporal_load(col + p)];
-  return s;
-}
-
 // Products of entries [0, n) of a row block with NV vectors into LDS, n <= 256 U:
 // every index and value is requested before the first gather, and every gather
 // before the first product (entries past the end repeat the last one, whose LDS
@@ -570,12 +510,6 @@ __device__ __forceinline__ void block_rows(int r0, int r1, const int32_t* __rest
                                            const TV* const (&xs)[NV], double* lds, Fn&& fn) {
   block_rows<NV>(r0, r1, ptr, idx, val, xs, lds, [](int) { return NoRow{}; },
                  [&](int r, const double* s, const NoRow&) { fn(r, s); });
-}
-
-// Sum over the L-lane groups of a wavefront (L a power of two <= 64).
-__device__ __forceinline__ double group_sum(double s, int L) {
-  for (int off = L >> 1; off > 0; off >>= 1) s += __shfl_xor(s, off, kWave);
-  return s;
 }
 
 __device__ __forceinline__ double clampd(double v, double lo, double hi) {

@@ -61,18 +61,8 @@ struct HostProblem {
 // Tile schedule parameters (chosen by pdcs_batch_autotune or set explicitly).
 struct Schedule {
   int iter_max = 8;        // passes per lane group in a multi-row wavefront tile
-  int block_nnz = 8192;    // work units (nonzeros + 4 per row) per workgroup
+  int block_nnz = 8192;    // recorded (row blocks hold kRowBlockCap nonzeros)
   int vec_per_block = 1024;  // elements per workgroup in elementwise passes
-};
-
-struct TileSet {
-  DBuf row0, row1, lg, btile0, btile1, binst_d, iblk0_d;
-  int nblk = 0, ntiles = 0;
-  std::vector<int32_t> h_bt0, h_bt1, h_t0, h_t1, h_binst;
-  // active: optional per-instance mask; instances outside it get no workgroups
-  void build(const std::vector<int32_t>& ptr, const std::vector<int64_t>& inst_r0, const Schedule& s,
-             const std::vector<char>* active = nullptr);
-  Tiles view() const;
 };
 
 // Row blocks: a single row of any length, or consecutive rows with at most
@@ -121,6 +111,7 @@ struct BandSet {
   int P = 1;
   int ntile = 0, nslot = 0, slots = 1;
   int64_t R = 0, nent = 0;
+  DBuf tile0;  // first tile per instance
   DBuf group, slot, start, row0, nrows, used, tinst, col0, panel, run_start, run_row, run_ext, ext, pk, src;
   DBuf val32, val64, part32, part64, part64b;
   DBuf orig32, orig64;  // unscaled values (plain products), filled by Engine::prepare_plain
@@ -181,7 +172,6 @@ struct Engine {
   IterBufs<float> it32;
   IterBufs<double> it64;
   Schedule sched;
-  TileSet trow, tcol;
   RowBlockSet brow, bcol;
   SocTable soc;                // second-order-cone row blocks (absolute rows)
   RangeSet vrow, vcol;
@@ -213,6 +203,7 @@ struct Engine {
   void ensure_iter(int prec);
   bool fold_trials(bool band) const;
   KernelCtx ctx(int probe_passes) const;
+  SetupCtx setup_ctx(const pdcs_options& o);
   void enqueue_chunk(const KernelCtx& k, int mask, int64_t K, bool timed);
   void harvest_events();
   std::vector<struct pdcs_result_s*> solve(const pdcs_options& o, const WarmStart& ws);

@@ -148,107 +148,6 @@ void HostProblem::build(int64_t m_, int64_t n_, int64_t mz, const int64_t* row_p
 // ---------------------------------------------------------------------------
 // Schedules
 // ---------------------------------------------------------------------------
-static int lanes_for(int rows) {
-  int L = 64;
-  while (L > 1 && L * rows > 64) L >>= 1;
-  return L;
-}
-
-static int ilog2(int v) {
-  int r = 0;
-  while ((1 << r) < v) ++r;
-  return r;
-}
-
-// Wavefront tiles over the rows of a CSR structure (instance-aligned):
-// a row longer than 64 * iter_max is a tile of its own (the wavefront strides
-// over it); otherwise consecutive rows share a tile as long as each row's
-// group of lanes needs at most iter_max passes.  Tiles are then grouped into
-// workgroups of about block_work units (nonzeros plus 4 per row).
-void TileSet::build(const std::vector<int32_t>& ptr, const std::vector<int64_t>& inst_r0, const Schedule& s,
-                    const std::vector<char>* active) {
-  std::vector<int32_t> t0, t1, tlg, bt0, bt1, binst, iblk0;
-  const int64_t cap = 64LL * s.iter_max;
-  const int B = (int)inst_r0.size() - 1;
-  iblk0.push_back(0);
-  for (int b = 0; b < B; ++b) {
-    int64_t r = inst_r0[b];
-    const int64_t end = (active && !(*active)[b]) ? r : inst_r0[b + 1];
-    const size_t first = t0.size();
-    while (r < end) {
-      const int64_t len0 = ptr[r + 1] - ptr[r];
-      if (len0 > cap) {
-        t0.push_back((int32_t)r);
-        t1.push_back((int32_t)(r + 1));
-        tlg.push_back(6);
-        ++r;
-        continue;
-      }
-      const int64_t start = r;
-      int R = 0;
-      int64_t maxlen = 0;
-      while (r < end && R < 64) {
-        const int64_t len = ptr[r + 1] - ptr[r];
-        if (len > cap) break;
-        const int nR = R + 1;
-        const int64_t nmax = std::max(maxlen, len);
-        const int L = lanes_for(nR);
-        if ((nmax + L - 1) / L > s.iter_max) break;
-        R = nR;
-        maxlen = nmax;
-        ++r;
-      }
-      t0.push_back((int32_t)start);
-      t1.push_back((int32_t)r);
-      tlg.push_back(ilog2(lanes_for(R)));
-    }
-    size_t i = first;
-    const size_t tend = t0.size();
-    while (i < tend) {
-      size_t j = i;
-      int64_t acc = 0;
-      while (j < tend) {
-        const int64_t w = (int64_t)(ptr[t1[j]] - ptr[t0[j]]) + 4LL * (t1[j] - t0[j]);
-        if (j > i && acc + w > s.block_nnz) break;
-        acc += w;
-        ++j;
-      }
-      bt0.push_back((int32_t)i);
-      bt1.push_back((int32_t)j);
-      binst.push_back(b);
-      i = j;
-    }
-    iblk0.push_back((int32_t)bt0.size());
-  }
-  ntiles = (int)t0.size();
-  nblk = (int)bt0.size();
-  h_bt0 = bt0;
-  h_bt1 = bt1;
-  h_t0 = t0;
-  h_t1 = t1;
-  h_binst = binst;
-  upload(row0, t0);
-  upload(row1, t1);
-  upload(lg, tlg);
-  upload(btile0, bt0);
-  upload(btile1, bt1);
-  upload(binst_d, binst);
-  upload(iblk0_d, iblk0);
-}
-
-Tiles TileSet::view() const {
-  Tiles t;
-  t.tile_row0 = row0.as<int32_t>();
-  t.tile_row1 = row1.as<int32_t>();
-  t.tile_lg = lg.as<int32_t>();
-  t.blk_tile0 = btile0.as<int32_t>();
-  t.blk_tile1 = btile1.as<int32_t>();
-  t.blk_inst = binst_d.as<int32_t>();
-  t.inst_blk0 = iblk0_d.as<int32_t>();
-  t.nblk = nblk;
-  return t;
-}
-
 static int threads_per_row(int R) {
   int T = 64;
   while (T > 1 && T * R > 256) T >>= 1;
@@ -678,6 +577,10 @@ void BandSet::build(const std::vector<int64_t>& r0s, const std::vector<int64_t>&
         if (bb.ext[q] < bb.nrows[t] || bb.ext[q] >= bb.used[t]) fail("extra slot");
     }
   }
+  std::vector<int32_t> first(NB + 1, ntile);
+  for (int t = ntile - 1; t >= 0; --t) first[bb.tinst[t]] = t;
+  for (int b = NB - 1; b >= 0; --b) first[b] = std::min(first[b], first[b + 1]);
+  upload(tile0, first);
   upload(group, grp);
   upload(slot, sl);
   upload(start, bb.start);
@@ -706,7 +609,7 @@ void BandSet::reset() {
   slots = 1;
   R = nent = 0;
   band_rows = 0;
-  for (DBuf* d : {&group, &slot, &start, &row0, &nrows, &used, &tinst, &col0, &panel, &run_start, &run_row, &run_ext,
+  for (DBuf* d : {&tile0, &group, &slot, &start, &row0, &nrows, &used, &tinst, &col0, &panel, &run_start, &run_row, &run_ext,
                   &ext, &pk, &src, &val32, &val64, &part32, &part64, &part64b, &orig32, &orig64})
     d->release();
 }
@@ -854,8 +757,6 @@ void Engine::clear_graphs() {
 
 void Engine::build_iteration_schedules(const std::vector<char>* active) {
   clear_graphs();
-  trow.build(h_rp, row0, sched, active);
-  tcol.build(h_cp, col0, sched, active);
   brow.build(h_rp, row0, sched.iter_max * 4, active);
   bcol.build(h_cp, col0, sched.iter_max * 4, active);
   vrow.cone_cap = kConeBlocksPerRange;
@@ -913,7 +814,7 @@ void Engine::build_schedule() {
   rec_cand_r.alloc((size_t)vr * 14 * 8);
   rec_nc.alloc((size_t)vc * 3 * 8);
   rec_nr.alloc((size_t)vr * 3 * 8);
-  rec_nm.alloc((size_t)std::max(trow.nblk, 1) * 8);
+  rec_nm.alloc((size_t)std::max({brow.nblk, band1.ntile, 1}) * 8);
 }
 
 // Dynamic LDS of k_trials_lds for the largest instance, per precision (0 when
@@ -974,8 +875,6 @@ KernelCtx Engine::ctx(int probe_passes) const {
   k.nb = B;
   k.M = M;
   k.N = N;
-  k.trow = trow.view();
-  k.tcol = tcol.view();
   k.brow = brow.view();
   k.bcol = bcol.view();
   k.vrow = vrow.view();
@@ -1040,6 +939,45 @@ KernelCtx Engine::ctx(int probe_passes) const {
     k.bpartT64b = band2.part64b.as<double>();
   }
   return k;
+}
+
+// The set-up of a solve (no warm start).
+SetupCtx Engine::setup_ctx(const pdcs_options& o) {
+  SetupCtx su{};
+  su.precondition = o.use_preconditioner ? 1 : 0;
+  su.ruiz_iters = (int)o.ruiz_iters;
+  su.l2_pass = o.l2_pass ? 1 : 0;
+  su.A = MatPtrs<double>{d_rp.as<int32_t>(), d_ci.as<int32_t>(), d_v.as<double>()};
+  su.AT = MatPtrs<double>{d_cp.as<int32_t>(), d_ri.as<int32_t>(), d_vt.as<double>()};
+  su.c = d_c.as<double>();
+  su.l = d_l.as<double>();
+  su.u = d_u.as<double>();
+  su.h = d_h.as<double>();
+  su.val64 = val64.as<double>();
+  su.valT64 = valT64.as<double>();
+  su.val32 = val32.as<float>();
+  su.valT32 = valT32.as<float>();
+  su.d64m = DataMut{c64.as<double>(), l64.as<double>(), u64.as<double>(), h64.as<double>()};
+  su.d32m = DataMut32{c32.as<float>(), l32.as<float>(), u32.as<float>(), h32.as<float>()};
+  su.stat_r = stat_r.as<double>();
+  su.stat_c = stat_c.as<double>();
+  su.rec_nc = rec_nc.as<double>();
+  su.rec_nr = rec_nr.as<double>();
+  su.rec_nm = rec_nm.as<double>();
+  if (use_band) {
+    su.bsrc = band1.src.as<int32_t>();
+    su.bsrcT = band2.src.as<int32_t>();
+    su.bn = band1.nent;
+    su.bnT = band2.nent;
+    su.borig64 = band1.orig64.p && band2.orig64.p ? band1.orig64.as<double>() : nullptr;
+    su.borigT64 = band2.orig64.as<double>();
+    su.btile0 = band1.tile0.as<int32_t>();
+    su.bval64 = band1.val64.as<double>();
+    su.bval32 = band1.val32.as<float>();
+    su.bvalT64 = band2.val64.as<double>();
+    su.bvalT32 = band2.val32.as<float>();
+  }
+  return su;
 }
 
 static void validate_options(const pdcs_options& o) {
@@ -1257,39 +1195,9 @@ std::vector<pdcs_result> Engine::solve(const pdcs_options& o, const WarmStart& w
     if (nan_seen) throw Error(PDCS_ERR_INVALID_ARG, "NaN in the device warm start");
   }
   KernelCtx k = ctx(probe_passes);
-  SetupCtx su{};
-  su.precondition = o.use_preconditioner ? 1 : 0;
-  su.ruiz_iters = (int)o.ruiz_iters;
-  su.l2_pass = o.l2_pass ? 1 : 0;
-  su.A = MatPtrs<double>{d_rp.as<int32_t>(), d_ci.as<int32_t>(), d_v.as<double>()};
-  su.AT = MatPtrs<double>{d_cp.as<int32_t>(), d_ri.as<int32_t>(), d_vt.as<double>()};
-  su.c = d_c.as<double>();
-  su.l = d_l.as<double>();
-  su.u = d_u.as<double>();
-  su.h = d_h.as<double>();
-  su.val64 = val64.as<double>();
-  su.valT64 = valT64.as<double>();
-  su.val32 = val32.as<float>();
-  su.valT32 = valT32.as<float>();
-  su.d64m = DataMut{c64.as<double>(), l64.as<double>(), u64.as<double>(), h64.as<double>()};
-  su.d32m = DataMut32{c32.as<float>(), l32.as<float>(), u32.as<float>(), h32.as<float>()};
-  su.stat_r = stat_r.as<double>();
-  su.stat_c = stat_c.as<double>();
-  su.rec_nc = rec_nc.as<double>();
-  su.rec_nr = rec_nr.as<double>();
-  su.rec_nm = rec_nm.as<double>();
+  SetupCtx su = setup_ctx(o);
   su.x0 = dx0;
   su.y0 = dy0;
-  if (use_band) {
-    su.bsrc = band1.src.as<int32_t>();
-    su.bsrcT = band2.src.as<int32_t>();
-    su.bn = band1.nent;
-    su.bnT = band2.nent;
-    su.bval64 = band1.val64.as<double>();
-    su.bval32 = band1.val32.as<float>();
-    su.bvalT64 = band2.val64.as<double>();
-    su.bvalT32 = band2.val32.as<float>();
-  }
   launch_setup(k, su, stream, start_mask);
   HIP_OK(hipGetLastError());
 
@@ -1337,8 +1245,11 @@ std::vector<pdcs_result> Engine::solve(const pdcs_options& o, const WarmStart& w
       build_iteration_schedules(&act);
       // the automatic layout choice, made again for the instances still running:
       // few large tiles would leave most of the chip idle, compacted row blocks do not
+      const bool was_band = use_band && !band_suspended;
       if (layout == PDCS_LAYOUT_AUTO && soc.empty() && act_nnz < ((int64_t)1 << 22)) band_suspended = true;
       k = ctx(probe_passes);
+      // (the set-up of a band solve scales the entries of the band tiles only)
+      if (was_band && band_suspended) launch_scale_values(k, su, stream, nullptr);
       active_built = a32 + a64;
       compacted = true;
     }
@@ -2191,6 +2102,10 @@ void Engine::autotune(double budget_ms) {
   // set aside).
   const bool band = use_band;
   band_suspended = band;
+  if (band) {
+    launch_scale_values(ctx(7), setup_ctx(o), stream, nullptr);
+    HIP_OK(hipStreamSynchronize(stream));
+  }
   Schedule best = sched;
   double best_t = 1e300;
   for (const Cand& c : cands) {

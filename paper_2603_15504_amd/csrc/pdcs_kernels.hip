@@ -929,9 +929,26 @@ __device__ __forceinline__ bool prec_selects(const Inst& I, int mode, int prec) 
   return mode == kModeRay || I.precision == prec;
 }
 
-// One wave's band-tile t: part[panel * R + r] = sum over the tile's entries of
-// row r of val * x[col], values TV, gathered vector TX, accumulation and output TA.
-template <typename TV, typename TX, typename TA>
+// What a band-tile accumulates per row.
+struct SumProduct {
+  template <typename TA>
+  static __device__ __forceinline__ TA term(TA a, TA v, TA x) { return a + v * x; }
+  template <typename TA>
+  static __device__ __forceinline__ TA join(TA a, TA b) { return a + b; }
+};
+struct MaxProduct {  // of magnitudes, x >= 0
+  static __device__ __forceinline__ double term(double a, double v, double x) { return fmax(a, fabs(v) * x); }
+  static __device__ __forceinline__ double join(double a, double b) { return fmax(a, b); }
+};
+struct SumSquares {
+  static __device__ __forceinline__ double term(double a, double v, double x) { return a + (v * x) * (v * x); }
+  static __device__ __forceinline__ double join(double a, double b) { return a + b; }
+};
+
+// One wave's band-tile t: part[panel * R + r] = sum (or what OP joins) over the
+// tile's entries of row r of val * x[col], values TV, gathered vector TX,
+// accumulation and output TA.
+template <typename TV, typename TX, typename TA, class OP = SumProduct>
 __device__ __forceinline__ void band_tile_product(const BandTiles& bt, int t, TA* a, const TV* __restrict__ val,
                                                   const TX* __restrict__ x, TA* __restrict__ part, int64_t R) {
   constexpr int U = kBandUnroll;
@@ -988,7 +1005,7 @@ __device__ __forceinline__ void band_tile_product(const BandTiles& bt, int t, TA
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t sl = pA[u] & kSlotMask;
-      a[sl] = a[sl] + (TA)vA[u] * (TA)xA[u];
+      a[sl] = OP::term(a[sl], (TA)vA[u], (TA)xA[u]);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -1003,7 +1020,7 @@ __device__ __forceinline__ void band_tile_product(const BandTiles& bt, int t, TA
   for (int r = bt.run_start[t] + lane; r < bt.run_start[t + 1]; r += kWave) {
     const int row = bt.run_row[r];
     TA s = a[row];
-    for (int q = bt.run_ext[r]; q < bt.run_ext[r + 1]; ++q) s += a[bt.ext[q]];
+    for (int q = bt.run_ext[r]; q < bt.run_ext[r + 1]; ++q) s = OP::join(s, a[bt.ext[q]]);
     a[row] = s;
   }
   const int nr = bt.nrows[t];
@@ -2744,171 +2761,310 @@ __global__ void k_clear_pending(Inst* __restrict__ inst, int nb) {
 // Set-up: diagonal rescaling (Section 2.6), norms, start point
 // ===========================================================================
 
-// Per row of a CSR-like structure: max_j (D1_i |a_ij|) D2_j   (mode 0)
-// or sum_j ((D1_i a_ij) D2_j)^2 (mode 1).  For the transposed structure pass
-// swap=1, so that the row scale is indexed by the stored index.
-__global__ __launch_bounds__(kBlock) void k_scale_stat(Tiles tl, MatPtrs<double> A,
-                                                       const double* __restrict__ Drow,
-                                                       const double* __restrict__ Dcol, int swap,
-                                                       int mode, double* __restrict__ out) {
-  const int b = blockIdx.x;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
-  const int t1 = tl.blk_tile1[b];
-  for (int t = tl.blk_tile0[b] + wave; t < t1; t += kWavesPerBlock) {
-    const int r0 = tl.tile_row0[t], r1 = tl.tile_row1[t], lg = tl.tile_lg[t];
-    const int L = 1 << lg;
-    const int r = r0 + (lane >> lg);
-    const int li = lane & (L - 1);
-    double s = 0.0;
-    if (r < r1) {
-      const int p1 = A.ptr[r + 1];
-      for (int p = A.ptr[r] + li; p < p1; p += L) {
-        const int c = A.idx[p];
-        const double di = swap ? Drow[c] : Drow[r];
-        const double dj = swap ? Dcol[r] : Dcol[c];
-        if (mode == 0) {
-          s = fmax(s, (di * fabs(A.val[p])) * dj);
-        } else {
-          const double e = (di * A.val[p]) * dj;
-          s += e * e;
+// The scaling passes work on both sides at once: each computes, from the D1 and D2
+// of the pass before, every row's and every column's statistic -- max |D1_i a_ij D2_j|
+// (Ruiz, kScaleMax) or the sum of its squares (the 2-norm pass, kScaleSquares) --
+// and from it the new factor.  A statistic of 0 keeps the factor.
+enum { kScaleMax = 0, kScaleSquares = 1 };
+__device__ __forceinline__ double scaled_factor(double D, double stat, int mode) {
+  if (!(stat > 0.0)) return D;
+  return D / (mode == kScaleMax ? sqrt(stat) : sqrt(sqrt(stat)));
+}
+
+// One side of the matrix in row blocks: rows of G (own factor D1, the gathered one
+// D2) or columns (own D2, gathered D1).  An entry's scaled value is
+// (D1_i a_ij) D2_j on either side.
+struct ScaleSide {
+  RowBlocks rb;
+  const int32_t *ptr, *idx;
+  const double* val;
+  const double *own, *other;  // null: all ones
+  int cols;
+  __device__ __forceinline__ double entry(double o, double a, double g) const {
+    return cols ? (g * a) * o : (o * a) * g;
+  }
+};
+
+// Row block b of a side: the entries' values and gathered factors in LDS (a block of
+// several rows), then fn(row, own factor, first entry, end, lanes of the row, this
+// lane) per row, entries relative to the block; for a single row of any length,
+// fn1(row, own factor).  Latency bound like the trial products, and as they are
+// done: all indices, then all gathers in flight.
+template <class Fn, class Fn1>
+__device__ __forceinline__ void scale_block(const ScaleSide& S, int b, double (*lds)[kRowBlockCap], const Fn& fn,
+                                            const Fn1& fn1) {
+  const int r0 = S.rb.blk_row0[b], r1 = S.rb.blk_row1[b], R = r1 - r0;
+  const int q0 = S.ptr[r0], n = S.ptr[r1] - q0;
+  const int tid = threadIdx.x;
+  if (R == 1) {
+    fn1(r0, S.own ? S.own[r0] : 1.0);
+    return;
+  }
+  for (int i0 = 0; i0 < n; i0 += 4 * kBlock) {
+    int c[4];
+    double v[4], g[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = q0 + min(i0 + u * kBlock + tid, n - 1);
+      c[u] = S.idx[i];
+      v[u] = S.val[i];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) g[u] = S.other ? S.other[c[u]] : 1.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      lds[0][i0 + u * kBlock + tid] = v[u];
+      lds[1][i0 + u * kBlock + tid] = g[u];
+    }
+  }
+  __syncthreads();
+  int T = kWave;
+  while (T > 1 && T * R > kBlock) T >>= 1;
+  for (int g = tid / T; g < (R + kBlock / T - 1) / (kBlock / T) * (kBlock / T); g += kBlock / T) {
+    const int r = r0 + min(g, R - 1);
+    fn(r, S.own ? S.own[r] : 1.0, S.ptr[r] - q0, S.ptr[r + 1] - q0, T, tid & (T - 1), g < R);
+  }
+}
+
+// One scaling pass over row blocks: workgroups [0, a.rb.nblk) take the rows, the
+// others the columns.  (m = 2e4, n = 4e4, nnz = 3e5: a launch of 8.7 us where the two
+// statistics and the two updates were four of 18 + 18 + 4.6 + 4.6 us.)
+__global__ __launch_bounds__(kBlock) void k_scale_pass(ScaleSide a, ScaleSide c, int mode, double* __restrict__ D1o,
+                                                       double* __restrict__ D2o) {
+  __shared__ double lds[2][kRowBlockCap];
+  __shared__ double red[kWavesPerBlock];
+  const bool cols = (int)blockIdx.x >= a.rb.nblk;
+  const ScaleSide& S = cols ? c : a;
+  double* out = cols ? D2o : D1o;
+  const int b = (int)blockIdx.x - (cols ? a.rb.nblk : 0);
+  scale_block(
+      S, b, lds,
+      [&](int r, double own, int i0, int i1, int T, int li, bool live) {
+        double s = 0.0;
+        for (int i = i0 + li; i < i1; i += T) {
+          if (mode == kScaleMax) {
+            s = fmax(s, S.entry(own, fabs(lds[0][i]), lds[1][i]));
+          } else {
+            const double e = S.entry(own, lds[0][i], lds[1][i]);
+            s += e * e;
+          }
         }
-      }
+        for (int off = T >> 1; off > 0; off >>= 1) {
+          const double o = __shfl_xor(s, off, kWave);
+          s = mode == kScaleMax ? fmax(s, o) : s + o;
+        }
+        if (li == 0 && live) out[r] = scaled_factor(own, s, mode);
+      },
+      [&](int r, double own) {
+        double s = 0.0;
+        for (int q = S.ptr[r] + (int)threadIdx.x; q < S.ptr[r + 1]; q += kBlock) {
+          const double g = S.other ? S.other[S.idx[q]] : 1.0;
+          if (mode == kScaleMax) {
+            s = fmax(s, S.entry(own, fabs(S.val[q]), g));
+          } else {
+            const double e = S.entry(own, S.val[q], g);
+            s += e * e;
+          }
+        }
+        s = mode == kScaleMax ? wave_max(s) : wave_sum(s);
+        if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = s;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+          s = red[0];
+          for (int w = 1; w < kWavesPerBlock; ++w) s = mode == kScaleMax ? fmax(s, red[w]) : s + red[w];
+          out[r] = scaled_factor(own, s, mode);
+        }
+      });
+}
+
+// Scaled values of both sides in FP64 and FP32, and per row block of G the largest
+// magnitude (rec, may be null).
+__global__ __launch_bounds__(kBlock) void k_scale_values(ScaleSide a, ScaleSide c, double* __restrict__ v64,
+                                                         float* __restrict__ v32, double* __restrict__ vt64,
+                                                         float* __restrict__ vt32, double* __restrict__ rec) {
+  __shared__ double lds[2][kRowBlockCap];
+  __shared__ double red[kWavesPerBlock];
+  const bool cols = (int)blockIdx.x >= a.rb.nblk;
+  const ScaleSide& S = cols ? c : a;
+  double* o64 = cols ? vt64 : v64;
+  float* o32 = cols ? vt32 : v32;
+  const int b = (int)blockIdx.x - (cols ? a.rb.nblk : 0);
+  double big[1] = {0.0};
+  scale_block(
+      S, b, lds,
+      [&](int, double own, int i0, int i1, int T, int li, bool live) {
+        if (!live) return;
+        for (int i = i0 + li; i < i1; i += T) {  // (each entry read and written by one lane)
+          const double e = S.entry(own, lds[0][i], lds[1][i]);
+          lds[0][i] = e;
+          big[0] = fmax(big[0], fabs(e));
+        }
+      },
+      [&](int r, double own) {
+        for (int q = S.ptr[r] + (int)threadIdx.x; q < S.ptr[r + 1]; q += kBlock) {
+          const double e = S.entry(own, S.val[q], S.other ? S.other[S.idx[q]] : 1.0);
+          o64[q] = e;
+          o32[q] = (float)e;
+          big[0] = fmax(big[0], fabs(e));
+        }
+      });
+  const int r0 = S.rb.blk_row0[b], r1 = S.rb.blk_row1[b];
+  __syncthreads();
+  if (r1 - r0 > 1) {
+    const int q0 = S.ptr[r0], n = S.ptr[r1] - q0;
+    for (int i = threadIdx.x; i < n; i += kBlock) {
+      o64[q0 + i] = lds[0][i];
+      o32[q0 + i] = (float)lds[0][i];
     }
-    if (mode == 0) {
-      for (int off = L >> 1; off > 0; off >>= 1) s = fmax(s, __shfl_xor(s, off, kWave));
-    } else {
-      s = group_sum(s, L);
-    }
-    if (li == 0 && r < r1) out[r] = s;
   }
+  if (!cols && rec) block_summax_store<1, 0>(big, red, rec + b);
 }
 
-// D <- D / sqrt(stat) (Ruiz, mode 0) or D <- D / sqrt(sqrt(stat)) (L2, mode 1); 0 keeps D.
-__global__ void k_scale_update(double* __restrict__ D, const double* __restrict__ stat, int n, int mode) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double s = stat[i];
-  if (s > 0.0) {
-    const double r = mode == 0 ? sqrt(s) : sqrt(sqrt(s));
-    D[i] = D[i] / r;
-  }
+// The same passes on band tiles (problems that take them): the statistics by the
+// band kernel's sweep over the unscaled values in entry order, one launch for both
+// matrices, without their own factor, which the update applies to the windows'
+// results.  (Gathers from an L2 window instead of the whole vector: m = 2.5e5,
+// n = 5e5, nnz = 1.35e7: 157 us per side of a pass from the CSR, 138 us here for
+// both sides; m = 2e5, n = 5e5, nnz = 5e6: 49 per side, 63 here for both.)
+template <class OP>
+__global__ __launch_bounds__(kBandWaves * kWave) void k_scale_bands(BandTiles b1, const double* __restrict__ v1,
+                                                                    const double* __restrict__ D2,
+                                                                    double* __restrict__ part1, int64_t M, BandTiles b2,
+                                                                    const double* __restrict__ v2,
+                                                                    const double* __restrict__ D1,
+                                                                    double* __restrict__ part2, int64_t N) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
+  const bool second = (int)blockIdx.x >= b1.nslot;
+  const BandTiles& bt = second ? b2 : b1;
+  const int g = bt.slot[(int)blockIdx.x - (second ? b1.nslot : 0)];
+  if (g < 0) return;
+  const int w = threadIdx.x / kWave;
+  const int t = bt.group[g * kBandWaves + w];
+  if (t < 0) return;
+  double* acc = reinterpret_cast<double*>(dyn) + w * bt.slots;
+  if (second) band_tile_product<double, double, double, OP>(bt, t, acc, v2, D1, part2, N);
+  else band_tile_product<double, double, double, OP>(bt, t, acc, v1, D2, part1, M);
 }
 
-__global__ void k_fill(double* __restrict__ p, double v, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
+// D1 (elements [0, M)) and D2 (the next N) from the windows' statistics.
+__global__ void k_scale_bands_update(double* __restrict__ D1, const double* __restrict__ part1, int P1, int64_t M,
+                                     double* __restrict__ D2, const double* __restrict__ part2, int P2, int64_t N,
+                                     int mode) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= M + N) return;
+  const bool second = e >= M;
+  const int64_t i = second ? e - M : e, n = second ? N : M;
+  double* D = second ? D2 : D1;
+  const double* part = second ? part2 : part1;
+  const int P = second ? P2 : P1;
+  double s = part[i];
+  for (int p = 1; p < P; ++p) s = mode == kScaleMax ? fmax(s, part[(size_t)p * n + i]) : s + part[(size_t)p * n + i];
+  const double d = D[i];
+  D[i] = scaled_factor(d, mode == kScaleMax ? d * s : d * d * s, mode);
 }
 
-// Scaled values: a_hat = (D1_i a_ij) D2_j, FP64 and FP32 copies.
-__global__ __launch_bounds__(kBlock) void k_scale_vals(Tiles tl, MatPtrs<double> A,
-                                                       const double* __restrict__ Drow,
-                                                       const double* __restrict__ Dcol, int swap,
-                                                       int vmod, double* __restrict__ v64,
-                                                       float* __restrict__ v32) {
-  const int b = blockIdx.x;
+// Scaled band-entry values from the unscaled ones (in place where src == v64), and
+// per band-tile the largest magnitude.  A tile's own factors sit in LDS by slot.
+__device__ __forceinline__ void band_scale_tile(const BandTiles& bt, int t, bool cols, double* own,
+                                                const double* __restrict__ D_own, const double* __restrict__ D_other,
+                                                const double* src, double* v64, float* __restrict__ v32,
+                                                double* __restrict__ rec) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
-  const int t1 = tl.blk_tile1[b];
-  for (int t = tl.blk_tile0[b] + wave; t < t1; t += kWavesPerBlock) {
-    const int r0 = tl.tile_row0[t], r1 = tl.tile_row1[t], lg = tl.tile_lg[t];
-    const int L = 1 << lg;
-    const int r = r0 + (lane >> lg);
-    const int li = lane & (L - 1);
-    if (r < r1) {
-      const int rr = vmod > 0 ? r % vmod : r;  // panel-major structures: real row of virtual row r
-      const int p1 = A.ptr[r + 1];
-      for (int p = A.ptr[r] + li; p < p1; p += L) {
-        const int c = A.idx[p];
-        const double di = swap ? Drow[c] : Drow[rr];
-        const double dj = swap ? Dcol[rr] : Dcol[c];
-        const double e = (di * A.val[p]) * dj;
-        v64[p] = e;
-        v32[p] = (float)e;
-      }
+  const int nr = bt.nrows[t], r0 = bt.row0[t];
+  for (int i = lane; i < nr; i += kWave) own[i] = D_own[r0 + i];
+  if (lane == 0) own[bt.slots - 1] = 0.0;  // the padding's sink (its values are 0)
+  for (int r = bt.run_start[t] + lane; r < bt.run_start[t + 1]; r += kWave)
+    for (int q = bt.run_ext[r]; q < bt.run_ext[r + 1]; ++q) own[bt.ext[q]] = D_own[r0 + bt.run_row[r]];
+  const double* other = D_other + bt.col0[t];
+  double big = 0.0;
+  constexpr int U = 8;  // the padding makes whole groups of kBandUnroll
+  for (int e0 = bt.start[t] + lane; e0 < bt.start[t + 1]; e0 += U * kWave) {
+    uint32_t pk[U];
+    double v[U], g[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      pk[u] = bt.pk[e0 + u * kWave];
+      v[u] = src[e0 + u * kWave];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) g[u] = other[pk[u] >> kBandSlotBits];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double o = own[pk[u] & ((1u << kBandSlotBits) - 1u)];
+      const double e = cols ? (g[u] * v[u]) * o : (o * v[u]) * g[u];
+      v64[e0 + u * kWave] = e;
+      v32[e0 + u * kWave] = (float)e;
+      big = fmax(big, fabs(e));
     }
   }
+  big = wave_max(big);
+  if (rec && lane == 0) rec[t] = big;
 }
 
-// Rescaled vectors: c_hat = D2 c, l_hat = l / D2, u_hat = u / D2 (columns).
-__global__ __launch_bounds__(kBlock) void k_scale_cols(Ranges R, const double* __restrict__ c,
-                                                       const double* __restrict__ l,
-                                                       const double* __restrict__ u,
-                                                       const double* __restrict__ D2,
-                                                       DataMut d64, DataMut32 d32) {
-  const int b = blockIdx.x;
-  const int j1 = R.blk_end[b];
-  for (int j = R.blk_start[b] + (int)threadIdx.x; j < j1; j += kBlock) {
-    const double dj = D2[j];
-    const double cv = dj * c[j], lv = l[j] / dj, uv = u[j] / dj;
-    d64.c[j] = cv;
-    d64.l[j] = lv;
-    d64.u[j] = uv;
-    d32.c[j] = (float)cv;
-    d32.l[j] = (float)lv;
-    d32.u[j] = (float)uv;
-  }
+__global__ __launch_bounds__(kBandWaves * kWave) void k_scale_bands_values(BandTiles b1, const double* s1, double* v1,
+                                                                           float* __restrict__ f1, BandTiles b2,
+                                                                           const double* s2, double* v2,
+                                                                           float* __restrict__ f2,
+                                                                           const double* __restrict__ D1,
+                                                                           const double* __restrict__ D2,
+                                                                           double* __restrict__ rec) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
+  const bool second = (int)blockIdx.x >= b1.nslot;
+  const BandTiles& bt = second ? b2 : b1;
+  const int g = bt.slot[(int)blockIdx.x - (second ? b1.nslot : 0)];
+  if (g < 0) return;
+  const int w = threadIdx.x / kWave;
+  const int t = bt.group[g * kBandWaves + w];
+  if (t < 0) return;
+  double* own = reinterpret_cast<double*>(dyn) + w * bt.slots;
+  if (second) band_scale_tile(bt, t, true, own, D2, D1, s2, v2, f2, nullptr);
+  else band_scale_tile(bt, t, false, own, D1, D2, s1, v1, f1, rec);
 }
 
-__global__ __launch_bounds__(kBlock) void k_scale_rows(Ranges R, const double* __restrict__ h,
-                                                       const double* __restrict__ D1, DataMut d64,
-                                                       DataMut32 d32) {
-  const int b = blockIdx.x;
-  const int i1 = R.blk_end[b];
-  for (int i = R.blk_start[b] + (int)threadIdx.x; i < i1; i += kBlock) {
-    const double hv = D1[i] * h[i];
-    d64.h[i] = hv;
-    d32.h[i] = (float)hv;
-  }
+__global__ void k_fill(double* __restrict__ a, int64_t na, double* __restrict__ b, int64_t nb, double v) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < na) a[i] = v;
+  else if (i < na + nb) b[i - na] = v;
 }
 
-// Norm records over columns: |c_hat|_1, |c_hat|_2^2 (sums); |c|_inf (max).
-__global__ __launch_bounds__(kBlock) void k_norm_cols(Ranges R, const double* __restrict__ chat,
-                                                      const double* __restrict__ c,
-                                                      double* __restrict__ rec) {
+// Rescaled vectors and the records of their norms: columns (workgroups [0, rc.nblk))
+// c_hat = D2 c, l_hat = l / D2, u_hat = u / D2, with |c_hat|_1, |c_hat|_2^2 (sums) and
+// |c|_inf (max); rows h_hat = D1 h, with |h_hat|_1, |h_hat|_2^2 and |h|_inf.
+__global__ __launch_bounds__(kBlock) void k_scale_vectors(Ranges rc, Ranges rr, const double* __restrict__ c,
+                                                          const double* __restrict__ l, const double* __restrict__ u,
+                                                          const double* __restrict__ h, const double* __restrict__ D1,
+                                                          const double* __restrict__ D2, DataMut d64, DataMut32 d32,
+                                                          double* __restrict__ rec_c, double* __restrict__ rec_r) {
   __shared__ double lds[kWavesPerBlock * 3];
-  const int b = blockIdx.x;
+  const bool rows = (int)blockIdx.x >= rc.nblk;
+  const int b = (int)blockIdx.x - (rows ? rc.nblk : 0);
+  const Ranges& R = rows ? rr : rc;
   double acc[3] = {0.0, 0.0, 0.0};
-  const int j1 = R.blk_end[b];
-  for (int j = R.blk_start[b] + (int)threadIdx.x; j < j1; j += kBlock) {
-    const double v = chat[j];
+  const int e1 = R.blk_end[b];
+  for (int e = R.blk_start[b] + (int)threadIdx.x; e < e1; e += kBlock) {
+    double raw, v;
+    if (rows) {
+      raw = h[e];
+      v = D1[e] * raw;
+      d64.h[e] = v;
+      d32.h[e] = (float)v;
+    } else {
+      const double dj = D2[e];
+      raw = c[e];
+      v = dj * raw;
+      const double lv = l[e] / dj, uv = u[e] / dj;
+      d64.c[e] = v;
+      d64.l[e] = lv;
+      d64.u[e] = uv;
+      d32.c[e] = (float)v;
+      d32.l[e] = (float)lv;
+      d32.u[e] = (float)uv;
+    }
     acc[0] += fabs(v);
     acc[1] += v * v;
-    acc[2] = fmax(acc[2], fabs(c[j]));
+    acc[2] = fmax(acc[2], fabs(raw));
   }
-  block_summax_store<3, 2>(acc, lds, rec + (size_t)b * 3);
-}
-
-// Norm records over rows: |h_hat|_1, |h_hat|_2^2 (sums); |h|_inf (max).
-__global__ __launch_bounds__(kBlock) void k_norm_rows(Ranges R, const double* __restrict__ hhat,
-                                                      const double* __restrict__ h,
-                                                      double* __restrict__ rec) {
-  __shared__ double lds[kWavesPerBlock * 3];
-  const int b = blockIdx.x;
-  double acc[3] = {0.0, 0.0, 0.0};
-  const int i1 = R.blk_end[b];
-  for (int i = R.blk_start[b] + (int)threadIdx.x; i < i1; i += kBlock) {
-    const double v = hhat[i];
-    acc[0] += fabs(v);
-    acc[1] += v * v;
-    acc[2] = fmax(acc[2], fabs(h[i]));
-  }
-  block_summax_store<3, 2>(acc, lds, rec + (size_t)b * 3);
-}
-
-// max |G_hat_ij| per workgroup of the CSR schedule.
-__global__ __launch_bounds__(kBlock) void k_norm_mat(Tiles tl, const int32_t* __restrict__ ptr,
-                                                     const double* __restrict__ v64,
-                                                     double* __restrict__ rec) {
-  __shared__ double lds[kWavesPerBlock];
-  const int b = blockIdx.x;
-  double acc[1] = {0.0};
-  const int t0 = tl.blk_tile0[b], t1 = tl.blk_tile1[b];
-  if (t1 > t0) {
-    const int p0 = ptr[tl.tile_row0[t0]], p1 = ptr[tl.tile_row1[t1 - 1]];
-    for (int p = p0 + (int)threadIdx.x; p < p1; p += kBlock) acc[0] = fmax(acc[0], fabs(v64[p]));
-  }
-  block_summax_store<1, 0>(acc, lds, rec + b);
+  block_summax_store<3, 2>(acc, lds, (rows ? rec_r : rec_c) + (size_t)b * 3);
 }
 
 // Per-instance set-up of the scalars from the norm records (Algorithm 1
@@ -2916,7 +3072,8 @@ __global__ __launch_bounds__(kBlock) void k_norm_mat(Tiles tl, const int32_t* __
 // initialization of Section 2.5).
 __global__ __launch_bounds__(kBlock) void k_init_inst(Ranges rc, const double* __restrict__ rec_c,
                                                       Ranges rr, const double* __restrict__ rec_r,
-                                                      Tiles tr, const double* __restrict__ rec_m,
+                                                      const int32_t* __restrict__ iblk_m,
+                                                      const double* __restrict__ rec_m,
                                                       Inst* __restrict__ inst) {
   __shared__ double lds[kWavesPerBlock * 3];
   const int iid = blockIdx.x;
@@ -2924,7 +3081,7 @@ __global__ __launch_bounds__(kBlock) void k_init_inst(Ranges rc, const double* _
   double cs[3], rs[3], ms[1];
   reduce_records<3, 2>(rec_c, rc.inst_blk0[iid], rc.inst_blk0[iid + 1], lds, cs);
   reduce_records<3, 2>(rec_r, rr.inst_blk0[iid], rr.inst_blk0[iid + 1], lds, rs);
-  reduce_records<1, 0>(rec_m, tr.inst_blk0[iid], tr.inst_blk0[iid + 1], lds, ms);
+  reduce_records<1, 0>(rec_m, iblk_m[iid], iblk_m[iid + 1], lds, ms);
   if (threadIdx.x != 0) return;
   I.c1 = cs[0];
   I.c2 = sqrt(cs[1]);
@@ -3063,7 +3220,10 @@ static void launch_band_cand(const BandTiles& bt, const double* val, const TX* x
 // wave on the current device.
 hipError_t band_raise_lds_limit() {
   const void* const fns[] = {reinterpret_cast<const void*>(&k_band_spmv<float>), reinterpret_cast<const void*>(&k_band_spmv<double>),
-                             reinterpret_cast<const void*>(&k_band_cand<float>), reinterpret_cast<const void*>(&k_band_cand<double>)};
+                             reinterpret_cast<const void*>(&k_band_cand<float>), reinterpret_cast<const void*>(&k_band_cand<double>),
+                             reinterpret_cast<const void*>(&k_scale_bands<MaxProduct>),
+                             reinterpret_cast<const void*>(&k_scale_bands<SumSquares>),
+                             reinterpret_cast<const void*>(&k_scale_bands_values)};
   for (const void* f : fns) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kBandWaves * kBandSlots * 8);
     if (e != hipSuccess) return e;
@@ -3413,47 +3573,64 @@ void launch_flush_commit(const KernelCtx& k, hipStream_t s, int mask) {
 }
 
 // ---- set-up ----
+static ScaleSide scale_side(const KernelCtx& k, const SetupCtx& su, int cols, const double* D1, const double* D2) {
+  return cols ? ScaleSide{k.bcol, su.AT.ptr, su.AT.idx, su.AT.val, D2, D1, 1}
+              : ScaleSide{k.brow, su.A.ptr, su.A.idx, su.A.val, D1, D2, 0};
+}
+
+void launch_scale_values(const KernelCtx& k, const SetupCtx& su, hipStream_t s, double* rec) {
+  const unsigned nblk = (unsigned)(k.brow.nblk + k.bcol.nblk);
+  if (nblk > 0)
+    k_scale_values<<<nblk, kBlock, 0, s>>>(scale_side(k, su, 0, k.D1, k.D2), scale_side(k, su, 1, k.D1, k.D2), su.val64,
+                                           su.val32, su.valT64, su.valT32, rec);
+}
+
 void launch_setup(const KernelCtx& k, const SetupCtx& su, hipStream_t s, int mask) {
   const int tpb = 256;
   auto blocks = [&](int64_t n) { return dim3((unsigned)((n + tpb - 1) / tpb)); };
-  if (k.M > 0) k_fill<<<blocks(k.M), tpb, 0, s>>>(k.D1, 1.0, k.M);
-  if (k.N > 0) k_fill<<<blocks(k.N), tpb, 0, s>>>(k.D2, 1.0, k.N);
-  if (su.precondition) {
-    for (int it = 0; it < su.ruiz_iters; ++it) {
-      if (k.trow.nblk > 0)
-        k_scale_stat<<<grid1(k.trow.nblk), kBlock, 0, s>>>(k.trow, su.A, k.D1, k.D2, 0, 0, su.stat_r);
-      if (k.tcol.nblk > 0)
-        k_scale_stat<<<grid1(k.tcol.nblk), kBlock, 0, s>>>(k.tcol, su.AT, k.D1, k.D2, 1, 0, su.stat_c);
-      if (k.M > 0) k_scale_update<<<blocks(k.M), tpb, 0, s>>>(k.D1, su.stat_r, (int)k.M, 0);
-      if (k.N > 0) k_scale_update<<<blocks(k.N), tpb, 0, s>>>(k.D2, su.stat_c, (int)k.N, 0);
-    }
-    if (su.l2_pass) {
-      if (k.trow.nblk > 0)
-        k_scale_stat<<<grid1(k.trow.nblk), kBlock, 0, s>>>(k.trow, su.A, k.D1, k.D2, 0, 1, su.stat_r);
-      if (k.tcol.nblk > 0)
-        k_scale_stat<<<grid1(k.tcol.nblk), kBlock, 0, s>>>(k.tcol, su.AT, k.D1, k.D2, 1, 1, su.stat_c);
-      if (k.M > 0) k_scale_update<<<blocks(k.M), tpb, 0, s>>>(k.D1, su.stat_r, (int)k.M, 1);
-      if (k.N > 0) k_scale_update<<<blocks(k.N), tpb, 0, s>>>(k.D2, su.stat_c, (int)k.N, 1);
-    }
-  }
-  if (k.trow.nblk > 0)
-    k_scale_vals<<<grid1(k.trow.nblk), kBlock, 0, s>>>(k.trow, su.A, k.D1, k.D2, 0, 0, su.val64, su.val32);
-  if (k.tcol.nblk > 0)
-    k_scale_vals<<<grid1(k.tcol.nblk), kBlock, 0, s>>>(k.tcol, su.AT, k.D1, k.D2, 1, 0, su.valT64, su.valT32);
+  const int passes = su.precondition ? su.ruiz_iters + (su.l2_pass ? 1 : 0) : 0;
   if (k.use_band) {
-    if (su.bn > 0)
-      k_band_vals<<<blocks(su.bn), tpb, 0, s>>>(su.bsrc, su.bn, su.val64, su.bval64, su.bval32);
-    if (su.bnT > 0)
-      k_band_vals<<<blocks(su.bnT), tpb, 0, s>>>(su.bsrcT, su.bnT, su.valT64, su.bvalT64, su.bvalT32);
+    k_fill<<<blocks(k.M + k.N), tpb, 0, s>>>(k.D1, k.M, k.D2, k.N, 1.0);
+    const unsigned slots = (unsigned)(k.band1.nslot + k.band2.nslot);
+    const size_t lds = (size_t)kBandWaves * std::max(k.band1.slots, k.band2.slots) * 8;
+    const double *v1 = su.borig64, *v2 = su.borigT64;
+    if (!v1) {  // a batch keeps no unscaled values in entry order: they pass through the scaled ones' place
+      if (su.bn > 0) launch_band_vals(su.bsrc, su.bn, su.A.val, su.bval64, su.bval32, s);
+      if (su.bnT > 0) launch_band_vals(su.bsrcT, su.bnT, su.AT.val, su.bvalT64, su.bvalT32, s);
+      v1 = su.bval64, v2 = su.bvalT64;
+    }
+    if (slots > 0) {
+      for (int i = 0; i < passes; ++i) {
+        const int mode = i < su.ruiz_iters ? kScaleMax : kScaleSquares;
+        if (mode == kScaleMax)
+          k_scale_bands<MaxProduct><<<slots, kBandWaves * kWave, lds, s>>>(k.band1, v1, k.D2, k.bpart64, k.M, k.band2, v2,
+                                                                           k.D1, k.bpartT64, k.N);
+        else
+          k_scale_bands<SumSquares><<<slots, kBandWaves * kWave, lds, s>>>(k.band1, v1, k.D2, k.bpart64, k.M, k.band2, v2,
+                                                                           k.D1, k.bpartT64, k.N);
+        k_scale_bands_update<<<blocks(k.M + k.N), tpb, 0, s>>>(k.D1, k.bpart64, k.band1.P, k.M, k.D2, k.bpartT64,
+                                                               k.band2.P, k.N, mode);
+      }
+      k_scale_bands_values<<<slots, kBandWaves * kWave, lds, s>>>(k.band1, v1, su.bval64, su.bval32, k.band2, v2,
+                                                                  su.bvalT64, su.bvalT32, k.D1, k.D2, su.rec_nm);
+    }
+  } else {
+    const unsigned nblk = (unsigned)(k.brow.nblk + k.bcol.nblk);
+    if (passes == 0) k_fill<<<blocks(k.M + k.N), tpb, 0, s>>>(k.D1, k.M, k.D2, k.N, 1.0);
+    double *d1[2] = {k.D1, su.stat_r}, *d2[2] = {k.D2, su.stat_c};  // the last pass writes D1, D2
+    for (int i = 0; i < passes; ++i) {
+      const int to = (passes - 1 - i) & 1;
+      k_scale_pass<<<nblk, kBlock, 0, s>>>(
+          scale_side(k, su, 0, i ? d1[!to] : nullptr, i ? d2[!to] : nullptr),
+          scale_side(k, su, 1, i ? d1[!to] : nullptr, i ? d2[!to] : nullptr),
+          i < su.ruiz_iters ? kScaleMax : kScaleSquares, d1[to], d2[to]);
+    }
+    launch_scale_values(k, su, s, su.rec_nm);
   }
-  if (k.vcol.nblk > 0)
-    k_scale_cols<<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, su.c, su.l, su.u, k.D2, su.d64m, su.d32m);
-  if (k.vrow.nblk > 0)
-    k_scale_rows<<<grid1(k.vrow.nblk), kBlock, 0, s>>>(k.vrow, su.h, k.D1, su.d64m, su.d32m);
-  if (k.vcol.nblk > 0) k_norm_cols<<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, su.d64m.c, su.c, su.rec_nc);
-  if (k.vrow.nblk > 0) k_norm_rows<<<grid1(k.vrow.nblk), kBlock, 0, s>>>(k.vrow, su.d64m.h, su.h, su.rec_nr);
-  if (k.trow.nblk > 0) k_norm_mat<<<grid1(k.trow.nblk), kBlock, 0, s>>>(k.trow, su.A.ptr, su.val64, su.rec_nm);
-  k_init_inst<<<grid1(k.nb), kBlock, 0, s>>>(k.vcol, su.rec_nc, k.vrow, su.rec_nr, k.trow, su.rec_nm, k.inst);
+  k_scale_vectors<<<grid1(k.vcol.nblk + k.vrow.nblk), kBlock, 0, s>>>(k.vcol, k.vrow, su.c, su.l, su.u, su.h, k.D1, k.D2,
+                                                                      su.d64m, su.d32m, su.rec_nc, su.rec_nr);
+  k_init_inst<<<grid1(k.nb), kBlock, 0, s>>>(k.vcol, su.rec_nc, k.vrow, su.rec_nr,
+                                             k.use_band ? su.btile0 : k.brow.inst_blk0, su.rec_nm, k.inst);
   // start point and its products
   if (mask & 1) {
     if (k.vcol.nblk > 0)

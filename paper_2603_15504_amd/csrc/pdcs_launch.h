@@ -76,8 +76,7 @@ __host__ __device__ inline LdsLayout lds_layout(int64_t m, int64_t n, int64_t nn
 struct KernelCtx {
   int nb;
   int64_t M, N;
-  Tiles trow, tcol;   // CSR of G (rows) and of G^T (columns): wavefront tiles (set-up passes)
-  RowBlocks brow, bcol;  // the same structures in row blocks (iteration passes)
+  RowBlocks brow, bcol;  // CSR of G (rows) and of G^T (columns) in row blocks
   Ranges vrow, vcol;  // elementwise passes over rows and columns
   Ranges crow, ccol;  // the multisection passes: kCheckCoarsen times larger blocks
   Inst *inst, *inst2;  // inst2: the other copy of the records, for launch_trials_fold
@@ -133,6 +132,8 @@ struct SetupCtx {
   // band-tile values: entry e takes the scaled CSR (CSC) value at src[e] (-1: padding)
   const int32_t *bsrc, *bsrcT;
   int64_t bn, bnT;
+  const double *borig64, *borigT64;  // unscaled values in entry order, or null
+  const int32_t* btile0;             // band1: first tile per instance (nb + 1)
   double *bval64, *bvalT64;
   float *bval32, *bvalT32;
 };
@@ -141,6 +142,8 @@ struct SetupCtx {
 hipError_t band_raise_lds_limit();
 
 void launch_setup(const KernelCtx& k, const SetupCtx& su, hipStream_t s, int mask);
+// The scaled CSR and CSC values under the current D1, D2 (rec: the row blocks' largest magnitudes, or null)
+void launch_scale_values(const KernelCtx& k, const SetupCtx& su, hipStream_t s, double* rec);
 // K trials of every instance, the finalizers folded into the passes (k.fold)
 void launch_trials_fold(const KernelCtx& k, hipStream_t s, int mask, int K);
 // K trials of every instance, one workgroup per instance (k.wg_trials layouts)
