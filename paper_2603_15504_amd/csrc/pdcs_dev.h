@@ -144,7 +144,7 @@ struct BandTiles {
 // Row ranges never split a cone block: the blocks inside range b are
 // [blk_soc0[b], blk_soc1[b]) of the table (soc_r0: first row, soc_dim:
 // dimension, soc_kind: 0 second-order cone, 1 exponential cone, 2 dual
-// exponential cone); all five are null when no instance has cone blocks.
+// exponential cone; second-order cones first); all six are null when no instance has cone blocks.
 struct Ranges {
   const int32_t* blk_start;
   const int32_t* blk_end;
@@ -152,6 +152,7 @@ struct Ranges {
   const int32_t* inst_blk0;    // per instance: first workgroup (B+1 entries)
   const int32_t* blk_soc0;
   const int32_t* blk_soc1;
+  const int32_t* blk_exp0;     // first exponential cone of the range (blk_soc1 when none)
   const int32_t* soc_r0;
   const int32_t* soc_dim;
   const int8_t* soc_kind;

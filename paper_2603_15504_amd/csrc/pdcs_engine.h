@@ -86,11 +86,12 @@ struct SocTable {
 };
 
 struct RangeSet {
-  DBuf start, end, binst_d, iblk0_d, soc0_d, soc1_d;
+  DBuf start, end, binst_d, iblk0_d, soc0_d, soc1_d, exp0_d;
   int nblk = 0;
   std::vector<int32_t> h_iblk0;  // host copy: instance -> first block
   const SocTable* soc = nullptr;  // set for row ranges that must not split cone blocks
-  int cone_cap = 1;               // at most this many cone blocks per range
+  int cone_cap = 1;               // at most this many cone blocks per range, an exponential cone
+                                  // counting for 1 / kExpPerSoc of one
   void build(const std::vector<int64_t>& inst_off, int per_block, const std::vector<char>* active = nullptr);
   Ranges view() const;
 };

@@ -219,7 +219,7 @@ RowBlocks RowBlockSet::view() const {
 }
 
 void RangeSet::build(const std::vector<int64_t>& inst_off, int per_block, const std::vector<char>* active) {
-  std::vector<int32_t> st, en, bi, iblk0, s0, s1;
+  std::vector<int32_t> st, en, bi, iblk0, s0, s1, x0;
   const int B = (int)inst_off.size() - 1;
   const bool cones = soc && !soc->empty();
   size_t q = 0;  // next cone block (cone blocks are in row order)
@@ -232,17 +232,21 @@ void RangeSet::build(const std::vector<int64_t>& inst_off, int per_block, const 
     while (s < stop) {
       int64_t e = std::min<int64_t>(s + per_block, stop);
       const size_t q0 = q;
+      size_t qe = q;  // past the second-order cones (an instance's first)
       if (cones) {
         // a range ends at a cone block boundary: blocks starting inside it are
         // taken whole, and a range that reaches a block's rows takes the block;
         // a range holds at most cone_cap blocks, so that the blocks' tasks
         // spread over the waves of many workgroups
+        int weight = 0;
         while (q < soc->r0.size() && soc->r0[q] < e && soc->r0[q] < stop) {
-          if (q - q0 == (size_t)cone_cap) {
+          weight += soc->kind[q] == 0 ? kExpPerSoc : 1;
+          if (weight > cone_cap * kExpPerSoc) {
             e = soc->r0[q];
             break;
           }
           e = std::max<int64_t>(e, (int64_t)soc->r0[q] + soc->dim[q]);
+          if (soc->kind[q] == 0) qe = q + 1;
           ++q;
         }
       }
@@ -251,6 +255,7 @@ void RangeSet::build(const std::vector<int64_t>& inst_off, int per_block, const 
       bi.push_back(b);
       s0.push_back((int32_t)q0);
       s1.push_back((int32_t)q);
+      x0.push_back((int32_t)qe);
       s = e;
     }
     if (cones)  // cone blocks of an inactive instance
@@ -266,9 +271,11 @@ void RangeSet::build(const std::vector<int64_t>& inst_off, int per_block, const 
   if (cones) {
     upload(soc0_d, s0);
     upload(soc1_d, s1);
+    upload(exp0_d, x0);
   } else {
     soc0_d.release();
     soc1_d.release();
+    exp0_d.release();
   }
 }
 
@@ -281,6 +288,7 @@ Ranges RangeSet::view() const {
   const bool cones = soc && !soc->empty() && soc0_d.p;
   r.blk_soc0 = cones ? soc0_d.as<int32_t>() : nullptr;
   r.blk_soc1 = cones ? soc1_d.as<int32_t>() : nullptr;
+  r.blk_exp0 = cones ? exp0_d.as<int32_t>() : nullptr;
   r.soc_r0 = cones ? soc->r0_d.as<int32_t>() : nullptr;
   r.soc_dim = cones ? soc->dim_d.as<int32_t>() : nullptr;
   r.soc_kind = cones ? soc->kind_d.as<int8_t>() : nullptr;

@@ -24,6 +24,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace pdcs {
 
@@ -309,17 +310,21 @@ __device__ __forceinline__ bool exp_wave_pick(double bd, double b0, double b1, d
   return true;
 }
 
-// Projection of v onto F K_exp, F = diag(f) > 0, by one wave (every lane gets
-// the result).  v itself if v / f is in K_exp; 0 if -F v is in K_exp* (the
+// Projection of v onto F K_exp, F = diag(f) > 0, for a point each of whose lanes
+// is its own: v itself if v / f is in K_exp; 0 if -F v is in K_exp* (the
 // polar cone); the clip onto the face {(x, 0, z): x <= 0, z >= 0} if -F times
 // its residual is in K_exp* up to rounding (then the clip is within rounding
 // of the projection: this takes the points whose projection lies on a ray
-// so far out that it meets the face's edge to working precision); otherwise,
-// among the face's clip and the
-// best points of the rays s F a(r): the local maxima of the angle along the
-// rays (+ to - sign changes of exp_ray_turn) and, for rays below the scanned
-// range, whose third coordinate is then below e^-300 of the others, the ray
-// through v's own x / y, r = (v_1 / f_1) / (v_2 / f_2).  A first scan on a
+// so far out that it meets the face's edge to working precision); otherwise
+// the point of the ray at the root of the slope that carries the projection's
+// certificate (exp_lane), and where a lane finds none, the wave's scan for that
+// lane (exp_scan_wave).
+
+// The projection among the face's clip and the best points of the rays
+// s F a(r), by one wave: the local maxima of the angle along the rays (+ to -
+// sign changes of exp_ray_turn) and, for rays below the scanned range, whose
+// third coordinate is then below e^-300 of the others, the ray through v's own
+// x / y, r = (v_1 / f_1) / (v_2 / f_2).  A first scan on a
 // coarse grid (step 0.4 over |r| <= 307.2) ends the search when a candidate
 // carries the projection's certificate; else a scan on a fine grid (step
 // 0.05 over |r| <= 300.8) takes a certified candidate if one turns up, else
@@ -327,30 +332,17 @@ __device__ __forceinline__ bool exp_wave_pick(double bd, double b0, double b1, d
 // scanned range the rays lie within e^-300 of the face's edge (0, 0, 1).
 constexpr double kExpTail = -300.0;
 
-__device__ __forceinline__ void exp_proj_wave(const double (&v)[3], const double (&f)[3], double (&p)[3]) {
-  ExpPoint P;
-  for (int i = 0; i < 3; ++i) P.v[i] = v[i], P.f[i] = f[i], P.fi[i] = 1.0 / f[i];
-  if (exp_cone_has(v[0] / f[0], v[1] / f[1], v[2] / f[2])) {
-    p[0] = v[0], p[1] = v[1], p[2] = v[2];
-    return;
-  }
-  if (exp_dual_has(-f[0] * v[0], -f[1] * v[1], -f[2] * v[2])) {
-    p[0] = p[1] = p[2] = 0.0;
-    return;
-  }
-  const double face[3] = {fmin(v[0], 0.0), 0.0, fmax(v[2], 0.0)};
-  if (exp_dual_near(-f[0] * (v[0] - face[0]), -f[1] * v[1], -f[2] * (v[2] - face[2]))) {
-    p[0] = face[0], p[1] = face[1], p[2] = face[2];
-    return;
-  }
-  const double face_d = (v[0] - face[0]) * (v[0] - face[0]) + v[1] * v[1] + (v[2] - face[2]) * (v[2] - face[2]);
-  const bool tail = v[0] < 0.0 && v[1] > 0.0 && (v[0] * P.fi[0]) / (v[1] * P.fi[1]) < kExpTail;
+__device__ __forceinline__ void exp_scan_wave(const ExpPoint& P, double (&p)[3]) {
+  const double face[3] = {fmin(P.v[0], 0.0), 0.0, fmax(P.v[2], 0.0)};
+  const double face_d =
+      (P.v[0] - face[0]) * (P.v[0] - face[0]) + P.v[1] * P.v[1] + (P.v[2] - face[2]) * (P.v[2] - face[2]);
+  const bool tail = P.v[0] < 0.0 && P.v[1] > 0.0 && (P.v[0] * P.fi[0]) / (P.v[1] * P.fi[1]) < kExpTail;
   const int lane = threadIdx.x & (kWave - 1);
 #pragma unroll 1
   for (int pass = 0; pass < 2; ++pass) {  // coarse, then fine
     double bd = face_d, b0 = face[0], b1 = face[1], b2 = face[2];
     bool cert = false;
-    if (tail && lane == 0) exp_ray_candidate((v[0] * P.fi[0]) / (v[1] * P.fi[1]), P, bd, b0, b1, b2, cert);
+    if (tail && lane == 0) exp_ray_candidate((P.v[0] * P.fi[0]) / (P.v[1] * P.fi[1]), P, bd, b0, b1, b2, cert);
     // e^0.4, e^-0.4, e^0.05, e^-0.05 to double precision
     exp_scan(pass == 0 ? 24 : 188, pass == 0 ? 0.4 : 0.05, pass == 0 ? 1.4918246976412703 : 1.0512710963760241,
              pass == 0 ? 0.6703200460356393 : 0.951229424500714, P, bd, b0, b1, b2, cert);
@@ -358,71 +350,220 @@ __device__ __forceinline__ void exp_proj_wave(const double (&v)[3], const double
   }
 }
 
-// Projection of a 3-row block onto F K_exp (dual = false) or onto F K_exp*
-// (dual = true: F K_exp* is the dual cone of F^-1 K_exp, so by Moreau's
-// decomposition P(v) = v + P_{F^-1 K_exp}(-v)), by one wave; ld, ef and st as
-// in wave_proj_soc (element i stored by lane i).
-template <class LD, class EF, class ST>
-__device__ __forceinline__ void wave_proj_exp(bool dual, const LD& ld, const EF& ef, const ST& st) {
+// The projection by one lane; returns whether p is certified.
+//
+// With w = v / f and z = f v, a point outside the cone, its polar and the
+// face's reach projects onto s F a(r), s > 0, with v - p = -t F^-1 n(r), t > 0,
+// and r is the one root of the slope in V = {psi < 0, chi > 0}.  At an end of an
+// interval of V the slope is positive where r enters it and negative where r
+// leaves it, so an interval with both ends holds a root: only one such interval
+// can exist, and the side of the root is known for every r outside V too.
+//   psi is convex in r for w_2 > 0 and concave for w_2 < 0; for w_1, w_2 > 0 it
+//   is lowest, and negative, at log(w_2 / w_1): psi >= 0 is then beyond the root
+//   on that seed's right and before it on its left; otherwise psi >= 0 lies
+//   beyond the root for w_1 > 0 and before it for w_1 <= 0.
+//   chi likewise with -z_2, z_0: highest, and positive, at log(z_0 / -z_2) for
+//   z_0 > 0 > z_2; otherwise chi <= 0 lies before the root for z_0 > 0 and
+//   beyond it for z_0 <= 0.
+// From a seed in the root's neighbourhood: Newton steps of the slope, steps of
+// growing length while the root has no bracket, bisection where Newton leaves
+// the bracket.  It is bound by its chain of dependent operations: 6 to 8 slopes
+// at the median over points of 16 decades and factors of 6, at most 24, 3 us for
+// one point and 6 us for 64.  (131072 projections of ordinary points: 20 us, 402 us
+// with a wave's scan of 1537 rays for each.)
+__device__ __forceinline__ bool exp_lane(const ExpPoint& P, double (&p)[3]) {
+  const double w0 = P.v[0] * P.fi[0], w1 = P.v[1] * P.fi[1], w2 = P.v[2] * P.fi[2];
+  const double z0 = P.v[0] * P.f[0], z1 = P.v[1] * P.f[1], z2 = P.v[2] * P.f[2];
+  double bd = INFINITY;
+  bool cert = false;
+  if (w0 < 0.0 && w1 > 0.0 && w0 / w1 < kExpTail) {
+    exp_ray_candidate(w0 / w1, P, bd, p[0], p[1], p[2], cert);
+    return cert;
+  }
+  const bool low = w1 > 0.0 && w2 > 0.0, high = w2 < 0.0 && w0 > 0.0;
+  const bool far = !low && !high && w2 > 0.0 && w1 <= 0.0;  // e^r / r = w_2 / w_0, nearly
+  const double lg = log((low || far ? w2 : (high ? -z0 : 1.0)) / (low ? w1 : (far ? w0 : (high ? z2 : 1.0))));
+  double seed = lg;
+  if (far) seed = fmax(1.0, lg + log(fmax(lg, 1.0)));
+  else if (!low && !high) seed = w1 > 0.0 ? (w0 <= 0.0 ? w0 / w1 : 0.5) : fmax(1.0, 1.0 - z1 / z0);
+  const double k0 = P.v[0] * P.f[1] * P.fi[2], k1 = P.v[0] * P.f[2] * P.fi[1], k2 = P.v[1] * P.f[2] * P.fi[0];
+  const double k3 = P.v[1] * P.f[0] * P.fi[2], k4 = P.v[2] * P.f[0] * P.fi[1], k5 = P.v[2] * P.f[1] * P.fi[0];
+  double r = seed, lo = -INFINITY, hi = INFINITY, reach = 2.0, last = INFINITY;
+#pragma unroll 1
+  for (int it = 0; it < 80; ++it) {
+    // slope, its derivative and size as in exp_ray_turn_d, in powers of r with the
+    // six products of v, f and 1 / f gathered: half the operations
+    const double q = exp(-fabs(r)), r1 = r - 1.0, rr = r * r1;
+    const bool neg = r <= 0.0;
+    const double x = neg ? q : 1.0, y = neg ? 1.0 : q, x2 = x * x, y2 = y * y;
+    const double u = k0 - k3 * r, w = k1 * r1 + k2, g = k4 * rr + k5;
+    const double t = u * y2 - w * x2 + q * g;
+    const double sc = (fabs(k0) + fabs(k3 * r)) * y2 + (fabs(k1 * r1) + fabs(k2)) * x2 +
+                      q * (fabs(k4 * rr) + fabs(k5));
+    const double dg = k4 * (r + r1), qg = q * (neg ? dg + g : dg - g);
+    const double dt = neg ? qg - k3 - (k1 + 2.0 * w) * x2 : qg - k1 - (k3 + 2.0 * u) * y2;
+    const double psi = (w1 * r1 - w0) * x + w2 * y, chi = (z0 * r + z1) * y + z2 * x;
+    const bool in = psi < 0.0 && chi > 0.0;
+    if (in && fabs(t) <= 1e-15 * sc) break;
+    const bool beyond =
+        in ? t <= 0.0 : (psi >= 0.0 ? (low ? r > seed : w1 > 0.0) : (high ? r > seed : w0 <= 0.0));
+    if (beyond) hi = r;
+    else lo = r;
+    const bool both = lo > -INFINITY && hi < INFINITY;
+    const double inv = __builtin_amdgcn_rcp(dt);  // one refinement: the step needs no more
+    const double step = -t * (inv * (2.0 - dt * inv));
+    double next = r + step;
+    const bool newton = in && dt < 0.0;
+    if (newton && fabs(step) <= 0x1p-52 * fabs(r)) break;  // no ray between this one and the root
+    if (!(newton && next > lo && next < hi && (both || fabs(step) <= reach)) ||
+        (both && it >= 8 && fabs(step) > 0.5 * last))  // (a Newton step that does not shrink: a cycle)
+      next = both ? 0.5 * (lo + hi) : (beyond ? r - reach : r + reach);
+    if (!(next > lo && next < hi)) break;
+    if (!both) reach *= 4.0;
+    last = fabs(next - r);
+    r = next;
+  }
+  exp_ray_candidate(r, P, bd, p[0], p[1], p[2], cert);
+  return cert;
+}
+
+// A projection for each active lane; all lanes of the wave call it together.
+__device__ __forceinline__ void exp_proj_lanes(bool active, const double (&v)[3], const double (&f)[3],
+                                               double (&p)[3]) {
+  bool done = true;
+  if (active) {
+    ExpPoint P;
+    for (int i = 0; i < 3; ++i) P.v[i] = v[i], P.f[i] = f[i], P.fi[i] = 1.0 / f[i];
+    const double c0 = fmin(v[0], 0.0), c2 = fmax(v[2], 0.0);
+    if (exp_cone_has(v[0] / f[0], v[1] / f[1], v[2] / f[2])) {
+      p[0] = v[0], p[1] = v[1], p[2] = v[2];
+    } else if (exp_dual_has(-f[0] * v[0], -f[1] * v[1], -f[2] * v[2])) {
+      p[0] = p[1] = p[2] = 0.0;
+    } else if (exp_dual_near(-f[0] * (v[0] - c0), -f[1] * v[1], -f[2] * (v[2] - c2))) {
+      p[0] = c0, p[1] = 0.0, p[2] = c2;
+    } else {
+      done = exp_lane(P, p);
+    }
+  }
   const int lane = threadIdx.x & (kWave - 1);
-  const double v[3] = {ld(0), ld(1), ld(2)};
-  const double f[3] = {ef(0), ef(1), ef(2)};
-  const double w[3] = {dual ? -v[0] : v[0], dual ? -v[1] : v[1], dual ? -v[2] : v[2]};
-  const double g[3] = {dual ? 1.0 / f[0] : f[0], dual ? 1.0 / f[1] : f[1], dual ? 1.0 / f[2] : f[2]};
-  double q[3];
-  exp_proj_wave(w, g, q);
-  const double p[3] = {dual ? v[0] + q[0] : q[0], dual ? v[1] + q[1] : q[1], dual ? v[2] + q[2] : q[2]};
-  if (lane < 3) st(lane, lane == 0 ? p[0] : (lane == 1 ? p[1] : p[2]));
+#pragma unroll 1
+  for (unsigned long long left = __ballot(!done); left; left &= left - 1) {
+    const int from = __ffsll(left) - 1;
+    ExpPoint P;
+    for (int i = 0; i < 3; ++i) {
+      P.v[i] = __shfl(v[i], from);
+      P.f[i] = __shfl(f[i], from);
+      P.fi[i] = 1.0 / P.f[i];
+    }
+    double q[3];
+    exp_scan_wave(P, q);
+    if (lane == from) p[0] = q[0], p[1] = q[1], p[2] = q[2];
+  }
+}
+
+// Projection of a 3-row block per active lane onto F K_exp (dual = false) or onto
+// F K_exp* (dual = true: F K_exp* is the dual cone of F^-1 K_exp, so by Moreau's
+// decomposition P(v) = v + P_{F^-1 K_exp}(-v)); ld, ef and st as in
+// wave_proj_soc, called by the block's lane for its three elements.
+template <class LD, class EF, class ST>
+__device__ __forceinline__ void lanes_proj_exp(bool active, bool dual, const LD& ld, const EF& ef, const ST& st) {
+  double v[3] = {0.0, 0.0, 0.0}, f[3] = {1.0, 1.0, 1.0}, w[3], g[3], q[3] = {0.0, 0.0, 0.0};
+  if (active)
+    for (int i = 0; i < 3; ++i) v[i] = ld(i), f[i] = ef(i);
+  for (int i = 0; i < 3; ++i) {
+    w[i] = dual ? -v[i] : v[i];
+    g[i] = dual ? 1.0 / f[i] : f[i];
+  }
+  exp_proj_lanes(active, w, g, q);
+  if (active)
+    for (int i = 0; i < 3; ++i) st(i, dual ? v[i] + q[i] : q[i]);
 }
 
 // Cone block kinds of the block table.
 constexpr int kConeSoc = 0, kConeExp = 1, kConeDualExp = 2;
 
+// Who handles a cone block: a wave (second-order cones) or one lane of a wave
+// whose other lanes have blocks of their own or none (exponential cones).
+// any(c) restricts the task to c and says whether the wave has work left;
+// elements of the block: for (i = first(); i < count(dim); i += stride()).
+struct WaveTask {
+  __device__ __forceinline__ bool any(bool c) const { return c; }
+  __device__ __forceinline__ int first() const { return threadIdx.x & (kWave - 1); }
+  __device__ __forceinline__ int count(int dim) const { return dim; }
+  __device__ __forceinline__ int stride() const { return kWave; }
+};
+struct LaneTask {
+  bool active;
+  __device__ __forceinline__ bool any(bool c) {
+    active = active && c;
+    return true;
+  }
+  __device__ __forceinline__ int first() const { return 0; }
+  __device__ __forceinline__ int count(int dim) const { return active ? dim : 0; }
+  __device__ __forceinline__ int stride() const { return 1; }
+};
+
 // Projection of one cone block of kind `kind` at a primal site (the cone of
 // G x - h: K_soc, K_exp or K_exp*) or a dual site (the cone of y, its dual:
 // K_soc, K_exp* or K_exp), rescaled by diag(ef).
 template <class LD, class EF, class ST>
-__device__ __forceinline__ void wave_proj_cone(int kind, bool dual_site, int d, const LD& ld, const EF& ef,
-                                               const ST& st) {
-  if (kind == kConeSoc) wave_proj_soc(d, ld, ef, st);
-  else wave_proj_exp((kind == kConeExp) == dual_site, ld, ef, st);
+__device__ __forceinline__ void proj_cone(const WaveTask&, int, bool, int d, const LD& ld, const EF& ef, const ST& st) {
+  wave_proj_soc(d, ld, ef, st);
+}
+template <class LD, class EF, class ST>
+__device__ __forceinline__ void proj_cone(const LaneTask& t, int kind, bool dual_site, int, const LD& ld, const EF& ef,
+                                          const ST& st) {
+  lanes_proj_exp(t.active, (kind == kConeExp) == dual_site, ld, ef, st);
 }
 
 // The cone blocks of row range b, each with S independent tasks (sub = 0 ..
-// S - 1), are handled by the waves of its workgroup: task j of the range
-// (block j / S, sub j mod S) by wave j mod kWavesPerBlock;
-// fn(first row, dimension, kind, sub).
+// S - 1): fn(who, first row, dimension, kind, sub).  Second-order cones, the first
+// in the table, go to the waves: task j of the range (block j / S, sub j mod S) to
+// wave j mod kWavesPerBlock.  Exponential cones go to the threads, task j to thread
+// j mod kBlock, so that sub is a thread's own where S divides kBlock; a wave takes
+// part with all its lanes or none.
+// (The dual epilogue of a problem with 310 second-order and 650 exponential cones,
+// two tasks each: 18.0 us with a wave for every cone, 12.0 us.)
 template <int S, class FN>
 __device__ __forceinline__ void for_cone_tasks(const Ranges& R, int b, const FN& fn) {
+  static_assert(kBlock % S == 0, "a thread keeps its sub");
   if (!R.blk_soc0) return;
   const int wave = threadIdx.x / kWave;
-  const int q0 = R.blk_soc0[b], n = (R.blk_soc1[b] - q0) * S;
+  const int q0 = R.blk_soc0[b], qe = R.blk_exp0[b], q1 = R.blk_soc1[b];
 #pragma unroll 1
-  for (int j = wave; j < n; j += kWavesPerBlock) {
+  for (int j = wave; j < (qe - q0) * S; j += kWavesPerBlock) {
     const int q = q0 + j / S;
-    fn(R.soc_r0[q], R.soc_dim[q], (int)R.soc_kind[q], j % S);
+    fn(WaveTask{}, R.soc_r0[q], R.soc_dim[q], kConeSoc, j % S);
+  }
+#pragma unroll 1
+  for (int j0 = wave * kWave; j0 < (q1 - qe) * S; j0 += kBlock) {
+    const int j = j0 + (int)(threadIdx.x & (kWave - 1));
+    const LaneTask who{j < (q1 - qe) * S};
+    const int q = who.active ? qe + j / S : qe;
+    fn(who, R.soc_r0[q], 3, (int)R.soc_kind[q], j % S);
   }
 }
 
 template <class FN>
 __device__ __forceinline__ void for_cone_blocks(const Ranges& R, int b, const FN& fn) {
-  for_cone_tasks<1>(R, b, [&](int r0, int dim, int kind, int) { fn(r0, dim, kind); });
+  for_cone_tasks<1>(R, b, [&](auto who, int r0, int dim, int kind, int) { fn(who, r0, dim, kind); });
 }
 
 // Projection of count vectors of dimension dim (v, f and out: dim doubles
 // each, contiguous) onto diag(f) K, K = K_soc (cone 0), K_exp (cone 1) or
-// K_exp* (cone 2, dim 3), one wave each.
+// K_exp* (cone 2, dim 3), one wave each (cone 0) or one lane each.
 __global__ __launch_bounds__(kBlock) void k_proj_cone(int cone, int dim, const double* __restrict__ v,
                                                       const double* __restrict__ f, double* __restrict__ out,
                                                       int64_t count) {
-  const int64_t q = (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave;
-  if (q >= count) return;
+  const int64_t q = cone == 0 ? (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave
+                              : (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (cone == 0 && q >= count) return;
   const size_t o = (size_t)q * dim;
   const auto ld = [&](int i) { return v[o + i]; };
   const auto ef = [&](int i) { return f[o + i]; };
   const auto st = [&](int i, double p) { out[o + i] = p; };
   if (cone == 0) wave_proj_soc(dim, ld, ef, st);
-  else wave_proj_exp(cone == 2, ld, ef, st);
+  else lanes_proj_exp(q < count, cone == 2, ld, ef, st);
 }
 
 // ===========================================================================
@@ -1174,10 +1315,10 @@ __global__ __launch_bounds__(kBlock) void k_dual_epi(Ranges R, const T* __restri
     // (the terms go through scalars: acc itself, written from the lambdas,
     // would be kept in scratch memory)
     double t0 = 0.0, t1 = 0.0, t2 = 0.0, t3 = 0.0;
-    for_cone_tasks<2>(R, b, [&](int r0, int dim, int kind, int pass) {
+    for_cone_tasks<2>(R, b, [&](auto who, int r0, int dim, int kind, int pass) {
       const bool dual = pass == 0;
-      wave_proj_cone(
-          kind, dual, dim,
+      proj_cone(
+          who, kind, dual, dim,
           [&](int i) { return dual ? (double)it.yh[r0 + i] : (double)it.gxh[r0 + i] - (double)d.h[r0 + i]; },
           [&](int i) { return dual ? 1.0 / D1[r0 + i] : D1[r0 + i]; },
           [&](int i, double p) {
@@ -1785,14 +1926,14 @@ __global__ __launch_bounds__(kBlock) void k_cand_rows(Ranges R, const T* __restr
   // per candidate: sums c[q][0..3] for acc[q*4 + i], maxima c[q][4..6] for acc[8 + q*3 + i - 4]
   double c00 = 0.0, c01 = 0.0, c02 = 0.0, c03 = 0.0, c04 = 0.0, c05 = 0.0, c06 = 0.0;
   double c10 = 0.0, c11 = 0.0, c12 = 0.0, c13 = 0.0, c14 = 0.0, c15 = 0.0, c16 = 0.0;
-  for_cone_tasks<2 * kMaxCand>(R, b, [&](int r0, int dim, int kind, int task) {
+  for_cone_tasks<2 * kMaxCand>(R, b, [&](auto who, int r0, int dim, int kind, int task) {
     const int q = task >> 1, pass = task & 1;
-    if (q < nc) {
+    if (who.any(q < nc)) {
       const T* yq = q == 0 ? y0 : y1;
       const double* gq = q == 0 ? g0 : g1;
       double t0 = 0.0, t1 = 0.0, t2 = 0.0, t3 = 0.0, t4 = 0.0, t5 = 0.0, t6 = 0.0;
       if (pass == 0) {
-        for (int i = (int)(threadIdx.x & (kWave - 1)); i < dim; i += kWave) {
+        for (int i = who.first(); i < who.count(dim); i += who.stride()) {
           const int r = r0 + i;
           const double yc = (double)yq[r], gx = gq[r], h = d.h[r];
           const double dya = yc - (double)ya[r], res = gx - h;
@@ -1803,8 +1944,8 @@ __global__ __launch_bounds__(kBlock) void k_cand_rows(Ranges R, const T* __restr
         }
       }
       const bool scaled = pass == 0;
-      wave_proj_cone(
-          kind, false, dim,
+      proj_cone(
+          who, kind, false, dim,
           [&](int i) { return scaled ? gq[r0 + i] - d.h[r0 + i] : (gq[r0 + i] - d.h[r0 + i]) / D1[r0 + i]; },
           [&](int i) { return scaled ? D1[r0 + i] : 1.0; },
           [&](int i, double p) {
@@ -1959,8 +2100,8 @@ __device__ __forceinline__ void probe_rows_body(int b, int q, const Ranges& R, c
   const T* ys = q == 0 ? y0 : y1;
   const double* gs = q == 0 ? g0 : g1;
   // cone blocks first: y(t) = Proj onto diag(1/D1) (dual cone) of
-  // y + t sigma b2, one task per block and probe spread over the waves (one
-  // inlined projection); each wave's sums go to its own LDS slots.  (Done
+  // y + t sigma b2, one task per block and probe (one inlined projection of a
+  // kind); each wave's sums go to its own LDS slots.  (Done
   // before the element loop below, whose 48 per-probe values are then not
   // live across the projection: the kernel keeps more waves per SIMD.)
   __shared__ double cone_acc[kWavesPerBlock][kProbeNV];
@@ -1968,11 +2109,12 @@ __device__ __forceinline__ void probe_rows_body(int b, int q, const Ranges& R, c
   const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
   if (cones) {
     for (int i = lane; i < kProbeNV; i += kWave) cone_acc[wave][i] = 0.0;
-    for_cone_tasks<kProbes>(R, b, [&](int r0, int dim, int kind, int p) {
+    double ld = 0.0, lb = 0.0;  // a lane's own blocks, all at probe lane % kProbes
+    for_cone_tasks<kProbes>(R, b, [&](auto who, int r0, int dim, int kind, int p) {
       const double tp = probe_t(C, p) * sigma;
       double dd = 0.0, bd = 0.0;
-      wave_proj_cone(
-          kind, true, dim, [&](int i) { return (double)ys[r0 + i] + tp * (d.h[r0 + i] - gs[r0 + i]); },
+      proj_cone(
+          who, kind, true, dim, [&](int i) { return (double)ys[r0 + i] + tp * (d.h[r0 + i] - gs[r0 + i]); },
           [&](int i) { return 1.0 / D1[r0 + i]; },
           [&](int i, double pv) {
             const double yc = (double)ys[r0 + i];
@@ -1980,13 +2122,27 @@ __device__ __forceinline__ void probe_rows_body(int b, int q, const Ranges& R, c
             dd += dy * dy;
             bd += (d.h[r0 + i] - gs[r0 + i]) * dy;
           });
-      dd = wave_sum(dd);
-      bd = wave_sum(bd);
-      if (lane == 0) {
-        cone_acc[wave][p * 2 + 0] += dd * inv_sigma;
-        cone_acc[wave][p * 2 + 1] += bd;
+      if constexpr (std::is_same_v<decltype(who), LaneTask>) {
+        ld += dd;
+        lb += bd;
+      } else {
+        dd = wave_sum(dd);
+        bd = wave_sum(bd);
+        if (lane == 0) {
+          cone_acc[wave][p * 2 + 0] += dd * inv_sigma;
+          cone_acc[wave][p * 2 + 1] += bd;
+        }
       }
     });
+#pragma unroll
+    for (int off = kProbes; off < kWave; off <<= 1) {
+      ld += __shfl_xor(ld, off);
+      lb += __shfl_xor(lb, off);
+    }
+    if (lane < kProbes) {
+      cone_acc[wave][lane * 2 + 0] += ld * inv_sigma;
+      cone_acc[wave][lane * 2 + 1] += lb;
+    }
   }
   double tq[kProbes];
 #pragma unroll
@@ -2482,9 +2638,9 @@ __global__ __launch_bounds__(kBlock) void k_ray_vec_rows(Ranges R, const T* __re
   }
   // cone blocks: the unscaled ray D1 (y_hat - y_start) projected onto the dual cone,
   // stored scaled back by 1 / D1 like the other rows
-  for_cone_blocks(R, b, [&](int r0, int dim, int kind) {
-    wave_proj_cone(
-        kind, true, dim, [&](int i) { return D1[r0 + i] * ((double)yh[r0 + i] - ys0[r0 + i]); }, [](int) { return 1.0; },
+  for_cone_blocks(R, b, [&](auto who, int r0, int dim, int kind) {
+    proj_cone(
+        who, kind, true, dim, [&](int i) { return D1[r0 + i] * ((double)yh[r0 + i] - ys0[r0 + i]); }, [](int) { return 1.0; },
         [&](int i, double p) { ry[r0 + i] = p / D1[r0 + i]; });
   });
 }
@@ -2562,9 +2718,9 @@ __global__ __launch_bounds__(kBlock) void k_ray_rows(Ranges R, const double* __r
   }
   // cone blocks: the unscaled G r_x against the block's cone
   if (rgx)
-    for_cone_blocks(R, b, [&](int r0, int dim, int kind) {
-      wave_proj_cone(
-          kind, false, dim, [&](int i) { return rgx[r0 + i] / D1[r0 + i]; }, [](int) { return 1.0; },
+    for_cone_blocks(R, b, [&](auto who, int r0, int dim, int kind) {
+      proj_cone(
+          who, kind, false, dim, [&](int i) { return rgx[r0 + i] / D1[r0 + i]; }, [](int) { return 1.0; },
           [&](int i, double p) {
             const double res = rgx[r0 + i] / D1[r0 + i] - p;
             acc[2] += res * res;
@@ -3138,9 +3294,9 @@ __global__ __launch_bounds__(kBlock) void k_start_rows(Ranges R, const double* _
     it.sy[i] = (T)0;
   }
   // cone blocks: y0 / D1 projected onto diag(1/D1) (dual cone)
-  for_cone_blocks(R, b, [&](int r0, int dim, int kind) {
-    wave_proj_cone(
-        kind, true, dim, [&](int i) { return y0 ? y0[r0 + i] / D1[r0 + i] : 0.0; }, [&](int i) { return 1.0 / D1[r0 + i]; },
+  for_cone_blocks(R, b, [&](auto who, int r0, int dim, int kind) {
+    proj_cone(
+        who, kind, true, dim, [&](int i) { return y0 ? y0[r0 + i] / D1[r0 + i] : 0.0; }, [&](int i) { return 1.0 / D1[r0 + i]; },
         [&](int i, double p) {
           const int r = r0 + i;
           const T y = (T)p;
@@ -3701,9 +3857,9 @@ void launch_to_f32(const double* in, float* out, int64_t n, hipStream_t s) {
 
 void launch_proj_cone(int cone, int dim, const double* v, const double* f, double* out, int64_t count,
                       hipStream_t s) {
+  const int per_block = cone == 0 ? kWavesPerBlock : kBlock;
   if (count > 0)
-    k_proj_cone<<<(unsigned)((count + kWavesPerBlock - 1) / kWavesPerBlock), kBlock, 0, s>>>(cone, dim, v, f, out,
-                                                                                           count);
+    k_proj_cone<<<(unsigned)((count + per_block - 1) / per_block), kBlock, 0, s>>>(cone, dim, v, f, out, count);
 }
 
 void launch_pack_warm(const void* const* src, const int32_t* off, int B, int64_t maxlen, int dtype, double* out,

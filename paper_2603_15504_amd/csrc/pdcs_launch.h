@@ -43,8 +43,12 @@ constexpr int kLdsRowMax = 64;
 // Cone blocks per row range: in the elementwise passes (two projections per
 // block in the dual epilogue: one per wave), and in the restart checks (one
 // block, its multisection probes or candidate terms spread over the waves).
+// An exponential cone is a lane's work, not a wave's: a range takes kExpPerSoc of
+// them for a second-order cone (32 in a trial, 64 tasks and a wave; 16 in a
+// check, 256 multisection tasks, one for each thread).
 constexpr int kConeBlocksPerRange = kWavesPerBlock / 2;
 constexpr int kConeBlocksPerCheckRange = 1;
+constexpr int kExpPerSoc = 16;
 
 // LDS footprint of one instance in k_trials_lds: the 14 iterate vectors the
 // trials touch, c, l, u, h, both CSR copies of the instance's part of G and
