@@ -366,6 +366,13 @@ int  pdcs_result_info(pdcs_result r, pdcs_info* out);
 int  pdcs_result_primal_device(pdcs_result r, double* x_dev, int64_t n, void* stream);
 int  pdcs_result_dual_device(pdcs_result r, double* y_dev, int64_t m, void* stream);
 int  pdcs_result_slack_device(pdcs_result r, double* lam_dev, int64_t n, void* stream);
+/* The three vectors of `count` results at once, each into the buffer at its index
+ * (x_dev[i] and lam_dev[i] of results[i]'s n, y_dev[i] of its m; y_dev[i] may be
+ * NULL when m is 0), in a few launches on `stream`, not synchronized: every
+ * result handle must stay alive until they have run.  infos: NULL or one per
+ * result.  Errors: PDCS_ERR_INVALID_ARG (null pointers), PDCS_ERR_HIP. */
+int  pdcs_results_device(int64_t count, const pdcs_result* results, pdcs_info* infos, double* const* x_dev,
+                         double* const* y_dev, double* const* lam_dev, void* stream);
 /* Copy results of instance 0 (single solves) to host buffers of exactly the
  * given length (mismatch: PDCS_ERR_INVALID_ARG). x: primal, y: dual,
  * lam: dual slack c - G^T y (the "slack" field of Section 3). */

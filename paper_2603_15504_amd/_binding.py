@@ -101,6 +101,7 @@ PROTOTYPES = {
     "pdcs_result_primal_device": (C.c_int, [_P, _P, _I64, _P]),
     "pdcs_result_dual_device": (C.c_int, [_P, _P, _I64, _P]),
     "pdcs_result_slack_device": (C.c_int, [_P, _P, _I64, _P]),
+    "pdcs_results_device": (C.c_int, [_I64, _P, _P, _P, _P, _P, _P]),
     "pdcs_result_scaling": (C.c_int, [_P, _P, _I64, _P, _I64]),
     "pdcs_result_state": (C.c_int, [_P, C.POINTER(pdcs_state_scalars), _P, _P, _P, _P, _P, _P]),
     "pdcs_result_products": (C.c_int, [_P, _P, _P]),
@@ -384,6 +385,17 @@ def pdcs_result_slack_device(r, lam_dev: int, n: int, stream: int = 0):
            "pdcs_result_slack_device")
 
 
+def pdcs_results_device(rs, xs_dev, ys_dev, lams_dev, stream: int = 0):
+    """The x, y and lam of every result into the device buffers at these addresses
+    (0: no rows), enqueued on `stream`; returns an array of their pdcs_info."""
+    count = len(rs)
+    table = C.c_void_p * count
+    infos = (pdcs_info * count)()
+    _check(lib.pdcs_results_device(count, table(*[r.value for r in rs]), infos, table(*xs_dev), table(*ys_dev),
+                                   table(*lams_dev), C.c_void_p(stream) if stream else None), "pdcs_results_device")
+    return infos
+
+
 def pdcs_result_scaling(r, m, n):
     D1 = np.empty(m, dtype=np.float64)
     D2 = np.empty(n, dtype=np.float64)
@@ -552,7 +564,7 @@ class Problem:
             r = pdcs_solve(self.handle, o, x0, y0)
         try:
             return _collect(r, self.m, self.n, with_scaling, bool(o.keep_state), int(o.trace_trials),
-                            device_out=device_out)
+                            _device_solutions([r], [(self.m, self.n)])[0] if device_out else None)
         finally:
             pdcs_result_destroy(r)
 
@@ -619,27 +631,28 @@ def _warm_dtype(x0, y0, want) -> int:
     return codes.pop()
 
 
-def _device_vectors(r, m, n):
+def _device_solutions(rs, dims) -> list:
+    """Solutions on the GPU of all results, in one call and with one wait."""
     import torch
 
-    x = torch.empty(n, dtype=torch.float64, device="cuda")
-    y = torch.empty(m, dtype=torch.float64, device="cuda")
-    lam = torch.empty(n, dtype=torch.float64, device="cuda")
-    st = _torch_stream()
-    pdcs_result_primal_device(r, x.data_ptr(), n, st)
-    pdcs_result_dual_device(r, y.data_ptr() if m > 0 else 0, m, st)
-    pdcs_result_slack_device(r, lam.data_ptr(), n, st)
-    # the copies are enqueued on torch's stream; the result handle is destroyed
-    # right after, so wait for them here
-    torch.cuda.current_stream().synchronize()
-    return x, y, lam
+    def vectors(side):
+        return [torch.empty(d[side], dtype=torch.float64, device="cuda") for d in dims]
+
+    xs, ys, lams = vectors(1), vectors(0), vectors(1)
+    # one stream for the tensors, the copies and the wait; the result handles are
+    # destroyed after this, so wait for the copies here
+    st = torch.cuda.current_stream()
+    infos = pdcs_results_device(rs, [t.data_ptr() for t in xs], [t.data_ptr() for t in ys],
+                                [t.data_ptr() for t in lams], int(st.cuda_stream))
+    st.synchronize()
+    return [Solution(x, y, lam, _info_dict(i)) for x, y, lam, i in zip(xs, ys, lams, infos)]
 
 
-def _collect(r, m, n, with_scaling, with_state, trace=0, device_out=False) -> Solution:
-    info = _info_dict(pdcs_result_info(r))
-    if device_out:
-        sol = Solution(*_device_vectors(r, m, n), info)
+def _collect(r, m, n, with_scaling, with_state, trace=0, device=None) -> Solution:
+    if device is not None:
+        sol = device
     else:
+        info = _info_dict(pdcs_result_info(r))
         sol = Solution(pdcs_result_primal(r, n), pdcs_result_dual(r, m) if m > 0 else np.zeros(0),
                        pdcs_result_slack(r, n), info)
     if with_scaling:
@@ -693,9 +706,10 @@ class Batch:
             rs = pdcs_batch_solve(self.handle, count, o, x0s, y0s, dims=[(p.m, p.n) for p in self.problems])
         out = []
         try:
+            device = _device_solutions(rs, [(p.m, p.n) for p in self.problems]) if device_out else [None] * count
             for i, (r, p) in enumerate(zip(rs, self.problems)):
                 out.append(_collect(r, p.m, p.n, with_scaling, bool(o.keep_state),
-                                    int(o.trace_trials) if i == 0 else 0, device_out=device_out))
+                                    int(o.trace_trials) if i == 0 else 0, device[i]))
         finally:
             for r in rs:
                 pdcs_result_destroy(r)

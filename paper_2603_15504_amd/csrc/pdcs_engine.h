@@ -135,7 +135,8 @@ struct IterBufs {
 // Device copies of one solve's outputs, shared by the results of a batch.
 struct OutBlock {
   int64_t M = 0, N = 0;
-  DBuf x, y, lam, D1, D2;
+  DBuf all;  // x, y, lam, D1 and D2
+  double *x = nullptr, *y = nullptr, *lam = nullptr, *D1 = nullptr, *D2 = nullptr;
   DBuf st[2][8];  // [fp64, fp32] x [x, y, x_hat, y_hat, x_a, y_a, G^T y_hat, G x_hat]
 };
 

@@ -1303,16 +1303,21 @@ std::vector<pdcs_result> Engine::solve(const pdcs_options& o, const WarmStart& w
   auto out = std::make_shared<OutBlock>();
   out->M = M;
   out->N = N;
-  out->x.alloc((size_t)N * 8);
-  out->lam.alloc((size_t)N * 8);
-  out->y.alloc((size_t)M * 8);
-  out->D1.alloc((size_t)M * 8);
-  out->D2.alloc((size_t)N * 8);
-  HIP_OK(hipMemcpyAsync(out->x.p, xout.p, (size_t)N * 8, hipMemcpyDeviceToDevice, stream));
-  HIP_OK(hipMemcpyAsync(out->lam.p, lamout.p, (size_t)N * 8, hipMemcpyDeviceToDevice, stream));
-  HIP_OK(hipMemcpyAsync(out->y.p, yout.p, (size_t)M * 8, hipMemcpyDeviceToDevice, stream));
-  HIP_OK(hipMemcpyAsync(out->D1.p, D1.p, (size_t)M * 8, hipMemcpyDeviceToDevice, stream));
-  HIP_OK(hipMemcpyAsync(out->D2.p, D2.p, (size_t)N * 8, hipMemcpyDeviceToDevice, stream));
+  // (one allocation and one launch: five of each were 60 us of a solve's end)
+  const auto padded = [](int64_t len) { return (size_t)((len + 31) / 32 * 32); };
+  out->all.alloc((3 * padded(N) + 2 * padded(M)) * 8);
+  out->x = out->all.as<double>();
+  out->lam = out->x + padded(N);
+  out->D2 = out->lam + padded(N);
+  out->y = out->D2 + padded(N);
+  out->D1 = out->y + padded(M);
+  const CopyItem copies[5] = {{xout.as<double>(), out->x, N},
+                              {lamout.as<double>(), out->lam, N},
+                              {D2.as<double>(), out->D2, N},
+                              {yout.as<double>(), out->y, M},
+                              {D1.as<double>(), out->D1, M}};
+  launch_copies(copies, 5, stream);
+  HIP_OK(hipGetLastError());
   if (o.keep_state) {
     for (int pi = 0; pi < 2; ++pi) {
       const bool ok = pi == 0 ? it64.ready : it32.ready;
@@ -1786,17 +1791,17 @@ int pdcs_result_info(pdcs_result r, pdcs_info* out) {
   });
 }
 
-static void copy_out(const DBuf& src, int64_t off, int64_t len, double* dst, int64_t want) {
+static void copy_out(const double* src, int64_t off, int64_t len, double* dst, int64_t want) {
   if (!dst) throw Error(PDCS_ERR_INVALID_ARG, "destination is null");
   if (want != len) throw Error(PDCS_ERR_INVALID_ARG, "length mismatch");
-  if (len > 0) HIP_OK(hipMemcpy(dst, src.as<double>() + off, (size_t)len * 8, hipMemcpyDeviceToHost));
+  if (len > 0) HIP_OK(hipMemcpy(dst, src + off, (size_t)len * 8, hipMemcpyDeviceToHost));
 }
 
-static void copy_out_device(const DBuf& src, int64_t off, int64_t len, double* dst, int64_t want, void* stream) {
+static void copy_out_device(const double* src, int64_t off, int64_t len, double* dst, int64_t want, void* stream) {
   if (!dst) throw Error(PDCS_ERR_INVALID_ARG, "destination is null");
   if (want != len) throw Error(PDCS_ERR_INVALID_ARG, "length mismatch");
   if (len > 0)
-    HIP_OK(hipMemcpyAsync(dst, src.as<double>() + off, (size_t)len * 8, hipMemcpyDeviceToDevice, (hipStream_t)stream));
+    HIP_OK(hipMemcpyAsync(dst, src + off, (size_t)len * 8, hipMemcpyDeviceToDevice, (hipStream_t)stream));
 }
 
 int pdcs_result_primal_device(pdcs_result r, double* x_dev, int64_t n, void* stream) {
@@ -1820,6 +1825,29 @@ int pdcs_result_slack_device(pdcs_result r, double* lam_dev, int64_t n, void* st
   return guarded([&]() {
     if (!r) throw Error(PDCS_ERR_INVALID_ARG, "result is null");
     copy_out_device(r->out->lam, r->col0, r->n, lam_dev, n, stream);
+    return PDCS_OK;
+  });
+}
+
+int pdcs_results_device(int64_t count, const pdcs_result* results, pdcs_info* infos, double* const* x_dev,
+                        double* const* y_dev, double* const* lam_dev, void* stream) {
+  return guarded([&]() {
+    if (count < 1 || !results || !x_dev || !y_dev || !lam_dev) throw Error(PDCS_ERR_INVALID_ARG, "null argument");
+    std::vector<CopyItem> items;
+    items.reserve((size_t)count * 3);
+    for (int64_t i = 0; i < count; ++i) {
+      const pdcs_result r = results[i];
+      if (!r) throw Error(PDCS_ERR_INVALID_ARG, "result is null");
+      if (!x_dev[i] || !lam_dev[i] || (!y_dev[i] && r->m > 0))
+        throw Error(PDCS_ERR_INVALID_ARG, "destination is null");
+      items.push_back({r->out->x + r->col0, x_dev[i], r->n});
+      items.push_back({r->out->y + r->row0, y_dev[i], r->m});
+      items.push_back({r->out->lam + r->col0, lam_dev[i], r->n});
+    }
+    if (infos)
+      for (int64_t i = 0; i < count; ++i) infos[i] = results[i]->info;
+    launch_copies(items.data(), items.size(), (hipStream_t)stream);
+    HIP_OK(hipGetLastError());
     return PDCS_OK;
   });
 }
