@@ -3,8 +3,8 @@
 // BF16 weights and activations feed the matrix cores (v_mfma_f32_32x32x16_bf16
 // on gfx950) with FP32 accumulation; an FP32 master copy of the weights takes
 // the Adam updates.  Every GEMM is C = op(A) op(B) with row-major operands,
-// tiled 128 x 128 x 32 per workgroup (four wavefronts of 64 x 64), split along
-// K when M x N alone cannot fill the chip; split partials are summed in a fixed
+// tiled 128 x 128 (four wavefronts of 64 x 64) or 64 x 64 (of 32 x 32) per
+// workgroup, split along K when M x N alone cannot fill the chip; split partials are summed in a fixed
 // order, so results are deterministic.  The products' epilogues do the rest of
 // a training step where the data already sits in registers: bias and ReLU in
 // the forward pass, the loss and its gradient in the output layer, the ReLU
@@ -12,6 +12,7 @@
 // weight gradients never travel through HBM during training.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <random>
@@ -28,31 +29,33 @@ typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int TM = 128, TN = 128;
+// Sides of a workgroup's output tile.  A K-split is chosen on tiles of kTileWide, so
+// that a product's sums have the same order with either tile.
+constexpr int kTileWide = 128, kTileNarrow = 64;
 
 __device__ __forceinline__ bf16 to_bf16(float v) { return (bf16)v; }
 
-// One operand tile (128 rows of op(X) x KT) staged through registers.  op(X)
+// One operand tile (TT rows of op(X) x KT) staged through registers.  op(X)
 // row r, column k lives at X[k * ld + r] when trans, else X[r * ld + k].  Each
-// thread loads KT / 16 8-element vectors, each along the source's contiguous
-// direction:
+// thread loads KQ = TT KT / 2048 8-element vectors, each along the source's
+// contiguous direction:
 //   not trans: vector e = tid + 256 q holds row e / (KT/8), k-block e % (KT/8);
-//   trans    : thread t holds rows 8 (t % 16) .. +7 for the KT/16 consecutive
-//              k = (t / 16) KT/16 + q, one vector per k; lanes 0-15 of a k read
-//              256 contiguous bytes.  The store transposes these in registers so
-//              that each row goes to LDS as one run of KT/16 k-values.
+//   trans    : thread t holds rows 8 (t % (TT/8)) .. +7 for the KQ consecutive
+//              k = (t / (TT/8)) KQ + q, one vector per k; the TT/8 lanes of a k
+//              read 2 TT contiguous bytes.  The store transposes these in registers
+//              so that each row goes to LDS as one run of KQ k-values.
 // vec: the launch guarantees 16-byte alignment of the source and ld % 8 == 0,
 // so whole vectors inside the bounds load with one 16-byte access; anything
 // else loads element by element.
 //
-// LDS holds 128 rows of KT + 8 elements.  The 16-byte blocks of a row are
+// LDS holds TT rows of KT + 8 elements.  The 16-byte blocks of a row are
 // swizzled by the row's group of eight (block b of row r sits at block
 // b ^ ((r / 8) mod KT/8)): the transposed stores of 16 lanes (rows eight apart)
 // and the MFMA reads of 32 lanes (32 consecutive rows) then fall on different
 // banks.
-template <int KT>
+template <int TT, int KT>
 struct TileRegs {
-  bf16x8 v[KT / 16];
+  bf16x8 v[TT * KT / 2048];
 };
 
 template <int KT>
@@ -60,11 +63,11 @@ __device__ __forceinline__ int swz(int row, int blk) {
   return blk ^ ((row >> 3) & (KT / 8 - 1));
 }
 
-template <int KT>
+template <int TT, int KT>
 __device__ __forceinline__ void tile_load(const bf16* __restrict__ X, int ld, int trans, int vec, int r0, int R,
-                                          int k0, int kend, TileRegs<KT>& t) {
+                                          int k0, int kend, TileRegs<TT, KT>& t) {
   const int tid = threadIdx.x;
-  constexpr int KQ = KT / 16;
+  constexpr int KQ = TT * KT / 2048;
 #pragma unroll
   for (int q = 0; q < KQ; ++q) {
     bf16x8 v;
@@ -78,7 +81,7 @@ __device__ __forceinline__ void tile_load(const bf16* __restrict__ X, int ld, in
         for (int i = 0; i < 8; ++i) v[i] = (gr < R && gk + i < kend) ? X[(size_t)gr * ld + gk + i] : to_bf16(0.0f);
       }
     } else {
-      const int gr = r0 + (tid & 15) * 8, gk = k0 + (tid >> 4) * KQ + q;
+      const int gr = r0 + (tid % (TT / 8)) * 8, gk = k0 + (tid / (TT / 8)) * KQ + q;
       if (vec && gk < kend && gr + 8 <= R) {
         v = *reinterpret_cast<const bf16x8*>(X + (size_t)gk * ld + gr);
       } else {
@@ -90,10 +93,10 @@ __device__ __forceinline__ void tile_load(const bf16* __restrict__ X, int ld, in
   }
 }
 
-template <int KT>
-__device__ __forceinline__ void tile_store(bf16 (*S)[KT + 8], int trans, const TileRegs<KT>& t) {
+template <int TT, int KT>
+__device__ __forceinline__ void tile_store(bf16 (*S)[KT + 8], int trans, const TileRegs<TT, KT>& t) {
   const int tid = threadIdx.x;
-  constexpr int KQ = KT / 16;
+  constexpr int KQ = TT * KT / 2048;
   if (!trans) {
 #pragma unroll
     for (int q = 0; q < KQ; ++q) {
@@ -101,9 +104,13 @@ __device__ __forceinline__ void tile_store(bf16 (*S)[KT + 8], int trans, const T
       const int rr = e / (KT / 8), blk = e % (KT / 8);
       *reinterpret_cast<bf16x8*>(&S[rr][swz<KT>(rr, blk) * 8]) = t.v[q];
     }
+  } else if constexpr (KQ == 1) {
+    const int rb = (tid % (TT / 8)) * 8, kq = tid / (TT / 8);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) S[rb + i][swz<KT>(rb + i, kq >> 3) * 8 + (kq & 7)] = t.v[0][i];
   } else {
     typedef __bf16 bf16xq __attribute__((ext_vector_type(KQ)));
-    const int rb = (tid & 15) * 8, kq = (tid >> 4) * KQ;  // k-run kq .. kq + KQ - 1: within one 8-block
+    const int rb = (tid % (TT / 8)) * 8, kq = (tid / (TT / 8)) * KQ;  // k-run kq .. kq + KQ - 1: within one 8-block
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       bf16xq w;
@@ -118,21 +125,24 @@ __device__ __forceinline__ void tile_store(bf16 (*S)[KT + 8], int trans, const T
 // How a GEMM output element is used once its FP32 sum s is known.
 //   EPI_STORE: C[z][row][col] = s (split partials, or a plain FP32 product)
 //   EPI_ACT  : s (+ bias[col]), ReLU, times (mask[idx] > 0) -- the derivative of
-//              ReLU read from the BF16 activation it produced -- stored as FP32
-//              and/or BF16
+//              ReLU read from the BF16 activation it produced -- then times
+//              osc[col] plus omu[col] (the network output in the caller's units),
+//              stored as FP32 and/or BF16
 //   EPI_ADAM : s is the gradient of weight idx: Adam on the FP32 master weight
 //              and its moments, and the BF16 copy the next products read, so the
 //              gradient itself never reaches memory
 //   EPI_MSE  : s + bias[col] is the network output; with the target t
 //              (standardized per column when tmu is set) the loss gradient
 //              g = 2 (v - t) * gscale goes out as BF16, and each workgroup leaves
-//              one loss partial (FP64) and per-column sums of g for its row tile
+//              one loss partial (FP64) and per-column sums of g for each 64 rows
 enum { EPI_STORE = 0, EPI_ACT = 1, EPI_ADAM = 2, EPI_MSE = 3 };
 
 struct Epi {
   const float* bias = nullptr;
   int relu = 0;
   const bf16* mask = nullptr;
+  const float* osc = nullptr;
+  const float* omu = nullptr;
   float* out32 = nullptr;
   bf16* out16 = nullptr;
   float *p = nullptr, *m = nullptr, *v = nullptr;
@@ -151,8 +161,17 @@ __device__ __forceinline__ void epi_act(const Epi& e, size_t idx, int col, float
   if (e.bias) s += e.bias[col];
   if (e.relu) s = fmaxf(s, 0.0f);
   if (e.mask) s = (float)e.mask[idx] > 0.0f ? s : 0.0f;
+  if (e.osc) s = s * e.osc[col] + e.omu[col];
   if (e.out32) e.out32[idx] = s;
   if (e.out16) e.out16[idx] = to_bf16(s);
+}
+
+// Adam on one weight.  The multiply-adds are written out, so that a weight has the
+// same bits whichever path its tile takes.
+__device__ __forceinline__ void adam_update(const Epi& e, float g, float& p, float& m, float& v) {
+  m = fmaf(e.b1, m, (1.0f - e.b1) * g);
+  v = fmaf(e.b2, v, (1.0f - e.b2) * g * g);
+  p = p - e.lr * (m / e.c1) / (sqrtf(v / e.c2) + e.eps);
 }
 
 // Raw buffer access (vector memory instructions with a uniform resource):
@@ -192,7 +211,7 @@ __device__ __forceinline__ double wave_sum64(double v) {
   return v;
 }
 
-// C = op(A)[M x K] op(B)[K x N] by 128 x 128 output tiles, split S =
+// C = op(A)[M x K] op(B)[K x N] by TT x TT output tiles, split S =
 // gridDim.x / (gx * gy) ways along K (split z takes every S-th K-tile):
 //   op(A)[m][k] = ta ? A[k * lda + m] : A[m * lda + k]
 //   op(B)[k][n] = tb ? B[n * ldb + k] : B[k * ldb + n]
@@ -202,18 +221,19 @@ __device__ __forceinline__ double wave_sum64(double v) {
 // tile order runs fastest along the shorter grid side, so the tiles that read
 // the same operand panel (the same K-chunk of a split product, the same row or
 // column panel otherwise) meet in one L2.
-template <int KIND, int KT>
+template <int KIND, int KT, int TT>
 __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int lda, int ta, int veca,
                                               const bf16* __restrict__ B, int ldb, int tb, int vecb,
                                               float* __restrict__ C, int M, int N, int K, int gx,
                                               int gy, Epi e) {
   // operand tiles for the K-loop; the Adam epilogue reuses the same LDS to
   // stage the FP32 output tile (rows padded by 4 floats)
-  constexpr int kTileBytes = (TM + TN) * (KT + 8) * 2;
-  constexpr int kStageBytes = KIND == EPI_ADAM ? TM * (TN + 4) * 4 : 0;
+  constexpr int kTileBytes = 2 * TT * (KT + 8) * 2;
+  constexpr int kStageBytes = KIND == EPI_ADAM ? TT * (TT + 4) * 4 : 0;
+  constexpr int NF = TT / 64;  // 32 x 32 fragments of a wave along each side
   __shared__ __attribute__((aligned(16))) unsigned char smem[kTileBytes > kStageBytes ? kTileBytes : kStageBytes];
   bf16(*As)[KT + 8] = reinterpret_cast<bf16(*)[KT + 8]>(smem);
-  bf16(*Bs)[KT + 8] = reinterpret_cast<bf16(*)[KT + 8]>(smem + TM * (KT + 8) * 2);
+  bf16(*Bs)[KT + 8] = reinterpret_cast<bf16(*)[KT + 8]>(smem + TT * (KT + 8) * 2);
   const int L = blockIdx.x, total = gridDim.x;
   const int full = total & ~7;
   const int Q = L < full ? (L & 7) * (full >> 3) + (L >> 3) : L;
@@ -227,52 +247,52 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
     by = tq % gy;
     bx = tq / gy;
   }
-  const int m0 = by * TM, n0 = bx * TN;
+  const int m0 = by * TT, n0 = bx * TT;
   // K-tiles z, z + S, z + 2S, ... of the S-way split: the workgroups of one
   // output tile read adjacent K-tiles at about the same time, so each row of an
   // operand is fetched in long runs rather than one K-tile at a time
   const int S = total / tiles, kstep = S * KT;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
-  f32x16 acc[2][2];
+  const int wm = (wave >> 1) * (TT / 2), wn = (wave & 1) * (TT / 2);
+  f32x16 acc[NF][NF];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NF; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NF; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-  TileRegs<KT> ra, rb;
+  TileRegs<TT, KT> ra, rb;
   if (z * KT < K) {
-    tile_load<KT>(A, lda, ta, veca, m0, M, z * KT, min(K, z * KT + KT), ra);
-    tile_load<KT>(B, ldb, !tb, vecb, n0, N, z * KT, min(K, z * KT + KT), rb);
+    tile_load<TT, KT>(A, lda, ta, veca, m0, M, z * KT, min(K, z * KT + KT), ra);
+    tile_load<TT, KT>(B, ldb, !tb, vecb, n0, N, z * KT, min(K, z * KT + KT), rb);
   }
   for (int k0 = z * KT; k0 < K; k0 += kstep) {
-    tile_store<KT>(As, ta, ra);
-    tile_store<KT>(Bs, !tb, rb);
+    tile_store<TT, KT>(As, ta, ra);
+    tile_store<TT, KT>(Bs, !tb, rb);
     __syncthreads();
     const int kn = k0 + kstep;
     if (kn < K) {  // prefetch the next tile while the matrix cores work
-      tile_load<KT>(A, lda, ta, veca, m0, M, kn, min(K, kn + KT), ra);
-      tile_load<KT>(B, ldb, !tb, vecb, n0, N, kn, min(K, kn + KT), rb);
+      tile_load<TT, KT>(A, lda, ta, veca, m0, M, kn, min(K, kn + KT), ra);
+      tile_load<TT, KT>(B, ldb, !tb, vecb, n0, N, kn, min(K, kn + KT), rb);
     }
 #pragma unroll
     for (int kk = 0; kk < KT; kk += 16) {
-      bf16x8 a[2], b[2];
+      bf16x8 a[NF], b[NF];
       const int kb = (kk >> 3) + (lane >> 5);  // 16-byte block of k-values kk + 8 (lane / 32) ..
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < NF; ++i) {
         const int row = wm + i * 32 + (lane & 31);
         a[i] = *reinterpret_cast<const bf16x8*>(&As[row][swz<KT>(row, kb) * 8]);
       }
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < NF; ++j) {
         const int row = wn + j * 32 + (lane & 31);
         b[j] = *reinterpret_cast<const bf16x8*>(&Bs[row][swz<KT>(row, kb) * 8]);
       }
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < NF; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < NF; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     }
     __syncthreads();
   }
@@ -281,9 +301,9 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
   if constexpr (KIND == EPI_STORE) {
     float* Cz = C + (size_t)z * M * N;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NF; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < NF; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int row = row0 + i * 32 + (r / 4) * 8 + (r % 4), col = col0 + j * 32;
@@ -293,11 +313,12 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
     // per 16-element group: the bias (one column) and the masks are loaded
     // before the first store, so the loads are all in flight together
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NF; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < NF; ++j) {
         const int col = col0 + j * 32;
         const float bv = (e.bias && col < N) ? e.bias[col] : 0.0f;
+        const float sc = (e.osc && col < N) ? e.osc[col] : 1.0f, mu = (e.osc && col < N) ? e.omu[col] : 0.0f;
         float mk[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -311,6 +332,7 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
             float s = acc[i][j][r] + bv;
             if (e.relu) s = fmaxf(s, 0.0f);
             if (!(mk[r] > 0.0f)) s = 0.0f;
+            if (e.osc) s = s * sc + mu;
             const size_t idx = (size_t)row * N + col;
             if (e.out32) e.out32[idx] = s;
             if (e.out16) e.out16[idx] = to_bf16(s);
@@ -321,24 +343,25 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
     // Element offsets are 32-bit (each weight matrix holds < 2^30 entries).
     // Interior tiles address the moments and weights through buffer resources:
     // one per-lane byte offset per column half plus a uniform row offset, so an
-    // element costs no address registers.  The 64 accumulators go in 8 groups
+    // element costs no address registers.  The accumulators go in groups
     // of 8; the loads of group q+1 are issued before group q is updated and
     // stored, so they are in flight meanwhile.  Tiles that stick out of the
     // matrix take the guarded loop.
-    if (e.vec4 && m0 + TM <= M && n0 + TN <= N) {
+    if (e.vec4 && m0 + TT <= M && n0 + TT <= N) {
       // The tile goes through LDS so that each thread updates whole 16-byte
-      // runs of a row: thread t takes columns 4 (t % 32) .. +3 of rows
-      // t / 32 + 8 q (q < 16), in 4 groups of 4 rows; the first group's
+      // runs of a row: thread t takes columns 4 (t % LPR) .. +3 of rows
+      // t / LPR + RP q, q < TT / RP, in groups of 4; the first group's
       // weights and moments are requested before the tile is staged, and each
       // next group's before the current one is updated.
-      float(*S)[TN + 4] = reinterpret_cast<float(*)[TN + 4]>(smem);
-      const int lr = threadIdx.x >> 5, lc = (threadIdx.x & 31) * 4;
+      constexpr int LPR = TT / 4, RP = 256 / LPR, NG = TT / RP / 4;
+      float(*S)[TT + 4] = reinterpret_cast<float(*)[TT + 4]>(smem);
+      const int lr = threadIdx.x / LPR, lc = (threadIdx.x % LPR) * 4;
       // buffer resources: one per-lane offset, the row step as a uniform offset
       const uint32_t bytes = (uint32_t)M * (uint32_t)N * 4u;
       const __amdgpu_buffer_rsrc_t rp = make_rsrc(e.p, bytes), rm = make_rsrc(e.m, bytes),
                                    rv = make_rsrc(e.v, bytes), rw = make_rsrc(e.w16, bytes / 2);
       const uint32_t vo = (uint32_t)(m0 + lr) * (uint32_t)N + (uint32_t)(n0 + lc);  // element offset
-      const uint32_t s8 = 8u * (uint32_t)N;                                          // elements per 8 rows
+      const uint32_t s8 = (uint32_t)RP * (uint32_t)N;                                // elements per RP rows
       float4 cp[4], cm[4], cv[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -347,17 +370,17 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
         cv[u] = bload4(rv, vo * 4u, (uint32_t)u * s8 * 4u);
       }
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < NF; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NF; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r)
             S[wm + i * 32 + (r / 4) * 8 + (lane >> 5) * 4 + (r % 4)][wn + j * 32 + (lane & 31)] = acc[i][j][r];
       __syncthreads();
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int g = 0; g < NG; ++g) {
         float4 np_[4], nm[4], nv[4];
-        if (g + 1 < 4) {
+        if (g + 1 < NG) {
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const uint32_t so = (uint32_t)(4 * (g + 1) + u) * s8 * 4u;
@@ -370,7 +393,7 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
         for (int u = 0; u < 4; ++u) {
           const int q = 4 * g + u;
           const uint32_t so = (uint32_t)q * s8;
-          const float4 g4 = *reinterpret_cast<const float4*>(&S[lr + 8 * q][lc]);
+          const float4 g4 = *reinterpret_cast<const float4*>(&S[lr + RP * q][lc]);
           const float gg[4] = {g4.x, g4.y, g4.z, g4.w};
           const float pp[4] = {cp[u].x, cp[u].y, cp[u].z, cp[u].w};
           const float mm[4] = {cm[u].x, cm[u].y, cm[u].z, cm[u].w};
@@ -379,9 +402,8 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
           unsigned short wo[4];
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
-            mo[k] = e.b1 * mm[k] + (1.0f - e.b1) * gg[k];
-            vq[k] = e.b2 * vv[k] + (1.0f - e.b2) * gg[k] * gg[k];
-            po[k] = pp[k] - e.lr * (mo[k] / e.c1) / (sqrtf(vq[k] / e.c2) + e.eps);
+            mo[k] = mm[k], vq[k] = vv[k], po[k] = pp[k];
+            adam_update(e, gg[k], po[k], mo[k], vq[k]);
             wo[k] = __builtin_bit_cast(unsigned short, to_bf16(po[k]));
           }
           bstore4(rm, vo * 4u, so * 4u, make_float4(mo[0], mo[1], mo[2], mo[3]));
@@ -390,7 +412,7 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
           bstore_2x32(rw, vo * 2u, so * 2u, (uint32_t)wo[0] | ((uint32_t)wo[1] << 16),
                       (uint32_t)wo[2] | ((uint32_t)wo[3] << 16));
         }
-        if (g + 1 < 4) {
+        if (g + 1 < NG) {
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             cp[u] = np_[u];
@@ -399,14 +421,14 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
           }
         }
       }
-    } else if (m0 + TM <= M && n0 + TN <= N) {
+    } else if (m0 + TT <= M && n0 + TT <= N) {
       const uint32_t bytes = (uint32_t)M * (uint32_t)N * 4u;
       const __amdgpu_buffer_rsrc_t rp = make_rsrc(e.p, bytes), rm = make_rsrc(e.m, bytes),
                                    rv = make_rsrc(e.v, bytes), rw = make_rsrc(e.w16, bytes / 2);
       const uint32_t un = (uint32_t)N;
       const uint32_t vbase = (uint32_t)row0 * un + (uint32_t)col0;  // element offset of (row0, col0)
       auto soff = [&](int q, int rr) {  // uniform element offset of group q, element rr
-        const int i = q >> 2, h = q & 1;
+        const int i = q / (2 * NF), h = q & 1;
         return (uint32_t)(i * 32 + h * 16 + (rr / 4) * 8 + (rr % 4)) * un;
       };
       float cp[8], cm[8], cv[8];
@@ -418,10 +440,10 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
         cv[rr] = bload(rv, v, s);
       }
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
+      for (int q = 0; q < 2 * NF * NF; ++q) {
         float np_[8], nm[8], nv[8];
-        if (q + 1 < 8) {
-          const uint32_t v = (vbase + (uint32_t)((((q + 1) >> 1) & 1) * 32)) * 4u;
+        if (q + 1 < 2 * NF * NF) {
+          const uint32_t v = (vbase + (uint32_t)((((q + 1) >> 1) % NF) * 32)) * 4u;
 #pragma unroll
           for (int rr = 0; rr < 8; ++rr) {
             const uint32_t s = soff(q + 1, rr) * 4u;
@@ -430,21 +452,19 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
             nv[rr] = bload(rv, v, s);
           }
         }
-        const int i = q >> 2, j = (q >> 1) & 1, h = q & 1;
+        const int i = q / (2 * NF), j = (q >> 1) % NF, h = q & 1;
         const uint32_t ve = vbase + (uint32_t)(j * 32);
 #pragma unroll
         for (int rr = 0; rr < 8; ++rr) {
           const uint32_t s = soff(q, rr);
-          const float g = acc[i][j][h * 8 + rr];
-          const float mi = e.b1 * cm[rr] + (1.0f - e.b1) * g;
-          const float vi = e.b2 * cv[rr] + (1.0f - e.b2) * g * g;
-          const float pi = cp[rr] - e.lr * (mi / e.c1) / (sqrtf(vi / e.c2) + e.eps);
+          float pi = cp[rr], mi = cm[rr], vi = cv[rr];
+          adam_update(e, acc[i][j][h * 8 + rr], pi, mi, vi);
           bstore(rm, ve * 4u, s * 4u, mi);
           bstore(rv, ve * 4u, s * 4u, vi);
           bstore(rp, ve * 4u, s * 4u, pi);
           bstore16(rw, ve * 2u, s * 2u, to_bf16(pi));
         }
-        if (q + 1 < 8) {
+        if (q + 1 < 2 * NF * NF) {
 #pragma unroll
           for (int rr = 0; rr < 8; ++rr) {
             cp[rr] = np_[rr];
@@ -455,18 +475,16 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < NF; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NF; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int row = row0 + i * 32 + (r / 4) * 8 + (r % 4), col = col0 + j * 32;
             if (row < M && col < N) {
               const uint32_t o = (uint32_t)row * (uint32_t)N + (uint32_t)col;
-              const float g = acc[i][j][r];
-              const float mi = e.b1 * e.m[o] + (1.0f - e.b1) * g;
-              const float vi = e.b2 * e.v[o] + (1.0f - e.b2) * g * g;
-              const float pi = e.p[o] - e.lr * (mi / e.c1) / (sqrtf(vi / e.c2) + e.eps);
+              float pi = e.p[o], mi = e.m[o], vi = e.v[o];
+              adam_update(e, acc[i][j][r], pi, mi, vi);
               e.m[o] = mi;
               e.v[o] = vi;
               e.p[o] = pi;
@@ -476,14 +494,19 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
     }
   } else {
     static_assert(KIND == EPI_MSE, "unknown epilogue");
-    __shared__ float csum[2][TN];
+    // The column sums of 64 rows run over them in one order for either tile: a
+    // wave's fragments one after the other; with narrow tiles the second row
+    // half's wave goes on from the first one's sums.
+    __shared__ float csum[2][TT];
     __shared__ double lsum[4];
-    float cs[2] = {0.0f, 0.0f};
+    float cs[NF], g0[16];
     double e2 = 0.0;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int j = 0; j < NF; ++j) cs[j] = 0.0f;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+      for (int j = 0; j < NF; ++j) {
         const int col = col0 + j * 32;
         const bool cok = col < N;
         const float bv = cok ? e.bias[col] : 0.0f;
@@ -498,29 +521,50 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int row = row0 + i * 32 + (r / 4) * 8 + (r % 4);
+          g0[r] = 0.0f;
           if (row < M && cok) {
             const float vo = acc[i][j][r] + bv;
             const float tt = e.tmu ? (tv[r] - mu) * inv : tv[r];
             const float d = vo - tt;
             e2 += (double)d * (double)d;
-            const float g = 2.0f * d * e.gscale;
-            e.out16[(size_t)row * N + col] = to_bf16(g);
-            cs[j] += g;
+            const float d2 = 2.0f * d;
+            e.out16[(size_t)row * N + col] = to_bf16(d2 * e.gscale);
+            if constexpr (NF == 1) g0[r] = d2;
+            else cs[j] = fmaf(d2, e.gscale, cs[j]);
           }
         }
       }
-    // column sums: the two row halves of the wave, then the two waves of a column half
+    if constexpr (NF == 1) {
+      __shared__ float first[2][64];
+      if (wave < 2) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) cs[j] += __shfl_xor(cs[j], 32, 64);
-    if (lane < 32) {
-      csum[wave >> 1][wn + lane] = cs[0];
-      csum[wave >> 1][wn + 32 + lane] = cs[1];
+        for (int r = 0; r < 16; ++r) cs[0] = fmaf(g0[r], e.gscale, cs[0]);
+        first[wave][lane] = cs[0];
+      }
+      __syncthreads();
+      if (wave >= 2) {
+        cs[0] = first[wave & 1][lane];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) cs[0] = fmaf(g0[r], e.gscale, cs[0]);
+        cs[0] += __shfl_xor(cs[0], 32, 64);
+        const int c = col0;
+        if (lane < 32 && c < N) e.colpart[(size_t)by * N + c] = cs[0];
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < NF; ++j) cs[j] += __shfl_xor(cs[j], 32, 64);
+      if (lane < 32) {
+#pragma unroll
+        for (int j = 0; j < NF; ++j) csum[wave >> 1][wn + j * 32 + lane] = cs[j];
+      }
     }
     e2 = wave_sum64(e2);
     if (lane == 0) lsum[wave] = e2;
     __syncthreads();
-    const int c = threadIdx.x;
-    if (c < TN && n0 + c < N) e.colpart[(size_t)by * N + n0 + c] = csum[0][c] + csum[1][c];
+    if constexpr (NF == 2) {
+      const int c = threadIdx.x & (TT - 1), half = threadIdx.x / TT;
+      if (n0 + c < N && m0 + half * 64 < M) e.colpart[(size_t)(2 * by + half) * N + n0 + c] = csum[half][c];
+    }
     if (threadIdx.x == 0) e.lossp[(size_t)by * gx + bx] = ((lsum[0] + lsum[1]) + lsum[2]) + lsum[3];
   }
 }
@@ -531,6 +575,7 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
 __global__ void k_epilogue(const float* __restrict__ part, int splits, int64_t MN, int N, Epi e) {
   const int64_t i = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
   if (i >= MN) return;
+  int col = MN <= UINT32_MAX ? (int)((uint32_t)i % (uint32_t)N) : (int)(i % N);
   if (MN % 4 == 0) {
     float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll 8
@@ -540,13 +585,17 @@ __global__ void k_epilogue(const float* __restrict__ part, int splits, int64_t M
     }
     const float sv[4] = {s.x, s.y, s.z, s.w};
 #pragma unroll
-    for (int k = 0; k < 4; ++k) epi_act(e, (size_t)(i + k), (int)((i + k) % N), sv[k]);
+    for (int k = 0; k < 4; ++k) {
+      epi_act(e, (size_t)(i + k), col, sv[k]);
+      if (++col == N) col = 0;
+    }
     return;
   }
   for (int64_t j = i; j < i + 4 && j < MN; ++j) {
     float s = 0.0f;
     for (int z = 0; z < splits; ++z) s += part[(size_t)z * MN + j];
-    epi_act(e, (size_t)j, (int)(j % N), s);
+    epi_act(e, (size_t)j, col, s);
+    if (++col == N) col = 0;
   }
 }
 
@@ -556,122 +605,129 @@ __global__ void k_to_bf16(const float* __restrict__ in, bf16* __restrict__ out, 
 }
 
 // Standardized BF16 input: (u - mean) / scale per feature (identity when mean
-// is null).  Four consecutive elements per thread (one 16-byte load, one
-// 8-byte store) when vec4 (n % 4 == 0 and both arrays 16 / 8-byte aligned).
+// is null), rows blockIdx.y, + gridDim.y ..  Four consecutive elements per thread
+// (one 16-byte load, one 8-byte store) when vec4 (d % 4 == 0 and both arrays
+// 16 / 8-byte aligned).  (64 x 60000: 11.7 us with a 64-bit division per element.)
 __global__ void k_in_norm(const float* __restrict__ in, const float* __restrict__ mu,
-                          const float* __restrict__ inv_scale, int64_t n, int d, int vec4, bf16* __restrict__ out) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                          const float* __restrict__ inv_scale, int64_t rows, int d, int vec4, bf16* __restrict__ out) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (vec4) {
-    if (4 * t >= n) return;
-    const float4 v4 = reinterpret_cast<const float4*>(in)[t];
-    float v[4] = {v4.x, v4.y, v4.z, v4.w};
-    if (mu) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int j = (int)((4 * t + k) % d);
-        v[k] = (v[k] - mu[j]) * inv_scale[j];
+    if (4 * (int64_t)t >= d) return;
+    float4 mu4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), inv4 = mu4;
+    if (mu) mu4 = reinterpret_cast<const float4*>(mu)[t], inv4 = reinterpret_cast<const float4*>(inv_scale)[t];
+    for (int64_t r = blockIdx.y; r < rows; r += gridDim.y) {
+      float4 v = reinterpret_cast<const float4*>(in + r * d)[t];
+      if (mu) {
+        v.x = (v.x - mu4.x) * inv4.x, v.y = (v.y - mu4.y) * inv4.y;
+        v.z = (v.z - mu4.z) * inv4.z, v.w = (v.w - mu4.w) * inv4.w;
+      }
+      typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+      reinterpret_cast<bf16x4*>(out + r * d)[t] = bf16x4{to_bf16(v.x), to_bf16(v.y), to_bf16(v.z), to_bf16(v.w)};
+    }
+    return;
+  }
+  if (t >= d) return;
+  const float m0 = mu ? mu[t] : 0.0f, s0 = mu ? inv_scale[t] : 0.0f;
+  for (int64_t r = blockIdx.y; r < rows; r += gridDim.y) {
+    float v = in[r * d + t];
+    if (mu) v = (v - m0) * s0;
+    out[r * d + t] = to_bf16(v);
+  }
+}
+
+// Column sums of an FP32 matrix in a fixed order (bias gradients), the Adam step
+// on the biases they belong to, and the loss from its partials: all that is left
+// of a training step beside its products, in one launch.
+//   seg < 2: hidden layers' biases, b[seg] = column sums of g[seg] (rows x cols);
+//     a workgroup takes 64 columns.  Up to 32 rows are added one after the other;
+//     more in blocks of 32 rows, of which wave w takes every fourth row from
+//     w with four independent partial sums, the blocks' sums then in order.
+//   seg 2: the output layer's, from sums of 64 rows each (rows of them),
+//     added in pairs, the pairs in order; 1024 columns a workgroup.
+//   last workgroup: loss = scale * sum of the partials (when loss is set).
+// (Batch 256, width 512, 6000 outputs: seven launches of 4 to 6 us each before.)
+struct BiasSeg {
+  const float* g;
+  int rows, cols, nblk;
+  int64_t off;  // of the biases in the parameters
+};
+struct BiasStep {
+  BiasSeg seg[3];
+  float *grads, *p, *m, *v;
+  int adam;
+  float lr, b1, b2, eps, c1, c2;
+  const double* lossp;
+  int nloss;
+  double scale;
+  float* loss;
+};
+
+__global__ __launch_bounds__(1024) void k_bias_step(BiasStep q) {
+  __shared__ float red[16][64];
+  __shared__ double lred[256];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  int b = blockIdx.x, k = 0;
+  while (k < 3 && b >= q.seg[k].nblk) b -= q.seg[k++].nblk;
+  if (k == 3) {
+    if (t < 256) {
+      double s = 0.0;
+      for (int i = t; i < q.nloss; i += 256) s += q.lossp[i];
+      lred[t] = s;
+    }
+    __syncthreads();
+    for (int n = 128; n > 0; n >>= 1) {
+      if (t < n) lred[t] += lred[t + n];
+      __syncthreads();
+    }
+    if (t == 0) q.loss[0] = (float)(lred[0] * q.scale);
+    return;
+  }
+  const BiasSeg s = q.seg[k];
+  int c;
+  float sum = 0.0f;
+  if (k == 2) {
+    c = b * 1024 + t;
+    if (c >= s.cols) return;
+    for (int r = 0; r < s.rows; r += 2)
+      sum += r + 1 < s.rows ? s.g[(size_t)r * s.cols + c] + s.g[(size_t)(r + 1) * s.cols + c] : s.g[(size_t)r * s.cols + c];
+  } else {
+    c = b * 64 + lane;
+    if (s.rows <= 32) {
+      if (wave == 0 && c < s.cols)
+        for (int r = 0; r < s.rows; ++r) sum += s.g[(size_t)r * s.cols + c];
+    } else {
+      for (int y0 = 0; y0 * 32 < s.rows; y0 += 4) {  // four blocks of 32 rows at a time
+        const int y = y0 + (wave >> 2), r1 = min(s.rows, y * 32 + 32);
+        float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
+        if (c < s.cols) {
+          int r = y * 32 + (wave & 3);
+          for (; r + 12 < r1; r += 16) {
+            s0 += s.g[(size_t)r * s.cols + c];
+            s1 += s.g[(size_t)(r + 4) * s.cols + c];
+            s2 += s.g[(size_t)(r + 8) * s.cols + c];
+            s3 += s.g[(size_t)(r + 12) * s.cols + c];
+          }
+          for (; r < r1; r += 4) s0 += s.g[(size_t)r * s.cols + c];
+        }
+        red[wave][lane] = (s0 + s1) + (s2 + s3);
+        __syncthreads();
+        if (wave == 0)
+          for (int u = 0; u < 4 && (y0 + u) * 32 < s.rows; ++u)
+            sum += ((red[4 * u][lane] + red[4 * u + 1][lane]) + red[4 * u + 2][lane]) + red[4 * u + 3][lane];
+        __syncthreads();
       }
     }
-    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-    bf16x4 o;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] = to_bf16(v[k]);
-    reinterpret_cast<bf16x4*>(out)[t] = o;
-    return;
+    if (wave != 0 || c >= s.cols) return;
   }
-  if (t >= n) return;
-  float v = in[t];
-  if (mu) {
-    const int j = (int)(t % d);
-    v = (v - mu[j]) * inv_scale[j];
+  const int64_t j = s.off + c;
+  q.grads[j] = sum;
+  if (q.adam) {
+    const float mi = fmaf(1.0f - q.b1, sum, q.b1 * q.m[j]);
+    const float vi = fmaf((1.0f - q.b2) * sum, sum, q.b2 * q.v[j]);
+    q.m[j] = mi;
+    q.v[j] = vi;
+    q.p[j] -= q.lr * (mi / q.c1) / (sqrtf(vi / q.c2) + q.eps);
   }
-  out[t] = to_bf16(v);
-}
-
-// Network output in the caller's units: z * scale + mean per feature.
-__global__ void k_out_denorm(const float* __restrict__ z, const float* __restrict__ mu,
-                             const float* __restrict__ scale, int64_t n, int d, float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float v = z[i];
-  if (mu) {
-    const int j = (int)(i % d);
-    v = v * scale[j] + mu[j];
-  }
-  out[i] = v;
-}
-
-__global__ void k_sum_parts(const double* __restrict__ part, int n, double scale, float* __restrict__ out) {
-  __shared__ double red[256];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) s += part[i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int k = blockDim.x / 2; k > 0; k >>= 1) {
-    if (threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[0] = (float)(red[0] * scale);
-}
-
-// Column sums of a [rows x cols] FP32 matrix (bias gradients), fixed order.
-__global__ void k_colsum(const float* __restrict__ g, int rows, int cols, float* __restrict__ out) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= cols) return;
-  float s = 0.0f;
-  for (int r = 0; r < rows; ++r) s += g[(size_t)r * cols + c];
-  out[c] = s;
-}
-
-// First level of a column sum over many rows: workgroup (x, y) adds rows
-// [y * chunk, (y + 1) * chunk) of 64 columns, wave w taking every fourth row
-// from w with four independent partial sums; part[y][col] = the waves' sums in
-// order.  Fixed order: deterministic.
-__global__ __launch_bounds__(256) void k_colsum_part(const float* __restrict__ g, int rows, int cols, int chunk,
-                                                     float* __restrict__ part) {
-  __shared__ float red[4][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int c = blockIdx.x * 64 + lane;
-  const int r0 = blockIdx.y * chunk, r1 = min(rows, r0 + chunk);
-  float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-  if (c < cols) {
-    int r = r0 + wave;
-    for (; r + 12 < r1; r += 16) {
-      s0 += g[(size_t)r * cols + c];
-      s1 += g[(size_t)(r + 4) * cols + c];
-      s2 += g[(size_t)(r + 8) * cols + c];
-      s3 += g[(size_t)(r + 12) * cols + c];
-    }
-    for (; r < r1; r += 4) s0 += g[(size_t)r * cols + c];
-  }
-  red[wave][lane] = (s0 + s1) + (s2 + s3);
-  __syncthreads();
-  if (wave == 0 && c < cols) part[(size_t)blockIdx.y * cols + c] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
-}
-
-// Adam step on FP32 parameters outside the weight matrices (whose updates run
-// inside their gradient products): three segments [o, o + n) in one launch,
-// the three bias vectors.
-__global__ void k_adam3(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                        float* __restrict__ v, int64_t o0, int64_t n0, int64_t o1, int64_t n1, int64_t o2,
-                        int64_t n2, float lr, float b1, float b2, float eps, float c1, float c2) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t j;
-  if (i < n0) {
-    j = o0 + i;
-  } else if ((i -= n0) < n1) {
-    j = o1 + i;
-  } else if ((i -= n1) < n2) {
-    j = o2 + i;
-  } else {
-    return;
-  }
-  const float gi = g[j];
-  const float mi = b1 * m[j] + (1.0f - b1) * gi;
-  const float vi = b2 * v[j] + (1.0f - b2) * gi * gi;
-  m[j] = mi;
-  v[j] = vi;
-  p[j] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
 inline dim3 lin(int64_t n, int t = 256) { return dim3((unsigned)((n + t - 1) / t)); }
@@ -692,11 +748,17 @@ struct pdcs_mlp_s {
   int64_t last = 0;   // batch of the last forward / gradient / training call
   bool have_grad_acts = false;  // the last call computed the backward activations
   // activations: BF16 operands of the products (input, h1, h2, dL/dv, dL/dz2,
-  // dL/dz1), the FP32 output, FP32 masked hidden gradients (bias sums), the
-  // loss gradient's per-row-tile column sums and the loss partials
-  DBuf u16, h1_16, h2_16, vout, dv16, dz16a, dz16b, dh, colpart, part, cspart, lossp, lossv;
-  size_t part_bytes = 0, cs_bytes = 0;
+  // dL/dz1), FP32 masked hidden gradients of both layers (bias sums), the loss
+  // gradient's column sums per 64 rows and the loss partials
+  DBuf u16, h1_16, h2_16, dv16, dz16a, dz16b, dh, colpart, part, lossp;
+  float* loss_host = nullptr;  // pinned: the loss is stored where the host reads it
+  size_t part_bytes = 0;
   hipStream_t stream = nullptr;
+
+  ~pdcs_mlp_s() {
+    if (loss_host) (void)hipHostFree(loss_host);
+    if (stream) (void)hipStreamDestroy(stream);
+  }
 
   bf16* W1() const { return wbf.as<bf16>(); }
   bf16* W2() const { return wbf.as<bf16>() + w * din; }
@@ -715,18 +777,15 @@ struct pdcs_mlp_s {
   void ensure(int64_t B) {
     if (B <= cap) return;
     cap = B;
-    const int64_t rt = (B + TM - 1) / TM;  // row tiles of the output layer
     u16.alloc(B * din * 2);
     h1_16.alloc(B * w * 2);
     h2_16.alloc(B * w * 2);
-    vout.alloc(B * dout * 4);
     dv16.alloc(B * dout * 2);
     dz16a.alloc(B * w * 2);
     dz16b.alloc(B * w * 2);
-    dh.alloc(B * w * 4);
-    colpart.alloc(rt * dout * 4);
-    lossp.alloc(rt * ((dout + TN - 1) / TN) * 8);
-    lossv.alloc(8);
+    dh.alloc(2 * B * w * 4);
+    colpart.alloc(((B + 63) / 64) * dout * 4);
+    lossp.alloc(((B + 63) / 64) * ((dout + 63) / 64) * 8);
   }
 
   // op(A)[M x K] op(B)[K x N] with epilogue `kind`.  Products whose output tiles
@@ -737,8 +796,7 @@ struct pdcs_mlp_s {
   // at batch 256), 32 below.
   void gemm(int kind, const bf16* A, int lda, int ta, const bf16* Bm, int ldb, int tb, int M, int N, int K,
             Epi e, hipStream_t s) {
-    const int gx = (N + TN - 1) / TN, gy = (M + TM - 1) / TM;
-    const int tiles = gx * gy;
+    const int tiles = ((N + kTileWide - 1) / kTileWide) * ((M + kTileWide - 1) / kTileWide);
     if (kind == EPI_ADAM) e.vec4 = adam_vec4(e, N);
     // (products of a few tiles split down to K-ranges of 128: a handful of
     // workgroups walking the whole K serially would leave the chip idle)
@@ -757,61 +815,60 @@ struct pdcs_mlp_s {
         part.alloc(need);
         part_bytes = need;
       }
-      launch(EPI_STORE, kt, A, lda, ta, Bm, ldb, tb, part.as<float>(), M, N, K, gx, gy, splits, e, s);
+      launch(EPI_STORE, kt, A, lda, ta, Bm, ldb, tb, part.as<float>(), M, N, K, splits, e, s);
       k_epilogue<<<lin(((int64_t)M * N + 3) / 4), 256, 0, s>>>(part.as<float>(), splits, (int64_t)M * N, N, e);
       return;
     }
-    launch(kind, kt, A, lda, ta, Bm, ldb, tb, kind == EPI_STORE ? e.out32 : nullptr, M, N, K, gx, gy, 1, e, s);
+    launch(kind, kt, A, lda, ta, Bm, ldb, tb, kind == EPI_STORE ? e.out32 : nullptr, M, N, K, 1, e, s);
+  }
+
+  // The tile's side: narrow while wide tiles make fewer than two workgroups for
+  // each CU (wide and narrow, us: weight gradients with Adam 6000 x 512 and
+  // 512 x 6000 at batch 256, and 512 x 512, 39.4 and 19.1 on average; split
+  // products of 256 workgroups 12.2 and 7.9; the output layer 64 x 60000 of width
+  // 512 35 and 20, with loss 256 x 6000 30 and 25).
+  static bool narrow(int M, int N, int splits) {
+    return ((N + kTileWide - 1) / kTileWide) * ((M + kTileWide - 1) / kTileWide) * splits < 512;
+  }
+
+  template <int KIND, int TT>
+  static void launch_tile(int kt, const bf16* A, int lda, int ta, int veca, const bf16* Bm, int ldb, int tb, int vecb,
+                          float* C, int M, int N, int K, int splits, const Epi& e, hipStream_t s) {
+    const int gx = (N + TT - 1) / TT, gy = (M + TT - 1) / TT;
+    const dim3 grid((unsigned)(gx * gy * splits));
+    if (kt == 64)
+      k_gemm<KIND, 64, TT><<<grid, 256, 0, s>>>(A, lda, ta, veca, Bm, ldb, tb, vecb, C, M, N, K, gx, gy, e);
+    else
+      k_gemm<KIND, 32, TT><<<grid, 256, 0, s>>>(A, lda, ta, veca, Bm, ldb, tb, vecb, C, M, N, K, gx, gy, e);
   }
 
   template <int KIND>
-  static void launch_kt(int kt, dim3 grid, const bf16* A, int lda, int ta, int veca, const bf16* Bm, int ldb, int tb,
-                        int vecb, float* C, int M, int N, int K, int gx, int gy, const Epi& e,
-                        hipStream_t s) {
-    if (kt == 64)
-      k_gemm<KIND, 64><<<grid, 256, 0, s>>>(A, lda, ta, veca, Bm, ldb, tb, vecb, C, M, N, K, gx, gy, e);
-    else
-      k_gemm<KIND, 32><<<grid, 256, 0, s>>>(A, lda, ta, veca, Bm, ldb, tb, vecb, C, M, N, K, gx, gy, e);
-  }
-
-  static void launch(int kind, int kt, const bf16* A, int lda, int ta, const bf16* Bm, int ldb, int tb, float* C, int M,
-                     int N, int K, int gx, int gy, int splits, const Epi& e, hipStream_t s) {
+  static void launch_kind(int kt, const bf16* A, int lda, int ta, const bf16* Bm, int ldb, int tb, float* C, int M,
+                          int N, int K, int splits, const Epi& e, hipStream_t s) {
     // 16-byte vector loads need 16-byte aligned operands with row strides in whole vectors
     const int veca = ((uintptr_t)A % 16 == 0 && lda % 8 == 0) ? 1 : 0;
     const int vecb = ((uintptr_t)Bm % 16 == 0 && ldb % 8 == 0) ? 1 : 0;
-    const dim3 grid((unsigned)(gx * gy * splits));
-    switch (kind) {
-      case EPI_STORE:
-        launch_kt<EPI_STORE>(kt, grid, A, lda, ta, veca, Bm, ldb, tb, vecb, C, M, N, K, gx, gy, e, s);
-        break;
-      case EPI_ACT:
-        launch_kt<EPI_ACT>(kt, grid, A, lda, ta, veca, Bm, ldb, tb, vecb, C, M, N, K, gx, gy, e, s);
-        break;
-      case EPI_ADAM:
-        launch_kt<EPI_ADAM>(kt, grid, A, lda, ta, veca, Bm, ldb, tb, vecb, C, M, N, K, gx, gy, e, s);
-        break;
-      default:
-        launch_kt<EPI_MSE>(kt, grid, A, lda, ta, veca, Bm, ldb, tb, vecb, C, M, N, K, gx, gy, e, s);
-    }
+    if (narrow(M, N, splits))
+      launch_tile<KIND, kTileNarrow>(kt, A, lda, ta, veca, Bm, ldb, tb, vecb, C, M, N, K, splits, e, s);
+    else
+      launch_tile<KIND, kTileWide>(kt, A, lda, ta, veca, Bm, ldb, tb, vecb, C, M, N, K, splits, e, s);
   }
 
-  // Column sums of g [rows x cols] into out (fixed order): one pass for a few
-  // rows, else 32-row partial sums by many workgroups, then their sum.
-  void colsum(const float* g, int64_t rows, int64_t cols, float* out, hipStream_t s) {
-    if (rows <= 32) {
-      k_colsum<<<lin(cols), 256, 0, s>>>(g, (int)rows, (int)cols, out);
-      return;
+  static void launch(int kind, int kt, const bf16* A, int lda, int ta, const bf16* Bm, int ldb, int tb, float* C, int M,
+                     int N, int K, int splits, const Epi& e, hipStream_t s) {
+    switch (kind) {
+      case EPI_STORE:
+        launch_kind<EPI_STORE>(kt, A, lda, ta, Bm, ldb, tb, C, M, N, K, splits, e, s);
+        break;
+      case EPI_ACT:
+        launch_kind<EPI_ACT>(kt, A, lda, ta, Bm, ldb, tb, C, M, N, K, splits, e, s);
+        break;
+      case EPI_ADAM:
+        launch_kind<EPI_ADAM>(kt, A, lda, ta, Bm, ldb, tb, C, M, N, K, splits, e, s);
+        break;
+      default:
+        launch_kind<EPI_MSE>(kt, A, lda, ta, Bm, ldb, tb, C, M, N, K, splits, e, s);
     }
-    const int chunk = 32;
-    const int64_t ny = (rows + chunk - 1) / chunk;
-    const size_t need = (size_t)ny * cols * 4;
-    if (need > cs_bytes) {
-      cspart.alloc(need);
-      cs_bytes = need;
-    }
-    k_colsum_part<<<dim3((unsigned)((cols + 63) / 64), (unsigned)ny), 256, 0, s>>>(g, (int)rows, (int)cols, chunk,
-                                                                                  cspart.as<float>());
-    k_colsum<<<lin(cols), 256, 0, s>>>(cspart.as<float>(), (int)ny, (int)cols, out);
   }
 
   static Epi act(const float* bias, int relu, const bf16* mask, float* out32, bf16* out16) {
@@ -857,33 +914,37 @@ struct pdcs_mlp_s {
   void hidden(const float* in, int64_t B, hipStream_t s) {
     ensure(B);
     last = B;
-    const int64_t n = B * din;
-    const int vec4 = (n % 4 == 0 && (uintptr_t)in % 16 == 0 && (uintptr_t)u16.p % 8 == 0) ? 1 : 0;
-    k_in_norm<<<lin(vec4 ? n / 4 : n), 256, 0, s>>>(in, imu(), in_inv.as<float>(), n, (int)din, vec4, u16.as<bf16>());
+    const int vec4 = (din % 4 == 0 && (uintptr_t)in % 16 == 0 && (uintptr_t)u16.p % 8 == 0) ? 1 : 0;
+    const dim3 grid((unsigned)(((vec4 ? din / 4 : din) + 255) / 256), (unsigned)std::min<int64_t>(B, 65535));
+    k_in_norm<<<grid, 256, 0, s>>>(in, imu(), in_inv.as<float>(), B, (int)din, vec4, u16.as<bf16>());
     gemm(EPI_ACT, u16.as<bf16>(), din, 0, W1(), din, 1, B, w, din, act(P(off_b1), 1, nullptr, nullptr, h1_16.as<bf16>()),
          s);
     gemm(EPI_ACT, h1_16.as<bf16>(), w, 0, W2(), w, 1, B, w, w, act(P(off_b2), 1, nullptr, nullptr, h2_16.as<bf16>()),
          s);
   }
 
-  void forward(const float* in, int64_t B, hipStream_t s) {
+  // The network output in the caller's units: z * scale + mean per feature.
+  void forward(const float* in, int64_t B, float* out, hipStream_t s) {
     hidden(in, B, s);
     have_grad_acts = false;
-    gemm(EPI_ACT, h2_16.as<bf16>(), w, 0, W3(), w, 1, B, dout, w, act(P(off_b3), 0, nullptr, vout.as<float>(), nullptr),
-         s);
+    Epi e = act(P(off_b3), 0, nullptr, out, nullptr);
+    if (norm_out) {
+      e.osc = out_sc.as<float>();
+      e.omu = out_mu.as<float>();
+    }
+    gemm(EPI_ACT, h2_16.as<bf16>(), w, 0, W3(), w, 1, B, dout, w, e, s);
   }
 
   // Forward and backward of the mean squared error; the weight gradients are
   // stored in `grads`, or, when `adam`, applied as an Adam step inside the
   // weight-gradient products (each layer's BF16 weights are read by the
   // backward product before its own update rewrites them).  Bias gradients go
-  // to `grads` either way; the loss stays on the device (lossv), summed from
-  // its partials only when `need_loss`.
+  // to `grads` either way; the loss is summed from its partials into loss_host
+  // only when `need_loss`.
   void train(const float* in, const float* target, int64_t B, bool adam, float lr, bool need_loss, hipStream_t s) {
     hidden(in, B, s);
     have_grad_acts = true;
     const int64_t n = B * dout;
-    const int rt = (int)((B + TM - 1) / TM), ct = (int)((dout + TN - 1) / TN);
     // output layer fused with the loss: dv16 = BF16 dL/dv, column sums, loss partials
     Epi mse;
     mse.bias = P(off_b3);
@@ -895,29 +956,33 @@ struct pdcs_mlp_s {
     mse.colpart = colpart.as<float>();
     mse.lossp = lossp.as<double>();
     gemm(EPI_MSE, h2_16.as<bf16>(), w, 0, W3(), w, 1, B, dout, w, mse, s);
-    if (need_loss) k_sum_parts<<<1, 256, 0, s>>>(lossp.as<double>(), rt * ct, 1.0 / (double)n, lossv.as<float>());
-    colsum(colpart.as<float>(), rt, dout, G(off_b3), s);
     // layer 3: dZ2 = (dV W3) * (h2 > 0) before W3 changes, then dW3 = dV^T H2
     gemm(EPI_ACT, dv16.as<bf16>(), dout, 0, W3(), w, 0, B, w, dout,
          act(nullptr, 0, h2_16.as<bf16>(), dh.as<float>(), dz16a.as<bf16>()), s);
     gemm(adam ? EPI_ADAM : EPI_STORE, dv16.as<bf16>(), dout, 1, h2_16.as<bf16>(), w, 0, dout, w, B,
          wgrad(adam, off_w3, W3(), lr), s);
-    colsum(dh.as<float>(), B, w, G(off_b2), s);
     // layer 2: dZ1 = (dZ2 W2) * (h1 > 0), then dW2 = dZ2^T H1
     gemm(EPI_ACT, dz16a.as<bf16>(), w, 0, W2(), w, 0, B, w, w,
-         act(nullptr, 0, h1_16.as<bf16>(), dh.as<float>(), dz16b.as<bf16>()), s);
+         act(nullptr, 0, h1_16.as<bf16>(), dh.as<float>() + B * w, dz16b.as<bf16>()), s);
     gemm(adam ? EPI_ADAM : EPI_STORE, dz16a.as<bf16>(), w, 1, h1_16.as<bf16>(), w, 0, w, w, B,
          wgrad(adam, off_w2, W2(), lr), s);
-    colsum(dh.as<float>(), B, w, G(off_b1), s);
     // layer 1: dW1 = dZ1^T U
     gemm(adam ? EPI_ADAM : EPI_STORE, dz16b.as<bf16>(), w, 1, u16.as<bf16>(), din, 0, w, din, B,
          wgrad(adam, off_w1, W1(), lr), s);
-    if (adam) {  // the biases: FP32 only, one small pass
-      const Epi e = wgrad(true, off_b1, nullptr, lr);
-      k_adam3<<<lin(2 * w + dout), 256, 0, s>>>(params.as<float>(), grads.as<float>(), adam_m.as<float>(),
-                                                 adam_v.as<float>(), off_b1, w, off_b2, w, off_b3, dout, lr, e.b1,
-                                                 e.b2, e.eps, e.c1, e.c2);
-    }
+    const Epi e = wgrad(true, off_b1, nullptr, lr);
+    BiasStep q;
+    const int hb = (int)((w + 63) / 64), side = narrow((int)B, (int)dout, 1) ? kTileNarrow : kTileWide;
+    q.seg[0] = {dh.as<float>(), (int)B, (int)w, hb, off_b2};
+    q.seg[1] = {dh.as<float>() + B * w, (int)B, (int)w, hb, off_b1};
+    q.seg[2] = {colpart.as<float>(), (int)((B + 63) / 64), (int)dout, (int)((dout + 1023) / 1024), off_b3};
+    q.grads = grads.as<float>(), q.p = params.as<float>(), q.m = adam_m.as<float>(), q.v = adam_v.as<float>();
+    q.adam = adam ? 1 : 0;
+    q.lr = lr, q.b1 = e.b1, q.b2 = e.b2, q.eps = e.eps, q.c1 = e.c1, q.c2 = e.c2;
+    q.lossp = lossp.as<double>();
+    q.nloss = (int)(((B + side - 1) / side) * ((dout + side - 1) / side));
+    q.scale = 1.0 / (double)n;
+    q.loss = loss_host;
+    k_bias_step<<<(unsigned)(2 * hb + q.seg[2].nblk + (need_loss ? 1 : 0)), 1024, 0, s>>>(q);
   }
 };
 
@@ -942,6 +1007,7 @@ int pdcs_mlp_create(int64_t d_in, int64_t width, int64_t d_out, uint64_t seed, p
     net->off_b3 = net->off_w3 + d_out * width;
     net->np = net->off_b3 + d_out;
     HIP_OK(hipStreamCreateWithFlags(&net->stream, hipStreamNonBlocking));
+    HIP_OK(hipHostMalloc((void**)&net->loss_host, sizeof(float), hipHostMallocDefault));
     // Glorot-uniform weights, zero biases, from a seeded host generator
     std::vector<float> p(net->np, 0.0f);
     std::mt19937_64 gen(seed);
@@ -984,9 +1050,7 @@ int pdcs_mlp_forward(pdcs_mlp net, const float* in_dev, float* out_dev, int64_t 
   try {
     if (!net || !in_dev || !out_dev || batch < 1) throw Error(PDCS_ERR_INVALID_ARG, "bad forward arguments");
     hipStream_t s = pick(net, stream);
-    net->forward(in_dev, batch, s);
-    k_out_denorm<<<lin(batch * net->dout), 256, 0, s>>>(net->vout.as<float>(), net->omu(), net->out_sc.as<float>(),
-                                                       batch * net->dout, (int)net->dout, out_dev);
+    net->forward(in_dev, batch, out_dev, s);
     HIP_OK(hipGetLastError());
     return PDCS_OK;
   } catch (const Error& e) {
@@ -1003,10 +1067,8 @@ int pdcs_mlp_gradients(pdcs_mlp net, const float* in_dev, const float* target_de
     net->train(in_dev, target_dev, batch, false, 0.0f, loss_out != nullptr, s);
     if (grad_dev) HIP_OK(hipMemcpyAsync(grad_dev, net->grads.p, net->np * 4, hipMemcpyDeviceToDevice, s));
     HIP_OK(hipGetLastError());
-    float loss = 0.0f;
-    if (loss_out) HIP_OK(hipMemcpyAsync(&loss, net->lossv.p, 4, hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
-    if (loss_out) *loss_out = loss;
+    if (loss_out) *loss_out = *(volatile float*)net->loss_host;
     return PDCS_OK;
   } catch (const Error& e) {
     set_last_error(e.what());
@@ -1024,10 +1086,8 @@ int pdcs_mlp_train_step(pdcs_mlp net, const float* in_dev, const float* target_d
     net->train(in_dev, target_dev, batch, true, lr, loss_out != nullptr, s);
     HIP_OK(hipGetLastError());
     if (loss_out) {  // without a loss pointer the step stays asynchronous on `stream`
-      float loss = 0.0f;
-      HIP_OK(hipMemcpyAsync(&loss, net->lossv.p, 4, hipMemcpyDeviceToHost, s));
       HIP_OK(hipStreamSynchronize(s));
-      *loss_out = loss;
+      *loss_out = *(volatile float*)net->loss_host;
     }
     return PDCS_OK;
   } catch (const Error& e) {
@@ -1136,8 +1196,6 @@ int pdcs_mlp_set_params(pdcs_mlp net, const float* params_host) {
 }
 
 void pdcs_mlp_destroy(pdcs_mlp net) {
-  if (!net) return;
-  if (net->stream) (void)hipStreamDestroy(net->stream);
   delete net;
 }
 
