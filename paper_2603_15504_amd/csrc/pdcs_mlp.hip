@@ -190,10 +190,14 @@ __device__ __forceinline__ float4 bload4(__amdgpu_buffer_rsrc_t r, uint32_t voff
   const i32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0);
   return make_float4(__int_as_float(v[0]), __int_as_float(v[1]), __int_as_float(v[2]), __int_as_float(v[3]));
 }
-__device__ __forceinline__ void bstore4(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, float4 x) {
+// (The whole offset per lane: a 16-byte store still reads its data registers while
+// the next instruction runs, and the compiler keeps that one from overwriting
+// them only when the scalar offset is no register.  With one, stores followed
+// at once by a write of their first register left that value in memory.)
+__device__ __forceinline__ void bstore4(__amdgpu_buffer_rsrc_t r, uint32_t off, float4 x) {
   typedef int i32x4 __attribute__((ext_vector_type(4)));
   const i32x4 v = {__float_as_int(x.x), __float_as_int(x.y), __float_as_int(x.z), __float_as_int(x.w)};
-  __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)voff, (int)soff, 0);
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)off, 0, 0);
 }
 __device__ __forceinline__ void bstore_2x32(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, uint32_t lo,
                                             uint32_t hi) {
@@ -221,20 +225,37 @@ __device__ __forceinline__ double wave_sum64(double v) {
 // tile order runs fastest along the shorter grid side, so the tiles that read
 // the same operand panel (the same K-chunk of a split product, the same row or
 // column panel otherwise) meet in one L2.
+struct GemmArgs {
+  const bf16* A;
+  int lda, ta, veca;
+  const bf16* B;
+  int ldb, tb, vecb;
+  float* C;
+  int M, N, K, gx, gy;
+  Epi e;
+};
+
+// Workgroup L of the total that the product takes.
 template <int KIND, int KT, int TT>
-__global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int lda, int ta, int veca,
-                                              const bf16* __restrict__ B, int ldb, int tb, int vecb,
-                                              float* __restrict__ C, int M, int N, int K, int gx,
-                                              int gy, Epi e) {
+__device__ __forceinline__ void gemm_block(const GemmArgs& q, int L, int total) {
+  const bf16 *__restrict__ A = q.A, *__restrict__ B = q.B;
+  float* __restrict__ C = q.C;
+  const int lda = q.lda, ta = q.ta, veca = q.veca, ldb = q.ldb, tb = q.tb, vecb = q.vecb;
+  const int M = q.M, N = q.N, K = q.K, gx = q.gx, gy = q.gy;
+  const Epi& e = q.e;
   // operand tiles for the K-loop; the Adam epilogue reuses the same LDS to
   // stage the FP32 output tile (rows padded by 4 floats)
-  constexpr int kTileBytes = 2 * TT * (KT + 8) * 2;
+  // K-tiles staged together, the order of the sums staying: two narrow ones in the
+  // loss layer, whose few workgroups (376 for 256 x 6000) each wait for every
+  // K-tile's loads (25.4 us with one, 15.9 with two; the other kinds, one and two:
+  // split products 7.9 and 8.9, 64 x 60000 outputs 19.7 and 20.5, Adam 19.1 and 19.0)
+  constexpr int U = KIND == EPI_MSE && TT == kTileNarrow ? 2 : 1;
+  constexpr int kTileBytes = U * 2 * TT * (KT + 8) * 2;
   constexpr int kStageBytes = KIND == EPI_ADAM ? TT * (TT + 4) * 4 : 0;
   constexpr int NF = TT / 64;  // 32 x 32 fragments of a wave along each side
   __shared__ __attribute__((aligned(16))) unsigned char smem[kTileBytes > kStageBytes ? kTileBytes : kStageBytes];
-  bf16(*As)[KT + 8] = reinterpret_cast<bf16(*)[KT + 8]>(smem);
-  bf16(*Bs)[KT + 8] = reinterpret_cast<bf16(*)[KT + 8]>(smem + TT * (KT + 8) * 2);
-  const int L = blockIdx.x, total = gridDim.x;
+  bf16(*As)[TT][KT + 8] = reinterpret_cast<bf16(*)[TT][KT + 8]>(smem);
+  bf16(*Bs)[TT][KT + 8] = reinterpret_cast<bf16(*)[TT][KT + 8]>(smem + U * TT * (KT + 8) * 2);
   const int full = total & ~7;
   const int Q = L < full ? (L & 7) * (full >> 3) + (L >> 3) : L;
   const int tiles = gx * gy;
@@ -261,38 +282,50 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
     for (int j = 0; j < NF; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-  TileRegs<TT, KT> ra, rb;
-  if (z * KT < K) {
-    tile_load<TT, KT>(A, lda, ta, veca, m0, M, z * KT, min(K, z * KT + KT), ra);
-    tile_load<TT, KT>(B, ldb, !tb, vecb, n0, N, z * KT, min(K, z * KT + KT), rb);
-  }
-  for (int k0 = z * KT; k0 < K; k0 += kstep) {
-    tile_store<TT, KT>(As, ta, ra);
-    tile_store<TT, KT>(Bs, !tb, rb);
-    __syncthreads();
-    const int kn = k0 + kstep;
-    if (kn < K) {  // prefetch the next tile while the matrix cores work
-      tile_load<TT, KT>(A, lda, ta, veca, m0, M, kn, min(K, kn + KT), ra);
-      tile_load<TT, KT>(B, ldb, !tb, vecb, n0, N, kn, min(K, kn + KT), rb);
+  TileRegs<TT, KT> ra[U], rb[U];
+  const auto load = [&](int k0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int ku = k0 + u * kstep;
+      if (ku < K) {
+        tile_load<TT, KT>(A, lda, ta, veca, m0, M, ku, min(K, ku + KT), ra[u]);
+        tile_load<TT, KT>(B, ldb, !tb, vecb, n0, N, ku, min(K, ku + KT), rb[u]);
+      }
     }
+  };
+  load(z * KT);
+  for (int k0 = z * KT; k0 < K; k0 += U * kstep) {
 #pragma unroll
-    for (int kk = 0; kk < KT; kk += 16) {
-      bf16x8 a[NF], b[NF];
-      const int kb = (kk >> 3) + (lane >> 5);  // 16-byte block of k-values kk + 8 (lane / 32) ..
-#pragma unroll
-      for (int i = 0; i < NF; ++i) {
-        const int row = wm + i * 32 + (lane & 31);
-        a[i] = *reinterpret_cast<const bf16x8*>(&As[row][swz<KT>(row, kb) * 8]);
+    for (int u = 0; u < U; ++u)
+      if (k0 + u * kstep < K) {
+        tile_store<TT, KT>(As[u], ta, ra[u]);
+        tile_store<TT, KT>(Bs[u], !tb, rb[u]);
       }
+    __syncthreads();
+    load(k0 + U * kstep);  // prefetch the next tiles while the matrix cores work
 #pragma unroll
-      for (int j = 0; j < NF; ++j) {
-        const int row = wn + j * 32 + (lane & 31);
-        b[j] = *reinterpret_cast<const bf16x8*>(&Bs[row][swz<KT>(row, kb) * 8]);
+    for (int u = 0; u < U; ++u) {
+      if (k0 + u * kstep >= K) break;
+#pragma unroll
+      for (int kk = 0; kk < KT; kk += 16) {
+        bf16x8 a[NF], b[NF];
+        const int kb = (kk >> 3) + (lane >> 5);  // 16-byte block of k-values kk + 8 (lane / 32) ..
+#pragma unroll
+        for (int i = 0; i < NF; ++i) {
+          const int row = wm + i * 32 + (lane & 31);
+          a[i] = *reinterpret_cast<const bf16x8*>(&As[u][row][swz<KT>(row, kb) * 8]);
+        }
+#pragma unroll
+        for (int j = 0; j < NF; ++j) {
+          const int row = wn + j * 32 + (lane & 31);
+          b[j] = *reinterpret_cast<const bf16x8*>(&Bs[u][row][swz<KT>(row, kb) * 8]);
+        }
+#pragma unroll
+        for (int i = 0; i < NF; ++i)
+#pragma unroll
+          for (int j = 0; j < NF; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
       }
-#pragma unroll
-      for (int i = 0; i < NF; ++i)
-#pragma unroll
-        for (int j = 0; j < NF; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     }
     __syncthreads();
   }
@@ -406,9 +439,9 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
             adam_update(e, gg[k], po[k], mo[k], vq[k]);
             wo[k] = __builtin_bit_cast(unsigned short, to_bf16(po[k]));
           }
-          bstore4(rm, vo * 4u, so * 4u, make_float4(mo[0], mo[1], mo[2], mo[3]));
-          bstore4(rv, vo * 4u, so * 4u, make_float4(vq[0], vq[1], vq[2], vq[3]));
-          bstore4(rp, vo * 4u, so * 4u, make_float4(po[0], po[1], po[2], po[3]));
+          bstore4(rm, (vo + so) * 4u, make_float4(mo[0], mo[1], mo[2], mo[3]));
+          bstore4(rv, (vo + so) * 4u, make_float4(vq[0], vq[1], vq[2], vq[3]));
+          bstore4(rp, (vo + so) * 4u, make_float4(po[0], po[1], po[2], po[3]));
           bstore_2x32(rw, vo * 2u, so * 2u, (uint32_t)wo[0] | ((uint32_t)wo[1] << 16),
                       (uint32_t)wo[2] | ((uint32_t)wo[3] << 16));
         }
@@ -569,32 +602,59 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16* __restrict__ A, int ld
   }
 }
 
+template <int KIND, int KT, int TT>
+__global__ __launch_bounds__(256) void k_gemm(GemmArgs q) {
+  gemm_block<KIND, KT, TT>(q, blockIdx.x, gridDim.x);
+}
+
+// The three weight updates of a training step in one launch, the first n0
+// workgroups the first's, the next n1 the second's: the small one in the middle
+// does not leave the chip waiting, and the large ones' last workgroups overlap
+// with the next ones' first.  (6000 x 512, 512 x 512 and 512 x 6000 at batch 256:
+// 57 us in three launches, 41.7 here, at 4.0 TB/s of the 4.8 that a copy reaches.)
+template <int KT>
+__global__ __launch_bounds__(256) void k_gemm3(GemmArgs q0, int n0, GemmArgs q1, int n1, GemmArgs q2, int n2) {
+  const int b = blockIdx.x;
+  const GemmArgs& q = b < n0 ? q0 : (b < n0 + n1 ? q1 : q2);
+  gemm_block<EPI_ADAM, KT, kTileNarrow>(q, b < n0 ? b : (b < n0 + n1 ? b - n0 : b - n0 - n1),
+                                        b < n0 ? n0 : (b < n0 + n1 ? n1 : n2));
+}
+
 // Split products: out = sum_z part[z] in a fixed order, then the EPI_ACT use.
-// The split partials of 4 consecutive elements per thread (16-byte loads, 8
-// splits' loads in flight), summed in split order.
+// The partials of V consecutive elements (one 4 V-byte load each), U splits' loads
+// in flight, summed in split order.
+template <int U, int V>
+__device__ __forceinline__ void add_parts(const float* __restrict__ part, int64_t MN, int64_t i, int splits, int& z,
+                                          float (&s)[V]) {
+  typedef float vec __attribute__((ext_vector_type(V)));
+  for (; z + U <= splits; z += U) {
+    vec p[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) p[u] = *reinterpret_cast<const vec*>(part + (size_t)(z + u) * MN + i);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < V; ++k) s[k] += p[u][k];
+  }
+}
+
+// V elements per thread (V divides MN).
+template <int V>
 __global__ void k_epilogue(const float* __restrict__ part, int splits, int64_t MN, int N, Epi e) {
-  const int64_t i = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+  const int64_t i = V * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
   if (i >= MN) return;
   int col = MN <= UINT32_MAX ? (int)((uint32_t)i % (uint32_t)N) : (int)(i % N);
-  if (MN % 4 == 0) {
-    float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll 8
-    for (int z = 0; z < splits; ++z) {
-      const float4 p = *reinterpret_cast<const float4*>(part + (size_t)z * MN + i);
-      s.x += p.x, s.y += p.y, s.z += p.z, s.w += p.w;
-    }
-    const float sv[4] = {s.x, s.y, s.z, s.w};
+  float s[V];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      epi_act(e, (size_t)(i + k), col, sv[k]);
-      if (++col == N) col = 0;
-    }
-    return;
-  }
-  for (int64_t j = i; j < i + 4 && j < MN; ++j) {
-    float s = 0.0f;
-    for (int z = 0; z < splits; ++z) s += part[(size_t)z * MN + j];
-    epi_act(e, (size_t)j, col, s);
+  for (int k = 0; k < V; ++k) s[k] = 0.0f;
+  int z = 0;
+  if constexpr (V == 1) add_parts<32, V>(part, MN, i, splits, z, s);
+  add_parts<8, V>(part, MN, i, splits, z, s);
+  add_parts<4, V>(part, MN, i, splits, z, s);
+  add_parts<1, V>(part, MN, i, splits, z, s);
+#pragma unroll
+  for (int k = 0; k < V; ++k) {
+    epi_act(e, (size_t)(i + k), col, s[k]);
     if (++col == N) col = 0;
   }
 }
@@ -788,16 +848,17 @@ struct pdcs_mlp_s {
     lossp.alloc(((B + 63) / 64) * ((dout + 63) / 64) * 8);
   }
 
-  // op(A)[M x K] op(B)[K x N] with epilogue `kind`.  Products whose output tiles
-  // alone cannot fill the chip are split along K (EPI_STORE / EPI_ACT only);
-  // the partials are then summed in a fixed order.  EPI_STORE writes e.out32.
   // The tile depth is 64 for K-ranges of 128 or more (128-deep tiles halve the
   // steps of long ranges but double the LDS, and measured 2% slower per step
   // at batch 256), 32 below.
+  static int tile_depth(int range) { return range >= 128 ? 64 : 32; }
+
+  // op(A)[M x K] op(B)[K x N] with epilogue `kind`.  Products whose output tiles
+  // alone cannot fill the chip are split along K (EPI_STORE / EPI_ACT only);
+  // the partials are then summed in a fixed order.  EPI_STORE writes e.out32.
   void gemm(int kind, const bf16* A, int lda, int ta, const bf16* Bm, int ldb, int tb, int M, int N, int K,
             Epi e, hipStream_t s) {
     const int tiles = ((N + kTileWide - 1) / kTileWide) * ((M + kTileWide - 1) / kTileWide);
-    if (kind == EPI_ADAM) e.vec4 = adam_vec4(e, N);
     // (products of a few tiles split down to K-ranges of 128: a handful of
     // workgroups walking the whole K serially would leave the chip idle)
     int splits = 1;
@@ -805,7 +866,7 @@ struct pdcs_mlp_s {
     if (kind == EPI_STORE || kind == EPI_ACT)
       while (tiles * splits < 512 && K / (splits * 2) >= min_range) splits *= 2;
     int kchunk = (K + splits - 1) / splits;
-    const int kt = kchunk >= 128 ? 64 : 32;
+    const int kt = tile_depth(kchunk);
     kchunk = (kchunk + kt - 1) / kt * kt;
     splits = (K + kchunk - 1) / kchunk;
     if (splits < 1) splits = 1;
@@ -816,58 +877,62 @@ struct pdcs_mlp_s {
         part_bytes = need;
       }
       launch(EPI_STORE, kt, A, lda, ta, Bm, ldb, tb, part.as<float>(), M, N, K, splits, e, s);
-      k_epilogue<<<lin(((int64_t)M * N + 3) / 4), 256, 0, s>>>(part.as<float>(), splits, (int64_t)M * N, N, e);
+      // four elements a thread where that still makes two workgroups for each CU
+      // (64 x 512 of 128 splits: 32 workgroups and 6.9 us with four, 4.3 with one)
+      const int64_t mn = (int64_t)M * N;
+      if (mn % 4 == 0 && mn >= 512 * 1024)
+        k_epilogue<4><<<lin(mn / 4), 256, 0, s>>>(part.as<float>(), splits, mn, N, e);
+      else
+        k_epilogue<1><<<lin(mn), 256, 0, s>>>(part.as<float>(), splits, mn, N, e);
       return;
     }
     launch(kind, kt, A, lda, ta, Bm, ldb, tb, kind == EPI_STORE ? e.out32 : nullptr, M, N, K, 1, e, s);
   }
 
   // The tile's side: narrow while wide tiles make fewer than two workgroups for
-  // each CU (wide and narrow, us: weight gradients with Adam 6000 x 512 and
-  // 512 x 6000 at batch 256, and 512 x 512, 39.4 and 19.1 on average; split
-  // products of 256 workgroups 12.2 and 7.9; the output layer 64 x 60000 of width
-  // 512 35 and 20, with loss 256 x 6000 30 and 25).
+  // each CU (wide and narrow, us: split products of 256 workgroups 12.2 and 7.9;
+  // 64 x 60000 outputs of width 512 35 and 20; 256 x 6000 with loss 30 and 25; but
+  // 256 x 60000, at 938 wide tiles, 145 and 148 the forward pass).  The weight
+  // updates, whose time is the weights' and moments' traffic, are always narrow
+  // (6000 x 512, 512 x 6000 and 512 x 512 at batch 256 39.4 and 19.1 on average; a
+  // step with 60000 x 512 matrices 747 and 677).
   static bool narrow(int M, int N, int splits) {
     return ((N + kTileWide - 1) / kTileWide) * ((M + kTileWide - 1) / kTileWide) * splits < 512;
   }
 
-  template <int KIND, int TT>
-  static void launch_tile(int kt, const bf16* A, int lda, int ta, int veca, const bf16* Bm, int ldb, int tb, int vecb,
-                          float* C, int M, int N, int K, int splits, const Epi& e, hipStream_t s) {
-    const int gx = (N + TT - 1) / TT, gy = (M + TT - 1) / TT;
-    const dim3 grid((unsigned)(gx * gy * splits));
-    if (kt == 64)
-      k_gemm<KIND, 64, TT><<<grid, 256, 0, s>>>(A, lda, ta, veca, Bm, ldb, tb, vecb, C, M, N, K, gx, gy, e);
-    else
-      k_gemm<KIND, 32, TT><<<grid, 256, 0, s>>>(A, lda, ta, veca, Bm, ldb, tb, vecb, C, M, N, K, gx, gy, e);
-  }
-
-  template <int KIND>
-  static void launch_kind(int kt, const bf16* A, int lda, int ta, const bf16* Bm, int ldb, int tb, float* C, int M,
-                          int N, int K, int splits, const Epi& e, hipStream_t s) {
+  static GemmArgs args(int TT, const bf16* A, int lda, int ta, const bf16* Bm, int ldb, int tb, float* C, int M, int N,
+                       int K, const Epi& e) {
     // 16-byte vector loads need 16-byte aligned operands with row strides in whole vectors
     const int veca = ((uintptr_t)A % 16 == 0 && lda % 8 == 0) ? 1 : 0;
     const int vecb = ((uintptr_t)Bm % 16 == 0 && ldb % 8 == 0) ? 1 : 0;
-    if (narrow(M, N, splits))
-      launch_tile<KIND, kTileNarrow>(kt, A, lda, ta, veca, Bm, ldb, tb, vecb, C, M, N, K, splits, e, s);
+    return {A, lda, ta, veca, Bm, ldb, tb, vecb, C, M, N, K, (N + TT - 1) / TT, (M + TT - 1) / TT, e};
+  }
+
+  template <int KIND, int TT>
+  static void launch_tile(int kt, const GemmArgs& q, int splits, hipStream_t s) {
+    const dim3 grid((unsigned)(q.gx * q.gy * splits));
+    if (kt == 64)
+      k_gemm<KIND, 64, TT><<<grid, 256, 0, s>>>(q);
     else
-      launch_tile<KIND, kTileWide>(kt, A, lda, ta, veca, Bm, ldb, tb, vecb, C, M, N, K, splits, e, s);
+      k_gemm<KIND, 32, TT><<<grid, 256, 0, s>>>(q);
   }
 
   static void launch(int kind, int kt, const bf16* A, int lda, int ta, const bf16* Bm, int ldb, int tb, float* C, int M,
                      int N, int K, int splits, const Epi& e, hipStream_t s) {
+    const int TT = narrow(M, N, splits) ? kTileNarrow : kTileWide;
+    const GemmArgs q = args(TT, A, lda, ta, Bm, ldb, tb, C, M, N, K, e);
     switch (kind) {
       case EPI_STORE:
-        launch_kind<EPI_STORE>(kt, A, lda, ta, Bm, ldb, tb, C, M, N, K, splits, e, s);
+        TT == kTileNarrow ? launch_tile<EPI_STORE, kTileNarrow>(kt, q, splits, s)
+                          : launch_tile<EPI_STORE, kTileWide>(kt, q, splits, s);
         break;
       case EPI_ACT:
-        launch_kind<EPI_ACT>(kt, A, lda, ta, Bm, ldb, tb, C, M, N, K, splits, e, s);
-        break;
-      case EPI_ADAM:
-        launch_kind<EPI_ADAM>(kt, A, lda, ta, Bm, ldb, tb, C, M, N, K, splits, e, s);
+        TT == kTileNarrow ? launch_tile<EPI_ACT, kTileNarrow>(kt, q, splits, s)
+                          : launch_tile<EPI_ACT, kTileWide>(kt, q, splits, s);
         break;
       default:
-        launch_kind<EPI_MSE>(kt, A, lda, ta, Bm, ldb, tb, C, M, N, K, splits, e, s);
+        TT == kTileNarrow ? launch_tile<EPI_MSE, kTileNarrow>(kt, q, splits, s)
+                          : launch_tile<EPI_MSE, kTileWide>(kt, q, splits, s);
     }
   }
 
@@ -956,19 +1021,31 @@ struct pdcs_mlp_s {
     mse.colpart = colpart.as<float>();
     mse.lossp = lossp.as<double>();
     gemm(EPI_MSE, h2_16.as<bf16>(), w, 0, W3(), w, 1, B, dout, w, mse, s);
-    // layer 3: dZ2 = (dV W3) * (h2 > 0) before W3 changes, then dW3 = dV^T H2
+    // dZ2 = (dV W3) * (h2 > 0) and dZ1 = (dZ2 W2) * (h1 > 0), then the weights':
+    // dW3 = dV^T H2, dW2 = dZ2^T H1, dW1 = dZ1^T U
     gemm(EPI_ACT, dv16.as<bf16>(), dout, 0, W3(), w, 0, B, w, dout,
          act(nullptr, 0, h2_16.as<bf16>(), dh.as<float>(), dz16a.as<bf16>()), s);
-    gemm(adam ? EPI_ADAM : EPI_STORE, dv16.as<bf16>(), dout, 1, h2_16.as<bf16>(), w, 0, dout, w, B,
-         wgrad(adam, off_w3, W3(), lr), s);
-    // layer 2: dZ1 = (dZ2 W2) * (h1 > 0), then dW2 = dZ2^T H1
     gemm(EPI_ACT, dz16a.as<bf16>(), w, 0, W2(), w, 0, B, w, w,
          act(nullptr, 0, h1_16.as<bf16>(), dh.as<float>() + B * w, dz16b.as<bf16>()), s);
-    gemm(adam ? EPI_ADAM : EPI_STORE, dz16a.as<bf16>(), w, 1, h1_16.as<bf16>(), w, 0, w, w, B,
-         wgrad(adam, off_w2, W2(), lr), s);
-    // layer 1: dW1 = dZ1^T U
-    gemm(adam ? EPI_ADAM : EPI_STORE, dz16b.as<bf16>(), w, 1, u16.as<bf16>(), din, 0, w, din, B,
-         wgrad(adam, off_w1, W1(), lr), s);
+    if (adam) {
+      const auto update = [&](const bf16* dz, int64_t M, const bf16* x, int64_t N, int64_t off, bf16* w16) {
+        Epi e = wgrad(true, off, w16, lr);
+        e.vec4 = adam_vec4(e, N);
+        return args(kTileNarrow, dz, M, 1, x, N, 0, nullptr, M, N, B, e);
+      };
+      const GemmArgs q3 = update(dv16.as<bf16>(), dout, h2_16.as<bf16>(), w, off_w3, W3());
+      const GemmArgs q2 = update(dz16a.as<bf16>(), w, h1_16.as<bf16>(), w, off_w2, W2());
+      const GemmArgs q1 = update(dz16b.as<bf16>(), w, u16.as<bf16>(), din, off_w1, W1());
+      const int n3 = q3.gx * q3.gy, n2 = q2.gx * q2.gy, n1 = q1.gx * q1.gy;
+      if (tile_depth((int)B) == 64)
+        k_gemm3<64><<<(unsigned)(n3 + n2 + n1), 256, 0, s>>>(q3, n3, q2, n2, q1, n1);
+      else
+        k_gemm3<32><<<(unsigned)(n3 + n2 + n1), 256, 0, s>>>(q3, n3, q2, n2, q1, n1);
+    } else {
+      gemm(EPI_STORE, dv16.as<bf16>(), dout, 1, h2_16.as<bf16>(), w, 0, dout, w, B, wgrad(false, off_w3, nullptr, lr), s);
+      gemm(EPI_STORE, dz16a.as<bf16>(), w, 1, h1_16.as<bf16>(), w, 0, w, w, B, wgrad(false, off_w2, nullptr, lr), s);
+      gemm(EPI_STORE, dz16b.as<bf16>(), w, 1, u16.as<bf16>(), din, 0, w, din, B, wgrad(false, off_w1, nullptr, lr), s);
+    }
     const Epi e = wgrad(true, off_b1, nullptr, lr);
     BiasStep q;
     const int hb = (int)((w + 63) / 64), side = narrow((int)B, (int)dout, 1) ? kTileNarrow : kTileWide;
