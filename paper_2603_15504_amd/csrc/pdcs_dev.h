@@ -217,6 +217,44 @@ __device__ __forceinline__ void block_sum_store(double (&v)[NV], double* lds, do
   }
 }
 
+// Totals of 32 values over the wave: lane l gets that of value bitrev5(l % 32).
+// Each step halves the values a lane carries (31 exchanges and additions for
+// 32 separate sums' 192), and adds in wave_sum's tree: the same bits.
+template <int N>
+__device__ __forceinline__ void sum_step(double (&v)[32]) {
+  constexpr int off = 16 / N;
+  const bool up = (threadIdx.x & off) != 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const double lo = v[i], hi = v[i + N];
+    v[i] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, off, kWave);
+  }
+}
+
+__device__ __forceinline__ double wave_sum32(double (&v)[32]) {
+  sum_step<16>(v);
+  sum_step<8>(v);
+  sum_step<4>(v);
+  sum_step<2>(v);
+  sum_step<1>(v);
+  return v[0] + __shfl_xor(v[0], 32, kWave);
+}
+
+// block_sum_store of 32 values by it.
+__device__ __forceinline__ void block_sum32_store(double (&v)[32], double* lds, double* out) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = threadIdx.x / kWave;
+  const double s = wave_sum32(v);
+  if (lane < 32) lds[wave * 32 + (int)(__brev((unsigned)lane) >> 27)] = s;
+  __syncthreads();
+  if (threadIdx.x < 32) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWavesPerBlock; ++w) t += lds[w * 32 + threadIdx.x];
+    out[threadIdx.x] = t;
+  }
+}
+
 // As block_sum_store, but the first NS entries are sums and the rest maxima.
 template <int NV, int NS>
 __device__ __forceinline__ void block_summax_store(double (&v)[NV], double* lds, double* out) {
@@ -239,41 +277,6 @@ __device__ __forceinline__ void block_summax_store(double (&v)[NV], double* lds,
 // Reduce the NV-wide records [b0, b1) of one instance inside one workgroup;
 // the first NS fields are summed, the rest take the maximum.  Result is
 // returned to every thread.  Fixed order: deterministic.
-// Sums of NV-value records b0..b1-1 (NV dividing kBlock) into out[0..NV) in
-// LDS: thread t adds value t % NV of every (kBlock / NV)-th record, reading
-// consecutive doubles across threads, then the kBlock / NV partial sums of
-// each value are added in a fixed order.  red: kBlock doubles of LDS.
-template <int NV>
-__device__ __forceinline__ void reduce_records_wide(const double* rec, int b0, int b1, double* red, double* out) {
-  static_assert(kBlock % NV == 0, "record width divides the block");
-  if (b1 - b0 == 1) {  // a single record (uniform across the workgroup)
-    if (threadIdx.x < NV) out[threadIdx.x] = rec[(size_t)b0 * NV + threadIdx.x];
-    __syncthreads();
-    return;
-  }
-  constexpr int R = kBlock / NV;
-  const int i = threadIdx.x % NV;
-  int b = b0 + (int)threadIdx.x / NV;
-  double acc = 0.0;
-  for (; b + 3 * R < b1; b += 4 * R) {
-    const double v0 = rec[(size_t)b * NV + i], v1 = rec[(size_t)(b + R) * NV + i];
-    const double v2 = rec[(size_t)(b + 2 * R) * NV + i], v3 = rec[(size_t)(b + 3 * R) * NV + i];
-    acc += v0;
-    acc += v1;
-    acc += v2;
-    acc += v3;
-  }
-  for (; b < b1; b += R) acc += rec[(size_t)b * NV + i];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  if (threadIdx.x < NV) {
-    double t = red[threadIdx.x];
-    for (int k = 1; k < R; ++k) t += red[k * NV + threadIdx.x];
-    out[threadIdx.x] = t;
-  }
-  __syncthreads();
-}
-
 template <int NV, int NS>
 __device__ __forceinline__ void reduce_records(const double* rec, int b0, int b1, double* lds,
                                                double (&res)[NV]) {

@@ -2059,8 +2059,7 @@ constexpr int kProbeNV = kProbes * 2;
 template <typename T>
 __device__ __forceinline__ void probe_cols_body(int b, int q, const Ranges& R, const T* x0, const T* x1,
                                                 const double* g0, const double* g1, const DataPtrs<double>& d,
-                                                const Inst* inst, int prec, double* rec) {
-  __shared__ double lds[kWavesPerBlock * kProbeNV];
+                                                const Inst* inst, int prec, double* rec, double* lds) {
   const Inst& I = inst[R.blk_inst[b]];
   if (I.status != kActive || I.check_due == 0 || I.precision != prec) return;
   const CandState& C = I.cand[q];
@@ -2087,24 +2086,13 @@ __device__ __forceinline__ void probe_cols_body(int b, int q, const Ranges& R, c
       acc[p * 2 + 1] += b1 * dx;
     }
   }
-  block_sum_store<kProbeNV>(acc, lds, rec + ((size_t)q * R.nblk + b) * kProbeNV);
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_probe_cols(Ranges R, const T* __restrict__ x0,
-                                                       const T* __restrict__ x1,
-                                                       const double* __restrict__ g0,
-                                                       const double* __restrict__ g1,
-                                                       DataPtrs<double> d, const Inst* __restrict__ inst,
-                                                       int prec, double* __restrict__ rec) {
-  probe_cols_body<T>(blockIdx.x, blockIdx.y, R, x0, x1, g0, g1, d, inst, prec, rec);
+  block_sum32_store(acc, lds, rec + ((size_t)q * R.nblk + b) * kProbeNV);
 }
 
 template <typename T>
 __device__ __forceinline__ void probe_rows_body(int b, int q, const Ranges& R, const T* y0, const T* y1,
                                                 const double* g0, const double* g1, const DataPtrs<double>& d,
-                                                const double* D1, const Inst* inst, int prec, double* rec) {
-  __shared__ double lds[kWavesPerBlock * kProbeNV];
+                                                const double* D1, const Inst* inst, int prec, double* rec, double* lds) {
   const Inst& I = inst[R.blk_inst[b]];
   if (I.status != kActive || I.check_due == 0 || I.precision != prec) return;
   const CandState& C = I.cand[q];
@@ -2183,202 +2171,224 @@ __device__ __forceinline__ void probe_rows_body(int b, int q, const Ranges& R, c
 #pragma unroll
     for (int i = 0; i < kProbeNV; ++i) acc[i] += cone_acc[wave][i];
   }
-  block_sum_store<kProbeNV>(acc, lds, rec + ((size_t)q * R.nblk + b) * kProbeNV);
+  block_sum32_store(acc, lds, rec + ((size_t)q * R.nblk + b) * kProbeNV);
 }
 
+// A multisection pass, blockIdx.y the candidate: workgroups [0, rr.nblk) take the
+// rows (cone blocks take longest, so they go first), the others the columns.
+// (m = 2e4, n = 4e4: a launch each and the update, 8.7 + 8.7 + 12.2 us a pass; 7.6 +
+// 4.5 here.  n = 5e5, m = 2e5: 15.6 + 11.0 + 24.4, and 21.7 + 10.3.)
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_probe_rows(Ranges R, const T* __restrict__ y0,
-                                                       const T* __restrict__ y1,
-                                                       const double* __restrict__ g0,
-                                                       const double* __restrict__ g1,
-                                                       DataPtrs<double> d, const double* __restrict__ D1,
-                                                       const Inst* __restrict__ inst, int prec,
-                                                       double* __restrict__ rec) {
-  probe_rows_body<T>(blockIdx.x, blockIdx.y, R, y0, y1, g0, g1, d, D1, inst, prec, rec);
+__global__ __launch_bounds__(kBlock) void k_probe(Ranges rc, Ranges rr, const T* __restrict__ x0,
+                                                  const T* __restrict__ x1, const T* __restrict__ y0,
+                                                  const T* __restrict__ y1, const double* __restrict__ gc0,
+                                                  const double* __restrict__ gc1, const double* __restrict__ gr0,
+                                                  const double* __restrict__ gr1, DataPtrs<double> d,
+                                                  const double* __restrict__ D1, const Inst* __restrict__ inst, int prec,
+                                                  double* __restrict__ rec_c, double* __restrict__ rec_r) {
+  __shared__ double lds[kWavesPerBlock * kProbeNV];
+  const int b = blockIdx.x;
+  if (b < rr.nblk) probe_rows_body<T>(b, blockIdx.y, rr, y0, y1, gr0, gr1, d, D1, inst, prec, rec_r, lds);
+  else probe_cols_body<T>(b - rr.nblk, blockIdx.y, rc, x0, x1, gc0, gc1, d, inst, prec, rec_c, lds);
 }
 
-// Update every candidate's bracket from one multisection pass (Algorithm 3:
-// exponential search from t0, then bisection; here kProbes points per pass).
-__device__ __forceinline__ void probe_fin_body(int iid, const Ranges& rc, const double* rec_c, const Ranges& rr,
-                                               const double* rec_r, Inst* inst) {
-  __shared__ double red[kBlock];
-  // the bracket update below indexes probes at run time: its inputs live in
-  // LDS (registers indexed at run time would go to scratch memory)
-  __shared__ double s_dist[kMaxCand][kProbes], s_val[kMaxCand][kProbes], s_t[kMaxCand][kProbes];
-  __shared__ double s_cols[kProbeNV], s_rows[kProbeNV];
+__device__ __forceinline__ bool searching(const CandState& C) {
+  return C.phase == kPhaseExp || C.phase == kPhaseBisect;
+}
+
+// A candidate's bracket from the sums of one multisection pass (Algorithm 3:
+// exponential search from t0, then bisection; here kProbes points per pass);
+// dist, val and tp in memory that may be indexed at run time.
+__device__ __forceinline__ void probe_update(CandState& C, double eps, const double* dist, const double* val,
+                                             const double* tp) {
+  if (C.phase == kPhaseExp) {
+    bool decided = false;
+    for (int p = 0; p < kProbes; ++p) {
+      const bool first = (C.doublings == 0 && p == 0);
+      if (dist[p] > C.r) {
+        if (first) {
+          C.t_lo = 0.0;
+          C.val_lo = 0.0;
+        } else {
+          C.t_lo = p > 0 ? tp[p - 1] : C.t_base * 0.5;
+          // val_lo was recorded with the previous probe
+        }
+        C.t_hi = tp[p];
+        C.phase = kPhaseBisect;
+        decided = true;
+        break;
+      }
+      if (!first && dist[p] <= C.last_dist) {  // saturated: z(2t) = z(t)
+        C.phase = kPhaseDone;
+        decided = true;
+        break;
+      }
+      C.last_dist = dist[p];
+      C.val_lo = val[p];
+      C.t_lo = tp[p];
+      C.doublings += 1;
+    }
+    if (!decided) {
+      C.t_base = tp[kProbes - 1] * 2.0;
+      if (C.doublings >= 64) C.phase = kPhaseDone;
+    }
+  } else {
+    int last_in = -1;
+    for (int p = 0; p < kProbes; ++p)
+      if (dist[p] < C.r) last_in = p;
+    const double new_hi = (last_in + 1 < kProbes) ? tp[last_in + 1] : C.t_hi;
+    if (last_in >= 0) {
+      C.t_lo = tp[last_in];
+      C.val_lo = val[last_in];
+    }
+    C.t_hi = new_hi;
+  }
+  if (C.phase == kPhaseBisect && C.t_hi - C.t_lo <= eps * C.t_hi) C.phase = kPhaseDone;
+}
+
+// Work of a multisection pass that is one workgroup's: kBlock threads for each
+// candidate q and each side (columns, rows), thread t of group 2 q + side.
+constexpr int kProbeGroups = 2 * kMaxCand;
+struct ProbeLds {
+  double part[kProbeGroups][kBlock];     // partial sums of the groups
+  double sums[kProbeGroups][kProbeNV];
+  double dist[kMaxCand][kProbes], val[kMaxCand][kProbes], t[kMaxCand][kProbes];
+};
+
+// The brackets of both candidates from L.sums: first kProbes threads of a
+// candidate's first group; C: its state.
+__device__ __forceinline__ void probe_brackets(ProbeLds& L, int q, int p, CandState& C, double eps) {
+  if (p < kProbes) {
+    L.dist[q][p] = sqrt(L.sums[2 * q][p * 2] + L.sums[2 * q + 1][p * 2]);
+    L.val[q][p] = L.sums[2 * q][p * 2 + 1] + L.sums[2 * q + 1][p * 2 + 1];
+    L.t[q][p] = probe_t(C, p);
+  }
+  __builtin_amdgcn_wave_barrier();  // one wave's LDS operations are in order
+  if (p == 0) probe_update(C, eps, L.dist[q], L.val[q], L.t[q]);
+}
+
+// Update every candidate's bracket from the records of one multisection pass.
+// Thread t of a group adds value t % kProbeNV of every eighth record, eight loads
+// in flight, and the group's partial sums are added in a fixed order.  (The four
+// sums one after the other by 256 threads: 12.2 us at 40 + 20 records, 24.4 at
+// 489 + 196; 4.5 and 10.3 here.)
+__global__ __launch_bounds__(kProbeGroups* kBlock) void k_probe_fin(Ranges rc, const double* __restrict__ rec_c,
+                                                                    Ranges rr, const double* __restrict__ rec_r,
+                                                                    Inst* __restrict__ inst) {
+  __shared__ ProbeLds L;
+  const int iid = blockIdx.x;
   Inst& I = inst[iid];
   if (I.status != kActive || I.check_due == 0) return;
-  const bool s0 = I.cand[0].phase == kPhaseExp || I.cand[0].phase == kPhaseBisect;
-  const bool s1 = I.cand[1].phase == kPhaseExp || I.cand[1].phase == kPhaseBisect;
-  if (!s0 && !s1) return;
+  if (!searching(I.cand[0]) && !searching(I.cand[1])) return;
+  const int g = threadIdx.x / kBlock, t = threadIdx.x % kBlock, q = g >> 1;
+  const bool rows = g & 1, on = searching(I.cand[q]);
+  constexpr int R = kBlock / kProbeNV, U = 8;
+  if (on) {
+    const Ranges& side = rows ? rr : rc;
+    const double* rec = (rows ? rec_r : rec_c) + (size_t)q * side.nblk * kProbeNV;
+    const int i = t % kProbeNV, b1 = side.inst_blk0[iid + 1];
+    int b = side.inst_blk0[iid] + t / kProbeNV;
+    double acc = 0.0;
+    for (; b + (U - 1) * R < b1; b += U * R) {
+      double v[U];
 #pragma unroll
-  for (int q = 0; q < kMaxCand; ++q) {
-    const bool sq = q == 0 ? s0 : s1;
-    if (!sq) continue;  // uniform across the workgroup
-    reduce_records_wide<kProbeNV>(rec_c + (size_t)q * rc.nblk * kProbeNV, rc.inst_blk0[iid], rc.inst_blk0[iid + 1],
-                                  red, s_cols);
-    reduce_records_wide<kProbeNV>(rec_r + (size_t)q * rr.nblk * kProbeNV, rr.inst_blk0[iid], rr.inst_blk0[iid + 1],
-                                  red, s_rows);
-    if (threadIdx.x == 0) {
-      const CandState& C = I.cand[q];
-      for (int p = 0; p < kProbes; ++p) {
-        s_dist[q][p] = sqrt(s_cols[p * 2] + s_rows[p * 2]);
-        s_val[q][p] = s_cols[p * 2 + 1] + s_rows[p * 2 + 1];
-        s_t[q][p] = probe_t(C, p);
-      }
+      for (int u = 0; u < U; ++u) v[u] = rec[(size_t)(b + u * R) * kProbeNV + i];
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc += v[u];
     }
+    for (; b < b1; b += R) acc += rec[(size_t)b * kProbeNV + i];
+    L.part[g][t] = acc;
   }
-  if (threadIdx.x != 0) return;
-  const double eps = I.bisect_eps;
-  for (int q = 0; q < kMaxCand; ++q) {
-    CandState& C = I.cand[q];
-    if (C.phase != kPhaseExp && C.phase != kPhaseBisect) continue;
-    const double* dist = s_dist[q];
-    const double* val = s_val[q];
-    const double* tp = s_t[q];
-    if (C.phase == kPhaseExp) {
-      bool decided = false;
-      for (int p = 0; p < kProbes; ++p) {
-        const bool first = (C.doublings == 0 && p == 0);
-        if (dist[p] > C.r) {
-          if (first) {
-            C.t_lo = 0.0;
-            C.val_lo = 0.0;
-          } else {
-            C.t_lo = p > 0 ? tp[p - 1] : C.t_base * 0.5;
-            // val_lo was recorded with the previous probe
-          }
-          C.t_hi = tp[p];
-          C.phase = kPhaseBisect;
-          decided = true;
-          break;
-        }
-        if (!first && dist[p] <= C.last_dist) {  // saturated: z(2t) = z(t)
-          C.phase = kPhaseDone;
-          decided = true;
-          break;
-        }
-        C.last_dist = dist[p];
-        C.val_lo = val[p];
-        C.t_lo = tp[p];
-        C.doublings += 1;
-      }
-      if (!decided) {
-        C.t_base = tp[kProbes - 1] * 2.0;
-        if (C.doublings >= 64) C.phase = kPhaseDone;
-      }
-    } else {
-      int last_in = -1;
-      for (int p = 0; p < kProbes; ++p)
-        if (dist[p] < C.r) last_in = p;
-      const double new_hi = (last_in + 1 < kProbes) ? tp[last_in + 1] : C.t_hi;
-      if (last_in >= 0) {
-        C.t_lo = tp[last_in];
-        C.val_lo = val[last_in];
-      }
-      C.t_hi = new_hi;
-    }
-    if (C.phase == kPhaseBisect && C.t_hi - C.t_lo <= eps * C.t_hi) C.phase = kPhaseDone;
+  __syncthreads();
+  if (on && t < kProbeNV) {
+    double s = L.part[g][t];
+    for (int k = 1; k < R; ++k) s += L.part[g][k * kProbeNV + t];
+    L.sums[g][t] = s;
   }
-}
-
-__global__ __launch_bounds__(kBlock) void k_probe_fin(Ranges rc, const double* __restrict__ rec_c,
-                                                      Ranges rr, const double* __restrict__ rec_r,
-                                                      Inst* __restrict__ inst) {
-  probe_fin_body(blockIdx.x, rc, rec_c, rr, rec_r, inst);
+  __syncthreads();
+  if (on && !rows && t < kWave) probe_brackets(L, q, t, I.cand[q], I.bisect_eps);
 }
 
 // All multisection passes of a restart check in one launch, one workgroup per
 // instance of precision prec (the layouts that run trials in one workgroup per
-// instance; no cone blocks there).  Wave w evaluates candidate w % 2 on the
-// columns (w < 2) or the rows (w >= 2) of the whole instance, with the
-// arithmetic of k_probe_cols / k_probe_rows, and leaves its sums in the record
-// of the instance's first block; k_probe_fin's update then reads that one
-// record per side.
+// instance; no cone blocks there): the groups of k_probe_fin sum the whole
+// instance with the arithmetic of k_probe and keep the candidates in LDS.  It is
+// bound by each pass' chain of loads, exchanges and the bracket's update.
+// (n = 500, m = 200: 7 passes of 14.8 us with one wave per candidate and side,
+// its sums through memory; of 5.0 here.)
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_probes_wg(Ranges ccol, Ranges crow, const T* x0, const T* x1,
-                                                      const T* y0, const T* y1, const double* gc0,
-                                                      const double* gc1, const double* gr0, const double* gr1,
-                                                      DataPtrs<double> d, Inst* inst, int prec, double* rec_c,
-                                                      double* rec_r, int passes) {
-  __shared__ int32_t first[4];
-  const int iid = blockIdx.x;
-  {
-    const Inst& I = inst[iid];
-    if (I.status != kActive || I.check_due == 0 || I.precision != prec) return;  // uniform
-  }
-  if (threadIdx.x == 0) {
-    first[0] = ccol.inst_blk0[iid];
-    first[1] = first[0] + 1;
-    first[2] = crow.inst_blk0[iid];
-    first[3] = first[2] + 1;
-  }
+__global__ __launch_bounds__(kProbeGroups* kBlock) void k_probes_wg(const T* x0, const T* x1, const T* y0, const T* y1,
+                                                                    const double* gc0, const double* gc1,
+                                                                    const double* gr0, const double* gr1,
+                                                                    DataPtrs<double> d, Inst* inst, int prec,
+                                                                    int passes) {
+  __shared__ ProbeLds L;
+  __shared__ CandState cand[kMaxCand];
+  __shared__ double tq[kProbeGroups][kProbes];
+  Inst& I = inst[blockIdx.x];
+  if (I.status != kActive || I.check_due == 0 || I.precision != prec) return;  // uniform
+  if (threadIdx.x < kMaxCand) cand[threadIdx.x] = I.cand[threadIdx.x];
   __syncthreads();
-  Ranges rc1 = ccol, rr1 = crow;
-  rc1.inst_blk0 = first - iid;
-  rr1.inst_blk0 = first + 2 - iid;
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int q = wave & 1;
-  const bool cols = wave < 2;
+  const int g = threadIdx.x / kBlock, t = threadIdx.x % kBlock, q = g >> 1;
+  const int lane = threadIdx.x & (kWave - 1), wave = t / kWave;
+  const bool rows = g & 1;
+  const double step = rows ? I.eta_hat * I.omega : I.eta_hat / I.omega, inv = 1.0 / step;
+  const int mz_end = I.row0 + I.m_zero;
   for (int pass = 0; pass < passes; ++pass) {
-    const Inst& I = inst[iid];
-    const CandState& C = I.cand[q];
-    if (C.phase == kPhaseExp || C.phase == kPhaseBisect) {  // uniform within the wave
+    const bool on = searching(cand[q]);
+    if (!searching(cand[0]) && !searching(cand[1])) break;  // uniform
+    if (on && t < kProbes) tq[g][t] = probe_t(cand[q], t) * step;
+    __syncthreads();
+    if (on) {
       double acc[kProbeNV];
 #pragma unroll
       for (int i = 0; i < kProbeNV; ++i) acc[i] = 0.0;
-      if (cols) {
-        const double tau = I.eta_hat / I.omega, inv_tau = 1.0 / tau;
-        double tq[kProbes];
-#pragma unroll
-        for (int p = 0; p < kProbes; ++p) tq[p] = probe_t(C, p) * tau;
+      if (!rows) {
         const T* xs = q == 0 ? x0 : x1;
         const double* gs = q == 0 ? gc0 : gc1;
-        for (int j = I.col0 + lane; j < I.col0 + I.cols; j += kWave) {
+        for (int j = I.col0 + t; j < I.col0 + I.cols; j += kBlock) {
           const double lo = d.l[j], hi = d.u[j];
           const double xc = (double)xs[j];
           const double b1 = gs[j] - d.c[j];
 #pragma unroll
           for (int p = 0; p < kProbes; ++p) {
-            const double dx = clampd(xc + tq[p] * b1, lo, hi) - xc;
-            acc[p * 2 + 0] += dx * dx * inv_tau;
+            const double dx = clampd(xc + tq[g][p] * b1, lo, hi) - xc;
+            acc[p * 2 + 0] += dx * dx * inv;
             acc[p * 2 + 1] += b1 * dx;
+            if (p % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // (16 probes' t at once would spill)
           }
         }
       } else {
-        const double sigma = I.eta_hat * I.omega, inv_sigma = 1.0 / sigma;
-        const int mz_end = I.row0 + I.m_zero;
-        double tq[kProbes];
-#pragma unroll
-        for (int p = 0; p < kProbes; ++p) tq[p] = probe_t(C, p) * sigma;
         const T* ys = q == 0 ? y0 : y1;
         const double* gs = q == 0 ? gr0 : gr1;
-        for (int i = I.row0 + lane; i < I.row0 + I.rows; i += kWave) {
+        for (int i = I.row0 + t; i < I.row0 + I.rows; i += kBlock) {
           const bool zero_row = i < mz_end;
           const double yc = (double)ys[i];
           const double b2 = d.h[i] - gs[i];
 #pragma unroll
           for (int p = 0; p < kProbes; ++p) {
-            const double v = yc + tq[p] * b2;
+            const double v = yc + tq[g][p] * b2;
             const double dy = (zero_row ? v : fmax(v, 0.0)) - yc;
-            acc[p * 2 + 0] += dy * dy * inv_sigma;
+            acc[p * 2 + 0] += dy * dy * inv;
             acc[p * 2 + 1] += b2 * dy;
+            if (p % 4 == 3) __builtin_amdgcn_sched_barrier(0);
           }
         }
       }
-      double* rec = cols ? rec_c + ((size_t)q * ccol.nblk + first[0]) * kProbeNV
-                         : rec_r + ((size_t)q * crow.nblk + first[2]) * kProbeNV;
-#pragma unroll
-      for (int i = 0; i < kProbeNV; ++i) {
-        const double s = wave_sum(acc[i]);
-        if (lane == 0) rec[i] = s;
-      }
+      const double s = wave_sum32(acc);
+      if (lane < 32) L.part[g][wave * kProbeNV + (int)(__brev((unsigned)lane) >> 27)] = s;
     }
     __syncthreads();
-    probe_fin_body(iid, rc1, rec_c, rr1, rec_r, inst);
+    if (on && t < kProbeNV)
+      L.sums[g][t] =
+          ((L.part[g][t] + L.part[g][kProbeNV + t]) + L.part[g][2 * kProbeNV + t]) + L.part[g][3 * kProbeNV + t];
+    __syncthreads();
+    if (on && !rows && t < kWave) probe_brackets(L, q, t, cand[q], I.bisect_eps);
     __syncthreads();
   }
+  if (threadIdx.x < kMaxCand) I.cand[threadIdx.x] = cand[threadIdx.x];
 }
+static_assert(kProbeNV == 32 && kWavesPerBlock == 4, "the sums of a pass are 32 values over four waves");
 
 // Restart decision (Section 2.3), primal weight (Section 2.5), termination
 // (Section 3) and the mixed-precision polish switch.  Thread 0 only.
@@ -3596,12 +3606,10 @@ static void launch_check_pre_t(const KernelCtx& k, hipStream_t s, int prec, cons
 
 template <typename T>
 static void launch_probe_t(const KernelCtx& k, hipStream_t s, int prec, const IterPtrs<T>& it) {
-  if (k.ccol.nblk > 0)
-    k_probe_cols<T><<<dim3(k.ccol.nblk, kMaxCand), kBlock, 0, s>>>(k.ccol, it.xh, it.xbar, k.cgty0, k.cgty1, k.d64,
-                                                           k.inst, prec, k.rec_probe_c);
-  if (k.crow.nblk > 0)
-    k_probe_rows<T><<<dim3(k.crow.nblk, kMaxCand), kBlock, 0, s>>>(k.crow, it.yh, it.ybar, k.cgx0, k.cgx1, k.d64,
-                                                                    k.D1, k.inst, prec, k.rec_probe_r);
+  if (k.ccol.nblk + k.crow.nblk > 0)
+    k_probe<T><<<dim3(k.ccol.nblk + k.crow.nblk, kMaxCand), kBlock, 0, s>>>(
+        k.ccol, k.crow, it.xh, it.xbar, it.yh, it.ybar, k.cgty0, k.cgty1, k.cgx0, k.cgx1, k.d64, k.D1, k.inst, prec,
+        k.rec_probe_c, k.rec_probe_r);
 }
 
 template <typename T>
@@ -3672,18 +3680,18 @@ void launch_check(const KernelCtx& k, hipStream_t s, int mask) {
   k_cand_fin<<<grid1(k.nb), kBlock, 0, s>>>(k.vcol, k.rec_cand_c, k.vrow, k.rec_cand_r, k.inst, kModeCheck);
   if (k.wg_trials && !k.use_band) {
     if (mask & 1)
-      k_probes_wg<float><<<k.nb, kBlock, 0, s>>>(k.ccol, k.crow, k.it32.xh, k.it32.xbar, k.it32.yh, k.it32.ybar,
-                                                 k.cgty0, k.cgty1, k.cgx0, k.cgx1, k.d64, k.inst, kFP32,
-                                                 k.rec_probe_c, k.rec_probe_r, k.probe_passes);
+      k_probes_wg<float><<<k.nb, kProbeGroups * kBlock, 0, s>>>(k.it32.xh, k.it32.xbar, k.it32.yh, k.it32.ybar, k.cgty0,
+                                                                k.cgty1, k.cgx0, k.cgx1, k.d64, k.inst, kFP32,
+                                                                k.probe_passes);
     if (mask & 2)
-      k_probes_wg<double><<<k.nb, kBlock, 0, s>>>(k.ccol, k.crow, k.it64.xh, k.it64.xbar, k.it64.yh, k.it64.ybar,
-                                                  k.cgty0, k.cgty1, k.cgx0, k.cgx1, k.d64, k.inst, kFP64,
-                                                  k.rec_probe_c, k.rec_probe_r, k.probe_passes);
+      k_probes_wg<double><<<k.nb, kProbeGroups * kBlock, 0, s>>>(k.it64.xh, k.it64.xbar, k.it64.yh, k.it64.ybar, k.cgty0,
+                                                                 k.cgty1, k.cgx0, k.cgx1, k.d64, k.inst, kFP64,
+                                                                 k.probe_passes);
   } else {
     for (int pass = 0; pass < k.probe_passes; ++pass) {
       if (mask & 1) launch_probe_t<float>(k, s, kFP32, k.it32);
       if (mask & 2) launch_probe_t<double>(k, s, kFP64, k.it64);
-      k_probe_fin<<<grid1(k.nb), kBlock, 0, s>>>(k.ccol, k.rec_probe_c, k.crow, k.rec_probe_r, k.inst);
+      k_probe_fin<<<grid1(k.nb), kProbeGroups * kBlock, 0, s>>>(k.ccol, k.rec_probe_c, k.crow, k.rec_probe_r, k.inst);
     }
   }
   k_decide<<<nbt, 64, 0, s>>>(k.inst, k.nb);
