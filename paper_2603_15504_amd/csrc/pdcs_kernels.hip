@@ -1225,25 +1225,33 @@ __global__ __launch_bounds__(kBandWaves * kWave) void k_band_cand(BandTiles bt, 
   band_tile_product<double, TX, double>(bt, t, acc + w * bt.slots, val, x, part, R);
 }
 
-// Window sums of the check / evaluation products, per instance.
-__global__ __launch_bounds__(kBlock) void k_band_combine2(Ranges Rg, int P, int64_t R,
-                                                          const double* __restrict__ part0,
-                                                          const double* __restrict__ part1,
-                                                          double* __restrict__ out0, double* __restrict__ out1,
+// Window sums of the check / evaluation products (G^T y, then G x), per instance;
+// a side without workgroups or without a vector is left out.
+struct CombineSide {
+  Ranges Rg;
+  int P;
+  int64_t R;
+  const double *part0, *part1;
+  double *out0, *out1;
+};
+
+__global__ __launch_bounds__(kBlock) void k_band_combine2(CombineSide cols, CombineSide rows,
                                                           const Inst* __restrict__ inst, int mode) {
-  const int b = blockIdx.x;
-  const Inst& I = inst[Rg.blk_inst[b]];
+  const bool first = (int)blockIdx.x < cols.Rg.nblk;
+  const int b = first ? (int)blockIdx.x : (int)blockIdx.x - cols.Rg.nblk;
+  const CombineSide& q = first ? cols : rows;
+  const Inst& I = inst[q.Rg.blk_inst[b]];
   if (!mode_selects(I, mode)) return;
-  const bool two = part1 != nullptr && (mode != kModeCheck || I.use_avg != 0);
-  const int r1 = Rg.blk_end[b];
-  for (int r = Rg.blk_start[b] + (int)threadIdx.x; r < r1; r += kBlock) {
+  const bool two = q.part1 != nullptr && (mode != kModeCheck || I.use_avg != 0);
+  const int r1 = q.Rg.blk_end[b];
+  for (int r = q.Rg.blk_start[b] + (int)threadIdx.x; r < r1; r += kBlock) {
     double s0 = 0.0, s1 = 0.0;
-    for (int p = 0; p < P; ++p) {
-      s0 += part0[(size_t)p * R + r];
-      if (two) s1 += part1[(size_t)p * R + r];
+    for (int p = 0; p < q.P; ++p) {
+      s0 += q.part0[(size_t)p * q.R + r];
+      if (two) s1 += q.part1[(size_t)p * q.R + r];
     }
-    out0[r] = s0;
-    if (two) out1[r] = s1;
+    q.out0[r] = s0;
+    if (two) q.out1[r] = s1;
   }
 }
 
@@ -1780,15 +1788,36 @@ __global__ __launch_bounds__(kBlock) void k_trials_lds(Ranges vcol, RowBlocks br
 // Restart / termination check
 // ===========================================================================
 
+// The column and the row side of a step of a check or an evaluation depend on
+// nothing of each other: one launch takes both, its first workgroups the columns.
+// (Each of these launches is 4.7 us for a problem of a few hundred rows and 6 to 7
+// for 2e4 x 4e4, 3e5 nonzeros: start-up, not traffic.)
+
 // Apply the pending Halpern commit, then form the average candidate S / sum(eta).
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_commit_avg(Ranges R, T* __restrict__ z,
-                                                       T* __restrict__ zh, const T* __restrict__ za,
-                                                       T* __restrict__ g, const T* __restrict__ gh,
-                                                       const T* __restrict__ ga, T* __restrict__ s,
-                                                       T* __restrict__ zbar, Inst* __restrict__ inst,
-                                                       int prec) {
-  const int b = blockIdx.x;
+struct CommitSide {
+  Ranges R;
+  T* z;
+  const T *zh, *za;
+  T* g;
+  const T *gh, *ga;
+  T *s, *zbar;
+};
+
+template <typename T>
+static CommitSide<T> commit_cols(const Ranges& R, const IterPtrs<T>& it) {
+  return {R, it.x, it.xh, it.xa, it.gty, it.gtyh, it.gtya, it.sx, it.xbar};
+}
+template <typename T>
+static CommitSide<T> commit_rows(const Ranges& R, const IterPtrs<T>& it) {
+  return {R, it.y, it.yh, it.ya, it.gx, it.gxh, it.gxa, it.sy, it.ybar};
+}
+
+template <typename T>
+__device__ __forceinline__ void commit_avg(int b, const CommitSide<T>& q, const Inst* __restrict__ inst, int prec) {
+  const Ranges& R = q.R;
+  T *__restrict__ z = q.z, *__restrict__ g = q.g, *__restrict__ s = q.s, *__restrict__ zbar = q.zbar;
+  const T *__restrict__ zh = q.zh, *__restrict__ za = q.za, *__restrict__ gh = q.gh, *__restrict__ ga = q.ga;
   const Inst& I = inst[R.blk_inst[b]];
   if (I.status != kActive || I.check_due == 0 || I.precision != prec) return;
   const bool commit = I.pending != 0;
@@ -1811,15 +1840,34 @@ __global__ __launch_bounds__(kBlock) void k_commit_avg(Ranges R, T* __restrict__
   }
 }
 
-// Two products with one matrix pass: out0 = A in0, out1 = A in1 (FP64 values,
-// FP64 output).  in1 may be null.  Selected instances only.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_spmv2(RowBlocks rb, MatPtrs<double> A, const T* __restrict__ in0,
-                                                  const T* __restrict__ in1, double* __restrict__ out0,
-                                                  double* __restrict__ out1, const Inst* __restrict__ inst,
+__global__ __launch_bounds__(kBlock) void k_commit_avg(CommitSide<T> cols, CommitSide<T> rows,
+                                                       const Inst* __restrict__ inst, int prec) {
+  const int b = blockIdx.x;
+  if (b < cols.R.nblk) commit_avg(b, cols, inst, prec);
+  else commit_avg(b - cols.R.nblk, rows, inst, prec);
+}
+
+// Two products with one matrix pass: out0 = A in0, out1 = A in1 (FP64 values,
+// FP64 output), of G^T and of G.  in1 may be null.  Selected instances only.
+template <typename T>
+struct Spmv2Side {
+  RowBlocks rb;
+  MatPtrs<double> A;
+  const T *in0, *in1;
+  double *out0, *out1;
+};
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_spmv2(Spmv2Side<T> cols, Spmv2Side<T> rows, const Inst* __restrict__ inst,
                                                   int prec, int mode) {
   __shared__ double lds[2 * kRowBlockCap + kWavesPerBlock * 2];
-  const int b = blockIdx.x;
+  const bool first = (int)blockIdx.x < cols.rb.nblk;
+  const int b = first ? (int)blockIdx.x : (int)blockIdx.x - cols.rb.nblk;
+  const RowBlocks rb = first ? cols.rb : rows.rb;
+  const MatPtrs<double> A = first ? cols.A : rows.A;
+  const T *__restrict__ in0 = first ? cols.in0 : rows.in0, *__restrict__ in1 = first ? cols.in1 : rows.in1;
+  double *__restrict__ out0 = first ? cols.out0 : rows.out0, *__restrict__ out1 = first ? cols.out1 : rows.out1;
   const Inst& I = inst[rb.blk_inst[b]];
   if (!mode_selects(I, mode) || !prec_selects(I, mode, prec)) return;
   const bool two = (in1 != nullptr) && (mode != kModeCheck || I.use_avg != 0);
@@ -2517,13 +2565,11 @@ __global__ void k_decide(Inst* __restrict__ inst, int nb) {
 // candidate products) or, for an optimal candidate, write the unscaled answer.
 // Columns: x, G^T y, average sums, x_out = D2 x, lam_out = (c_hat - G^T y_hat)/D2.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_restart_cols(Ranges R, IterPtrs<T> it, IterPtrs<double> it64,
-                                                         const double* __restrict__ g0,
-                                                         const double* __restrict__ g1,
-                                                         DataPtrs<double> d, const double* __restrict__ D2,
-                                                         double* __restrict__ xout, double* __restrict__ lamout,
-                                                         const Inst* __restrict__ inst, int prec) {
-  const int b = blockIdx.x;
+__device__ __forceinline__ void restart_cols(int b, const Ranges& R, const IterPtrs<T>& it, const IterPtrs<double>& it64,
+                                             const double* __restrict__ g0, const double* __restrict__ g1,
+                                             const DataPtrs<double>& d, const double* __restrict__ D2,
+                                             double* __restrict__ xout, double* __restrict__ lamout,
+                                             const Inst* __restrict__ inst, int prec) {
   const Inst& I = inst[R.blk_inst[b]];
   if (I.check_due == 0 || I.restart == 0 || I.precision != prec) return;
   const int ch = I.chosen;
@@ -2556,13 +2602,10 @@ __global__ __launch_bounds__(kBlock) void k_restart_cols(Ranges R, IterPtrs<T> i
 }
 
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_restart_rows(Ranges R, IterPtrs<T> it, IterPtrs<double> it64,
-                                                         const double* __restrict__ g0,
-                                                         const double* __restrict__ g1,
-                                                         const double* __restrict__ D1,
-                                                         double* __restrict__ yout,
-                                                         const Inst* __restrict__ inst, int prec) {
-  const int b = blockIdx.x;
+__device__ __forceinline__ void restart_rows(int b, const Ranges& R, const IterPtrs<T>& it, const IterPtrs<double>& it64,
+                                             const double* __restrict__ g0, const double* __restrict__ g1,
+                                             const double* __restrict__ D1, double* __restrict__ yout,
+                                             const Inst* __restrict__ inst, int prec) {
   const Inst& I = inst[R.blk_inst[b]];
   if (I.check_due == 0 || I.restart == 0 || I.precision != prec) return;
   const int ch = I.chosen;
@@ -2591,6 +2634,19 @@ __global__ __launch_bounds__(kBlock) void k_restart_rows(Ranges R, IterPtrs<T> i
       it.sy[i] = (T)0;
     }
   }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_restart(Ranges rc, Ranges rr, IterPtrs<T> it, IterPtrs<double> it64,
+                                                    const double* __restrict__ gc0, const double* __restrict__ gc1,
+                                                    const double* __restrict__ gr0, const double* __restrict__ gr1,
+                                                    DataPtrs<double> d, const double* __restrict__ D1,
+                                                    const double* __restrict__ D2, double* __restrict__ xout,
+                                                    double* __restrict__ lamout, double* __restrict__ yout,
+                                                    const Inst* __restrict__ inst, int prec) {
+  const int b = blockIdx.x;
+  if (b < rc.nblk) restart_cols<T>(b, rc, it, it64, gc0, gc1, d, D2, xout, lamout, inst, prec);
+  else restart_rows<T>(b - rc.nblk, rr, it, it64, gr0, gr1, D1, yout, inst, prec);
 }
 
 __global__ void k_check_end(Inst* __restrict__ inst, int nb) {
@@ -2843,33 +2899,27 @@ __global__ void k_eval_fin(Inst* __restrict__ inst, int nb, int mode) {
 // Write the evaluated point (x_hat, y_hat) unscaled.  Start mode: only for
 // instances found optimal (which then stop); final mode: every selected instance.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_eval_out_cols(Ranges R, const T* __restrict__ xh,
-                                                          const double* __restrict__ g0,
-                                                          DataPtrs<double> d, const double* __restrict__ D2,
-                                                          double* __restrict__ xout, double* __restrict__ lamout,
-                                                          const Inst* __restrict__ inst, int prec, int mode) {
-  const int b = blockIdx.x;
+__global__ __launch_bounds__(kBlock) void k_eval_out(Ranges rc, Ranges rr, const T* __restrict__ xh,
+                                                     const T* __restrict__ yh, const double* __restrict__ g0,
+                                                     DataPtrs<double> d, const double* __restrict__ D1,
+                                                     const double* __restrict__ D2, double* __restrict__ xout,
+                                                     double* __restrict__ lamout, double* __restrict__ yout,
+                                                     const Inst* __restrict__ inst, int prec, int mode) {
+  const bool cols = (int)blockIdx.x < rc.nblk;
+  const int b = cols ? (int)blockIdx.x : (int)blockIdx.x - rc.nblk;
+  const Ranges& R = cols ? rc : rr;
   const Inst& I = inst[R.blk_inst[b]];
   if (!mode_selects(I, mode) || I.precision != prec) return;
   if (mode == kModeEvalStart && !I.optimal) return;
-  const int j1 = R.blk_end[b];
-  for (int j = R.blk_start[b] + (int)threadIdx.x; j < j1; j += kBlock) {
-    xout[j] = D2[j] * (double)xh[j];
-    lamout[j] = (d.c[j] - g0[j]) / D2[j];
+  const int e = R.blk_end[b];
+  if (cols) {
+    for (int j = R.blk_start[b] + (int)threadIdx.x; j < e; j += kBlock) {
+      xout[j] = D2[j] * (double)xh[j];
+      lamout[j] = (d.c[j] - g0[j]) / D2[j];
+    }
+  } else {
+    for (int i = R.blk_start[b] + (int)threadIdx.x; i < e; i += kBlock) yout[i] = D1[i] * (double)yh[i];
   }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_eval_out_rows(Ranges R, const T* __restrict__ yh,
-                                                          const double* __restrict__ D1,
-                                                          double* __restrict__ yout,
-                                                          const Inst* __restrict__ inst, int prec, int mode) {
-  const int b = blockIdx.x;
-  const Inst& I = inst[R.blk_inst[b]];
-  if (!mode_selects(I, mode) || I.precision != prec) return;
-  if (mode == kModeEvalStart && !I.optimal) return;
-  const int i1 = R.blk_end[b];
-  for (int i = R.blk_start[b] + (int)threadIdx.x; i < i1; i += kBlock) yout[i] = D1[i] * (double)yh[i];
 }
 
 __global__ void k_eval_start_end(Inst* __restrict__ inst, int nb) {
@@ -3569,21 +3619,16 @@ static void launch_cand_t(const KernelCtx& k, hipStream_t s, int prec, const Ite
     // band tiles with FP64 values: one pass per vector, then the window sums
     launch_band_cand<T>(k.band1, k.bval64, x0, k.bpart64, k.M, k.inst, prec, mode, 0, s);
     if (x1) launch_band_cand<T>(k.band1, k.bval64, x1, k.bpart64b, k.M, k.inst, prec, mode, 1, s);
-    if (k.vrow.nblk > 0)
-      k_band_combine2<<<grid1(k.vrow.nblk), kBlock, 0, s>>>(k.vrow, k.band1.P, k.M, k.bpart64,
-                                                             x1 ? k.bpart64b : nullptr, k.cgx0, k.cgx1, k.inst, mode);
     launch_band_cand<T>(k.band2, k.bvalT64, y0, k.bpartT64, k.N, k.inst, prec, mode, 0, s);
     if (y1) launch_band_cand<T>(k.band2, k.bvalT64, y1, k.bpartT64b, k.N, k.inst, prec, mode, 1, s);
-    if (k.vcol.nblk > 0)
-      k_band_combine2<<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, k.band2.P, k.N, k.bpartT64,
-                                                             y1 ? k.bpartT64b : nullptr, k.cgty0, k.cgty1, k.inst,
-                                                             mode);
-  } else if (k.brow.nblk > 0) {
-    k_spmv2<T><<<grid1(k.brow.nblk), kBlock, 0, s>>>(k.brow, k.A64, x0, x1, k.cgx0, k.cgx1, k.inst, prec, mode);
-  }
-  if (!k.use_band && k.bcol.nblk > 0) {
-    k_spmv2<T><<<grid1(k.bcol.nblk), kBlock, 0, s>>>(k.bcol, k.AT64, y0, y1, k.cgty0, k.cgty1, k.inst, prec,
-                                                      mode);
+    if (k.vcol.nblk + k.vrow.nblk > 0)
+      k_band_combine2<<<grid1(k.vcol.nblk + k.vrow.nblk), kBlock, 0, s>>>(
+          CombineSide{k.vcol, k.band2.P, k.N, k.bpartT64, y1 ? k.bpartT64b : nullptr, k.cgty0, k.cgty1},
+          CombineSide{k.vrow, k.band1.P, k.M, k.bpart64, x1 ? k.bpart64b : nullptr, k.cgx0, k.cgx1}, k.inst, mode);
+  } else if (k.bcol.nblk + k.brow.nblk > 0) {
+    k_spmv2<T><<<grid1(k.bcol.nblk + k.brow.nblk), kBlock, 0, s>>>(
+        Spmv2Side<T>{k.bcol, k.AT64, y0, y1, k.cgty0, k.cgty1}, Spmv2Side<T>{k.brow, k.A64, x0, x1, k.cgx0, k.cgx1},
+        k.inst, prec, mode);
   }
   if (k.vcol.nblk > 0)
     k_cand_cols<T><<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, x0, x1, it.xa, k.cgty0, k.cgty1, k.d64, k.D2,
@@ -3595,12 +3640,9 @@ static void launch_cand_t(const KernelCtx& k, hipStream_t s, int prec, const Ite
 
 template <typename T>
 static void launch_check_pre_t(const KernelCtx& k, hipStream_t s, int prec, const IterPtrs<T>& it) {
-  if (k.vcol.nblk > 0)
-    k_commit_avg<T><<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, it.x, it.xh, it.xa, it.gty, it.gtyh, it.gtya,
-                                                           it.sx, it.xbar, k.inst, prec);
-  if (k.vrow.nblk > 0)
-    k_commit_avg<T><<<grid1(k.vrow.nblk), kBlock, 0, s>>>(k.vrow, it.y, it.yh, it.ya, it.gx, it.gxh, it.gxa,
-                                                           it.sy, it.ybar, k.inst, prec);
+  if (k.vcol.nblk + k.vrow.nblk > 0)
+    k_commit_avg<T><<<grid1(k.vcol.nblk + k.vrow.nblk), kBlock, 0, s>>>(commit_cols(k.vcol, it), commit_rows(k.vrow, it),
+                                                                         k.inst, prec);
   launch_cand_t<T>(k, s, prec, it, it.xh, it.xbar, it.yh, it.ybar, kModeCheck);
 }
 
@@ -3614,12 +3656,10 @@ static void launch_probe_t(const KernelCtx& k, hipStream_t s, int prec, const It
 
 template <typename T>
 static void launch_restart_t(const KernelCtx& k, hipStream_t s, int prec, const IterPtrs<T>& it) {
-  if (k.vcol.nblk > 0)
-    k_restart_cols<T><<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, it, k.it64, k.cgty0, k.cgty1, k.d64, k.D2,
-                                                             k.xout, k.lamout, k.inst, prec);
-  if (k.vrow.nblk > 0)
-    k_restart_rows<T><<<grid1(k.vrow.nblk), kBlock, 0, s>>>(k.vrow, it, k.it64, k.cgx0, k.cgx1, k.D1, k.yout,
-                                                             k.inst, prec);
+  if (k.vcol.nblk + k.vrow.nblk > 0)
+    k_restart<T><<<grid1(k.vcol.nblk + k.vrow.nblk), kBlock, 0, s>>>(k.vcol, k.vrow, it, k.it64, k.cgty0, k.cgty1, k.cgx0,
+                                                                      k.cgx1, k.d64, k.D1, k.D2, k.xout, k.lamout,
+                                                                      k.yout, k.inst, prec);
 }
 
 // Products of the rays with FP64 values (every selected instance, whatever
@@ -3628,26 +3668,21 @@ static void launch_restart_t(const KernelCtx& k, hipStream_t s, int prec, const 
 static void launch_ray_products(const KernelCtx& k, hipStream_t s) {
   if (k.use_band) {
     launch_band_cand<double>(k.band2, k.bvalT64, k.ry, k.bpartT64, k.N, k.inst, kFP64, kModeRay, 0, s);
-    if (k.vcol.nblk > 0)
-      k_band_combine2<<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, k.band2.P, k.N, k.bpartT64, nullptr, k.rgty,
-                                                             nullptr, k.inst, kModeRay);
-    if (k.ray_x) {
-      launch_band_cand<double>(k.band1, k.bval64, k.rx, k.bpart64, k.M, k.inst, kFP64, kModeRay, 0, s);
-      if (k.vrow.nblk > 0)
-        k_band_combine2<<<grid1(k.vrow.nblk), kBlock, 0, s>>>(k.vrow, k.band1.P, k.M, k.bpart64, nullptr, k.rgx,
-                                                               nullptr, k.inst, kModeRay);
-    }
+    if (k.ray_x) launch_band_cand<double>(k.band1, k.bval64, k.rx, k.bpart64, k.M, k.inst, kFP64, kModeRay, 0, s);
+    Ranges rows = k.vrow;
+    if (!k.ray_x) rows.nblk = 0;
+    if (k.vcol.nblk + rows.nblk > 0)
+      k_band_combine2<<<grid1(k.vcol.nblk + rows.nblk), kBlock, 0, s>>>(
+          CombineSide{k.vcol, k.band2.P, k.N, k.bpartT64, nullptr, k.rgty, nullptr},
+          CombineSide{rows, k.band1.P, k.M, k.bpart64, nullptr, k.rgx, nullptr}, k.inst, kModeRay);
     return;
   }
-  if (k.bcol.nblk > 0) {
-    k_spmv2<double><<<grid1(k.bcol.nblk), kBlock, 0, s>>>(k.bcol, k.AT64, k.ry, nullptr, k.rgty, nullptr, k.inst,
-                                                           kFP64, kModeRay);
-  }
-  if (!k.ray_x) return;
-  if (k.brow.nblk > 0) {
-    k_spmv2<double><<<grid1(k.brow.nblk), kBlock, 0, s>>>(k.brow, k.A64, k.rx, nullptr, k.rgx, nullptr, k.inst,
-                                                           kFP64, kModeRay);
-  }
+  RowBlocks rows = k.brow;
+  if (!k.ray_x) rows.nblk = 0;
+  if (k.bcol.nblk + rows.nblk > 0)
+    k_spmv2<double><<<grid1(k.bcol.nblk + rows.nblk), kBlock, 0, s>>>(
+        Spmv2Side<double>{k.bcol, k.AT64, k.ry, nullptr, k.rgty, nullptr},
+        Spmv2Side<double>{rows, k.A64, k.rx, nullptr, k.rgx, nullptr}, k.inst, kFP64, kModeRay);
 }
 
 template <typename T>
@@ -3716,11 +3751,9 @@ static void launch_eval_t(const KernelCtx& k, hipStream_t s, int prec, const Ite
 
 template <typename T>
 static void launch_eval_out_t(const KernelCtx& k, hipStream_t s, int prec, const IterPtrs<T>& it, int mode) {
-  if (k.vcol.nblk > 0)
-    k_eval_out_cols<T><<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, it.xh, k.cgty0, k.d64, k.D2, k.xout,
-                                                              k.lamout, k.inst, prec, mode);
-  if (k.vrow.nblk > 0)
-    k_eval_out_rows<T><<<grid1(k.vrow.nblk), kBlock, 0, s>>>(k.vrow, it.yh, k.D1, k.yout, k.inst, prec, mode);
+  if (k.vcol.nblk + k.vrow.nblk > 0)
+    k_eval_out<T><<<grid1(k.vcol.nblk + k.vrow.nblk), kBlock, 0, s>>>(k.vcol, k.vrow, it.xh, it.yh, k.cgty0, k.d64, k.D1,
+                                                                       k.D2, k.xout, k.lamout, k.yout, k.inst, prec, mode);
 }
 
 void launch_eval(const KernelCtx& k, hipStream_t s, int mask, int final_mode) {
