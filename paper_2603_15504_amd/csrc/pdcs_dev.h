@@ -198,8 +198,8 @@ __device__ __forceinline__ double wave_max(double v) {
 }
 
 // Sum NV values over the workgroup; thread 0..NV-1 of the block write out[i].
-// lds must hold kWavesPerBlock * NV doubles.  Order is fixed: deterministic.
-template <int NV>
+// lds must hold WAVES * NV doubles.  Order is fixed: deterministic.
+template <int NV, int WAVES = kWavesPerBlock>
 __device__ __forceinline__ void block_sum_store(double (&v)[NV], double* lds, double* out) {
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
@@ -212,7 +212,7 @@ __device__ __forceinline__ void block_sum_store(double (&v)[NV], double* lds, do
   if (threadIdx.x < NV) {
     double s = 0.0;
 #pragma unroll
-    for (int w = 0; w < kWavesPerBlock; ++w) s += lds[w * NV + threadIdx.x];
+    for (int w = 0; w < WAVES; ++w) s += lds[w * NV + threadIdx.x];
     out[threadIdx.x] = s;
   }
 }

@@ -835,14 +835,14 @@ __global__ __launch_bounds__(kBlock) void k_fold_end(FoldIn f) {
 // at a time and requests all of their operands before the first is used
 // (elements past the end repeat the last one and are not stored).
 constexpr int kElems = 4;  // elements per thread of the passes over global memory
-template <typename T, int U>
+template <typename T, int U, int NT = kBlock>
 struct PrimalElems {
   T x[U], g[U], xh[U], gh[U], xa[U], ga[U], sx[U], c[U], lo[U], hi[U];
   __device__ __forceinline__ void load(const IterPtrs<T>& it, const DataPtrs<T>& d, int j0, int j1, bool commit,
                                        bool avg) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int j = min(j0 + u * kBlock, j1 - 1);
+      const int j = min(j0 + u * NT, j1 - 1);
       x[u] = it.x[j], g[u] = it.gty[j], c[u] = d.c[j], lo[u] = d.l[j], hi[u] = d.u[j];
       if (commit) xh[u] = it.xh[j], gh[u] = it.gtyh[j], xa[u] = it.xa[j], ga[u] = it.gtya[j];
       if (avg) sx[u] = it.sx[j];
@@ -855,7 +855,7 @@ struct PrimalElems {
     const double tau = I.eta / I.omega;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int j = j0 + u * kBlock;
+      const int j = j0 + u * NT;
       if (j >= j1) break;
       double xv = (double)x[u];
       double gty = (double)g[u];
@@ -1536,64 +1536,113 @@ __global__ __launch_bounds__(kBlock) void k_trials_wg(Ranges vcol, RowBlocks bro
 }
 
 // Row-wise passes of the LDS-resident chunk kernel (instances whose rows and
-// columns hold at most kLdsRowMax entries): one thread per row of G (dual
-// step) or of G^T (dual slack), the dot product in FP64 in entry order, and one
-// record for the whole instance.
-// One thread's dot product of entries [q0, q1) with x, in entry order (FP64);
-// four entries' indices, values and gathers are requested before they are added.
+// columns hold at most kLdsRowMax entries), by kRowThreads threads: a few lanes per
+// row of G (dual step) or of G^T (dual slack), the dot product in FP64, and one
+// record for the whole instance.  A trial is five such steps, each bound by its
+// chain of LDS reads, sums and barriers: 1.2 + 1.9 + 0.7 + 1.2 + 1.1 us at m = 200,
+// n = 500, 2500 nonzeros with 256 threads and one per row.  40 trials there: 262 us
+// with 256 threads, 242 with 512, 304 with 1024 (whose sums and barriers take more
+// than the shorter rounds save).
+constexpr int kRowThreads = 512;
+
+// Lanes per row of a row-wise pass over `rows` rows by NT threads: as many as
+// there are threads for, at most 8.
+template <int NT>
+__device__ __forceinline__ int row_lanes(int rows) {
+  int L = 1;
+  while (L < 8 && 2 * L * rows <= NT) L *= 2;
+  return L;
+}
+
+// Entries [q0, q1) of a row against x by L lanes, this one the li-th; four entries of
+// a lane in flight, the last up to three in one clamped step.  Every lane of the
+// row gets the sum.
 template <typename T>
-__device__ __forceinline__ double row_dot_seq(int q0, int q1, const int32_t* idx, const T* val, const T* x) {
+__device__ __forceinline__ double row_dot_lanes(int q0, int q1, int L, int li, const int32_t* idx, const T* val,
+                                                const T* x) {
   double s = 0.0;
-  int q = q0;
-  for (; q + 4 <= q1; q += 4) {
+  int q = q0 + li;
+  for (; q + 3 * L < q1; q += 4 * L) {
     int c[4];
     double v[4], g[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      c[u] = idx[q + u];
-      v[u] = (double)val[q + u];
+      c[u] = idx[q + u * L];
+      v[u] = (double)val[q + u * L];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) g[u] = (double)x[c[u]];
 #pragma unroll
     for (int u = 0; u < 4; ++u) s += v[u] * g[u];
   }
-  for (; q < q1; ++q) s += (double)val[q] * (double)x[idx[q]];
+  if (q < q1) {
+    int c[3];
+    double v[3], g[3];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      const int k = min(q + u * L, q1 - 1);
+      c[u] = idx[k];
+      v[u] = (double)val[k];
+    }
+#pragma unroll
+    for (int u = 0; u < 3; ++u) g[u] = (double)x[c[u]];
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+      if (q + u * L < q1) s += v[u] * g[u];
+  }
+  for (int off = L >> 1; off > 0; off >>= 1) s += __shfl_xor(s, off, kWave);
   return s;
 }
 
-template <typename T>
+template <typename T, int NT>
+__device__ __forceinline__ void primal_elems_lds(int c0, int c1, const IterPtrs<T>& it, const DataPtrs<T>& d,
+                                                 const Inst& I, double* rec) {
+  __shared__ double lds[NT / kWave * 2];
+  if (I.status != kActive) return;
+  const bool commit = I.pending != 0, avg = commit && I.use_avg != 0;
+  double acc[2] = {0.0, 0.0};
+  for (int j = c0 + (int)threadIdx.x; j < c1; j += NT) {
+    PrimalElems<T, 1, NT> e;
+    e.load(it, d, j, c1, commit, avg);
+    e.step(it, I, j, c1, acc);
+  }
+  block_sum_store<2, NT / kWave>(acc, lds, rec);
+}
+
+template <typename T, int NT>
 __device__ __forceinline__ void dual_rows_lds(int r0, int r1, const MatPtrs<T>& A, const IterPtrs<T>& it,
                                               const DataPtrs<T>& d, const Inst& I, double* rec) {
-  __shared__ double lds[kWavesPerBlock * 4];
+  __shared__ double lds[NT / kWave * 4];
   if (I.status != kActive) return;
   const DualEpilogue<T> epi = make_dual_epilogue(I, it, d);
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int r = r0 + (int)threadIdx.x; r < r1; r += kBlock) {
+  const int L = row_lanes<NT>(r1 - r0), li = threadIdx.x & (L - 1);
+  for (int r = r0 + (int)threadIdx.x / L; r < r1; r += NT / L) {
     const DualRow<T> o = epi.load(r);
-    const double s = row_dot_seq(A.ptr[r], A.ptr[r + 1], A.idx, A.val, it.xh);
-    epi(r, s, o, acc);
+    const double s = row_dot_lanes(A.ptr[r], A.ptr[r + 1], L, li, A.idx, A.val, it.xh);
+    if (li == 0) epi(r, s, o, acc);
   }
-  block_sum_store<4>(acc, lds, rec);
+  block_sum_store<4, NT / kWave>(acc, lds, rec);
 }
 
-template <typename T>
+template <typename T, int NT>
 __device__ __forceinline__ void lam_rows_lds(int c0, int c1, const MatPtrs<T>& AT, const IterPtrs<T>& it,
                                              const DataPtrs<T>& d, const Inst& I, double* rec) {
-  __shared__ double lds[kWavesPerBlock * 3];
+  __shared__ double lds[NT / kWave * 3];
   if (I.status != kActive || I.last_acc == 0) return;
   double acc[3] = {0.0, 0.0, 0.0};
-  for (int j = c0 + (int)threadIdx.x; j < c1; j += kBlock) {
+  const int L = row_lanes<NT>(c1 - c0), li = threadIdx.x & (L - 1);
+  for (int j = c0 + (int)threadIdx.x / L; j < c1; j += NT / L) {
     const LamCol<T> o = lam_load<T>(j, d);
-    const double s = row_dot_seq(AT.ptr[j], AT.ptr[j + 1], AT.idx, AT.val, it.yh);
-    lam_epilogue<T>(j, s, it, o, acc);
+    const double s = row_dot_lanes(AT.ptr[j], AT.ptr[j + 1], L, li, AT.idx, AT.val, it.yh);
+    if (li == 0) lam_epilogue<T>(j, s, it, o, acc);
   }
-  block_sum_store<3>(acc, lds, rec);
+  block_sum_store<3, NT / kWave>(acc, lds, rec);
 }
 
 template <typename T>
 __device__ __forceinline__ void lds_copy(T* __restrict__ dst, const T* __restrict__ src, int64_t n) {
-  for (int64_t i = threadIdx.x; i < n; i += kBlock) dst[i] = src[i];
+  for (int64_t i = threadIdx.x; i < n; i += blockDim.x) dst[i] = src[i];
 }
 
 // k_trials_wg with the instance resident in LDS: the kernel copies its
@@ -1603,10 +1652,11 @@ __device__ __forceinline__ void lds_copy(T* __restrict__ dst, const T* __restric
 // trials change.  Every dependent step of a trial is then an LDS access
 // instead of an HBM round trip.  The host launches it only when the largest
 // instance fits (dynamic LDS of lds_layout(...).total bytes).
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_trials_lds(Ranges vcol, RowBlocks brow, RowBlocks bcol, MatPtrs<T> A,
-                                                       MatPtrs<T> AT, IterPtrs<T> it, DataPtrs<T> d,
-                                                       Inst* __restrict__ inst, int prec, int K, int rowwise) {
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void k_trials_lds(Ranges vcol, RowBlocks brow, RowBlocks bcol, MatPtrs<T> A,
+                                                   MatPtrs<T> AT, IterPtrs<T> it, DataPtrs<T> d,
+                                                   Inst* __restrict__ inst, int prec, int K) {
+  constexpr bool rowwise = NT > kBlock;
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
   __shared__ Inst Ish;
   __shared__ int32_t iblk[6];
@@ -1614,7 +1664,7 @@ __global__ __launch_bounds__(kBlock) void k_trials_lds(Ranges vcol, RowBlocks br
   {
     const uint64_t* s = reinterpret_cast<const uint64_t*>(&inst[iid]);
     uint64_t* t = reinterpret_cast<uint64_t*>(&Ish);
-    for (int i = threadIdx.x; i < (int)(sizeof(Inst) / 8); i += kBlock) t[i] = s[i];
+    for (int i = threadIdx.x; i < (int)(sizeof(Inst) / 8); i += NT) t[i] = s[i];
     if (threadIdx.x == 0) {
       iblk[0] = vcol.inst_blk0[iid];
       iblk[1] = vcol.inst_blk0[iid + 1];
@@ -1711,17 +1761,13 @@ __global__ __launch_bounds__(kBlock) void k_trials_lds(Ranges vcol, RowBlocks br
   double* rp_ = recp - 2 * (size_t)p0;
   double* rd_ = recd - 4 * (size_t)d0;
   double* rl_ = recl - 3 * (size_t)l0;
-  // Row-wise instances take one range for the primal pass and the row-wise
-  // passes, each leaving one record (one[] is the per-instance block table of
-  // a single record); the others keep their blocks.
-  __shared__ int32_t one[2], rng[3];
+  // Row-wise instances leave one record in each pass (one[] is the per-instance
+  // block table of a single record); the others keep their blocks.
+  __shared__ int32_t one[2];
   __shared__ double pf[2];
   if (threadIdx.x == 0) {
     one[0] = 0;
     one[1] = 1;
-    rng[0] = c0;
-    rng[1] = c0 + n;
-    rng[2] = iid;
   }
   if (threadIdx.x == kWave) {  // line-search factors of the first trial
     const double kb = (double)Ish.kbar + 2.0;
@@ -1729,20 +1775,16 @@ __global__ __launch_bounds__(kBlock) void k_trials_lds(Ranges vcol, RowBlocks br
     pf[1] = pow(kb, -0.6);
   }
   __syncthreads();
-  Ranges l1 = vcol;
-  l1.blk_start = rng;
-  l1.blk_end = rng + 1;
-  l1.blk_inst = rng + 2;
   for (int s = 0; s < K; ++s) {
     if (Ish.status != kActive || Ish.precision != prec) break;
-    if (rowwise) {
-      primal_body<T, 2>(0, l1, li, ld, li_inst, prec, recp);
+    if constexpr (rowwise) {
+      primal_elems_lds<T, NT>(c0, c0 + n, li, ld, Ish, recp);
       __syncthreads();
-      dual_rows_lds<T>(r0, r0 + m, LA, li, ld, Ish, recd);
+      dual_rows_lds<T, NT>(r0, r0 + m, LA, li, ld, Ish, recd);
       __syncthreads();
       fin_ls_body(iid, one - iid, recp, one - iid, recd, li_inst, pf);
       __syncthreads();
-      lam_rows_lds<T>(c0, c0 + n, LAT, li, ld, Ish, recl);
+      lam_rows_lds<T, NT>(c0, c0 + n, LAT, li, ld, Ish, recl);
       __syncthreads();
       fin_beta_body(iid, one - iid, recl, li_inst);
     } else {
@@ -1772,15 +1814,15 @@ __global__ __launch_bounds__(kBlock) void k_trials_lds(Ranges vcol, RowBlocks br
   for (int v = 0; v < 5; ++v) {
     const T* src = vec + (size_t)wx[v] * n;
     T* dst = xs[wx[v]] + c0;
-    for (int i = threadIdx.x; i < n; i += kBlock) dst[i] = src[i];
+    for (int i = threadIdx.x; i < n; i += NT) dst[i] = src[i];
     const T* sy_ = ly0 + (size_t)wx[v] * m;
     T* dy_ = ys[wx[v]] + r0;
-    for (int i = threadIdx.x; i < m; i += kBlock) dy_[i] = sy_[i];
+    for (int i = threadIdx.x; i < m; i += NT) dy_[i] = sy_[i];
   }
   {
     const uint64_t* s = reinterpret_cast<const uint64_t*>(&Ish);
     uint64_t* t = reinterpret_cast<uint64_t*>(&inst[iid]);
-    for (int i = threadIdx.x; i < (int)(sizeof(Inst) / 8); i += kBlock) t[i] = s[i];
+    for (int i = threadIdx.x; i < (int)(sizeof(Inst) / 8); i += NT) t[i] = s[i];
   }
 }
 
@@ -2992,6 +3034,8 @@ __global__ void k_clear_pending(Inst* __restrict__ inst, int nb) {
 // Set-up: diagonal rescaling (Section 2.6), norms, start point
 // ===========================================================================
 
+constexpr int kScaleLdsThreads = 1024;
+
 // The scaling passes work on both sides at once: each computes, from the D1 and D2
 // of the pass before, every row's and every column's statistic -- max |D1_i a_ij D2_j|
 // (Ruiz, kScaleMax) or the sum of its squares (the 2-norm pass, kScaleSquares) --
@@ -3106,6 +3150,106 @@ __global__ __launch_bounds__(kBlock) void k_scale_pass(ScaleSide a, ScaleSide c,
           out[r] = scaled_factor(own, s, mode);
         }
       });
+}
+
+// All scaling passes and the scaled values of an instance by one workgroup, its
+// matrix (both sides) and the factors of two passes in LDS, a thread per row or
+// column: an instance that k_trials_lds takes with short rows (this needs 24 bytes
+// per nonzero and 20 per row and column, fewer than that kernel in FP64).  Each pass
+// is bound by its longest row's chain of LDS reads.  rec: the instance's largest
+// magnitude at its first row block, 0 at its others.  (n = 500, m = 200, 2500
+// nonzeros: 11 launches of 5.4 us and the values' 5.7 before, 33 here.)
+__global__ __launch_bounds__(kScaleLdsThreads) void k_scale_lds(MatPtrs<double> A, MatPtrs<double> AT,
+                                                                const int32_t* __restrict__ iblk, int passes, int ruiz,
+                                                                double* __restrict__ D1, double* __restrict__ D2,
+                                                                double* __restrict__ v64, float* __restrict__ v32,
+                                                                double* __restrict__ vt64, float* __restrict__ vt32,
+                                                                const Inst* __restrict__ inst, double* __restrict__ rec) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
+  __shared__ double red[kScaleLdsThreads / kWave];
+  const int iid = blockIdx.x, tid = threadIdx.x;
+  const Inst& I = inst[iid];
+  const int r0 = I.row0, m = I.rows, c0 = I.col0, n = I.cols;
+  const int q0 = A.ptr[r0], nnz = A.ptr[r0 + m] - q0;
+  const int t0 = AT.ptr[c0];
+  double* va = reinterpret_cast<double*>(dyn);
+  double* vt = va + nnz;
+  double* d = vt + nnz;  // factors: rows and columns of one pass, then of the other
+  int32_t* ci = reinterpret_cast<int32_t*>(d + 2 * (m + n));
+  int32_t* ri = ci + nnz;
+  int32_t* ptr = ri + nnz;  // first entries of the rows, then of the columns
+  for (int i = tid; i < nnz; i += kScaleLdsThreads) {
+    va[i] = A.val[q0 + i];
+    vt[i] = AT.val[t0 + i];
+    ci[i] = m + A.idx[q0 + i] - c0;  // places in d
+    ri[i] = AT.idx[t0 + i] - r0;
+  }
+  for (int i = tid; i < m + n; i += kScaleLdsThreads) {
+    d[i] = 1.0;
+    ptr[i] = i < m ? A.ptr[r0 + i] - q0 : AT.ptr[c0 + i - m] - t0;
+  }
+  __syncthreads();
+  const auto bounds = [&](int i, int& b, int& e) {  // entries of row i, or column i - m
+    b = ptr[i];
+    e = i == m - 1 || i == m + n - 1 ? nnz : ptr[i + 1];
+  };
+  const double* from = d;
+  double* to = d + (m + n);
+  for (int pass = 0; pass < passes; ++pass) {
+    const int mode = pass < ruiz ? kScaleMax : kScaleSquares;
+    for (int i = tid; i < m + n; i += kScaleLdsThreads) {
+      const bool row = i < m;
+      const double* v = row ? va : vt;
+      const int32_t* at = row ? ci : ri;
+      const double own = from[i];
+      int b, e;
+      bounds(i, b, e);
+      double s = 0.0;
+      for (; b < e; b += 4) {
+        double a[4], g[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int k = min(b + u, e - 1);
+          a[u] = v[k];
+          g[u] = from[at[k]];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const double x = row ? (own * a[u]) * g[u] : (g[u] * a[u]) * own;
+          if (mode == kScaleMax) s = fmax(s, fabs(x));
+          else if (b + u < e) s += x * x;
+        }
+      }
+      to[i] = scaled_factor(own, s, mode);
+    }
+    __syncthreads();
+    const double* t = from;
+    from = to;
+    to = const_cast<double*>(t);
+  }
+  double big = 0.0;
+  for (int i = tid; i < m + n; i += kScaleLdsThreads) {
+    const bool row = i < m;
+    const double own = from[i];
+    (row ? D1 + r0 : D2 + c0 - m)[i] = own;
+    int b, e;
+    bounds(i, b, e);
+    for (; b < e; ++b) {
+      const double x = row ? (own * va[b]) * from[ci[b]] : (from[ri[b]] * vt[b]) * own;
+      (row ? v64 + q0 : vt64 + t0)[b] = x;
+      (row ? v32 + q0 : vt32 + t0)[b] = (float)x;
+      big = fmax(big, fabs(x));
+    }
+  }
+  big = wave_max(big);
+  if ((tid & (kWave - 1)) == 0) red[tid / kWave] = big;
+  __syncthreads();
+  for (int b = iblk[iid] + tid; b < iblk[iid + 1]; b += kScaleLdsThreads) {
+    double x = 0.0;
+    if (b == iblk[iid])
+      for (int w = 0; w < kScaleLdsThreads / kWave; ++w) x = fmax(x, red[w]);
+    rec[b] = x;
+  }
 }
 
 // Scaled values of both sides in FP64 and FP32, and per row block of G the largest
@@ -3384,16 +3528,23 @@ __global__ __launch_bounds__(kBlock) void k_start_rows(Ranges R, const double* _
   });
 }
 
-// Copy FP64 products into the maintained products of the start point.
+// Copy FP64 products into the maintained products of the start point: G^T y (n
+// values), then G x (m).
 template <typename T>
-__global__ void k_set_products(T* __restrict__ g, T* __restrict__ ga, T* __restrict__ gh,
-                               const double* __restrict__ src, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const T v = (T)src[i];
-  g[i] = v;
-  ga[i] = v;
-  gh[i] = v;
+__global__ void k_set_products(IterPtrs<T> it, const double* __restrict__ gty, int64_t n, const double* __restrict__ gx,
+                               int64_t m) {
+  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) {
+    const T v = (T)gty[i];
+    it.gty[i] = v;
+    it.gtya[i] = v;
+    it.gtyh[i] = v;
+  } else if ((i -= n) < m) {
+    const T v = (T)gx[i];
+    it.gx[i] = v;
+    it.gxa[i] = v;
+    it.gxh[i] = v;
+  }
 }
 
 // Plain product out = A in (unscaled or scaled values) for the public SpMV call.
@@ -3563,8 +3714,9 @@ void launch_trials_fold(const KernelCtx& k, hipStream_t s, int mask, int K) {
 }
 
 // Dynamic LDS the LDS-resident chunk kernel can take: the device's LDS per
-// workgroup less the kernel's static LDS; the first call per precision also
-// raises the kernel's dynamic-LDS limit to that size.
+// workgroup less the most static LDS of the kernels that get it (both forms of
+// that kernel and, in FP64, the set-up's); the first call per precision also
+// raises these kernels' dynamic-LDS limits to that size.
 template <typename T>
 static size_t lds_capacity_t() {
   static size_t cap = 0;
@@ -3572,19 +3724,26 @@ static size_t lds_capacity_t() {
   if (!done) {
     done = true;
     int dev = 0, max_lds = 0, optin = 0;
-    hipFuncAttributes fa{};
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess) {
       if (hipDeviceGetAttribute(&optin, hipDeviceAttributeSharedMemPerBlockOptin, dev) == hipSuccess)
         max_lds = std::max(max_lds, optin);
     }
-    if (max_lds > 0 && hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(&k_trials_lds<T>)) == hipSuccess &&
-        (size_t)max_lds > fa.sharedSizeBytes + 1024) {
-      const size_t c = (size_t)max_lds - fa.sharedSizeBytes - 1024;
-      if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_trials_lds<T>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)c) == hipSuccess)
-        cap = c;
+    const void* kernels[3] = {reinterpret_cast<const void*>(&k_trials_lds<T, kBlock>),
+                              reinterpret_cast<const void*>(&k_trials_lds<T, kRowThreads>),
+                              reinterpret_cast<const void*>(&k_scale_lds)};
+    const int count = std::is_same_v<T, double> ? 3 : 2;
+    size_t fixed = 1024;
+    bool ok = max_lds > 0;
+    for (int i = 0; i < count && ok; ++i) {
+      hipFuncAttributes fa{};
+      ok = hipFuncGetAttributes(&fa, kernels[i]) == hipSuccess;
+      fixed = std::max(fixed, fa.sharedSizeBytes + 1024);
     }
+    ok = ok && (size_t)max_lds > fixed;
+    for (int i = 0; i < count && ok; ++i)
+      ok = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize, (int)(max_lds - fixed)) == hipSuccess;
+    if (ok) cap = (size_t)max_lds - fixed;
     (void)hipGetLastError();
   }
   return cap;
@@ -3592,24 +3751,22 @@ static size_t lds_capacity_t() {
 
 size_t trials_lds_capacity(int prec) { return prec == kFP32 ? lds_capacity_t<float>() : lds_capacity_t<double>(); }
 
+template <typename T>
+static void launch_trials_wg_t(const KernelCtx& k, hipStream_t s, int prec, int K, int lds, const MatPtrs<T>& A,
+                               const MatPtrs<T>& AT, const IterPtrs<T>& it, const DataPtrs<T>& d) {
+  if (lds > 0 && k.lds_rowwise)
+    k_trials_lds<T, kRowThreads><<<k.nb, kRowThreads, lds, s>>>(k.vcol, k.brow, k.bcol, A, AT, it, d, k.inst, prec, K);
+  else if (lds > 0)
+    k_trials_lds<T, kBlock><<<k.nb, kBlock, lds, s>>>(k.vcol, k.brow, k.bcol, A, AT, it, d, k.inst, prec, K);
+  else
+    k_trials_wg<T><<<k.nb, kBlock, 0, s>>>(k.vcol, k.brow, k.bcol, A, AT, it, d, k.inst, prec, k.rec_primal, k.rec_dual,
+                                           k.rec_lam, K);
+}
+
 void launch_trials_wg(const KernelCtx& k, hipStream_t s, int mask, int K) {
   if (k.nb < 1 || K < 1) return;
-  if (mask & 1) {
-    if (k.lds_trials32 > 0)
-      k_trials_lds<float><<<k.nb, kBlock, k.lds_trials32, s>>>(k.vcol, k.brow, k.bcol, k.A32, k.AT32, k.it32, k.d32,
-                                                              k.inst, kFP32, K, k.lds_rowwise);
-    else
-      k_trials_wg<float><<<k.nb, kBlock, 0, s>>>(k.vcol, k.brow, k.bcol, k.A32, k.AT32, k.it32, k.d32, k.inst, kFP32,
-                                                 k.rec_primal, k.rec_dual, k.rec_lam, K);
-  }
-  if (mask & 2) {
-    if (k.lds_trials64 > 0)
-      k_trials_lds<double><<<k.nb, kBlock, k.lds_trials64, s>>>(k.vcol, k.brow, k.bcol, k.A64, k.AT64, k.it64,
-                                                               k.d64, k.inst, kFP64, K, k.lds_rowwise);
-    else
-      k_trials_wg<double><<<k.nb, kBlock, 0, s>>>(k.vcol, k.brow, k.bcol, k.A64, k.AT64, k.it64, k.d64, k.inst, kFP64,
-                                                  k.rec_primal, k.rec_dual, k.rec_lam, K);
-  }
+  if (mask & 1) launch_trials_wg_t<float>(k, s, kFP32, K, k.lds_trials32, k.A32, k.AT32, k.it32, k.d32);
+  if (mask & 2) launch_trials_wg_t<double>(k, s, kFP64, K, k.lds_trials64, k.A64, k.AT64, k.it64, k.d64);
 }
 
 template <typename T>
@@ -3826,6 +3983,10 @@ void launch_setup(const KernelCtx& k, const SetupCtx& su, hipStream_t s, int mas
       k_scale_bands_values<<<slots, kBandWaves * kWave, lds, s>>>(k.band1, v1, su.bval64, su.bval32, k.band2, v2,
                                                                   su.bvalT64, su.bvalT32, k.D1, k.D2, su.rec_nm);
     }
+  } else if (k.lds_trials64 > 0 && k.lds_rowwise) {
+    k_scale_lds<<<k.nb, kScaleLdsThreads, k.lds_trials64, s>>>(su.A, su.AT, k.brow.inst_blk0, passes, su.ruiz_iters, k.D1,
+                                                               k.D2, su.val64, su.val32, su.valT64, su.valT32, k.inst,
+                                                               su.rec_nm);
   } else {
     const unsigned nblk = (unsigned)(k.brow.nblk + k.bcol.nblk);
     if (passes == 0) k_fill<<<blocks(k.M + k.N), tpb, 0, s>>>(k.D1, k.M, k.D2, k.N, 1.0);
@@ -3860,16 +4021,8 @@ void launch_setup(const KernelCtx& k, const SetupCtx& su, hipStream_t s, int mas
   }
   // FP64-value products of the start point: eval mode computes cgx0 = G x_hat, cgty0 = G^T y_hat
   launch_eval(k, s, mask, 0);
-  if (mask & 1) {
-    if (k.M > 0) k_set_products<float><<<blocks(k.M), tpb, 0, s>>>(k.it32.gx, k.it32.gxa, k.it32.gxh, k.cgx0, k.M);
-    if (k.N > 0)
-      k_set_products<float><<<blocks(k.N), tpb, 0, s>>>(k.it32.gty, k.it32.gtya, k.it32.gtyh, k.cgty0, k.N);
-  }
-  if (mask & 2) {
-    if (k.M > 0) k_set_products<double><<<blocks(k.M), tpb, 0, s>>>(k.it64.gx, k.it64.gxa, k.it64.gxh, k.cgx0, k.M);
-    if (k.N > 0)
-      k_set_products<double><<<blocks(k.N), tpb, 0, s>>>(k.it64.gty, k.it64.gtya, k.it64.gtyh, k.cgty0, k.N);
-  }
+  if (mask & 1) k_set_products<float><<<blocks(k.M + k.N), tpb, 0, s>>>(k.it32, k.cgty0, k.N, k.cgx0, k.M);
+  if (mask & 2) k_set_products<double><<<blocks(k.M + k.N), tpb, 0, s>>>(k.it64, k.cgty0, k.N, k.cgx0, k.M);
 }
 
 void launch_spmv_plain(const RowBlocks& rb, int prec, const int32_t* ptr, const int32_t* idx, const void* val,

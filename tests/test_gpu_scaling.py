@@ -28,6 +28,11 @@ def _instance(name):
         return lpgen.planted_lp(rng, 5000, 300, row_lengths=np.ones(5000, np.int64))
     if name == "windows":
         return lpgen.planted_lp(rng, 3000, 2 * 2**18 + 5, per_col=1)
+    if name == "lds":  # one workgroup's LDS; rows of up to 64 entries, empty ones, more rows and columns than threads
+        lengths = np.array([64, 0, 1, 4, 5, 0] + [2] * 500)
+        return lpgen.planted_lp(rng, lengths.size, 600, row_lengths=lengths)
+    if name == "lds_tiny":
+        return lpgen.planted_lp(rng, 3, 5, per_col=1)
     return lpgen.planted_lp(rng, 700, 1500, per_col=4, row_scale=10.0 ** rng.uniform(-3, 3, 700))
 
 
@@ -49,8 +54,8 @@ def _scaling(inst, ruiz, l2):
     return D1, D2
 
 
-@pytest.mark.parametrize("layout", ["rows", "bands"])
-@pytest.mark.parametrize("name,ruiz,l2", [("long_rows", 10, 1), ("short_rows", 3, 0), ("windows", 2, 1), ("plain", 10, 1),
+@pytest.mark.parametrize("layout", ["rows", "bands", "auto"])
+@pytest.mark.parametrize("name,ruiz,l2", [("lds", 10, 1), ("lds", 3, 0), ("lds", 0, 0), ("lds_tiny", 10, 1), ("long_rows", 10, 1), ("short_rows", 3, 0), ("windows", 2, 1), ("plain", 10, 1),
                                           ("plain", 0, 1), ("plain", 0, 0)])
 def test_scaling_matches_numpy(name, ruiz, l2, layout):
     inst = _instance(name)
