@@ -105,8 +105,8 @@ struct RowBlocks {
 // adds into: slots below the band's row count are the rows themselves, higher
 // slots are extra accumulators of rows that repeat within one group of kWave
 // consecutive entries (no two entries of such a group share a slot), and slot
-// BandTiles::slots - 1 is the sink of the padding.  A workgroup runs kBandWaves waves, each
-// on one band-tile of the same window index.  In a batch every instance has its
+// BandTiles::slots - 1 is the sink of the padding.  The extra slots of a row are
+// consecutive.  A workgroup is one wave with one band-tile.  In a batch every instance has its
 // own bands and windows; an instance with fewer windows than the batch's
 // largest count has empty tiles (zero partial sums) for the missing ones.
 constexpr int kBandRows = 8192;
@@ -118,26 +118,28 @@ constexpr int kBandColBits = 32 - kBandSlotBits;
 // n = 5e5, power-law rows, nnz = 1.35e7, 540 tiles, G x and G^T y: FP32 110 us in
 // pairs, 99 alone, FP64 153 and 130; m = 2e5, n = 5e5: 51 / 66 either way; a trial
 // of 48 LPs in FP64: 108 and 99 us.)
-constexpr int kBandWaves = 1;
 constexpr int kBandUnroll = 16;
+// All that a workgroup needs to know of its band-tile, in one read of its launch slot.
+struct alignas(16) BandTile {
+  int32_t tile;   // number of the band-tile, -1: an idle slot (all else 0)
+  int32_t start;  // first entry
+  int32_t nit;    // iterations of kBandUnroll * kWave entries
+  int32_t row0;   // first row
+  int32_t nrows;  // rows
+  int32_t used;   // slots in use (rows + extra slots; the sink excluded)
+  int32_t col0;   // window start
+  int32_t panel;  // window index (partial-sum array)
+  int32_t inst;   // instance (bands never cross instances)
+  int32_t fold0;  // first row's entry of BandTiles::fold
+  int32_t pad[2];
+};
 struct BandTiles {
-  const int32_t* group;      // per workgroup slot group, per wave: band-tile or -1
-  const int32_t* slot;       // launch slot -> group (-1: idle); slot s runs on XCD s % 8
-  const int32_t* start;      // per band-tile: first entry (ntile + 1 entries)
-  const int32_t* row0;       // per band-tile: first row
-  const int32_t* nrows;      // per band-tile: rows
-  const int32_t* used;       // per band-tile: slots in use (rows + extra slots; the sink excluded)
-  const int32_t* tinst;      // per band-tile: instance (bands never cross instances)
-  const int32_t* col0;       // per band-tile: window start
-  const int32_t* panel;      // per band-tile: window index (partial-sum array)
-  const int32_t* run_start;  // per band-tile: first run (ntile + 1 entries)
-  const int32_t* run_row;    // per run: row (band-local) owning extra slots
-  const int32_t* run_ext;    // per run: first extra slot in ext (nrun + 1 entries)
-  const int32_t* ext;        // extra slots, grouped by run
+  const BandTile* slot;      // launch slots; slot s runs on XCD s % 8
+  const uint32_t* fold;      // per tile and row: first extra slot | extra slots << 16
   const uint32_t* pk;        // packed entries
   int32_t nslot;             // launch slots (workgroups)
   int32_t P;                 // windows
-  int32_t slots;             // LDS accumulators per wave: the most a tile uses, and the sink
+  int32_t slots;             // LDS accumulators: the most a tile uses, and the sink
 };
 
 // Schedule of an elementwise pass: contiguous element ranges per workgroup.

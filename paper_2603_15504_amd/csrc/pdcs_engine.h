@@ -113,7 +113,7 @@ struct BandSet {
   int ntile = 0, nslot = 0, slots = 1;
   int64_t R = 0, nent = 0;
   DBuf tile0;  // first tile per instance
-  DBuf group, slot, start, row0, nrows, used, tinst, col0, panel, run_start, run_row, run_ext, ext, pk, src;
+  DBuf slot, fold, pk, src;
   DBuf val32, val64, part32, part64, part64b;
   DBuf orig32, orig64;  // unscaled values (plain products), filled by Engine::prepare_plain
   // instance b: rows [r0s[b], r0s[b+1]) gathering from [g0s[b], g0s[b+1])

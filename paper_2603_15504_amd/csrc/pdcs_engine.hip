@@ -301,28 +301,19 @@ Ranges RangeSet::view() const {
 // ---------------------------------------------------------------------------
 namespace {
 struct BandBuild {
-  std::vector<int32_t> start, row0, nrows, used, col0, panel, tinst, run_start, run_row, run_ext, ext, src;
-  std::vector<uint32_t> pk;
+  std::vector<BandTile> tile;
+  std::vector<int32_t> src;
+  std::vector<uint32_t> pk, fold;
   std::vector<int64_t> work;  // entries per band-tile
   std::vector<size_t> sizes() const {
-    return {start.size(), row0.size(), nrows.size(), col0.size(), panel.size(), run_start.size(), run_row.size(),
-            run_ext.size(), ext.size(), src.size(), pk.size(), work.size(), used.size(), tinst.size()};
+    return {tile.size(), src.size(), pk.size(), fold.size(), work.size()};
   }
   void truncate(const std::vector<size_t>& z) {
-    start.resize(z[0]);
-    row0.resize(z[1]);
-    nrows.resize(z[2]);
-    col0.resize(z[3]);
-    panel.resize(z[4]);
-    run_start.resize(z[5]);
-    run_row.resize(z[6]);
-    run_ext.resize(z[7]);
-    ext.resize(z[8]);
-    src.resize(z[9]);
-    pk.resize(z[10]);
-    work.resize(z[11]);
-    used.resize(z[12]);
-    tinst.resize(z[13]);
+    tile.resize(z[0]);
+    src.resize(z[1]);
+    pk.resize(z[2]);
+    fold.resize(z[3]);
+    work.resize(z[4]);
   }
 };
 
@@ -350,12 +341,6 @@ bool build_band_tile(int64_t r0, int64_t r1, int p, int64_t c0, int64_t c1, int6
   std::fill(next.begin(), next.end(), -1);
   int nxt = nr;
   const size_t base = out.pk.size();
-  out.start.push_back((int32_t)base);
-  out.row0.push_back((int32_t)r0);
-  out.nrows.push_back(nr);
-  out.col0.push_back((int32_t)c0);
-  out.panel.push_back(p);
-  out.tinst.push_back(inst);
   for (size_t k = 0; k < E.size(); ++k) {
     if (k % kWave == 0) ++gid;
     const uint32_t col = (uint32_t)(((int64_t)(E[k].first >> 20) + shift) % W);
@@ -371,20 +356,40 @@ bool build_band_tile(int64_t r0, int64_t r1, int p, int64_t c0, int64_t c1, int6
     out.pk.push_back((col << kBandSlotBits) | (uint32_t)s);
     out.src.push_back(E[k].second);
   }
+  // the extra slots numbered anew, each row's in the order they are added, one after the other
+  std::vector<int32_t> renum((size_t)(nxt - nr));
+  const size_t fold0 = out.fold.size();
+  int32_t e0 = nr;
+  for (int r = 0; r < nr; ++r) {
+    const int32_t first = e0;
+    for (int e = next[r]; e >= 0; e = next[e]) renum[(size_t)(e - nr)] = e0++;
+    out.fold.push_back((uint32_t)first | (uint32_t)(e0 - first) << 16);
+  }
+  constexpr uint32_t kSlotMask = (1u << kBandSlotBits) - 1u;
+  for (size_t k = base; k < out.pk.size(); ++k) {
+    const uint32_t s = out.pk[k] & kSlotMask;
+    if (s >= (uint32_t)nr) out.pk[k] = (out.pk[k] & ~kSlotMask) | (uint32_t)renum[s - (uint32_t)nr];
+  }
   const size_t q = (size_t)kBandUnroll * kWave;
   while ((out.pk.size() - base) % q) {
     out.pk.push_back(0u);  // padding: gets the layout's sink slot once that is known
     out.src.push_back(-1);
   }
-  for (int r = 0; r < nr; ++r) {
-    if (next[r] < 0) continue;
-    out.run_row.push_back(r);
-    for (int e = next[r]; e >= 0; e = next[e]) out.ext.push_back(e);
-    out.run_ext.push_back((int32_t)out.ext.size());
-  }
-  out.run_start.push_back((int32_t)out.run_row.size());
+  if (out.pk.size() >= (size_t)INT32_MAX || out.fold.size() >= (size_t)INT32_MAX)
+    throw Error(PDCS_ERR_SIZE, "band tiles exceed 2^31 entries");
+  BandTile t{};
+  t.tile = (int32_t)out.tile.size();
+  t.start = (int32_t)base;
+  t.nit = (int32_t)((out.pk.size() - base) / q);
+  t.row0 = (int32_t)r0;
+  t.nrows = nr;
+  t.used = nxt;
+  t.col0 = (int32_t)c0;
+  t.panel = p;
+  t.inst = inst;
+  t.fold0 = (int32_t)fold0;
+  out.tile.push_back(t);
   out.work.push_back((int64_t)E.size());
-  out.used.push_back(nxt);
   return true;
 }
 }  // namespace
@@ -417,8 +422,6 @@ void BandSet::build(const std::vector<int64_t>& r0s, const std::vector<int64_t>&
   while (rb > 256 && tiles_for(rb) < bs.min_tiles) rb /= 2;
   band_rows = (int)rb;
   BandBuild bb;
-  bb.run_start.push_back(0);
-  bb.run_ext.push_back(0);
   std::vector<int32_t> stamp(kBandSlots, -1), next(kBandSlots, -1);
   int32_t gid = 0;
   std::vector<std::pair<int64_t, int64_t>> bands;  // row ranges, split on slot overflow
@@ -482,21 +485,16 @@ void BandSet::build(const std::vector<int64_t>& r0s, const std::vector<int64_t>&
       todo.push_back({br.first, mid});
     }
   }
-  bb.start.push_back((int32_t)bb.pk.size());
-  if (bb.pk.size() >= (size_t)INT32_MAX) throw Error(PDCS_ERR_SIZE, "band tiles exceed 2^31 entries");
   ntile = (int)bands.size() * P;
   nent = (int64_t)bb.pk.size();
   slots = 1;
-  for (int32_t q : bb.used) slots = std::max(slots, q + 1);
+  for (const BandTile& t : bb.tile) slots = std::max(slots, t.used + 1);
   const uint32_t sink = (uint32_t)(slots - 1);
   for (int64_t e = 0; e < nent; ++e)
     if (bb.src[e] < 0) bb.pk[e] = sink;
   HIP_OK(band_raise_lds_limit());
-  // workgroups: kBandWaves consecutive bands of one window; windows routed to
-  // XCDs (slot s runs on XCD s % 8), window p to the XCDs x with x % P == p
+  // windows routed to XCDs (slot s runs on XCD s % 8), window p to the XCDs x with x % P == p
   const int nb = (int)bands.size();
-  const int ng = (nb + kBandWaves - 1) / kBandWaves;
-  std::vector<int32_t> grp;
   std::vector<std::vector<int32_t>> per_xcd(8);
   std::vector<int64_t> load(8, 0);
   // In a batch, every tile of an instance goes to one XCD (largest instances
@@ -508,7 +506,7 @@ void BandSet::build(const std::vector<int64_t>& r0s, const std::vector<int64_t>&
     std::vector<int64_t> iw(NB, 0);
     int64_t total = 0;
     for (int t = 0; t < ntile; ++t) {
-      iw[bb.tinst[t]] += bb.work[t] + 1;
+      iw[bb.tile[t].inst] += bb.work[t] + 1;
       total += bb.work[t] + 1;
     }
     std::vector<int> order(NB);
@@ -524,84 +522,63 @@ void BandSet::build(const std::vector<int64_t>& r0s, const std::vector<int64_t>&
     }
   }
   for (int p = 0; p < P; ++p)
-    for (int g = 0; g < ng; ++g) {
-      const int gi = (int)(grp.size() / kBandWaves);
-      int64_t work = 0;
-      int first = -1;
-      for (int w = 0; w < kBandWaves; ++w) {
-        const int b = g * kBandWaves + w;
-        const int t = b < nb ? b * P + p : -1;
-        grp.push_back(t);
-        if (t >= 0) {
-          work += bb.work[t];
-          if (first < 0) first = t;
-        }
-      }
-      int best = first >= 0 && NB > 1 ? inst_xcd[bb.tinst[first]] : -1;
+    for (int b = 0; b < nb; ++b) {
+      const int t = b * P + p;
+      int best = NB > 1 ? inst_xcd[bb.tile[t].inst] : -1;
       if (best < 0) {
         for (int x = 0; x < 8; ++x) {
           const bool serves = NB > 1 || (P >= 8 ? (p % 8 == x) : (x % P == p));
           if (serves && (best < 0 || load[x] < load[best])) best = x;
         }
-        load[best] += work + 1;
+        load[best] += bb.work[t] + 1;
       }
-      per_xcd[best].push_back(gi);
+      per_xcd[best].push_back(t);
     }
   size_t depth = 0;
   for (auto& l : per_xcd) depth = std::max(depth, l.size());
-  std::vector<int32_t> sl(depth * 8, -1);
+  BandTile idle{};
+  idle.tile = -1;
+  std::vector<BandTile> sl(depth * 8, idle);
   for (int x = 0; x < 8; ++x)
-    for (size_t k = 0; k < per_xcd[x].size(); ++k) sl[k * 8 + x] = per_xcd[x][k];
+    for (size_t k = 0; k < per_xcd[x].size(); ++k) sl[k * 8 + x] = bb.tile[per_xcd[x][k]];
   nslot = (int)sl.size();
   // every index the kernel reads, checked before anything reaches the device
   auto fail = [](const char* what) { throw Error(PDCS_ERR_STATE, std::string("band layout check: ") + what); };
   if (slots > kBandSlots) fail("slots");
-  if ((int)bb.start.size() != ntile + 1 || (int)bb.run_start.size() != ntile + 1 || (int)bb.used.size() != ntile)
-    fail("tile tables");
-  if (bb.run_ext.size() != bb.run_row.size() + 1 || bb.src.size() != bb.pk.size()) fail("run tables");
-  for (int32_t g : sl)
-    if (g >= (int32_t)(grp.size() / kBandWaves)) fail("slot table");
-  for (int32_t t : grp)
-    if (t >= ntile) fail("group table");
+  if ((int)bb.tile.size() != ntile || bb.src.size() != bb.pk.size()) fail("tile tables");
+  std::vector<char> seen((size_t)ntile, 0);
+  for (const BandTile& s : sl)
+    if (s.tile >= 0 && (s.tile >= ntile || seen[s.tile]++)) fail("slot table");
   for (int t = 0; t < ntile; ++t) {
-    const int64_t e0 = bb.start[t], e1 = bb.start[t + 1];
-    if (e1 < e0 || (e1 - e0) % ((int64_t)kBandUnroll * kWave)) fail("tile padding");
-    if (bb.nrows[t] < 0 || bb.nrows[t] > kBandRows || (int64_t)bb.row0[t] + bb.nrows[t] > R) fail("tile rows");
-    if (bb.panel[t] < 0 || bb.panel[t] >= P || bb.col0[t] < 0) fail("tile window");
-    if (bb.used[t] < bb.nrows[t] || bb.used[t] > slots - 1) fail("tile slots");
-    const int ti = bb.tinst[t];
-    if (ti < 0 || ti >= NB || bb.row0[t] < r0s[ti] || (int64_t)bb.row0[t] + bb.nrows[t] > r0s[ti + 1]) fail("tile instance");
-    if (bb.start[t + 1] > bb.start[t] && (bb.col0[t] < g0s[ti] || bb.col0[t] >= g0s[ti + 1])) fail("tile window instance");
-    if (e1 > e0 && bb.col0[t] >= G) fail("tile window start");
+    const BandTile& d = bb.tile[t];
+    const int64_t e0 = d.start, e1 = e0 + (int64_t)d.nit * kBandUnroll * kWave;
+    if (d.tile != t || !seen[t]) fail("tile number");
+    if (d.nit < 0 || e0 < 0 || e1 != (t + 1 < ntile ? bb.tile[t + 1].start : nent)) fail("tile padding");
+    if (d.nrows < 0 || d.nrows > kBandRows || (int64_t)d.row0 + d.nrows > R) fail("tile rows");
+    if (d.panel < 0 || d.panel >= P || d.col0 < 0) fail("tile window");
+    if (d.used < d.nrows || d.used > slots - 1) fail("tile slots");
+    const int ti = d.inst;
+    if (ti < 0 || ti >= NB || d.row0 < r0s[ti] || (int64_t)d.row0 + d.nrows > r0s[ti + 1]) fail("tile instance");
+    if (e1 > e0 && (d.col0 < g0s[ti] || d.col0 >= g0s[ti + 1])) fail("tile window instance");
+    if (e1 > e0 && d.col0 >= G) fail("tile window start");
     for (int64_t e = e0; e < e1; ++e) {
       const uint32_t slot_e = bb.pk[e] & ((1u << kBandSlotBits) - 1u);
-      const int64_t col = (int64_t)bb.col0[t] + (bb.pk[e] >> kBandSlotBits);
-      if ((slot_e >= (uint32_t)bb.used[t] && slot_e != sink) || col >= g0s[ti + 1]) fail("entry");
+      const int64_t col = (int64_t)d.col0 + (bb.pk[e] >> kBandSlotBits);
+      if ((slot_e >= (uint32_t)d.used && slot_e != sink) || col >= g0s[ti + 1]) fail("entry");
       if (bb.src[e] >= 0 && (bb.src[e] >= ptr[R] || idx[bb.src[e]] != col)) fail("entry source");
     }
-    for (int32_t r = bb.run_start[t]; r < bb.run_start[t + 1]; ++r) {
-      if (bb.run_row[r] < 0 || bb.run_row[r] >= bb.nrows[t]) fail("run row");
-      for (int32_t q = bb.run_ext[r]; q < bb.run_ext[r + 1]; ++q)
-        if (bb.ext[q] < bb.nrows[t] || bb.ext[q] >= bb.used[t]) fail("extra slot");
+    if (d.fold0 < 0 || (size_t)d.fold0 + d.nrows > bb.fold.size()) fail("fold table");
+    for (int32_t r = 0; r < d.nrows; ++r) {
+      const uint32_t f = bb.fold[(size_t)d.fold0 + r], q = f & 0xFFFFu;
+      if (q < (uint32_t)d.nrows || q + (f >> 16) > (uint32_t)d.used) fail("extra slot");
     }
   }
   std::vector<int32_t> first(NB + 1, ntile);
-  for (int t = ntile - 1; t >= 0; --t) first[bb.tinst[t]] = t;
+  for (int t = ntile - 1; t >= 0; --t) first[bb.tile[t].inst] = t;
   for (int b = NB - 1; b >= 0; --b) first[b] = std::min(first[b], first[b + 1]);
   upload(tile0, first);
-  upload(group, grp);
   upload(slot, sl);
-  upload(start, bb.start);
-  upload(row0, bb.row0);
-  upload(nrows, bb.nrows);
-  upload(used, bb.used);
-  upload(tinst, bb.tinst);
-  upload(col0, bb.col0);
-  upload(panel, bb.panel);
-  upload(run_start, bb.run_start);
-  upload(run_row, bb.run_row);
-  upload(run_ext, bb.run_ext);
-  upload(ext, bb.ext);
+  upload(fold, bb.fold);
   upload(pk, bb.pk);
   upload(src, bb.src);
   val32.alloc((size_t)nent * 4);
@@ -617,26 +594,14 @@ void BandSet::reset() {
   slots = 1;
   R = nent = 0;
   band_rows = 0;
-  for (DBuf* d : {&tile0, &group, &slot, &start, &row0, &nrows, &used, &tinst, &col0, &panel, &run_start, &run_row, &run_ext,
-                  &ext, &pk, &src, &val32, &val64, &part32, &part64, &part64b, &orig32, &orig64})
+  for (DBuf* d : {&tile0, &slot, &fold, &pk, &src, &val32, &val64, &part32, &part64, &part64b, &orig32, &orig64})
     d->release();
 }
 
 BandTiles BandSet::view() const {
   BandTiles b{};
-  b.group = group.as<int32_t>();
-  b.slot = slot.as<int32_t>();
-  b.start = start.as<int32_t>();
-  b.row0 = row0.as<int32_t>();
-  b.nrows = nrows.as<int32_t>();
-  b.used = used.as<int32_t>();
-  b.tinst = tinst.as<int32_t>();
-  b.col0 = col0.as<int32_t>();
-  b.panel = panel.as<int32_t>();
-  b.run_start = run_start.as<int32_t>();
-  b.run_row = run_row.as<int32_t>();
-  b.run_ext = run_ext.as<int32_t>();
-  b.ext = ext.as<int32_t>();
+  b.slot = slot.as<BandTile>();
+  b.fold = fold.as<uint32_t>();
   b.pk = pk.as<uint32_t>();
   b.nslot = nslot;
   b.P = P;

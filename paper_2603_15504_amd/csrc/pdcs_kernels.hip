@@ -1103,20 +1103,36 @@ struct SumSquares {
 
 // One wave's band-tile t: part[panel * R + r] = sum (or what OP joins) over the
 // tile's entries of row r of val * x[col], values TV, gathered vector TX,
-// accumulation and output TA.
-template <typename TV, typename TX, typename TA, class OP = SumProduct>
-__device__ __forceinline__ void band_tile_product(const BandTiles& bt, int t, TA* a, const TV* __restrict__ val,
-                                                  const TX* __restrict__ x, TA* __restrict__ part, int64_t R) {
+// accumulation and output TA.  skip() tells, once the first entries are under
+// way, whether the tile is left out.
+//
+// What a tile pays besides its entries: the descriptor and the instance's state,
+// the clearing of the slots, and at the end the rows' sums with their extra slots.
+// The entries do not wait for the first two.  The end reads one word per row,
+// requested before the sweep, and adds the extra slots (consecutive in LDS) of
+// eight rows a lane side by side.  (When the extra slots were listed in memory
+// and each lane followed its rows' lists, a row of 5000 entries kept its tile 33 us
+// behind its last entry; the products of m = 6e4, n = 1.2e5, nnz = 9.6e5 took 13.1
+// and 11.3 us in FP64 and take 11.5 and 10.6, G^T y at m = 2.5e5, n = 5e5,
+// nnz = 1.35e7 58 and 53, at m = 2e5, n = 5e5, nnz = 5e6 G x 35.2 and 33.4.)
+//
+// Deeper requests are no help where it counts: with 40 to 47 loads in flight per wave
+// the first of these took 10.5 us, but the last 36.1 and G x of the second 78 for 72,
+// and 23 and 48 with all lanes of a gather at one address: the lines that the gathers
+// touch bound them.
+template <typename TV, typename TX, typename TA, class OP = SumProduct, class Skip>
+__device__ __forceinline__ void band_tile_product(const BandTiles& bt, const BandTile& t, TA* a,
+                                                  const TV* __restrict__ val, const TX* __restrict__ x,
+                                                  TA* __restrict__ part, int64_t R, Skip skip) {
   constexpr int U = kBandUnroll;
+  constexpr int F = 8;  // rows per lane and step of the end
   const int lane = threadIdx.x & (kWave - 1);
-  // the sink slot of the padding is never read and stays uninitialized
-  const int used = bt.used[t];
-  for (int i = lane; i < used; i += kWave) a[i] = TA(0);
-  const TX* xs = x + bt.col0[t];
-  const int e0 = bt.start[t];
-  const int nit = (bt.start[t + 1] - e0) / (U * kWave);
-  const uint32_t* pp = bt.pk + e0 + lane;
-  const TV* vp = val + e0 + lane;
+  const TX* xs = x + t.col0;
+  const int nit = t.nit;
+  const uint32_t* pp = bt.pk + t.start + lane;
+  const TV* vp = val + t.start + lane;
+  const uint32_t* fold = bt.fold + t.fold0;
+  const int nr = t.nrows;
   constexpr uint32_t kSlotMask = (1u << kBandSlotBits) - 1u;
   uint32_t pA[U], pB[U], pC[U];
   TV vA[U], vB[U], vC[U];
@@ -1141,6 +1157,12 @@ __device__ __forceinline__ void band_tile_product(const BandTiles& bt, int t, TA
       vB[u] = __builtin_nontemporal_load(vp + (U + u) * kWave);
     }
   }
+  uint32_t f[F];
+#pragma unroll
+  for (int k = 0; k < F; ++k) f[k] = k * kWave + lane < nr ? fold[k * kWave + lane] : 0u;
+  if (skip()) return;
+  // the sink slot of the padding is never read and stays uninitialized
+  for (int i = lane; i < t.used; i += kWave) a[i] = TA(0);
   if (nit > 0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) xA[u] = xs[pA[u] >> kBandSlotBits];
@@ -1172,57 +1194,71 @@ __device__ __forceinline__ void band_tile_product(const BandTiles& bt, int t, TA
       vB[u] = vC[u];
     }
   }
-  // fold the extra slots into their rows (one lane per run, runs own distinct rows)
-  for (int r = bt.run_start[t] + lane; r < bt.run_start[t + 1]; r += kWave) {
-    const int row = bt.run_row[r];
-    TA s = a[row];
-    for (int q = bt.run_ext[r]; q < bt.run_ext[r + 1]; ++q) s = OP::join(s, a[bt.ext[q]]);
-    a[row] = s;
+  // each row's slot, then its extra slots in order
+  TA* out = part + (size_t)t.panel * R + t.row0;
+  for (int r = lane; r - lane < nr; r += F * kWave) {
+    uint32_t g[F];
+#pragma unroll
+    for (int k = 0; k < F; ++k) g[k] = r + (F + k) * kWave < nr ? fold[r + (F + k) * kWave] : 0u;
+    TA s[F];
+    uint32_t most = 0;
+#pragma unroll
+    for (int k = 0; k < F; ++k) {
+      s[k] = r + k * kWave < nr ? a[r + k * kWave] : TA(0);
+      most = max(most, f[k] >> 16);
+    }
+    constexpr uint32_t E = 4;
+    for (uint32_t q = 0; __any(q < most); q += E) {
+      TA e[F][E];
+#pragma unroll
+      for (int k = 0; k < F; ++k)
+#pragma unroll
+        for (uint32_t j = 0; j < E; ++j) e[k][j] = q + j < f[k] >> 16 ? a[(f[k] & 0xFFFFu) + q + j] : TA(0);
+#pragma unroll
+      for (int k = 0; k < F; ++k)
+#pragma unroll
+        for (uint32_t j = 0; j < E; ++j)
+          if (q + j < f[k] >> 16) s[k] = OP::join(s[k], e[k][j]);
+    }
+#pragma unroll
+    for (int k = 0; k < F; ++k) {
+      if (r + k * kWave < nr) out[r + k * kWave] = s[k];
+      f[k] = g[k];
+    }
   }
-  const int nr = bt.nrows[t];
-  TA* out = part + (size_t)bt.panel[t] * R + bt.row0[t];
-  for (int i = lane; i < nr; i += kWave) out[i] = a[i];
 }
 
 // Trial products (K1: G x_hat, K2: G^T y_hat) in the iterate precision T.
 template <typename T>
-__global__ __launch_bounds__(kBandWaves * kWave) void k_band_spmv(BandTiles bt, const T* __restrict__ val,
+__global__ __launch_bounds__(kWave) void k_band_spmv(BandTiles bt, const T* __restrict__ val,
                                                                   const T* __restrict__ x, T* __restrict__ part,
                                                                   int64_t R, const Inst* __restrict__ inst,
                                                                   int prec, int need_acc) {
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
-  T* acc = reinterpret_cast<T*>(dyn);
-  const int g = bt.slot[blockIdx.x];
-  if (g < 0) return;
-  const int w = threadIdx.x / kWave;
-  const int t = bt.group[g * kBandWaves + w];
-  if (t < 0) return;
-  if (inst) {  // solver passes: only instances iterating in this precision (and accepted, for G^T y)
-    const Inst& I = inst[bt.tinst[t]];
-    if (I.status != kActive || I.precision != prec || (need_acc && I.last_acc == 0)) return;
-  }
-  band_tile_product<T, T, T>(bt, t, acc + w * bt.slots, val, x, part, R);
+  const BandTile t = bt.slot[blockIdx.x];  // (an idle slot has no entries and no rows)
+  band_tile_product<T, T, T>(bt, t, reinterpret_cast<T*>(dyn), val, x, part, R, [&] {
+    if (!inst) return false;
+    // solver passes: only instances iterating in this precision (and accepted, for G^T y)
+    const Inst& I = inst[t.inst];
+    return I.status != kActive || I.precision != prec || (need_acc && I.last_acc == 0);
+  });
 }
 
 // Check / evaluation products with FP64 values of vectors in the iterate
 // precision TX (which = 1: the average candidate, skipped where unused).
 template <typename TX>
-__global__ __launch_bounds__(kBandWaves * kWave) void k_band_cand(BandTiles bt, const double* __restrict__ val,
+__global__ __launch_bounds__(kWave) void k_band_cand(BandTiles bt, const double* __restrict__ val,
                                                                   const TX* __restrict__ x,
                                                                   double* __restrict__ part, int64_t R,
                                                                   const Inst* __restrict__ inst, int prec, int mode,
                                                                   int which) {
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
-  double* acc = reinterpret_cast<double*>(dyn);
-  const int g = bt.slot[blockIdx.x];
-  if (g < 0) return;
-  const int w = threadIdx.x / kWave;
-  const int t = bt.group[g * kBandWaves + w];
-  if (t < 0) return;
-  const Inst& I = inst[bt.tinst[t]];
-  if (!mode_selects(I, mode) || !prec_selects(I, mode, prec)) return;
-  if (which == 1 && mode == kModeCheck && I.use_avg == 0) return;
-  band_tile_product<double, TX, double>(bt, t, acc + w * bt.slots, val, x, part, R);
+  const BandTile t = bt.slot[blockIdx.x];  // (an idle slot has no entries and no rows)
+  band_tile_product<double, TX, double>(bt, t, reinterpret_cast<double*>(dyn), val, x, part, R, [&] {
+    const Inst& I = inst[t.inst];
+    return !mode_selects(I, mode) || !prec_selects(I, mode, prec) ||
+           (which == 1 && mode == kModeCheck && I.use_avg == 0);
+  });
 }
 
 // Window sums of the check / evaluation products (G^T y, then G x), per instance;
@@ -3302,7 +3338,7 @@ __global__ __launch_bounds__(kBlock) void k_scale_values(ScaleSide a, ScaleSide 
 // n = 5e5, nnz = 1.35e7: 157 us per side of a pass from the CSR, 138 us here for
 // both sides; m = 2e5, n = 5e5, nnz = 5e6: 49 per side, 63 here for both.)
 template <class OP>
-__global__ __launch_bounds__(kBandWaves * kWave) void k_scale_bands(BandTiles b1, const double* __restrict__ v1,
+__global__ __launch_bounds__(kWave) void k_scale_bands(BandTiles b1, const double* __restrict__ v1,
                                                                     const double* __restrict__ D2,
                                                                     double* __restrict__ part1, int64_t M, BandTiles b2,
                                                                     const double* __restrict__ v2,
@@ -3311,14 +3347,10 @@ __global__ __launch_bounds__(kBandWaves * kWave) void k_scale_bands(BandTiles b1
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
   const bool second = (int)blockIdx.x >= b1.nslot;
   const BandTiles& bt = second ? b2 : b1;
-  const int g = bt.slot[(int)blockIdx.x - (second ? b1.nslot : 0)];
-  if (g < 0) return;
-  const int w = threadIdx.x / kWave;
-  const int t = bt.group[g * kBandWaves + w];
-  if (t < 0) return;
-  double* acc = reinterpret_cast<double*>(dyn) + w * bt.slots;
-  if (second) band_tile_product<double, double, double, OP>(bt, t, acc, v2, D1, part2, N);
-  else band_tile_product<double, double, double, OP>(bt, t, acc, v1, D2, part1, M);
+  const BandTile t = bt.slot[(int)blockIdx.x - (second ? b1.nslot : 0)];
+  double* acc = reinterpret_cast<double*>(dyn);
+  band_tile_product<double, double, double, OP>(bt, t, acc, second ? v2 : v1, second ? D1 : D2, second ? part2 : part1,
+                                                second ? N : M, [] { return false; });
 }
 
 // D1 (elements [0, M)) and D2 (the next N) from the windows' statistics.
@@ -3340,20 +3372,23 @@ __global__ void k_scale_bands_update(double* __restrict__ D1, const double* __re
 
 // Scaled band-entry values from the unscaled ones (in place where src == v64), and
 // per band-tile the largest magnitude.  A tile's own factors sit in LDS by slot.
-__device__ __forceinline__ void band_scale_tile(const BandTiles& bt, int t, bool cols, double* own,
+__device__ __forceinline__ void band_scale_tile(const BandTiles& bt, const BandTile& t, bool cols, double* own,
                                                 const double* __restrict__ D_own, const double* __restrict__ D_other,
                                                 const double* src, double* v64, float* __restrict__ v32,
                                                 double* __restrict__ rec) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int nr = bt.nrows[t], r0 = bt.row0[t];
-  for (int i = lane; i < nr; i += kWave) own[i] = D_own[r0 + i];
+  for (int i = lane; i < t.nrows; i += kWave) {
+    const double o = D_own[t.row0 + i];
+    const uint32_t f = bt.fold[t.fold0 + i];
+    own[i] = o;
+    for (uint32_t q = f & 0xFFFFu; q < (f & 0xFFFFu) + (f >> 16); ++q) own[q] = o;
+  }
   if (lane == 0) own[bt.slots - 1] = 0.0;  // the padding's sink (its values are 0)
-  for (int r = bt.run_start[t] + lane; r < bt.run_start[t + 1]; r += kWave)
-    for (int q = bt.run_ext[r]; q < bt.run_ext[r + 1]; ++q) own[bt.ext[q]] = D_own[r0 + bt.run_row[r]];
-  const double* other = D_other + bt.col0[t];
+  const double* other = D_other + t.col0;
   double big = 0.0;
   constexpr int U = 8;  // the padding makes whole groups of kBandUnroll
-  for (int e0 = bt.start[t] + lane; e0 < bt.start[t + 1]; e0 += U * kWave) {
+  const int end = t.start + t.nit * kBandUnroll * kWave;
+  for (int e0 = t.start + lane; e0 < end; e0 += U * kWave) {
     uint32_t pk[U];
     double v[U], g[U];
 #pragma unroll
@@ -3373,10 +3408,10 @@ __device__ __forceinline__ void band_scale_tile(const BandTiles& bt, int t, bool
     }
   }
   big = wave_max(big);
-  if (rec && lane == 0) rec[t] = big;
+  if (rec && lane == 0 && t.tile >= 0) rec[t.tile] = big;
 }
 
-__global__ __launch_bounds__(kBandWaves * kWave) void k_scale_bands_values(BandTiles b1, const double* s1, double* v1,
+__global__ __launch_bounds__(kWave) void k_scale_bands_values(BandTiles b1, const double* s1, double* v1,
                                                                            float* __restrict__ f1, BandTiles b2,
                                                                            const double* s2, double* v2,
                                                                            float* __restrict__ f2,
@@ -3386,12 +3421,8 @@ __global__ __launch_bounds__(kBandWaves * kWave) void k_scale_bands_values(BandT
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
   const bool second = (int)blockIdx.x >= b1.nslot;
   const BandTiles& bt = second ? b2 : b1;
-  const int g = bt.slot[(int)blockIdx.x - (second ? b1.nslot : 0)];
-  if (g < 0) return;
-  const int w = threadIdx.x / kWave;
-  const int t = bt.group[g * kBandWaves + w];
-  if (t < 0) return;
-  double* own = reinterpret_cast<double*>(dyn) + w * bt.slots;
+  const BandTile t = bt.slot[(int)blockIdx.x - (second ? b1.nslot : 0)];
+  double* own = reinterpret_cast<double*>(dyn);
   if (second) band_scale_tile(bt, t, true, own, D2, D1, s2, v2, f2, nullptr);
   else band_scale_tile(bt, t, false, own, D1, D2, s1, v1, f1, rec);
 }
@@ -3586,7 +3617,7 @@ template <typename T>
 static void launch_band_spmv(const BandTiles& bt, const T* val, const T* x, T* part, int64_t R, const Inst* inst, int prec,
                              int need_acc, hipStream_t s) {
   if (bt.nslot > 0)
-    k_band_spmv<T><<<grid1(bt.nslot), kBandWaves * kWave, (size_t)kBandWaves * bt.slots * sizeof(T), s>>>(
+    k_band_spmv<T><<<grid1(bt.nslot), kWave, (size_t)bt.slots * sizeof(T), s>>>(
         bt, val, x, part, R, inst, prec, need_acc);
 }
 
@@ -3594,7 +3625,7 @@ template <typename TX>
 static void launch_band_cand(const BandTiles& bt, const double* val, const TX* x, double* part, int64_t R,
                              const Inst* inst, int prec, int mode, int which, hipStream_t s) {
   if (bt.nslot > 0)
-    k_band_cand<TX><<<grid1(bt.nslot), kBandWaves * kWave, (size_t)kBandWaves * bt.slots * 8, s>>>(
+    k_band_cand<TX><<<grid1(bt.nslot), kWave, (size_t)bt.slots * 8, s>>>(
         bt, val, x, part, R, inst, prec, mode, which);
 }
 
@@ -3607,7 +3638,7 @@ hipError_t band_raise_lds_limit() {
                              reinterpret_cast<const void*>(&k_scale_bands<SumSquares>),
                              reinterpret_cast<const void*>(&k_scale_bands_values)};
   for (const void* f : fns) {
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kBandWaves * kBandSlots * 8);
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kBandSlots * 8);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -3961,7 +3992,7 @@ void launch_setup(const KernelCtx& k, const SetupCtx& su, hipStream_t s, int mas
   if (k.use_band) {
     k_fill<<<blocks(k.M + k.N), tpb, 0, s>>>(k.D1, k.M, k.D2, k.N, 1.0);
     const unsigned slots = (unsigned)(k.band1.nslot + k.band2.nslot);
-    const size_t lds = (size_t)kBandWaves * std::max(k.band1.slots, k.band2.slots) * 8;
+    const size_t lds = (size_t)std::max(k.band1.slots, k.band2.slots) * 8;
     const double *v1 = su.borig64, *v2 = su.borigT64;
     if (!v1) {  // a batch keeps no unscaled values in entry order: they pass through the scaled ones' place
       if (su.bn > 0) launch_band_vals(su.bsrc, su.bn, su.A.val, su.bval64, su.bval32, s);
@@ -3972,15 +4003,15 @@ void launch_setup(const KernelCtx& k, const SetupCtx& su, hipStream_t s, int mas
       for (int i = 0; i < passes; ++i) {
         const int mode = i < su.ruiz_iters ? kScaleMax : kScaleSquares;
         if (mode == kScaleMax)
-          k_scale_bands<MaxProduct><<<slots, kBandWaves * kWave, lds, s>>>(k.band1, v1, k.D2, k.bpart64, k.M, k.band2, v2,
+          k_scale_bands<MaxProduct><<<slots, kWave, lds, s>>>(k.band1, v1, k.D2, k.bpart64, k.M, k.band2, v2,
                                                                            k.D1, k.bpartT64, k.N);
         else
-          k_scale_bands<SumSquares><<<slots, kBandWaves * kWave, lds, s>>>(k.band1, v1, k.D2, k.bpart64, k.M, k.band2, v2,
+          k_scale_bands<SumSquares><<<slots, kWave, lds, s>>>(k.band1, v1, k.D2, k.bpart64, k.M, k.band2, v2,
                                                                            k.D1, k.bpartT64, k.N);
         k_scale_bands_update<<<blocks(k.M + k.N), tpb, 0, s>>>(k.D1, k.bpart64, k.band1.P, k.M, k.D2, k.bpartT64,
                                                                k.band2.P, k.N, mode);
       }
-      k_scale_bands_values<<<slots, kBandWaves * kWave, lds, s>>>(k.band1, v1, su.bval64, su.bval32, k.band2, v2,
+      k_scale_bands_values<<<slots, kWave, lds, s>>>(k.band1, v1, su.bval64, su.bval32, k.band2, v2,
                                                                   su.bvalT64, su.bvalT32, k.D1, k.D2, su.rec_nm);
     }
   } else if (k.lds_trials64 > 0 && k.lds_rowwise) {

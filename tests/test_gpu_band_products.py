@@ -1,6 +1,6 @@
 """Products of the band layout at tile counts below, at and past a round of the
-chip, with several windows and with power-law rows (launches whose LDS follows
-the tallest tile), against the host's FP64 product."""
+chip, with several windows, with power-law rows (launches whose LDS follows the
+tallest tile) and with rows of many extra slots, against the host's FP64 product."""
 import numpy as np
 import pytest
 
@@ -25,6 +25,9 @@ CASES = {
     "past_a_round": dict(m=513 * 256, n=1000, row_lengths=1),
     "three_windows": dict(m=40000, n=3 * 2**18 - 7, per_col=1),
     "power_law": dict(m=90000, n=270000, zipf=True),
+    "tall_tiles": dict(m=400 * 1024 + 13, n=3000, row_lengths=2),  # tiles of more than 512 rows
+    "long_rows": dict(m=700, n=6000, long_rows=(0, 255, 256, 699)),  # rows with up to 63 extra slots
+    "one_long_row": dict(m=1, n=5000, long_rows=(0,)),
 }
 
 
@@ -34,6 +37,9 @@ def test_products_over_tile_counts(name):
     rng = np.random.default_rng(17)
     if c.pop("zipf", False):
         c["row_lengths"] = lpgen.zipf_row_lengths(rng, c["m"], 1.5, 3000)
+    elif "long_rows" in c:
+        rows = c.pop("long_rows")
+        c["row_lengths"] = np.where(np.isin(np.arange(c["m"]), rows), c["n"] * 4 // 5, 3)
     elif "row_lengths" in c:
         c["row_lengths"] = np.full(c["m"], c["row_lengths"])
     inst = lpgen.planted_lp(rng, name=name, **c)
