@@ -1968,15 +1968,10 @@ __global__ __launch_bounds__(kBlock) void k_spmv2(Spmv2Side<T> cols, Spmv2Side<T
 // Record layout: [c0 sums(6), c1 sums(6), c0 max(2), c1 max(2)].
 constexpr int kCandColsNV = 16, kCandColsNS = 12;
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_cand_cols(Ranges R, const T* __restrict__ x0,
-                                                      const T* __restrict__ x1, const T* __restrict__ xa,
-                                                      const double* __restrict__ g0,
-                                                      const double* __restrict__ g1,
-                                                      DataPtrs<double> d, const double* __restrict__ D2,
-                                                      const Inst* __restrict__ inst, int prec, int mode,
-                                                      double* __restrict__ rec) {
+__device__ __forceinline__ void cand_cols(int b, const Ranges& R, const T* x0, const T* x1, const T* xa,
+                                          const double* g0, const double* g1, const DataPtrs<double>& d,
+                                          const double* D2, const Inst* inst, int prec, int mode, double* rec) {
   __shared__ double lds[kWavesPerBlock * kCandColsNV];
-  const int b = blockIdx.x;
   const Inst& I = inst[R.blk_inst[b]];
   if (!mode_selects(I, mode) || I.precision != prec) return;
   const int nc = (mode == kModeCheck && I.use_avg) ? 2 : 1;
@@ -2013,20 +2008,27 @@ __global__ __launch_bounds__(kBlock) void k_cand_cols(Ranges R, const T* __restr
   block_summax_store<kCandColsNV, kCandColsNS>(acc, lds, rec + (size_t)b * kCandColsNV);
 }
 
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_cand_cols(Ranges R, const T* __restrict__ x0,
+                                                      const T* __restrict__ x1, const T* __restrict__ xa,
+                                                      const double* __restrict__ g0,
+                                                      const double* __restrict__ g1,
+                                                      DataPtrs<double> d, const double* __restrict__ D2,
+                                                      const Inst* __restrict__ inst, int prec, int mode,
+                                                      double* __restrict__ rec) {
+  cand_cols<T>(blockIdx.x, R, x0, x1, xa, g0, g1, d, D2, inst, prec, mode, rec);
+}
+
 // Candidate reductions over the rows: sums ||y_c - y_a||^2, ||b2||^2,
 // ||(Gx-h) - Proj_Kd*||^2, h^T y_c; maxima of the unscaled primal residual,
 // |G x| and |Proj_Kd*(G x - h)|.  Layout: [c0 sums(4), c1 sums(4), c0 max(3), c1 max(3)].
 constexpr int kCandRowsNV = 14, kCandRowsNS = 8;
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_cand_rows(Ranges R, const T* __restrict__ y0,
-                                                      const T* __restrict__ y1, const T* __restrict__ ya,
-                                                      const double* __restrict__ g0,
-                                                      const double* __restrict__ g1,
-                                                      DataPtrs<double> d, const double* __restrict__ D1,
-                                                      const Inst* __restrict__ inst, int prec, int mode,
-                                                      double* __restrict__ rec) {
+// CONES: the range may hold cone blocks (as in the other passes over rows).
+template <typename T, bool CONES>
+__device__ __forceinline__ void cand_rows(int b, const Ranges& R, const T* y0, const T* y1, const T* ya,
+                                          const double* g0, const double* g1, const DataPtrs<double>& d,
+                                          const double* D1, const Inst* inst, int prec, int mode, double* rec) {
   __shared__ double lds[kWavesPerBlock * kCandRowsNV];
-  const int b = blockIdx.x;
   const Inst& I = inst[R.blk_inst[b]];
   if (!mode_selects(I, mode) || I.precision != prec) return;
   const int nc = (mode == kModeCheck && I.use_avg) ? 2 : 1;
@@ -2065,63 +2067,74 @@ __global__ __launch_bounds__(kBlock) void k_cand_rows(Ranges R, const T* __restr
   // over the waves, with one inlined projection; the terms go through scalars
   // to acc)
   // per candidate: sums c[q][0..3] for acc[q*4 + i], maxima c[q][4..6] for acc[8 + q*3 + i - 4]
-  double c00 = 0.0, c01 = 0.0, c02 = 0.0, c03 = 0.0, c04 = 0.0, c05 = 0.0, c06 = 0.0;
-  double c10 = 0.0, c11 = 0.0, c12 = 0.0, c13 = 0.0, c14 = 0.0, c15 = 0.0, c16 = 0.0;
-  for_cone_tasks<2 * kMaxCand>(R, b, [&](auto who, int r0, int dim, int kind, int task) {
-    const int q = task >> 1, pass = task & 1;
-    if (who.any(q < nc)) {
-      const T* yq = q == 0 ? y0 : y1;
-      const double* gq = q == 0 ? g0 : g1;
-      double t0 = 0.0, t1 = 0.0, t2 = 0.0, t3 = 0.0, t4 = 0.0, t5 = 0.0, t6 = 0.0;
-      if (pass == 0) {
-        for (int i = who.first(); i < who.count(dim); i += who.stride()) {
-          const int r = r0 + i;
-          const double yc = (double)yq[r], gx = gq[r], h = d.h[r];
-          const double dya = yc - (double)ya[r], res = gx - h;
-          t0 += dya * dya;
-          t1 += res * res;
-          t3 += h * yc;
-          t5 = fmax(t5, fabs(gx) / D1[r]);
+  if constexpr (CONES) {
+    double c00 = 0.0, c01 = 0.0, c02 = 0.0, c03 = 0.0, c04 = 0.0, c05 = 0.0, c06 = 0.0;
+    double c10 = 0.0, c11 = 0.0, c12 = 0.0, c13 = 0.0, c14 = 0.0, c15 = 0.0, c16 = 0.0;
+    for_cone_tasks<2 * kMaxCand>(R, b, [&](auto who, int r0, int dim, int kind, int task) {
+      const int q = task >> 1, pass = task & 1;
+      if (who.any(q < nc)) {
+        const T* yq = q == 0 ? y0 : y1;
+        const double* gq = q == 0 ? g0 : g1;
+        double t0 = 0.0, t1 = 0.0, t2 = 0.0, t3 = 0.0, t4 = 0.0, t5 = 0.0, t6 = 0.0;
+        if (pass == 0) {
+          for (int i = who.first(); i < who.count(dim); i += who.stride()) {
+            const int r = r0 + i;
+            const double yc = (double)yq[r], gx = gq[r], h = d.h[r];
+            const double dya = yc - (double)ya[r], res = gx - h;
+            t0 += dya * dya;
+            t1 += res * res;
+            t3 += h * yc;
+            t5 = fmax(t5, fabs(gx) / D1[r]);
+          }
+        }
+        const bool scaled = pass == 0;
+        proj_cone(
+            who, kind, false, dim,
+            [&](int i) { return scaled ? gq[r0 + i] - d.h[r0 + i] : (gq[r0 + i] - d.h[r0 + i]) / D1[r0 + i]; },
+            [&](int i) { return scaled ? D1[r0 + i] : 1.0; },
+            [&](int i, double p) {
+              if (scaled) {
+                const double pr = (gq[r0 + i] - d.h[r0 + i]) - p;
+                t2 += pr * pr;
+              } else {
+                const double ru = (gq[r0 + i] - d.h[r0 + i]) / D1[r0 + i];
+                t4 = fmax(t4, fabs(ru - p));
+                t6 = fmax(t6, fabs(p));
+              }
+            });
+        if (q == 0) {
+          c00 += t0, c01 += t1, c02 += t2, c03 += t3;
+          c04 = fmax(c04, t4), c05 = fmax(c05, t5), c06 = fmax(c06, t6);
+        } else {
+          c10 += t0, c11 += t1, c12 += t2, c13 += t3;
+          c14 = fmax(c14, t4), c15 = fmax(c15, t5), c16 = fmax(c16, t6);
         }
       }
-      const bool scaled = pass == 0;
-      proj_cone(
-          who, kind, false, dim,
-          [&](int i) { return scaled ? gq[r0 + i] - d.h[r0 + i] : (gq[r0 + i] - d.h[r0 + i]) / D1[r0 + i]; },
-          [&](int i) { return scaled ? D1[r0 + i] : 1.0; },
-          [&](int i, double p) {
-            if (scaled) {
-              const double pr = (gq[r0 + i] - d.h[r0 + i]) - p;
-              t2 += pr * pr;
-            } else {
-              const double ru = (gq[r0 + i] - d.h[r0 + i]) / D1[r0 + i];
-              t4 = fmax(t4, fabs(ru - p));
-              t6 = fmax(t6, fabs(p));
-            }
-          });
-      if (q == 0) {
-        c00 += t0, c01 += t1, c02 += t2, c03 += t3;
-        c04 = fmax(c04, t4), c05 = fmax(c05, t5), c06 = fmax(c06, t6);
-      } else {
-        c10 += t0, c11 += t1, c12 += t2, c13 += t3;
-        c14 = fmax(c14, t4), c15 = fmax(c15, t5), c16 = fmax(c16, t6);
-      }
-    }
-  });
-  acc[0] += c00, acc[1] += c01, acc[2] += c02, acc[3] += c03;
-  acc[4] += c10, acc[5] += c11, acc[6] += c12, acc[7] += c13;
-  acc[8] = fmax(acc[8], c04), acc[9] = fmax(acc[9], c05), acc[10] = fmax(acc[10], c06);
-  acc[11] = fmax(acc[11], c14), acc[12] = fmax(acc[12], c15), acc[13] = fmax(acc[13], c16);
+    });
+    acc[0] += c00, acc[1] += c01, acc[2] += c02, acc[3] += c03;
+    acc[4] += c10, acc[5] += c11, acc[6] += c12, acc[7] += c13;
+    acc[8] = fmax(acc[8], c04), acc[9] = fmax(acc[9], c05), acc[10] = fmax(acc[10], c06);
+    acc[11] = fmax(acc[11], c14), acc[12] = fmax(acc[12], c15), acc[13] = fmax(acc[13], c16);
+  }
   block_summax_store<kCandRowsNV, kCandRowsNS>(acc, lds, rec + (size_t)b * kCandRowsNV);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_cand_rows(Ranges R, const T* __restrict__ y0,
+                                                      const T* __restrict__ y1, const T* __restrict__ ya,
+                                                      const double* __restrict__ g0,
+                                                      const double* __restrict__ g1,
+                                                      DataPtrs<double> d, const double* __restrict__ D1,
+                                                      const Inst* __restrict__ inst, int prec, int mode,
+                                                      double* __restrict__ rec) {
+  cand_rows<T, true>(blockIdx.x, R, y0, y1, ya, g0, g1, d, D1, inst, prec, mode, rec);
 }
 
 // Combine the candidate reductions: radii, KKT errors, termination errors,
 // and the start of the bisection (t0 = r / sqrt(tau|b1|^2 + sigma|b2|^2)).
-__global__ __launch_bounds__(kBlock) void k_cand_fin(Ranges rc, const double* __restrict__ rec_c,
-                                                     Ranges rr, const double* __restrict__ rec_r,
-                                                     Inst* __restrict__ inst, int mode) {
+__device__ __forceinline__ void cand_fin(int iid, const Ranges& rc, const double* rec_c, const Ranges& rr,
+                                         const double* rec_r, Inst* inst, int mode) {
   __shared__ double lds[kWavesPerBlock * kCandColsNV];
-  const int iid = blockIdx.x;
   Inst& I = inst[iid];
   if (!mode_selects(I, mode)) return;
   double cs[kCandColsNV], rs[kCandRowsNV];
@@ -2171,6 +2184,12 @@ __global__ __launch_bounds__(kBlock) void k_cand_fin(Ranges rc, const double* __
   }
   if (nc < 2) I.cand[1].phase = kPhaseOff;
   if (mode == kModeCheck) I.pending = 0;
+}
+
+__global__ __launch_bounds__(kBlock) void k_cand_fin(Ranges rc, const double* __restrict__ rec_c,
+                                                     Ranges rr, const double* __restrict__ rec_r,
+                                                     Inst* __restrict__ inst, int mode) {
+  cand_fin(blockIdx.x, rc, rec_c, rr, rec_r, inst, mode);
 }
 
 __device__ __forceinline__ double probe_t(const CandState& C, int p) {
@@ -2435,93 +2454,9 @@ __global__ __launch_bounds__(kProbeGroups* kBlock) void k_probe_fin(Ranges rc, c
   if (on && !rows && t < kWave) probe_brackets(L, q, t, I.cand[q], I.bisect_eps);
 }
 
-// All multisection passes of a restart check in one launch, one workgroup per
-// instance of precision prec (the layouts that run trials in one workgroup per
-// instance; no cone blocks there): the groups of k_probe_fin sum the whole
-// instance with the arithmetic of k_probe and keep the candidates in LDS.  It is
-// bound by each pass' chain of loads, exchanges and the bracket's update.
-// (n = 500, m = 200: 7 passes of 14.8 us with one wave per candidate and side,
-// its sums through memory; of 5.0 here.)
-template <typename T>
-__global__ __launch_bounds__(kProbeGroups* kBlock) void k_probes_wg(const T* x0, const T* x1, const T* y0, const T* y1,
-                                                                    const double* gc0, const double* gc1,
-                                                                    const double* gr0, const double* gr1,
-                                                                    DataPtrs<double> d, Inst* inst, int prec,
-                                                                    int passes) {
-  __shared__ ProbeLds L;
-  __shared__ CandState cand[kMaxCand];
-  __shared__ double tq[kProbeGroups][kProbes];
-  Inst& I = inst[blockIdx.x];
-  if (I.status != kActive || I.check_due == 0 || I.precision != prec) return;  // uniform
-  if (threadIdx.x < kMaxCand) cand[threadIdx.x] = I.cand[threadIdx.x];
-  __syncthreads();
-  const int g = threadIdx.x / kBlock, t = threadIdx.x % kBlock, q = g >> 1;
-  const int lane = threadIdx.x & (kWave - 1), wave = t / kWave;
-  const bool rows = g & 1;
-  const double step = rows ? I.eta_hat * I.omega : I.eta_hat / I.omega, inv = 1.0 / step;
-  const int mz_end = I.row0 + I.m_zero;
-  for (int pass = 0; pass < passes; ++pass) {
-    const bool on = searching(cand[q]);
-    if (!searching(cand[0]) && !searching(cand[1])) break;  // uniform
-    if (on && t < kProbes) tq[g][t] = probe_t(cand[q], t) * step;
-    __syncthreads();
-    if (on) {
-      double acc[kProbeNV];
-#pragma unroll
-      for (int i = 0; i < kProbeNV; ++i) acc[i] = 0.0;
-      if (!rows) {
-        const T* xs = q == 0 ? x0 : x1;
-        const double* gs = q == 0 ? gc0 : gc1;
-        for (int j = I.col0 + t; j < I.col0 + I.cols; j += kBlock) {
-          const double lo = d.l[j], hi = d.u[j];
-          const double xc = (double)xs[j];
-          const double b1 = gs[j] - d.c[j];
-#pragma unroll
-          for (int p = 0; p < kProbes; ++p) {
-            const double dx = clampd(xc + tq[g][p] * b1, lo, hi) - xc;
-            acc[p * 2 + 0] += dx * dx * inv;
-            acc[p * 2 + 1] += b1 * dx;
-            if (p % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // (16 probes' t at once would spill)
-          }
-        }
-      } else {
-        const T* ys = q == 0 ? y0 : y1;
-        const double* gs = q == 0 ? gr0 : gr1;
-        for (int i = I.row0 + t; i < I.row0 + I.rows; i += kBlock) {
-          const bool zero_row = i < mz_end;
-          const double yc = (double)ys[i];
-          const double b2 = d.h[i] - gs[i];
-#pragma unroll
-          for (int p = 0; p < kProbes; ++p) {
-            const double v = yc + tq[g][p] * b2;
-            const double dy = (zero_row ? v : fmax(v, 0.0)) - yc;
-            acc[p * 2 + 0] += dy * dy * inv;
-            acc[p * 2 + 1] += b2 * dy;
-            if (p % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-      }
-      const double s = wave_sum32(acc);
-      if (lane < 32) L.part[g][wave * kProbeNV + (int)(__brev((unsigned)lane) >> 27)] = s;
-    }
-    __syncthreads();
-    if (on && t < kProbeNV)
-      L.sums[g][t] =
-          ((L.part[g][t] + L.part[g][kProbeNV + t]) + L.part[g][2 * kProbeNV + t]) + L.part[g][3 * kProbeNV + t];
-    __syncthreads();
-    if (on && !rows && t < kWave) probe_brackets(L, q, t, cand[q], I.bisect_eps);
-    __syncthreads();
-  }
-  if (threadIdx.x < kMaxCand) I.cand[threadIdx.x] = cand[threadIdx.x];
-}
-static_assert(kProbeNV == 32 && kWavesPerBlock == 4, "the sums of a pass are 32 values over four waves");
-
 // Restart decision (Section 2.3), primal weight (Section 2.5), termination
 // (Section 3) and the mixed-precision polish switch.  Thread 0 only.
-__global__ void k_decide(Inst* __restrict__ inst, int nb) {
-  const int iid = blockIdx.x * blockDim.x + threadIdx.x;
-  if (iid >= nb) return;
-  Inst& I = inst[iid];
+__device__ __forceinline__ void check_decide(Inst& I) {
   if (I.status != kActive || I.check_due == 0) return;
   I.checks += 1;
   I.ray_due = 0;
@@ -2639,15 +2574,20 @@ __global__ void k_decide(Inst* __restrict__ inst, int nb) {
   if (I.kbar >= I.max_iter) I.stop_max_iter = 1;
 }
 
+__global__ void k_decide(Inst* __restrict__ inst, int nb) {
+  const int iid = blockIdx.x * blockDim.x + threadIdx.x;
+  if (iid < nb) check_decide(inst[iid]);
+}
+
 // Apply a restart (anchor <- candidate, products refreshed from the FP64-value
 // candidate products) or, for an optimal candidate, write the unscaled answer.
 // Columns: x, G^T y, average sums, x_out = D2 x, lam_out = (c_hat - G^T y_hat)/D2.
 template <typename T>
 __device__ __forceinline__ void restart_cols(int b, const Ranges& R, const IterPtrs<T>& it, const IterPtrs<double>& it64,
-                                             const double* __restrict__ g0, const double* __restrict__ g1,
-                                             const DataPtrs<double>& d, const double* __restrict__ D2,
-                                             double* __restrict__ xout, double* __restrict__ lamout,
-                                             const Inst* __restrict__ inst, int prec) {
+                                             const double* g0, const double* g1,
+                                             const DataPtrs<double>& d, const double* D2,
+                                             double* xout, double* lamout,
+                                             const Inst* inst, int prec) {
   const Inst& I = inst[R.blk_inst[b]];
   if (I.check_due == 0 || I.restart == 0 || I.precision != prec) return;
   const int ch = I.chosen;
@@ -2681,9 +2621,9 @@ __device__ __forceinline__ void restart_cols(int b, const Ranges& R, const IterP
 
 template <typename T>
 __device__ __forceinline__ void restart_rows(int b, const Ranges& R, const IterPtrs<T>& it, const IterPtrs<double>& it64,
-                                             const double* __restrict__ g0, const double* __restrict__ g1,
-                                             const double* __restrict__ D1, double* __restrict__ yout,
-                                             const Inst* __restrict__ inst, int prec) {
+                                             const double* g0, const double* g1,
+                                             const double* D1, double* yout,
+                                             const Inst* inst, int prec) {
   const Inst& I = inst[R.blk_inst[b]];
   if (I.check_due == 0 || I.restart == 0 || I.precision != prec) return;
   const int ch = I.chosen;
@@ -2727,10 +2667,7 @@ __global__ __launch_bounds__(kBlock) void k_restart(Ranges rc, Ranges rr, IterPt
   else restart_rows<T>(b - rc.nblk, rr, it, it64, gr0, gr1, D1, yout, inst, prec);
 }
 
-__global__ void k_check_end(Inst* __restrict__ inst, int nb) {
-  const int iid = blockIdx.x * blockDim.x + threadIdx.x;
-  if (iid >= nb) return;
-  Inst& I = inst[iid];
+__device__ __forceinline__ void check_end(Inst& I) {
   if (I.check_due == 0) return;
   if (I.optimal && I.status == kActive) {
     I.status = kDone;
@@ -2753,6 +2690,11 @@ __global__ void k_check_end(Inst* __restrict__ inst, int nb) {
   I.ray_due = 0;
 }
 
+__global__ void k_check_end(Inst* __restrict__ inst, int nb) {
+  const int iid = blockIdx.x * blockDim.x + threadIdx.x;
+  if (iid < nb) check_end(inst[iid]);
+}
+
 // ===========================================================================
 // Infeasibility tests (option list of Section 3; exit codes 2-5)
 // ===========================================================================
@@ -2762,6 +2704,13 @@ __global__ void k_check_end(Inst* __restrict__ inst, int nb) {
 // (both projections commute with the positive diagonal scaling).  Unscaled,
 // G^T (D1 r_y) = D2^{-1} G_hat^T r_y and G (D2 r_x) = D1^{-1} G_hat r_x.
 template <typename T>
+__device__ __forceinline__ double ray_x(const T* xh, const double* xs0, const DataPtrs<double>& d, int j) {
+  const double v = (double)xh[j] - xs0[j];
+  const bool lf = isfinite(d.l[j]), uf = isfinite(d.u[j]);
+  return lf && uf ? 0.0 : lf ? fmax(v, 0.0) : uf ? fmin(v, 0.0) : v;
+}
+
+template <typename T>
 __global__ __launch_bounds__(kBlock) void k_ray_vec_cols(Ranges R, const T* __restrict__ xh,
                                                          const double* __restrict__ xs0, DataPtrs<double> d,
                                                          double* __restrict__ rx, const Inst* __restrict__ inst,
@@ -2770,14 +2719,7 @@ __global__ __launch_bounds__(kBlock) void k_ray_vec_cols(Ranges R, const T* __re
   const Inst& I = inst[R.blk_inst[b]];
   if (!mode_selects(I, kModeRay) || I.precision != prec) return;
   const int j1 = R.blk_end[b];
-  for (int j = R.blk_start[b] + (int)threadIdx.x; j < j1; j += kBlock) {
-    double v = (double)xh[j] - xs0[j];
-    const bool lf = isfinite(d.l[j]), uf = isfinite(d.u[j]);
-    if (lf && uf) v = 0.0;
-    else if (lf) v = fmax(v, 0.0);
-    else if (uf) v = fmin(v, 0.0);
-    rx[j] = v;
-  }
+  for (int j = R.blk_start[b] + (int)threadIdx.x; j < j1; j += kBlock) rx[j] = ray_x(xh, xs0, d, j);
 }
 
 template <typename T>
@@ -2804,18 +2746,114 @@ __global__ __launch_bounds__(kBlock) void k_ray_vec_rows(Ranges R, const T* __re
   });
 }
 
+// Where a check's rays go (rx null: every primal ray is 0).
+struct RayOut {
+  const double *xs0, *ys0;
+  double *rx, *ry;
+};
+
+// All multisection passes of a restart check in one launch, one workgroup per
+// instance of precision prec (the layouts that run trials in one workgroup per
+// instance; no cone blocks there): the groups of k_probe_fin sum the whole
+// instance with the arithmetic of k_probe and keep the candidates in LDS.  It is
+// bound by each pass' chain of loads, exchanges and the bracket's update.
+// (n = 500, m = 200: 7 passes of 14.8 us with one wave per candidate and side,
+// its sums through memory; of 5.0 here.)  The decision and the rays of the check
+// follow in the same launch.
+template <typename T>
+__global__ __launch_bounds__(kProbeGroups* kBlock) void k_probes_wg(const T* x0, const T* x1, const T* y0, const T* y1,
+                                                                    const double* gc0, const double* gc1,
+                                                                    const double* gr0, const double* gr1,
+                                                                    DataPtrs<double> d, Inst* inst, int prec,
+                                                                    int passes, RayOut ray) {
+  __shared__ ProbeLds L;
+  __shared__ CandState cand[kMaxCand];
+  __shared__ double tq[kProbeGroups][kProbes];
+  Inst& I = inst[blockIdx.x];
+  if (I.status != kActive || I.check_due == 0 || I.precision != prec) return;  // uniform
+  if (threadIdx.x < kMaxCand) cand[threadIdx.x] = I.cand[threadIdx.x];
+  __syncthreads();
+  const int g = threadIdx.x / kBlock, t = threadIdx.x % kBlock, q = g >> 1;
+  const int lane = threadIdx.x & (kWave - 1), wave = t / kWave;
+  const bool rows = g & 1;
+  const double step = rows ? I.eta_hat * I.omega : I.eta_hat / I.omega, inv = 1.0 / step;
+  const int mz_end = I.row0 + I.m_zero;
+  for (int pass = 0; pass < passes; ++pass) {
+    const bool on = searching(cand[q]);
+    if (!searching(cand[0]) && !searching(cand[1])) break;  // uniform
+    if (on && t < kProbes) tq[g][t] = probe_t(cand[q], t) * step;
+    __syncthreads();
+    if (on) {
+      double acc[kProbeNV];
+#pragma unroll
+      for (int i = 0; i < kProbeNV; ++i) acc[i] = 0.0;
+      if (!rows) {
+        const T* xs = q == 0 ? x0 : x1;
+        const double* gs = q == 0 ? gc0 : gc1;
+        for (int j = I.col0 + t; j < I.col0 + I.cols; j += kBlock) {
+          const double lo = d.l[j], hi = d.u[j];
+          const double xc = (double)xs[j];
+          const double b1 = gs[j] - d.c[j];
+#pragma unroll
+          for (int p = 0; p < kProbes; ++p) {
+            const double dx = clampd(xc + tq[g][p] * b1, lo, hi) - xc;
+            acc[p * 2 + 0] += dx * dx * inv;
+            acc[p * 2 + 1] += b1 * dx;
+            if (p % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // (16 probes' t at once would spill)
+          }
+        }
+      } else {
+        const T* ys = q == 0 ? y0 : y1;
+        const double* gs = q == 0 ? gr0 : gr1;
+        for (int i = I.row0 + t; i < I.row0 + I.rows; i += kBlock) {
+          const bool zero_row = i < mz_end;
+          const double yc = (double)ys[i];
+          const double b2 = d.h[i] - gs[i];
+#pragma unroll
+          for (int p = 0; p < kProbes; ++p) {
+            const double v = yc + tq[g][p] * b2;
+            const double dy = (zero_row ? v : fmax(v, 0.0)) - yc;
+            acc[p * 2 + 0] += dy * dy * inv;
+            acc[p * 2 + 1] += b2 * dy;
+            if (p % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+      }
+      const double s = wave_sum32(acc);
+      if (lane < 32) L.part[g][wave * kProbeNV + (int)(__brev((unsigned)lane) >> 27)] = s;
+    }
+    __syncthreads();
+    if (on && t < kProbeNV)
+      L.sums[g][t] =
+          ((L.part[g][t] + L.part[g][kProbeNV + t]) + L.part[g][2 * kProbeNV + t]) + L.part[g][3 * kProbeNV + t];
+    __syncthreads();
+    if (on && !rows && t < kWave) probe_brackets(L, q, t, cand[q], I.bisect_eps);
+    __syncthreads();
+  }
+  if (threadIdx.x < kMaxCand) I.cand[threadIdx.x] = cand[threadIdx.x];
+  __syncthreads();
+  if (threadIdx.x == 0) check_decide(I);
+  __syncthreads();
+  if (!mode_selects(I, kModeRay)) return;
+  for (int i = I.row0 + (int)threadIdx.x; i < I.row0 + I.rows; i += kProbeGroups * kBlock) {
+    const double v = (double)y0[i] - ray.ys0[i];
+    ray.ry[i] = i < mz_end ? v : fmax(v, 0.0);
+  }
+  if (ray.rx)
+    for (int j = I.col0 + (int)threadIdx.x; j < I.col0 + I.cols; j += kProbeGroups * kBlock)
+      ray.rx[j] = ray_x(x0, ray.xs0, d, j);
+}
+static_assert(kProbeNV == 32 && kWavesPerBlock == 4, "the sums of a pass are 32 values over four waves");
+
 // Column terms, with lam = -(G_hat^T r_y)_j / D2_j (the unscaled -G^T r_y) and
 // the unscaled bounds l_j = l_hat_j D2_j, u_j = u_hat_j D2_j:
 //   [0] ||lam - Proj_Lambda lam||^2   [1] sum l lam+ - u lam- (finite bounds)
 //   [2] its terms' magnitudes          [3] number of those terms
 //   [4] c^T r_x (= c_hat^T r_x)         [5] its terms' magnitudes
 constexpr int kRayColsNV = 6;
-__global__ __launch_bounds__(kBlock) void k_ray_cols(Ranges R, const double* __restrict__ rx,
-                                                     const double* __restrict__ rgty, DataPtrs<double> d,
-                                                     const double* __restrict__ D2, const Inst* __restrict__ inst,
-                                                     double* __restrict__ rec) {
+__device__ __forceinline__ void ray_cols(int b, const Ranges& R, const double* rx, const double* rgty,
+                                         const DataPtrs<double>& d, const double* D2, const Inst* inst, double* rec) {
   __shared__ double lds[kWavesPerBlock * kRayColsNV];
-  const int b = blockIdx.x;
   const Inst& I = inst[R.blk_inst[b]];
   if (!mode_selects(I, kModeRay)) return;
   double acc[kRayColsNV] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -2850,16 +2888,21 @@ __global__ __launch_bounds__(kBlock) void k_ray_cols(Ranges R, const double* __r
   block_sum_store<kRayColsNV>(acc, lds, rec + (size_t)b * kRayColsNV);
 }
 
+__global__ __launch_bounds__(kBlock) void k_ray_cols(Ranges R, const double* __restrict__ rx,
+                                                     const double* __restrict__ rgty, DataPtrs<double> d,
+                                                     const double* __restrict__ D2, const Inst* __restrict__ inst,
+                                                     double* __restrict__ rec) {
+  ray_cols(blockIdx.x, R, rx, rgty, d, D2, inst, rec);
+}
+
 // Row terms: [0] h^T r_y (= h_hat^T r_y), [1] its terms' magnitudes,
 // [2] ||G r_x - Proj_Kd*(G r_x)||^2 with (G r_x)_i = (G_hat r_x)_i / D1_i
 // (zero when no instance has a nonzero primal ray: rgx null).
 constexpr int kRayRowsNV = 3;
-__global__ __launch_bounds__(kBlock) void k_ray_rows(Ranges R, const double* __restrict__ ry,
-                                                     const double* __restrict__ rgx, DataPtrs<double> d,
-                                                     const double* __restrict__ D1, const Inst* __restrict__ inst,
-                                                     double* __restrict__ rec) {
+template <bool CONES>
+__device__ __forceinline__ void ray_rows(int b, const Ranges& R, const double* ry, const double* rgx,
+                                         const DataPtrs<double>& d, const double* D1, const Inst* inst, double* rec) {
   __shared__ double lds[kWavesPerBlock * kRayRowsNV];
-  const int b = blockIdx.x;
   const Inst& I = inst[R.blk_inst[b]];
   if (!mode_selects(I, kModeRay)) return;
   const int mz_end = I.row0 + I.m_zero;
@@ -2876,7 +2919,7 @@ __global__ __launch_bounds__(kBlock) void k_ray_rows(Ranges R, const double* __r
     }
   }
   // cone blocks: the unscaled G r_x against the block's cone
-  if (rgx)
+  if (CONES && rgx)
     for_cone_blocks(R, b, [&](auto who, int r0, int dim, int kind) {
       proj_cone(
           who, kind, false, dim, [&](int i) { return rgx[r0 + i] / D1[r0 + i]; }, [](int) { return 1.0; },
@@ -2888,6 +2931,13 @@ __global__ __launch_bounds__(kBlock) void k_ray_rows(Ranges R, const double* __r
   block_sum_store<kRayRowsNV>(acc, lds, rec + (size_t)b * kRayRowsNV);
 }
 
+__global__ __launch_bounds__(kBlock) void k_ray_rows(Ranges R, const double* __restrict__ ry,
+                                                     const double* __restrict__ rgx, DataPtrs<double> d,
+                                                     const double* __restrict__ D1, const Inst* __restrict__ inst,
+                                                     double* __restrict__ rec) {
+  ray_rows<true>(blockIdx.x, R, ry, rgx, d, D1, inst, rec);
+}
+
 // gamma_N = N u / (1 - N u), u = 2^-53: relative error bound of a sum of N terms.
 __device__ __forceinline__ double rounding_bound(double count) {
   const double nu = fmax(count, 1.0) * 0x1p-53;
@@ -2897,10 +2947,9 @@ __device__ __forceinline__ double rounding_bound(double count) {
 // Ratios, trend counters and the exit decision of the infeasibility tests.
 // Priority: high-accuracy primal (3), high-accuracy dual (5), low-accuracy
 // primal (2), low-accuracy dual (4); a tolerance of 0 never passes.
-__global__ __launch_bounds__(kBlock) void k_ray_fin(Ranges rc, const double* __restrict__ rec_c, Ranges rr,
-                                                    const double* __restrict__ rec_r, Inst* __restrict__ inst) {
+__device__ __forceinline__ void ray_fin(int iid, const Ranges& rc, const double* rec_c, const Ranges& rr,
+                                        const double* rec_r, Inst* inst) {
   __shared__ double lds[kWavesPerBlock * kRayColsNV];
-  const int iid = blockIdx.x;
   Inst& I = inst[iid];
   if (!mode_selects(I, kModeRay)) return;
   double cs[kRayColsNV], rs[kRayRowsNV];
@@ -2935,6 +2984,11 @@ __global__ __launch_bounds__(kBlock) void k_ray_fin(Ranges rc, const double* __r
   }
 }
 
+__global__ __launch_bounds__(kBlock) void k_ray_fin(Ranges rc, const double* __restrict__ rec_c, Ranges rr,
+                                                    const double* __restrict__ rec_r, Inst* __restrict__ inst) {
+  ray_fin(blockIdx.x, rc, rec_c, rr, rec_r, inst);
+}
+
 // Device warm starts into the packed FP64 start vector.
 template <typename TW>
 __global__ void k_pack_warm(const void* const* __restrict__ src, const int32_t* __restrict__ off, int B,
@@ -2951,10 +3005,7 @@ __global__ void k_pack_warm(const void* const* __restrict__ src, const int32_t* 
 }
 
 // Evaluated point (start point or final point): termination test and output.
-__global__ void k_eval_fin(Inst* __restrict__ inst, int nb, int mode) {
-  const int iid = blockIdx.x * blockDim.x + threadIdx.x;
-  if (iid >= nb) return;
-  Inst& I = inst[iid];
+__device__ __forceinline__ void eval_fin(Inst& I, int mode) {
   if (!mode_selects(I, mode)) return;
   const CandState& C = I.cand[0];
   I.pobj = C.pobj;
@@ -2974,18 +3025,17 @@ __global__ void k_eval_fin(Inst* __restrict__ inst, int nb, int mode) {
   }
 }
 
+__global__ void k_eval_fin(Inst* __restrict__ inst, int nb, int mode) {
+  const int iid = blockIdx.x * blockDim.x + threadIdx.x;
+  if (iid < nb) eval_fin(inst[iid], mode);
+}
+
 // Write the evaluated point (x_hat, y_hat) unscaled.  Start mode: only for
 // instances found optimal (which then stop); final mode: every selected instance.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_eval_out(Ranges rc, Ranges rr, const T* __restrict__ xh,
-                                                     const T* __restrict__ yh, const double* __restrict__ g0,
-                                                     DataPtrs<double> d, const double* __restrict__ D1,
-                                                     const double* __restrict__ D2, double* __restrict__ xout,
-                                                     double* __restrict__ lamout, double* __restrict__ yout,
-                                                     const Inst* __restrict__ inst, int prec, int mode) {
-  const bool cols = (int)blockIdx.x < rc.nblk;
-  const int b = cols ? (int)blockIdx.x : (int)blockIdx.x - rc.nblk;
-  const Ranges& R = cols ? rc : rr;
+__device__ __forceinline__ void eval_out(int b, bool cols, const Ranges& R, const T* xh, const T* yh, const double* g0,
+                                         const DataPtrs<double>& d, const double* D1, const double* D2, double* xout,
+                                         double* lamout, double* yout, const Inst* inst, int prec, int mode) {
   const Inst& I = inst[R.blk_inst[b]];
   if (!mode_selects(I, mode) || I.precision != prec) return;
   if (mode == kModeEvalStart && !I.optimal) return;
@@ -3000,14 +3050,28 @@ __global__ __launch_bounds__(kBlock) void k_eval_out(Ranges rc, Ranges rr, const
   }
 }
 
-__global__ void k_eval_start_end(Inst* __restrict__ inst, int nb) {
-  const int iid = blockIdx.x * blockDim.x + threadIdx.x;
-  if (iid >= nb) return;
-  Inst& I = inst[iid];
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_eval_out(Ranges rc, Ranges rr, const T* __restrict__ xh,
+                                                     const T* __restrict__ yh, const double* __restrict__ g0,
+                                                     DataPtrs<double> d, const double* __restrict__ D1,
+                                                     const double* __restrict__ D2, double* __restrict__ xout,
+                                                     double* __restrict__ lamout, double* __restrict__ yout,
+                                                     const Inst* __restrict__ inst, int prec, int mode) {
+  const bool cols = (int)blockIdx.x < rc.nblk;
+  eval_out<T>(cols ? (int)blockIdx.x : (int)blockIdx.x - rc.nblk, cols, cols ? rc : rr, xh, yh, g0, d, D1, D2, xout,
+              lamout, yout, inst, prec, mode);
+}
+
+__device__ __forceinline__ void eval_start_end(Inst& I) {
   if (I.status == kActive && I.optimal) {
     I.status = kDone;
     I.exit_code = 0;
   }
+}
+
+__global__ void k_eval_start_end(Inst* __restrict__ inst, int nb) {
+  const int iid = blockIdx.x * blockDim.x + threadIdx.x;
+  if (iid < nb) eval_start_end(inst[iid]);
 }
 
 // Counts of active instances per precision, for the host loop.
@@ -3436,15 +3500,10 @@ __global__ void k_fill(double* __restrict__ a, int64_t na, double* __restrict__ 
 // Rescaled vectors and the records of their norms: columns (workgroups [0, rc.nblk))
 // c_hat = D2 c, l_hat = l / D2, u_hat = u / D2, with |c_hat|_1, |c_hat|_2^2 (sums) and
 // |c|_inf (max); rows h_hat = D1 h, with |h_hat|_1, |h_hat|_2^2 and |h|_inf.
-__global__ __launch_bounds__(kBlock) void k_scale_vectors(Ranges rc, Ranges rr, const double* __restrict__ c,
-                                                          const double* __restrict__ l, const double* __restrict__ u,
-                                                          const double* __restrict__ h, const double* __restrict__ D1,
-                                                          const double* __restrict__ D2, DataMut d64, DataMut32 d32,
-                                                          double* __restrict__ rec_c, double* __restrict__ rec_r) {
+__device__ __forceinline__ void scale_vectors(int b, bool rows, const Ranges& R, const double* c, const double* l,
+                                              const double* u, const double* h, const double* D1, const double* D2,
+                                              const DataMut& d64, const DataMut32& d32, double* rec) {
   __shared__ double lds[kWavesPerBlock * 3];
-  const bool rows = (int)blockIdx.x >= rc.nblk;
-  const int b = (int)blockIdx.x - (rows ? rc.nblk : 0);
-  const Ranges& R = rows ? rr : rc;
   double acc[3] = {0.0, 0.0, 0.0};
   const int e1 = R.blk_end[b];
   for (int e = R.blk_start[b] + (int)threadIdx.x; e < e1; e += kBlock) {
@@ -3470,19 +3529,25 @@ __global__ __launch_bounds__(kBlock) void k_scale_vectors(Ranges rc, Ranges rr, 
     acc[1] += v * v;
     acc[2] = fmax(acc[2], fabs(raw));
   }
-  block_summax_store<3, 2>(acc, lds, (rows ? rec_r : rec_c) + (size_t)b * 3);
+  block_summax_store<3, 2>(acc, lds, rec + (size_t)b * 3);
+}
+
+__global__ __launch_bounds__(kBlock) void k_scale_vectors(Ranges rc, Ranges rr, const double* __restrict__ c,
+                                                          const double* __restrict__ l, const double* __restrict__ u,
+                                                          const double* __restrict__ h, const double* __restrict__ D1,
+                                                          const double* __restrict__ D2, DataMut d64, DataMut32 d32,
+                                                          double* __restrict__ rec_c, double* __restrict__ rec_r) {
+  const bool rows = (int)blockIdx.x >= rc.nblk;
+  scale_vectors((int)blockIdx.x - (rows ? rc.nblk : 0), rows, rows ? rr : rc, c, l, u, h, D1, D2, d64, d32,
+                rows ? rec_r : rec_c);
 }
 
 // Per-instance set-up of the scalars from the norm records (Algorithm 1
 // inputs: eta_hat = 1/||G_hat||_inf read as max |G_hat_ij|, primal weight
 // initialization of Section 2.5).
-__global__ __launch_bounds__(kBlock) void k_init_inst(Ranges rc, const double* __restrict__ rec_c,
-                                                      Ranges rr, const double* __restrict__ rec_r,
-                                                      const int32_t* __restrict__ iblk_m,
-                                                      const double* __restrict__ rec_m,
-                                                      Inst* __restrict__ inst) {
+__device__ __forceinline__ void init_inst(int iid, const Ranges& rc, const double* rec_c, const Ranges& rr,
+                                          const double* rec_r, const int32_t* iblk_m, const double* rec_m, Inst* inst) {
   __shared__ double lds[kWavesPerBlock * 3];
-  const int iid = blockIdx.x;
   Inst& I = inst[iid];
   double cs[3], rs[3], ms[1];
   reduce_records<3, 2>(rec_c, rc.inst_blk0[iid], rc.inst_blk0[iid + 1], lds, cs);
@@ -3502,13 +3567,19 @@ __global__ __launch_bounds__(kBlock) void k_init_inst(Ranges rc, const double* _
   I.omega = I.omega0;
 }
 
+__global__ __launch_bounds__(kBlock) void k_init_inst(Ranges rc, const double* __restrict__ rec_c,
+                                                      Ranges rr, const double* __restrict__ rec_r,
+                                                      const int32_t* __restrict__ iblk_m,
+                                                      const double* __restrict__ rec_m,
+                                                      Inst* __restrict__ inst) {
+  init_inst(blockIdx.x, rc, rec_c, rr, rec_r, iblk_m, rec_m, inst);
+}
+
 // Start point: x = Proj_[l,u](x0 / D2), y = Proj_Kd(y0 / D1); anchor = x_hat = x.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_start_cols(Ranges R, const double* __restrict__ x0,
-                                                       const double* __restrict__ D2, DataPtrs<double> d,
-                                                       IterPtrs<T> it, double* __restrict__ xs0,
-                                                       const Inst* __restrict__ inst, int prec) {
-  const int b = blockIdx.x;
+__device__ __forceinline__ void start_cols(int b, const Ranges& R, const double* x0, const double* D2,
+                                           const DataPtrs<double>& d, const IterPtrs<T>& it, double* xs0,
+                                           const Inst* inst, int prec) {
   const Inst& I = inst[R.blk_inst[b]];
   if (I.precision != prec) return;
   const int j1 = R.blk_end[b];
@@ -3524,11 +3595,16 @@ __global__ __launch_bounds__(kBlock) void k_start_cols(Ranges R, const double* _
 }
 
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_start_rows(Ranges R, const double* __restrict__ y0,
-                                                       const double* __restrict__ D1, IterPtrs<T> it,
-                                                       double* __restrict__ ys0, const Inst* __restrict__ inst,
-                                                       int prec) {
-  const int b = blockIdx.x;
+__global__ __launch_bounds__(kBlock) void k_start_cols(Ranges R, const double* __restrict__ x0,
+                                                       const double* __restrict__ D2, DataPtrs<double> d,
+                                                       IterPtrs<T> it, double* __restrict__ xs0,
+                                                       const Inst* __restrict__ inst, int prec) {
+  start_cols<T>(blockIdx.x, R, x0, D2, d, it, xs0, inst, prec);
+}
+
+template <typename T, bool CONES>
+__device__ __forceinline__ void start_rows(int b, const Ranges& R, const double* y0, const double* D1,
+                                           const IterPtrs<T>& it, double* ys0, const Inst* inst, int prec) {
   const Inst& I = inst[R.blk_inst[b]];
   if (I.precision != prec) return;
   const int mz_end = I.row0 + I.m_zero;
@@ -3544,7 +3620,7 @@ __global__ __launch_bounds__(kBlock) void k_start_rows(Ranges R, const double* _
     it.sy[i] = (T)0;
   }
   // cone blocks: y0 / D1 projected onto diag(1/D1) (dual cone)
-  for_cone_blocks(R, b, [&](auto who, int r0, int dim, int kind) {
+  if constexpr (CONES) for_cone_blocks(R, b, [&](auto who, int r0, int dim, int kind) {
     proj_cone(
         who, kind, true, dim, [&](int i) { return y0 ? y0[r0 + i] / D1[r0 + i] : 0.0; }, [&](int i) { return 1.0 / D1[r0 + i]; },
         [&](int i, double p) {
@@ -3557,6 +3633,14 @@ __global__ __launch_bounds__(kBlock) void k_start_rows(Ranges R, const double* _
           it.sy[r] = (T)0;
         });
   });
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_start_rows(Ranges R, const double* __restrict__ y0,
+                                                       const double* __restrict__ D1, IterPtrs<T> it,
+                                                       double* __restrict__ ys0, const Inst* __restrict__ inst,
+                                                       int prec) {
+  start_rows<T, true>(blockIdx.x, R, y0, D1, it, ys0, inst, prec);
 }
 
 // Copy FP64 products into the maintained products of the start point: G^T y (n
@@ -3589,9 +3673,116 @@ __global__ __launch_bounds__(kBlock) void k_spmv_plain(RowBlocks rb, MatPtrs<TM>
                 [&](int r, const double* s) { out[r] = (T)s[0]; });
 }
 
+// Instances that fit in LDS (one workgroup each, no cone blocks): what a check, an
+// evaluation and the set-up do between two products, in one launch each, with the
+// arithmetic of the kernels above and barriers in place of the launches.  Such a
+// pass is 1 to 2 us of loads and barriers, a launch of its own 4 to 5 us; the
+// products keep theirs, as their row blocks would follow one another here.
+// (m = 200, n = 500, 40 trials and one check: 23 launches fewer, 575 -> 531 us a solve;
+// 128 LPs of 60 to 220 rows 1605 -> 1560.)
+template <typename T>
+__device__ __forceinline__ const IterPtrs<T>& iter_of(const KernelCtx& k) {
+  if constexpr (sizeof(T) == 4) return k.it32;
+  else return k.it64;
+}
+
+// After the products of the candidates (of the evaluated point): the candidates'
+// sums and their finalizer; then, for an evaluated point, its test and the output,
+// and for the start point the products of the iterates.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_cand_wg(KernelCtx k, int prec, int mode) {
+  const int iid = blockIdx.x;
+  Inst& I = k.inst[iid];
+  if (!mode_selects(I, mode) || I.precision != prec) return;  // uniform
+  const IterPtrs<T>& it = iter_of<T>(k);
+  const int c0 = k.vcol.inst_blk0[iid], c1 = k.vcol.inst_blk0[iid + 1];
+  const int r0 = k.vrow.inst_blk0[iid], r1 = k.vrow.inst_blk0[iid + 1];
+  for (int b = c0; b < c1; ++b) {
+    cand_cols<T>(b, k.vcol, it.xh, it.xbar, it.xa, k.cgty0, k.cgty1, k.d64, k.D2, k.inst, prec, mode, k.rec_cand_c);
+    __syncthreads();
+  }
+  for (int b = r0; b < r1; ++b) {
+    cand_rows<T, false>(b, k.vrow, it.yh, it.ybar, it.ya, k.cgx0, k.cgx1, k.d64, k.D1, k.inst, prec, mode, k.rec_cand_r);
+    __syncthreads();
+  }
+  cand_fin(iid, k.vcol, k.rec_cand_c, k.vrow, k.rec_cand_r, k.inst, mode);
+  if (mode == kModeCheck) return;
+  if (threadIdx.x == 0) eval_fin(I, mode);
+  __syncthreads();
+  for (int b = c0; b < c1; ++b)
+    eval_out<T>(b, true, k.vcol, it.xh, it.yh, k.cgty0, k.d64, k.D1, k.D2, k.xout, k.lamout, k.yout, k.inst, prec, mode);
+  for (int b = r0; b < r1; ++b)
+    eval_out<T>(b, false, k.vrow, it.xh, it.yh, k.cgty0, k.d64, k.D1, k.D2, k.xout, k.lamout, k.yout, k.inst, prec, mode);
+  if (mode != kModeEvalStart) return;
+  __syncthreads();
+  if (threadIdx.x == 0) eval_start_end(I);
+  for (int j = I.col0 + (int)threadIdx.x; j < I.col0 + I.cols; j += kBlock) {
+    const T v = (T)k.cgty0[j];
+    it.gty[j] = it.gtya[j] = it.gtyh[j] = v;
+  }
+  for (int i = I.row0 + (int)threadIdx.x; i < I.row0 + I.rows; i += kBlock) {
+    const T v = (T)k.cgx0[i];
+    it.gx[i] = it.gxa[i] = it.gxh[i] = v;
+  }
+}
+
+// After the products of the rays: the infeasibility tests, the restart, the end of the check.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_check_wg(KernelCtx k, int prec) {
+  const int iid = blockIdx.x;
+  Inst& I = k.inst[iid];
+  if (I.check_due == 0 || I.precision != prec) return;  // uniform
+  const int c0 = k.vcol.inst_blk0[iid], c1 = k.vcol.inst_blk0[iid + 1];
+  const int r0 = k.vrow.inst_blk0[iid], r1 = k.vrow.inst_blk0[iid + 1];
+  if (mode_selects(I, kModeRay)) {
+    for (int b = c0; b < c1; ++b) {
+      ray_cols(b, k.vcol, k.ray_x ? k.rx : nullptr, k.rgty, k.d64, k.D2, k.inst, k.rec_cand_c);
+      __syncthreads();
+    }
+    for (int b = r0; b < r1; ++b) {
+      ray_rows<false>(b, k.vrow, k.ry, k.ray_x ? k.rgx : nullptr, k.d64, k.D1, k.inst, k.rec_cand_r);
+      __syncthreads();
+    }
+    ray_fin(iid, k.vcol, k.rec_cand_c, k.vrow, k.rec_cand_r, k.inst);
+  }
+  __syncthreads();
+  const IterPtrs<T>& it = iter_of<T>(k);
+  for (int b = c0; b < c1; ++b)
+    restart_cols<T>(b, k.vcol, it, k.it64, k.cgty0, k.cgty1, k.d64, k.D2, k.xout, k.lamout, k.inst, prec);
+  for (int b = r0; b < r1; ++b)
+    restart_rows<T>(b, k.vrow, it, k.it64, k.cgx0, k.cgx1, k.D1, k.yout, k.inst, prec);
+  __syncthreads();
+  if (threadIdx.x == 0) check_end(I);
+}
+
+// After the scaling: the rescaled vectors, the instance's scalars, the start point.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_start_wg(KernelCtx k, SetupCtx su, int prec) {
+  const int iid = blockIdx.x;
+  const IterPtrs<T>& it = iter_of<T>(k);
+  const int c0 = k.vcol.inst_blk0[iid], c1 = k.vcol.inst_blk0[iid + 1];
+  const int r0 = k.vrow.inst_blk0[iid], r1 = k.vrow.inst_blk0[iid + 1];
+  for (int b = c0; b < c1; ++b) {
+    scale_vectors(b, false, k.vcol, su.c, su.l, su.u, su.h, k.D1, k.D2, su.d64m, su.d32m, su.rec_nc);
+    __syncthreads();
+  }
+  for (int b = r0; b < r1; ++b) {
+    scale_vectors(b, true, k.vrow, su.c, su.l, su.u, su.h, k.D1, k.D2, su.d64m, su.d32m, su.rec_nr);
+    __syncthreads();
+  }
+  init_inst(iid, k.vcol, su.rec_nc, k.vrow, su.rec_nr, k.brow.inst_blk0, su.rec_nm, k.inst);
+  for (int b = c0; b < c1; ++b) start_cols<T>(b, k.vcol, su.x0, k.D2, k.d64, it, k.xs0, k.inst, prec);
+  for (int b = r0; b < r1; ++b) start_rows<T, false>(b, k.vrow, su.y0, k.D1, it, k.ys0, k.inst, prec);
+}
+
 // ===========================================================================
 // Launchers
 // ===========================================================================
+// Whether the instances take the kernels above: the layout runs trials in one
+// workgroup per instance and every instance fits in LDS in FP64 (larger ones have
+// enough elements for the launches of many workgroups to win).
+static inline bool small_instances(const KernelCtx& k) { return k.wg_trials && !k.use_band && k.lds_trials64 > 0; }
+
 static inline dim3 grid1(int n) { return dim3((unsigned)(n > 0 ? n : 0)); }
 
 template <typename T>
@@ -3803,6 +3994,14 @@ void launch_trials_wg(const KernelCtx& k, hipStream_t s, int mask, int K) {
 template <typename T>
 static void launch_cand_t(const KernelCtx& k, hipStream_t s, int prec, const IterPtrs<T>& it,
                           const T* x0, const T* x1, const T* y0, const T* y1, int mode) {
+  if (small_instances(k)) {
+    if (k.bcol.nblk + k.brow.nblk > 0)
+      k_spmv2<T><<<grid1(k.bcol.nblk + k.brow.nblk), kBlock, 0, s>>>(
+          Spmv2Side<T>{k.bcol, k.AT64, y0, y1, k.cgty0, k.cgty1}, Spmv2Side<T>{k.brow, k.A64, x0, x1, k.cgx0, k.cgx1},
+          k.inst, prec, mode);
+    k_cand_wg<T><<<grid1(k.nb), kBlock, 0, s>>>(k, prec, mode);
+    return;
+  }
   if (k.use_band) {
     // band tiles with FP64 values: one pass per vector, then the window sums
     launch_band_cand<T>(k.band1, k.bval64, x0, k.bpart64, k.M, k.inst, prec, mode, 0, s);
@@ -3840,6 +4039,13 @@ static void launch_probe_t(const KernelCtx& k, hipStream_t s, int prec, const It
     k_probe<T><<<dim3(k.ccol.nblk + k.crow.nblk, kMaxCand), kBlock, 0, s>>>(
         k.ccol, k.crow, it.xh, it.xbar, it.yh, it.ybar, k.cgty0, k.cgty1, k.cgx0, k.cgx1, k.d64, k.D1, k.inst, prec,
         k.rec_probe_c, k.rec_probe_r);
+}
+
+template <typename T>
+static void launch_probes_wg_t(const KernelCtx& k, hipStream_t s, int prec, const IterPtrs<T>& it) {
+  k_probes_wg<T><<<k.nb, kProbeGroups * kBlock, 0, s>>>(it.xh, it.xbar, it.yh, it.ybar, k.cgty0, k.cgty1, k.cgx0, k.cgx1,
+                                                        k.d64, k.inst, prec, k.probe_passes,
+                                                        RayOut{k.xs0, k.ys0, k.ray_x ? k.rx : nullptr, k.ry});
 }
 
 template <typename T>
@@ -3883,8 +4089,10 @@ static void launch_ray_vec_t(const KernelCtx& k, hipStream_t s, int prec, const 
 
 // The infeasibility tests of one check (instances selected by k_decide).
 static void launch_ray(const KernelCtx& k, hipStream_t s, int mask) {
-  if (mask & 1) launch_ray_vec_t<float>(k, s, kFP32, k.it32);
-  if (mask & 2) launch_ray_vec_t<double>(k, s, kFP64, k.it64);
+  if (!k.wg_trials || k.use_band) {  // (else with the multisection passes)
+    if (mask & 1) launch_ray_vec_t<float>(k, s, kFP32, k.it32);
+    if (mask & 2) launch_ray_vec_t<double>(k, s, kFP64, k.it64);
+  }
   launch_ray_products(k, s);
   // the candidate records are free once k_cand_fin has run
   if (k.vcol.nblk > 0)
@@ -3900,24 +4108,26 @@ void launch_check(const KernelCtx& k, hipStream_t s, int mask) {
   const int nbt = (k.nb + 63) / 64;
   if (mask & 1) launch_check_pre_t<float>(k, s, kFP32, k.it32);
   if (mask & 2) launch_check_pre_t<double>(k, s, kFP64, k.it64);
-  k_cand_fin<<<grid1(k.nb), kBlock, 0, s>>>(k.vcol, k.rec_cand_c, k.vrow, k.rec_cand_r, k.inst, kModeCheck);
+  const bool small = small_instances(k);
+  if (!small)
+    k_cand_fin<<<grid1(k.nb), kBlock, 0, s>>>(k.vcol, k.rec_cand_c, k.vrow, k.rec_cand_r, k.inst, kModeCheck);
   if (k.wg_trials && !k.use_band) {
-    if (mask & 1)
-      k_probes_wg<float><<<k.nb, kProbeGroups * kBlock, 0, s>>>(k.it32.xh, k.it32.xbar, k.it32.yh, k.it32.ybar, k.cgty0,
-                                                                k.cgty1, k.cgx0, k.cgx1, k.d64, k.inst, kFP32,
-                                                                k.probe_passes);
-    if (mask & 2)
-      k_probes_wg<double><<<k.nb, kProbeGroups * kBlock, 0, s>>>(k.it64.xh, k.it64.xbar, k.it64.yh, k.it64.ybar, k.cgty0,
-                                                                 k.cgty1, k.cgx0, k.cgx1, k.d64, k.inst, kFP64,
-                                                                 k.probe_passes);
+    if (mask & 1) launch_probes_wg_t<float>(k, s, kFP32, k.it32);
+    if (mask & 2) launch_probes_wg_t<double>(k, s, kFP64, k.it64);
   } else {
     for (int pass = 0; pass < k.probe_passes; ++pass) {
       if (mask & 1) launch_probe_t<float>(k, s, kFP32, k.it32);
       if (mask & 2) launch_probe_t<double>(k, s, kFP64, k.it64);
       k_probe_fin<<<grid1(k.nb), kProbeGroups * kBlock, 0, s>>>(k.ccol, k.rec_probe_c, k.crow, k.rec_probe_r, k.inst);
     }
+    k_decide<<<nbt, 64, 0, s>>>(k.inst, k.nb);
   }
-  k_decide<<<nbt, 64, 0, s>>>(k.inst, k.nb);
+  if (small) {
+    if (k.infeas) launch_ray_products(k, s);
+    if (mask & 1) k_check_wg<float><<<grid1(k.nb), kBlock, 0, s>>>(k, kFP32);
+    if (mask & 2) k_check_wg<double><<<grid1(k.nb), kBlock, 0, s>>>(k, kFP64);
+    return;
+  }
   if (k.infeas) launch_ray(k, s, mask);
   if (mask & 1) launch_restart_t<float>(k, s, kFP32, k.it32);
   if (mask & 2) launch_restart_t<double>(k, s, kFP64, k.it64);
@@ -3949,6 +4159,7 @@ void launch_eval(const KernelCtx& k, hipStream_t s, int mask, int final_mode) {
   const int nbt = (k.nb + 63) / 64;
   if (mask & 1) launch_eval_t<float>(k, s, kFP32, k.it32, mode);
   if (mask & 2) launch_eval_t<double>(k, s, kFP64, k.it64, mode);
+  if (small_instances(k)) return;
   k_cand_fin<<<grid1(k.nb), kBlock, 0, s>>>(k.vcol, k.rec_cand_c, k.vrow, k.rec_cand_r, k.inst, mode);
   k_eval_fin<<<nbt, 64, 0, s>>>(k.inst, k.nb, mode);
   if (mask & 1) launch_eval_out_t<float>(k, s, kFP32, k.it32, mode);
@@ -4031,6 +4242,12 @@ void launch_setup(const KernelCtx& k, const SetupCtx& su, hipStream_t s, int mas
     }
     launch_scale_values(k, su, s, su.rec_nm);
   }
+  if (small_instances(k) && (mask == 1 || mask == 2)) {
+    if (mask == 1) k_start_wg<float><<<grid1(k.nb), kBlock, 0, s>>>(k, su, kFP32);
+    else k_start_wg<double><<<grid1(k.nb), kBlock, 0, s>>>(k, su, kFP64);
+    launch_eval(k, s, mask, 0);
+    return;
+  }
   k_scale_vectors<<<grid1(k.vcol.nblk + k.vrow.nblk), kBlock, 0, s>>>(k.vcol, k.vrow, su.c, su.l, su.u, su.h, k.D1, k.D2,
                                                                       su.d64m, su.d32m, su.rec_nc, su.rec_nr);
   k_init_inst<<<grid1(k.nb), kBlock, 0, s>>>(k.vcol, su.rec_nc, k.vrow, su.rec_nr,
@@ -4052,6 +4269,7 @@ void launch_setup(const KernelCtx& k, const SetupCtx& su, hipStream_t s, int mas
   }
   // FP64-value products of the start point: eval mode computes cgx0 = G x_hat, cgty0 = G^T y_hat
   launch_eval(k, s, mask, 0);
+  if (small_instances(k)) return;
   if (mask & 1) k_set_products<float><<<blocks(k.M + k.N), tpb, 0, s>>>(k.it32, k.cgty0, k.N, k.cgx0, k.M);
   if (mask & 2) k_set_products<double><<<blocks(k.M + k.N), tpb, 0, s>>>(k.it64, k.cgty0, k.N, k.cgx0, k.M);
 }
