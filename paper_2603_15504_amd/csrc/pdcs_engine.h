@@ -132,10 +132,16 @@ struct IterBufs {
   void alloc(int64_t N, int64_t M);
 };
 
+// Outputs up to this size reach the host by the launch that copies them on the
+// device; a wait and a copy for each were 20 us apiece (three vectors, the records
+// and a summary per chunk).  Larger ones are not written over the bus unasked.
+constexpr size_t kStageLimit = 256 << 10;
+
 // Device copies of one solve's outputs, shared by the results of a batch.
 struct OutBlock {
   int64_t M = 0, N = 0;
   DBuf all;  // x, y, lam, D1 and D2
+  std::vector<double> host;  // x, lam, y of a small single solve, else empty
   double *x = nullptr, *y = nullptr, *lam = nullptr, *D1 = nullptr, *D2 = nullptr;
   DBuf st[2][8];  // [fp64, fp32] x [x, y, x_hat, y_hat, x_a, y_a, G^T y_hat, G x_hat]
 };
@@ -165,12 +171,16 @@ struct Engine {
   DBuf D1, D2, cgx0, cgx1, cgty0, cgty1, xout, yout, lamout, stat_r, stat_c;
   DBuf rec_primal, rec_dual, rec_lam, rec_cand_c, rec_cand_r, rec_probe_c, rec_probe_r;
   DBuf rec_nc, rec_nr, rec_nm;
-  DBuf d_inst, d_inst2, d_summary, warm_x, warm_y, d_trace;
+  DBuf d_inst, d_inst2, warm_x, warm_y, d_trace;
   DBuf d_row0i, d_col0i, warm_ptr, d_flag;       // instance offsets, device warm-start pointer table
   DBuf xs0, ys0, rx, ry, rgx, rgty;              // infeasibility rays (FP64)
   bool any_unbounded = false;                    // some column has an infinite bound
   int infeas_on = 0;                             // the running solve runs the infeasibility tests
+  // Pinned, written by kernels: the summary of a chunk (k_summary), and where
+  // stage_bytes is nonzero a solve's instance records and outputs.
   int32_t* h_summary = nullptr;
+  double* h_stage = nullptr;
+  size_t stage_bytes = 0;
   IterBufs<float> it32;
   IterBufs<double> it64;
   Schedule sched;

@@ -682,7 +682,6 @@ Engine::Engine(const std::vector<const HostProblem*>& probs) {
   for (DBuf* bf : {&c32, &l32, &u32}) bf->alloc((size_t)N * 4);
   d_inst.alloc(sizeof(Inst) * (size_t)std::max(B, 1));
   d_inst2.alloc(sizeof(Inst) * (size_t)std::max(B, 1));
-  d_summary.alloc(16);
   {
     std::vector<int32_t> r0i(row0.begin(), row0.end()), c0i(col0.begin(), col0.end());
     upload(d_row0i, r0i);
@@ -712,7 +711,10 @@ Engine::Engine(const std::vector<const HostProblem*>& probs) {
   }
   vrow.soc = &soc;
   crow.soc = &soc;
-  HIP_OK(hipHostMalloc((void**)&h_summary, 16, hipHostMallocDefault));
+  stage_bytes = sizeof(Inst) * (size_t)B + (B == 1 ? (size_t)(2 * N + M) * 8 : 0);
+  if (stage_bytes > kStageLimit) stage_bytes = 0;
+  HIP_OK(hipHostMalloc((void**)&h_summary, 64 + stage_bytes, hipHostMallocDefault));
+  h_stage = reinterpret_cast<double*>(h_summary + 16);
   build_schedule();
 }
 
@@ -988,13 +990,13 @@ void Engine::enqueue_chunk(const KernelCtx& k, int mask, int64_t K, bool timed) 
   if (k.wg_trials && !k.use_band && !timed) {  // timed runs keep the per-pass launches
     launch_trials_wg(k, stream, mask, (int)K);
     launch_check(k, stream, mask);
-    launch_summary(k, stream, d_summary.as<int32_t>());
+    launch_summary(k, stream, h_summary);
     return;
   }
   if (k.fold && !timed) {
     launch_trials_fold(k, stream, mask, (int)K);
     launch_check(k, stream, mask);
-    launch_summary(k, stream, d_summary.as<int32_t>());
+    launch_summary(k, stream, h_summary);
     return;
   }
   for (int64_t s = 0; s < K; ++s) {
@@ -1017,7 +1019,7 @@ void Engine::enqueue_chunk(const KernelCtx& k, int mask, int64_t K, bool timed) 
     launch_trial_part(k, stream, mask, 2);
   }
   launch_check(k, stream, mask);
-  launch_summary(k, stream, d_summary.as<int32_t>());
+  launch_summary(k, stream, h_summary);
 }
 
 void Engine::harvest_events() {
@@ -1179,7 +1181,7 @@ std::vector<pdcs_result> Engine::solve(const pdcs_options& o, const WarmStart& w
   timed_ms = 0.0;
   timed_count = 0;
   ev_used = 0;
-  launch_summary(k, stream, d_summary.as<int32_t>());
+  launch_summary(k, stream, h_summary);
   int64_t chunks = 0;
   int64_t printed = 0;  // progress lines written (verbose = 1: one per print_freq trials)
   // Retire-and-compact: when the active instances of a batch have halved
@@ -1188,7 +1190,6 @@ std::vector<pdcs_result> Engine::solve(const pdcs_options& o, const WarmStart& w
   int active_built = B;
   bool compacted = false;
   while (true) {
-    HIP_OK(hipMemcpyAsync(h_summary, d_summary.p, 8, hipMemcpyDeviceToHost, stream));
     HIP_OK(hipStreamSynchronize(stream));
     if (timed) harvest_events();
     const int a32 = h_summary[0], a64 = h_summary[1];
@@ -1263,7 +1264,7 @@ std::vector<pdcs_result> Engine::solve(const pdcs_options& o, const WarmStart& w
   if (o.keep_state) launch_flush_commit(k, stream, alloc_mask);
   HIP_OK(hipGetLastError());
   std::vector<Inst> fin(B);
-  HIP_OK(hipMemcpyAsync(fin.data(), d_inst.p, sizeof(Inst) * B, hipMemcpyDeviceToHost, stream));
+  if (!stage_bytes) HIP_OK(hipMemcpyAsync(fin.data(), d_inst.p, sizeof(Inst) * B, hipMemcpyDeviceToHost, stream));
   // results own a device copy of the outputs
   auto out = std::make_shared<OutBlock>();
   out->M = M;
@@ -1276,12 +1277,19 @@ std::vector<pdcs_result> Engine::solve(const pdcs_options& o, const WarmStart& w
   out->D2 = out->lam + padded(N);
   out->y = out->D2 + padded(N);
   out->D1 = out->y + padded(M);
-  const CopyItem copies[5] = {{xout.as<double>(), out->x, N},
+  static_assert(sizeof(Inst) % 8 == 0, "instance records are copied as doubles");
+  const int64_t irec = (int64_t)B * (int64_t)(sizeof(Inst) / 8);
+  const CopyItem copies[9] = {{xout.as<double>(), out->x, N},
                               {lamout.as<double>(), out->lam, N},
                               {D2.as<double>(), out->D2, N},
                               {yout.as<double>(), out->y, M},
-                              {D1.as<double>(), out->D1, M}};
-  launch_copies(copies, 5, stream);
+                              {D1.as<double>(), out->D1, M},
+                              // small: the host's copies by the same launch
+                              {d_inst.as<double>(), h_stage, irec},
+                              {xout.as<double>(), h_stage + irec, N},
+                              {lamout.as<double>(), h_stage + irec + N, N},
+                              {yout.as<double>(), h_stage + irec + 2 * N, M}};
+  launch_copies(copies, !stage_bytes ? 5 : B == 1 ? 9 : 6, stream);
   HIP_OK(hipGetLastError());
   if (o.keep_state) {
     for (int pi = 0; pi < 2; ++pi) {
@@ -1306,6 +1314,10 @@ std::vector<pdcs_result> Engine::solve(const pdcs_options& o, const WarmStart& w
     }
   }
   HIP_OK(hipStreamSynchronize(stream));
+  if (stage_bytes) {
+    std::memcpy(fin.data(), h_stage, sizeof(Inst) * (size_t)B);
+    if (B == 1) out->host.assign(h_stage + irec, h_stage + irec + 2 * N + M);
+  }
   const double elapsed = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
   std::vector<pdcs_result> res(B);
   for (int b = 0; b < B; ++b) {
@@ -1538,24 +1550,29 @@ int pdcs_project_cone(int64_t cone, int64_t dim, int64_t count, const double* v,
     if (!v || !f || !out) throw Error(PDCS_ERR_INVALID_ARG, "null array");
     if (dim > ((int64_t)1 << 24) || count > ((int64_t)1 << 28) / dim)
       throw Error(PDCS_ERR_SIZE, "count * dim must be <= 2^28");
-    for (int64_t i = 0; i < dim * count; ++i) {
+    // (a loop without exits, four values an instruction; which check fails is found only when one does)
+    const double largest = std::numeric_limits<double>::max();
+    int64_t bad = 0;
+    for (int64_t i = 0; i < dim * count; ++i)
+      bad |= (int64_t)(!(f[i] > 0.0) | !(f[i] <= largest) | !(std::fabs(v[i]) <= largest));
+    for (int64_t i = 0; bad && i < dim * count; ++i) {
       if (!(f[i] > 0.0) || !std::isfinite(f[i])) throw Error(PDCS_ERR_INVALID_ARG, "factors must be finite and > 0");
       if (!std::isfinite(v[i])) throw Error(PDCS_ERR_INVALID_ARG, "points must be finite");
     }
     const size_t bytes = (size_t)count * dim * sizeof(double);
-    DBuf dv, df, dout;
-    dv.alloc(bytes);
-    df.alloc(bytes);
-    dout.alloc(bytes);
-    HIP_OK(hipMemcpy(dv.p, v, bytes, hipMemcpyHostToDevice));
-    HIP_OK(hipMemcpy(df.p, f, bytes, hipMemcpyHostToDevice));
+    DBuf all;
+    const size_t part = (bytes + 255) / 256 * 32;  // doubles
+    all.alloc(3 * part * sizeof(double));
+    double *dv = all.as<double>(), *df = dv + part, *dout = df + part;
+    HIP_OK(hipMemcpy(dv, v, bytes, hipMemcpyHostToDevice));
+    HIP_OK(hipMemcpy(df, f, bytes, hipMemcpyHostToDevice));
     hipEvent_t ev[2] = {nullptr, nullptr};
     if (kernel_ms) {
       HIP_OK(hipEventCreate(&ev[0]));
       HIP_OK(hipEventCreate(&ev[1]));
       HIP_OK(hipEventRecord(ev[0], nullptr));
     }
-    launch_proj_cone((int)cone, (int)dim, dv.as<double>(), df.as<double>(), dout.as<double>(), count, nullptr);
+    launch_proj_cone((int)cone, (int)dim, dv, df, dout, count, nullptr);
     hipError_t le = hipGetLastError();
     if (kernel_ms) {
       float ms = 0.0f;
@@ -1568,7 +1585,7 @@ int pdcs_project_cone(int64_t cone, int64_t dim, int64_t count, const double* v,
       *kernel_ms = ms;
     }
     HIP_OK(le);
-    HIP_OK(hipMemcpy(out, dout.p, bytes, hipMemcpyDeviceToHost));
+    HIP_OK(hipMemcpy(out, dout, bytes, hipMemcpyDeviceToHost));
     return PDCS_OK;
   });
 }
@@ -1756,10 +1773,17 @@ int pdcs_result_info(pdcs_result r, pdcs_info* out) {
   });
 }
 
-static void copy_out(const double* src, int64_t off, int64_t len, double* dst, int64_t want) {
+// (host: the host's copy of src + off, or null)
+static void copy_out(const double* src, int64_t off, int64_t len, double* dst, int64_t want,
+                     const double* host = nullptr) {
   if (!dst) throw Error(PDCS_ERR_INVALID_ARG, "destination is null");
   if (want != len) throw Error(PDCS_ERR_INVALID_ARG, "length mismatch");
-  if (len > 0) HIP_OK(hipMemcpy(dst, src + off, (size_t)len * 8, hipMemcpyDeviceToHost));
+  if (host) std::memcpy(dst, host, (size_t)len * 8);
+  else if (len > 0) HIP_OK(hipMemcpy(dst, src + off, (size_t)len * 8, hipMemcpyDeviceToHost));
+}
+
+static const double* host_copy(pdcs_result r, int64_t at) {
+  return r->out->host.empty() ? nullptr : r->out->host.data() + at;
 }
 
 static void copy_out_device(const double* src, int64_t off, int64_t len, double* dst, int64_t want, void* stream) {
@@ -1820,7 +1844,7 @@ int pdcs_results_device(int64_t count, const pdcs_result* results, pdcs_info* in
 int pdcs_result_primal(pdcs_result r, double* x, int64_t n) {
   return guarded([&]() {
     if (!r) throw Error(PDCS_ERR_INVALID_ARG, "result is null");
-    copy_out(r->out->x, r->col0, r->n, x, n);
+    copy_out(r->out->x, r->col0, r->n, x, n, host_copy(r, 0));
     return PDCS_OK;
   });
 }
@@ -1829,7 +1853,7 @@ int pdcs_result_dual(pdcs_result r, double* y, int64_t m) {
   return guarded([&]() {
     if (!r) throw Error(PDCS_ERR_INVALID_ARG, "result is null");
     if (r->m == 0 && m == 0) return PDCS_OK;
-    copy_out(r->out->y, r->row0, r->m, y, m);
+    copy_out(r->out->y, r->row0, r->m, y, m, host_copy(r, 2 * r->n));
     return PDCS_OK;
   });
 }
@@ -1837,7 +1861,7 @@ int pdcs_result_dual(pdcs_result r, double* y, int64_t m) {
 int pdcs_result_slack(pdcs_result r, double* lam, int64_t n) {
   return guarded([&]() {
     if (!r) throw Error(PDCS_ERR_INVALID_ARG, "result is null");
-    copy_out(r->out->lam, r->col0, r->n, lam, n);
+    copy_out(r->out->lam, r->col0, r->n, lam, n, host_copy(r, r->n));
     return PDCS_OK;
   });
 }

@@ -15,6 +15,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <random>
 #include <vector>
 
@@ -812,11 +813,46 @@ struct pdcs_mlp_s {
   // gradient's column sums per 64 rows and the loss partials
   DBuf u16, h1_16, h2_16, dv16, dz16a, dz16b, dh, colpart, part, lossp;
   float* loss_host = nullptr;  // pinned: the loss is stored where the host reads it
+  // pinned pieces through which the parameters reach the host (get_params)
+  static constexpr int64_t kPiece = 1 << 18;  // floats
+  std::mutex stage_lock;
+  float* stage = nullptr;
+  hipEvent_t stage_ev[2] = {nullptr, nullptr};
   size_t part_bytes = 0;
   hipStream_t stream = nullptr;
 
+  // In two pinned pieces by turns: the copy of one under the transfer of the other.
+  // (32 training steps at 6000 -> 512 -> 512 -> 6000 and their 25.6 MB of parameters:
+  // 5690 us by one hipMemcpy, 5200 here.)
+  void params_to_host(float* dst) {
+    std::lock_guard<std::mutex> hold(stage_lock);
+    const float* src = params.as<float>();
+    if (np < 4 * kPiece) {
+      HIP_OK(hipMemcpy(dst, src, np * 4, hipMemcpyDeviceToHost));
+      return;
+    }
+    if (!stage) HIP_OK(hipHostMalloc((void**)&stage, 2 * kPiece * sizeof(float), hipHostMallocDefault));
+    for (hipEvent_t& e : stage_ev)
+      if (!e) HIP_OK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    auto fetch = [&](int64_t i) {
+      const int64_t n = std::min(kPiece, np - i * kPiece);
+      HIP_OK(hipMemcpyAsync(stage + (i & 1) * kPiece, src + i * kPiece, n * 4, hipMemcpyDeviceToHost, stream));
+      HIP_OK(hipEventRecord(stage_ev[i & 1], stream));
+    };
+    const int64_t pieces = (np + kPiece - 1) / kPiece;
+    fetch(0);
+    for (int64_t i = 0; i < pieces; ++i) {
+      if (i + 1 < pieces) fetch(i + 1);
+      HIP_OK(hipEventSynchronize(stage_ev[i & 1]));
+      std::memcpy(dst + i * kPiece, stage + (i & 1) * kPiece, (size_t)std::min(kPiece, np - i * kPiece) * 4);
+    }
+  }
+
   ~pdcs_mlp_s() {
     if (loss_host) (void)hipHostFree(loss_host);
+    if (stage) (void)hipHostFree(stage);
+    for (hipEvent_t e : stage_ev)
+      if (e) (void)hipEventDestroy(e);
     if (stream) (void)hipStreamDestroy(stream);
   }
 
@@ -1210,7 +1246,7 @@ int pdcs_mlp_get_params(pdcs_mlp net, float* params_host) {
   try {
     if (!net || !params_host) throw Error(PDCS_ERR_INVALID_ARG, "null argument");
     HIP_OK(hipDeviceSynchronize());
-    HIP_OK(hipMemcpy(params_host, net->params.p, net->np * 4, hipMemcpyDeviceToHost));
+    net->params_to_host(params_host);
     return PDCS_OK;
   } catch (const Error& e) {
     set_last_error(e.what());
