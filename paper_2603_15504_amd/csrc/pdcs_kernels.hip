@@ -782,7 +782,9 @@ struct FoldLs {
       fin_ls_apply(*S, ps, qs, f2, first);
     }
     __syncthreads();
-    if (first) inst_copy_out(f.out + iid, S);
+    // (in a batch whose instances iterate in both precisions the other one's pass follows:
+    // it must not put back the record it read)
+    if (first && S->precision == prec) inst_copy_out(f.out + iid, S);
   }
 };
 
