@@ -113,6 +113,7 @@ struct BandSet {
   int ntile = 0, nslot = 0, slots = 1;
   int64_t R = 0, nent = 0;
   DBuf tile0;  // first tile per instance
+  std::vector<int32_t> h_tile0;
   DBuf slot, fold, pk, src;
   DBuf val32, val64, part32, part64, part64b;
   DBuf orig32, orig64;  // unscaled values (plain products), filled by Engine::prepare_plain
@@ -214,6 +215,7 @@ struct Engine {
   void clear_graphs();
   void ensure_iter(int prec);
   bool fold_trials(bool band) const;
+  bool fold_tiles() const;
   KernelCtx ctx(int probe_passes) const;
   SetupCtx setup_ctx(const pdcs_options& o);
   void enqueue_chunk(const KernelCtx& k, int mask, int64_t K, bool timed);

@@ -577,6 +577,7 @@ void BandSet::build(const std::vector<int64_t>& r0s, const std::vector<int64_t>&
   for (int t = ntile - 1; t >= 0; --t) first[bb.tile[t].inst] = t;
   for (int b = NB - 1; b >= 0; --b) first[b] = std::min(first[b], first[b + 1]);
   upload(tile0, first);
+  h_tile0 = first;
   upload(slot, sl);
   upload(fold, bb.fold);
   upload(pk, bb.pk);
@@ -779,7 +780,7 @@ void Engine::build_schedule() {
               (layout == PDCS_LAYOUT_WORKGROUP || (layout == PDCS_LAYOUT_AUTO && lds_bytes[1] > 0));
   if (!wg_trials) lds_bytes[0] = lds_bytes[1] = 0;
   rec_dual_epi.alloc((size_t)std::max(vrow.nblk, 1) * 4 * 8);
-  rec_lam_epi.alloc((size_t)std::max(vcol.nblk, 1) * 3 * 8);
+  rec_lam_epi.alloc((size_t)std::max({vcol.nblk, band2.ntile, 1}) * 3 * 8);
   const int nr = std::max(brow.nblk, 1), nc = std::max(bcol.nblk, 1);
   const int vr = std::max(vrow.nblk, 1), vc = std::max(vcol.nblk, 1);
   rec_primal.alloc((size_t)vc * 2 * 8);
@@ -845,6 +846,20 @@ bool Engine::fold_trials(bool band) const {
   return bytes <= ((int64_t)64 << 20);
 }
 
+// Whether the dual-slack epilogue ends the tiles of G^T: one window (a row's sum is one
+// tile's), and the records of the tiles within the limits above.
+bool Engine::fold_tiles() const {
+  if (band2.P != 1 || (int)band2.h_tile0.size() != B + 1) return false;
+  const std::vector<int32_t>&p = vcol.h_iblk0, &d = vrow.h_iblk0;
+  int64_t bytes = 0;
+  for (int b = 0; b < B; ++b) {
+    const int64_t np = p[b + 1] - p[b], nd = d[b + 1] - d[b], nt = band2.h_tile0[b + 1] - band2.h_tile0[b];
+    if (nt > kFoldRecords) return false;
+    bytes += nt * (2 * np + 4 * nd) * 8 + np * 3 * nt * 8;
+  }
+  return bytes <= ((int64_t)64 << 20);
+}
+
 KernelCtx Engine::ctx(int probe_passes) const {
   KernelCtx k{};
   k.nb = B;
@@ -899,6 +914,8 @@ KernelCtx Engine::ctx(int probe_passes) const {
   k.rgty = rgty.as<double>();
   k.use_band = use_band && !band_suspended ? 1 : 0;
   k.fold = fold_trials(k.use_band != 0) ? 1 : 0;
+  k.band_lam = k.fold && k.use_band && fold_tiles() ? 1 : 0;
+  k.band2_tile0 = band2.tile0.as<int32_t>();
   if (k.use_band) {
     k.band1 = band1.view();
     k.band2 = band2.view();

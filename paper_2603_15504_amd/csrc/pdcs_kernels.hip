@@ -1103,9 +1103,9 @@ struct SumSquares {
   static __device__ __forceinline__ double join(double a, double b) { return a + b; }
 };
 
-// One wave's band-tile t: part[panel * R + r] = sum (or what OP joins) over the
-// tile's entries of row r of val * x[col], values TV, gathered vector TX,
-// accumulation and output TA.  skip() tells, once the first entries are under
+// One wave's band-tile t: sums (or what OP joins) over the tile's entries of each row r
+// of val * x[col], values TV, gathered vector TX, accumulation and output TA.  put(r, s)
+// takes those of rows r + k * kWave (while below t.nrows) of the tile.  skip() tells, once the first entries are under
 // way, whether the tile is left out.
 //
 // What a tile pays besides its entries: the descriptor and the instance's state,
@@ -1122,12 +1122,13 @@ struct SumSquares {
 // the first of these took 10.5 us, but the last 36.1 and G x of the second 78 for 72,
 // and 23 and 48 with all lanes of a gather at one address: the lines that the gathers
 // touch bound them.
-template <typename TV, typename TX, typename TA, class OP = SumProduct, class Skip>
+constexpr int kBandFold = 8;  // rows per lane and step of a tile's end
+template <typename TV, typename TX, typename TA, class OP = SumProduct, class Skip, class Put>
 __device__ __forceinline__ void band_tile_product(const BandTiles& bt, const BandTile& t, TA* a,
                                                   const TV* __restrict__ val, const TX* __restrict__ x,
-                                                  TA* __restrict__ part, int64_t R, Skip skip) {
+                                                  Skip skip, Put put) {
   constexpr int U = kBandUnroll;
-  constexpr int F = 8;  // rows per lane and step of the end
+  constexpr int F = kBandFold;
   const int lane = threadIdx.x & (kWave - 1);
   const TX* xs = x + t.col0;
   const int nit = t.nit;
@@ -1197,7 +1198,6 @@ __device__ __forceinline__ void band_tile_product(const BandTiles& bt, const Ban
     }
   }
   // each row's slot, then its extra slots in order
-  TA* out = part + (size_t)t.panel * R + t.row0;
   for (int r = lane; r - lane < nr; r += F * kWave) {
     uint32_t g[F];
 #pragma unroll
@@ -1223,12 +1223,24 @@ __device__ __forceinline__ void band_tile_product(const BandTiles& bt, const Ban
           if (q + j < f[k] >> 16) s[k] = OP::join(s[k], e[k][j]);
     }
 #pragma unroll
-    for (int k = 0; k < F; ++k) {
-      if (r + k * kWave < nr) out[r + k * kWave] = s[k];
-      f[k] = g[k];
-    }
+    for (int k = 0; k < F; ++k) f[k] = g[k];
+    put(r, s);
   }
 }
+
+// The tile's sums into its window's partial sums.
+template <typename TA>
+struct PutPart {
+  TA* out;
+  int nr;
+  __device__ __forceinline__ PutPart(const BandTile& t, TA* part, int64_t R)
+      : out(part + (size_t)t.panel * R + t.row0), nr(t.nrows) {}
+  __device__ __forceinline__ void operator()(int r, const TA (&s)[kBandFold]) const {
+#pragma unroll
+    for (int k = 0; k < kBandFold; ++k)
+      if (r + k * kWave < nr) out[r + k * kWave] = s[k];
+  }
+};
 
 // Trial products (K1: G x_hat, K2: G^T y_hat) in the iterate precision T.
 template <typename T>
@@ -1238,12 +1250,13 @@ __global__ __launch_bounds__(kWave) void k_band_spmv(BandTiles bt, const T* __re
                                                                   int prec, int need_acc) {
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
   const BandTile t = bt.slot[blockIdx.x];  // (an idle slot has no entries and no rows)
-  band_tile_product<T, T, T>(bt, t, reinterpret_cast<T*>(dyn), val, x, part, R, [&] {
+  const auto skip = [&] {
     if (!inst) return false;
     // solver passes: only instances iterating in this precision (and accepted, for G^T y)
     const Inst& I = inst[t.inst];
     return I.status != kActive || I.precision != prec || (need_acc && I.last_acc == 0);
-  });
+  };
+  band_tile_product<T, T, T>(bt, t, reinterpret_cast<T*>(dyn), val, x, skip, PutPart<T>(t, part, R));
 }
 
 // Check / evaluation products with FP64 values of vectors in the iterate
@@ -1256,11 +1269,12 @@ __global__ __launch_bounds__(kWave) void k_band_cand(BandTiles bt, const double*
                                                                   int which) {
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
   const BandTile t = bt.slot[blockIdx.x];  // (an idle slot has no entries and no rows)
-  band_tile_product<double, TX, double>(bt, t, reinterpret_cast<double*>(dyn), val, x, part, R, [&] {
+  const auto skip = [&] {
     const Inst& I = inst[t.inst];
     return !mode_selects(I, mode) || !prec_selects(I, mode, prec) ||
            (which == 1 && mode == kModeCheck && I.use_avg == 0);
-  });
+  };
+  band_tile_product<double, TX, double>(bt, t, reinterpret_cast<double*>(dyn), val, x, skip, PutPart<double>(t, part, R));
 }
 
 // Window sums of the check / evaluation products (G^T y, then G x), per instance;
@@ -1537,6 +1551,92 @@ __global__ __launch_bounds__(kBlock) void k_lam_epi_fold(Ranges R, const T* __re
       if (q0 + u * kBlock < j1) lam_epilogue<T>(q0 + u * kBlock, s[u], it, o[u], acc);
   }
   block_sum_store<3>(acc, lds, rec + (size_t)b * 3);
+}
+
+// The line-search decision by one wave: as FoldLs, in the same order.
+template <int NV>
+__device__ __forceinline__ void wave_records(const double* __restrict__ rec, int b0, int b1, double (&v)[NV]) {
+  const int lane = threadIdx.x & (kWave - 1);
+  double a[kWavesPerBlock][NV];
+#pragma unroll
+  for (int w = 0; w < kWavesPerBlock; ++w) {
+    const int k0 = b0 + w * kWave + lane, k1 = k0 + kBlock;
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      a[w][i] = (k0 < b1 ? rec[(size_t)k0 * NV + i] : 0.0) + (k1 < b1 ? rec[(size_t)k1 * NV + i] : 0.0);
+  }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] = wave_sum(a[0][i]);
+#pragma unroll
+  for (int w = 1; w < kWavesPerBlock; ++w)
+#pragma unroll
+    for (int i = 0; i < NV; ++i) v[i] += wave_sum(a[w][i]);
+}
+
+__device__ __forceinline__ void wave_decide(const FoldIn& f, int iid, Inst* S, double* pf, int prec, bool first) {
+  const int lane = threadIdx.x & (kWave - 1);
+  for (int i = lane; i < kInstWords; i += kWave)
+    reinterpret_cast<uint64_t*>(S)[i] = reinterpret_cast<const uint64_t*>(f.in + iid)[i];
+  double p[2], q[4];
+  wave_records<2>(f.rec_a, f.iblk_a[iid], f.iblk_a[iid + 1], p);
+  wave_records<4>(f.rec_b, f.iblk_b[iid], f.iblk_b[iid + 1], q);
+  if (first && lane >= kWave - 2) {
+    const int e = kWave - 1 - lane;
+    pf[e] = pow((double)f.in[iid].kbar + 2.0, e ? -0.6 : -0.3);
+  }
+  __syncthreads();
+  const bool mine = S->precision == prec;
+  if (lane == 0 && S->status == kActive && mine) {
+    const double f2[2] = {first ? pf[0] : 0.5, first ? pf[1] : 0.5};
+    fin_ls_apply(*S, p, q, f2, first);
+  }
+  __syncthreads();
+  if (first && mine)
+    for (int i = lane; i < kInstWords; i += kWave)
+      reinterpret_cast<uint64_t*>(f.out + iid)[i] = reinterpret_cast<const uint64_t*>(S)[i];
+}
+
+// G^T y_hat on band tiles of one window with the dual-slack epilogue at each tile's
+// end (records per tile), the line-search decision of the trial folded in: every tile
+// takes it under its first entries, and the launch's last workgroups, one per
+// instance, write the records.  In place of the product's launch and k_lam_epi_fold's:
+// a tile's end costs about 2 us more, the launch cost 9, and a rejected trial ends before
+// its sweep.  (64 trials with 960 cone blocks 2430 -> 2310 us; 48 LPs of 1e3 to 2e4 rows
+// 6910 -> 6680; m = 2e5, n = 5e5, nnz = 5e6 7450 -> 7310.)
+template <typename T>
+__global__ __launch_bounds__(kWave) void k_band_lam_fold(BandTiles bt, const T* __restrict__ val, IterPtrs<T> it,
+                                                         DataPtrs<T> d, FoldIn f, int prec, double* __restrict__ rec) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
+  __shared__ Inst S;
+  __shared__ double pf[2];
+  if ((int)blockIdx.x >= bt.nslot) {
+    wave_decide(f, (int)blockIdx.x - bt.nslot, &S, pf, prec, true);
+    return;
+  }
+  const BandTile t = bt.slot[blockIdx.x];
+  if (t.tile < 0) return;
+  bool live = false;
+  double acc[3] = {0.0, 0.0, 0.0};
+  const auto skip = [&] {
+    wave_decide(f, t.inst, &S, pf, prec, false);
+    live = S.status == kActive && S.precision == prec && S.last_acc != 0;
+    return !live;
+  };
+  const auto put = [&](int r, const T(&s)[kBandFold]) {
+    LamCol<T> o[kBandFold];
+#pragma unroll
+    for (int k = 0; k < kBandFold; ++k) o[k] = lam_load<T>(t.row0 + min(r + k * kWave, t.nrows - 1), d);
+#pragma unroll
+    for (int k = 0; k < kBandFold; ++k)
+      if (r + k * kWave < t.nrows) lam_epilogue<T>(t.row0 + r + k * kWave, 0.0 + (double)s[k], it, o[k], acc);
+  };
+  band_tile_product<T, T, T>(bt, t, reinterpret_cast<T*>(dyn), val, (const T*)it.yh, skip, put);
+  if (!live) return;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const double s = wave_sum(acc[i]);
+    if ((threadIdx.x & (kWave - 1)) == 0) rec[(size_t)t.tile * 3 + i] = s;
+  }
 }
 
 // A chunk of K trials of one instance per workgroup (small instances, row
@@ -3415,8 +3515,8 @@ __global__ __launch_bounds__(kWave) void k_scale_bands(BandTiles b1, const doubl
   const BandTiles& bt = second ? b2 : b1;
   const BandTile t = bt.slot[(int)blockIdx.x - (second ? b1.nslot : 0)];
   double* acc = reinterpret_cast<double*>(dyn);
-  band_tile_product<double, double, double, OP>(bt, t, acc, second ? v2 : v1, second ? D1 : D2, second ? part2 : part1,
-                                                second ? N : M, [] { return false; });
+  band_tile_product<double, double, double, OP>(bt, t, acc, second ? v2 : v1, second ? D1 : D2, [] { return false; },
+                                                PutPart<double>(t, second ? part2 : part1, second ? N : M));
 }
 
 // D1 (elements [0, M)) and D2 (the next N) from the windows' statistics.
@@ -3827,6 +3927,7 @@ static void launch_band_cand(const BandTiles& bt, const double* val, const TX* x
 hipError_t band_raise_lds_limit() {
   const void* const fns[] = {reinterpret_cast<const void*>(&k_band_spmv<float>), reinterpret_cast<const void*>(&k_band_spmv<double>),
                              reinterpret_cast<const void*>(&k_band_cand<float>), reinterpret_cast<const void*>(&k_band_cand<double>),
+                             reinterpret_cast<const void*>(&k_band_lam_fold<float>), reinterpret_cast<const void*>(&k_band_lam_fold<double>),
                              reinterpret_cast<const void*>(&k_scale_bands<MaxProduct>),
                              reinterpret_cast<const void*>(&k_scale_bands<SumSquares>),
                              reinterpret_cast<const void*>(&k_scale_bands_values)};
@@ -3904,7 +4005,11 @@ static void launch_primal_fold_t(const KernelCtx& k, hipStream_t s, int prec, co
 template <typename T>
 static void launch_lam_fold_t(const KernelCtx& k, hipStream_t s, int prec, const IterPtrs<T>& it, const DataPtrs<T>& d,
                               const MatPtrs<T>& AT, T* part, const FoldIn& f) {
-  if (k.use_band) {
+  if (k.use_band && k.band_lam) {
+    if (k.band2.nslot > 0)
+      k_band_lam_fold<T><<<grid1(k.band2.nslot + k.nb), kWave, (size_t)k.band2.slots * sizeof(T), s>>>(
+          k.band2, band_val<T>(k, 1), it, d, f, prec, k.rec_lam_epi);
+  } else if (k.use_band) {
     // (whether the trial is accepted is not known yet: the product runs either way)
     launch_band_spmv<T>(k.band2, band_val<T>(k, 1), it.yh, part, k.N, k.inst, prec, 0, s);
     if (k.vcol.nblk > 0)
@@ -3919,7 +4024,7 @@ void launch_trials_fold(const KernelCtx& k, hipStream_t s, int mask, int K) {
   const bool split = k.use_band != 0;
   const FoldIn ls{k.vcol.inst_blk0, split ? k.vrow.inst_blk0 : k.brow.inst_blk0, k.rec_primal,
                   split ? k.rec_dual_epi : k.rec_dual, k.inst, k.inst2};
-  const FoldIn beta{split ? k.vcol.inst_blk0 : k.bcol.inst_blk0, nullptr, split ? k.rec_lam_epi : k.rec_lam, nullptr,
+  const FoldIn beta{split ? (k.band_lam ? k.band2_tile0 : k.vcol.inst_blk0) : k.bcol.inst_blk0, nullptr, split ? k.rec_lam_epi : k.rec_lam, nullptr,
                     k.inst2, k.inst};
   for (int t = 0; t < K; ++t) {
     if (t == 0) {

@@ -116,6 +116,8 @@ struct KernelCtx {
   int wg_trials;
   int lds_trials32, lds_trials64;
   int fold;         // trials run by launch_trials_fold
+  int band_lam;     // there, the dual-slack epilogue ends the band tiles (k_band_lam_fold)
+  const int32_t* band2_tile0;  // band2: first tile per instance (nb + 1)
   int lds_rowwise;  // every row of G and of G^T has at most kLdsRowMax entries: row-wise passes
 
   // the K1 (K2) product is split into partial sums plus an epilogue pass
