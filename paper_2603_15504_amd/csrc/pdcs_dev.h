@@ -129,9 +129,9 @@ struct alignas(16) BandTile {
   int32_t used;   // slots in use (rows + extra slots; the sink excluded)
   int32_t col0;   // window start
   int32_t panel;  // window index (partial-sum array)
+  int64_t fold0;  // first row's entry of BandTiles::fold
   int32_t inst;   // instance (bands never cross instances)
-  int32_t fold0;  // first row's entry of BandTiles::fold
-  int32_t pad[2];
+  int32_t pad;
 };
 struct BandTiles {
   const BandTile* slot;      // launch slots; slot s runs on XCD s % 8

@@ -375,7 +375,7 @@ bool build_band_tile(int64_t r0, int64_t r1, int p, int64_t c0, int64_t c1, int6
     out.pk.push_back(0u);  // padding: gets the layout's sink slot once that is known
     out.src.push_back(-1);
   }
-  if (out.pk.size() >= (size_t)INT32_MAX || out.fold.size() >= (size_t)INT32_MAX)
+  if (out.pk.size() >= (size_t)INT32_MAX)
     throw Error(PDCS_ERR_SIZE, "band tiles exceed 2^31 entries");
   BandTile t{};
   t.tile = (int32_t)out.tile.size();
@@ -387,7 +387,7 @@ bool build_band_tile(int64_t r0, int64_t r1, int p, int64_t c0, int64_t c1, int6
   t.col0 = (int32_t)c0;
   t.panel = p;
   t.inst = inst;
-  t.fold0 = (int32_t)fold0;
+  t.fold0 = (int64_t)fold0;
   out.tile.push_back(t);
   out.work.push_back((int64_t)E.size());
   return true;
