@@ -445,11 +445,10 @@ def run_c3_mlp(args, P, np):
         {"roofline": roof, "cpu_baseline": None})
 
 
-# FP64 operations of one evaluation of the ray-angle slope on the coarse scan
-# (the running e^r and e^-r, the two scaled vectors, their cross product and
-# its dot product with v), times the 64 x 24 evaluations of that scan: the
-# work every projection off the closed-form cases does at least.
-EXP_FLOPS_PER_PROJECTION = 64 * 24 * 22
+# FP64 operations of one evaluation of the ray-angle slope (e^r and e^-r, the two
+# scaled vectors, their cross product and its dot product with v), times the 7
+# evaluations that the bracketed Newton search of a projection takes as a rule.
+EXP_FLOPS_PER_PROJECTION = 7 * 22
 FP64_VECTOR_PEAK_TFLOPS = 78.6
 
 
@@ -516,7 +515,7 @@ def run_cones(args, P, np):
     log(f"exp projection: {cnt} points in {ms:.3f} ms ({cnt / ms / 1e3:.1f} M/s), {tflops:.2f} TFLOP/s FP64")
     roof = {"bound": "alu", "achieved": round(tflops, 3), "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
             "frac": round(tflops / FP64_VECTOR_PEAK_TFLOPS, 4), "traffic": None,
-            "kernel": "k_proj_cone: projection onto diag(f) K_exp, one wave per point, random points and factors",
+            "kernel": "k_proj_cone: projection onto diag(f) K_exp, one lane per point, random points and factors",
             "flops_per_projection": EXP_FLOPS_PER_PROJECTION, "points": cnt, "kernel_ms": round(ms, 4)}
     cpu = None
     if not args.no_cpu_baseline:
