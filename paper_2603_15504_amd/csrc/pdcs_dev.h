@@ -129,13 +129,13 @@ struct alignas(16) BandTile {
   int32_t used;   // slots in use (rows + extra slots; the sink excluded)
   int32_t col0;   // window start
   int32_t panel;  // window index (partial-sum array)
-  int64_t fold0;  // first row's entry of BandTiles::fold
+  int64_t fold0;  // first entry in BandTiles::fold
   int32_t inst;   // instance (bands never cross instances)
-  int32_t pad;
+  int32_t nfold;  // rows with extra slots
 };
 struct BandTiles {
   const BandTile* slot;      // launch slots; slot s runs on XCD s % 8
-  const uint32_t* fold;      // per tile and row: first extra slot | extra slots << 16
+  const uint2* fold;         // per row with extra slots: row | extra slots << 16, first extra slot
   const uint32_t* pk;        // packed entries
   int32_t nslot;             // launch slots (workgroups)
   int32_t P;                 // windows

@@ -303,7 +303,8 @@ namespace {
 struct BandBuild {
   std::vector<BandTile> tile;
   std::vector<int32_t> src;
-  std::vector<uint32_t> pk, fold;
+  std::vector<uint32_t> pk;
+  std::vector<uint2> fold;
   std::vector<int64_t> work;  // entries per band-tile
   std::vector<size_t> sizes() const {
     return {tile.size(), src.size(), pk.size(), fold.size(), work.size()};
@@ -363,7 +364,7 @@ bool build_band_tile(int64_t r0, int64_t r1, int p, int64_t c0, int64_t c1, int6
   for (int r = 0; r < nr; ++r) {
     const int32_t first = e0;
     for (int e = next[r]; e >= 0; e = next[e]) renum[(size_t)(e - nr)] = e0++;
-    out.fold.push_back((uint32_t)first | (uint32_t)(e0 - first) << 16);
+    if (e0 > first) out.fold.push_back(uint2{(uint32_t)r | (uint32_t)(e0 - first) << 16, (uint32_t)first});
   }
   constexpr uint32_t kSlotMask = (1u << kBandSlotBits) - 1u;
   for (size_t k = base; k < out.pk.size(); ++k) {
@@ -388,6 +389,7 @@ bool build_band_tile(int64_t r0, int64_t r1, int p, int64_t c0, int64_t c1, int6
   t.panel = p;
   t.inst = inst;
   t.fold0 = (int64_t)fold0;
+  t.nfold = (int32_t)(out.fold.size() - fold0);
   out.tile.push_back(t);
   out.work.push_back((int64_t)E.size());
   return true;
@@ -567,10 +569,11 @@ void BandSet::build(const std::vector<int64_t>& r0s, const std::vector<int64_t>&
       if ((slot_e >= (uint32_t)d.used && slot_e != sink) || col >= g0s[ti + 1]) fail("entry");
       if (bb.src[e] >= 0 && (bb.src[e] >= ptr[R] || idx[bb.src[e]] != col)) fail("entry source");
     }
-    if (d.fold0 < 0 || (size_t)d.fold0 + d.nrows > bb.fold.size()) fail("fold table");
-    for (int32_t r = 0; r < d.nrows; ++r) {
-      const uint32_t f = bb.fold[(size_t)d.fold0 + r], q = f & 0xFFFFu;
-      if (q < (uint32_t)d.nrows || q + (f >> 16) > (uint32_t)d.used) fail("extra slot");
+    if (d.fold0 < 0 || d.nfold < 0 || (size_t)d.fold0 + d.nfold > bb.fold.size()) fail("fold table");
+    for (int32_t r = 0; r < d.nfold; ++r) {
+      const uint2 f = bb.fold[(size_t)d.fold0 + r];
+      if ((f.x & 0xFFFFu) >= (uint32_t)d.nrows || f.y < (uint32_t)d.nrows || f.y + (f.x >> 16) > (uint32_t)d.used)
+        fail("extra slot");
     }
   }
   std::vector<int32_t> first(NB + 1, ntile);
@@ -602,7 +605,7 @@ void BandSet::reset() {
 BandTiles BandSet::view() const {
   BandTiles b{};
   b.slot = slot.as<BandTile>();
-  b.fold = fold.as<uint32_t>();
+  b.fold = fold.as<uint2>();
   b.pk = pk.as<uint32_t>();
   b.nslot = nslot;
   b.P = P;

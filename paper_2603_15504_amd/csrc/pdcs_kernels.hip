@@ -1110,13 +1110,15 @@ struct SumSquares {
 //
 // What a tile pays besides its entries: the descriptor and the instance's state,
 // the clearing of the slots, and at the end the rows' sums with their extra slots.
-// The entries do not wait for the first two.  The end reads one word per row,
-// requested before the sweep, and adds the extra slots (consecutive in LDS) of
-// eight rows a lane side by side.  (When the extra slots were listed in memory
+// The entries do not wait for the first two.  The end reads an entry per row with
+// extra slots, the first requested before the sweep, and adds the slots (consecutive
+// in LDS) of eight rows a lane side by side.  (When the extra slots were listed in memory
 // and each lane followed its rows' lists, a row of 5000 entries kept its tile 33 us
 // behind its last entry; the products of m = 6e4, n = 1.2e5, nnz = 9.6e5 took 13.1
 // and 11.3 us in FP64 and take 11.5 and 10.6, G^T y at m = 2.5e5, n = 5e5,
-// nnz = 1.35e7 58 and 53, at m = 2e5, n = 5e5, nnz = 5e6 G x 35.2 and 33.4.)
+// nnz = 1.35e7 58 and 53, at m = 2e5, n = 5e5, nnz = 5e6 G x 35.2 and 33.4.  A word
+// for every row instead of the rows with extra slots alone costs 22 us on tiles of 8192
+// rows.)
 //
 // Deeper requests are no help where it counts: with 40 to 47 loads in flight per wave
 // the first of these took 10.5 us, but the last 36.1 and G x of the second 78 for 72,
@@ -1134,8 +1136,8 @@ __device__ __forceinline__ void band_tile_product(const BandTiles& bt, const Ban
   const int nit = t.nit;
   const uint32_t* pp = bt.pk + t.start + lane;
   const TV* vp = val + t.start + lane;
-  const uint32_t* fold = bt.fold + t.fold0;
-  const int nr = t.nrows;
+  const uint2* fold = bt.fold + t.fold0;
+  const int nr = t.nrows, nf = t.nfold;
   constexpr uint32_t kSlotMask = (1u << kBandSlotBits) - 1u;
   uint32_t pA[U], pB[U], pC[U];
   TV vA[U], vB[U], vC[U];
@@ -1160,9 +1162,9 @@ __device__ __forceinline__ void band_tile_product(const BandTiles& bt, const Ban
       vB[u] = __builtin_nontemporal_load(vp + (U + u) * kWave);
     }
   }
-  uint32_t f[F];
+  uint2 f[F];
 #pragma unroll
-  for (int k = 0; k < F; ++k) f[k] = k * kWave + lane < nr ? fold[k * kWave + lane] : 0u;
+  for (int k = 0; k < F; ++k) f[k] = k * kWave + lane < nf ? fold[k * kWave + lane] : uint2{0u, 0u};
   if (skip()) return;
   // the sink slot of the padding is never read and stays uninitialized
   for (int i = lane; i < t.used; i += kWave) a[i] = TA(0);
@@ -1197,17 +1199,17 @@ __device__ __forceinline__ void band_tile_product(const BandTiles& bt, const Ban
       vB[u] = vC[u];
     }
   }
-  // each row's slot, then its extra slots in order
-  for (int r = lane; r - lane < nr; r += F * kWave) {
-    uint32_t g[F];
+  // a row's slot, then its extra slots in order
+  for (int r = lane; r - lane < nf; r += F * kWave) {
+    uint2 g[F];
 #pragma unroll
-    for (int k = 0; k < F; ++k) g[k] = r + (F + k) * kWave < nr ? fold[r + (F + k) * kWave] : 0u;
+    for (int k = 0; k < F; ++k) g[k] = r + (F + k) * kWave < nf ? fold[r + (F + k) * kWave] : uint2{0u, 0u};
     TA s[F];
     uint32_t most = 0;
 #pragma unroll
     for (int k = 0; k < F; ++k) {
-      s[k] = r + k * kWave < nr ? a[r + k * kWave] : TA(0);
-      most = max(most, f[k] >> 16);
+      s[k] = f[k].x ? a[f[k].x & 0xFFFFu] : TA(0);
+      most = max(most, f[k].x >> 16);
     }
     constexpr uint32_t E = 4;
     for (uint32_t q = 0; __any(q < most); q += E) {
@@ -1215,15 +1217,23 @@ __device__ __forceinline__ void band_tile_product(const BandTiles& bt, const Ban
 #pragma unroll
       for (int k = 0; k < F; ++k)
 #pragma unroll
-        for (uint32_t j = 0; j < E; ++j) e[k][j] = q + j < f[k] >> 16 ? a[(f[k] & 0xFFFFu) + q + j] : TA(0);
+        for (uint32_t j = 0; j < E; ++j) e[k][j] = q + j < f[k].x >> 16 ? a[f[k].y + q + j] : TA(0);
 #pragma unroll
       for (int k = 0; k < F; ++k)
 #pragma unroll
         for (uint32_t j = 0; j < E; ++j)
-          if (q + j < f[k] >> 16) s[k] = OP::join(s[k], e[k][j]);
+          if (q + j < f[k].x >> 16) s[k] = OP::join(s[k], e[k][j]);
     }
 #pragma unroll
-    for (int k = 0; k < F; ++k) f[k] = g[k];
+    for (int k = 0; k < F; ++k) {
+      if (f[k].x) a[f[k].x & 0xFFFFu] = s[k];
+      f[k] = g[k];
+    }
+  }
+  for (int r = lane; r - lane < nr; r += F * kWave) {
+    TA s[F];
+#pragma unroll
+    for (int k = 0; k < F; ++k) s[k] = a[min(r + k * kWave, nr - 1)];
     put(r, s);
   }
 }
@@ -3545,9 +3555,12 @@ __device__ __forceinline__ void band_scale_tile(const BandTiles& bt, const BandT
   const int lane = threadIdx.x & (kWave - 1);
   for (int i = lane; i < t.nrows; i += kWave) {
     const double o = D_own[t.row0 + i];
-    const uint32_t f = bt.fold[t.fold0 + i];
     own[i] = o;
-    for (uint32_t q = f & 0xFFFFu; q < (f & 0xFFFFu) + (f >> 16); ++q) own[q] = o;
+  }
+  for (int i = lane; i < t.nfold; i += kWave) {
+    const uint2 f = bt.fold[t.fold0 + i];
+    const double o = D_own[t.row0 + (int)(f.x & 0xFFFFu)];
+    for (uint32_t q = f.y; q < f.y + (f.x >> 16); ++q) own[q] = o;
   }
   if (lane == 0) own[bt.slots - 1] = 0.0;  // the padding's sink (its values are 0)
   const double* other = D_other + t.col0;
