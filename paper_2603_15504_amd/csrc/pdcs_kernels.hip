@@ -3251,10 +3251,10 @@ constexpr int kScaleLdsThreads = 1024;
 // The scaling passes work on both sides at once: each computes, from the D1 and D2
 // of the pass before, every row's and every column's statistic -- max |D1_i a_ij D2_j|
 // (Ruiz, kScaleMax) or the sum of its squares (the 2-norm pass, kScaleSquares) --
-// and from it the new factor.  A statistic of 0 keeps the factor.
+// and from it the new factor.  A statistic of 0, or beyond FP64's range, keeps the factor.
 enum { kScaleMax = 0, kScaleSquares = 1 };
 __device__ __forceinline__ double scaled_factor(double D, double stat, int mode) {
-  if (!(stat > 0.0)) return D;
+  if (!(stat > 0.0) || !(stat <= __DBL_MAX__)) return D;
   return D / (mode == kScaleMax ? sqrt(stat) : sqrt(sqrt(stat)));
 }
 
@@ -3529,21 +3529,50 @@ __global__ __launch_bounds__(kWave) void k_scale_bands(BandTiles b1, const doubl
                                                 PutPart<double>(t, second ? part2 : part1, second ? N : M));
 }
 
-// D1 (elements [0, M)) and D2 (the next N) from the windows' statistics.
-__global__ void k_scale_bands_update(double* __restrict__ D1, const double* __restrict__ part1, int P1, int64_t M,
-                                     double* __restrict__ D2, const double* __restrict__ part2, int P2, int64_t N,
-                                     int mode) {
+// D1 (elements [0, M)) and D2 (the next N) from the windows' statistics, which lack the
+// element's own factor d: |a| D_other at most, or the sum of (a D_other)^2, where the
+// statistic proper is d times the one and d^2 times the other.  Once the Ruiz passes have
+// made d about 1 / (a D_other), the squares without it leave FP64's range for rows of
+// magnitude beyond 1e154 or below 1e-154, whose scaled entries are about 1 all the same
+// (row_scale 1e-157: d^2 infinite, the factor 0).  So whatever is not well inside
+// the range -- empty rows among them -- is taken again from the element's entries, as
+// the row blocks take it; what lies inside lost at most 2^-1043 of a sum of 2^-900.
+__global__ void k_scale_bands_update(ScaleSide a, ScaleSide c, const double* __restrict__ part1, int P1, int64_t M,
+                                     const double* __restrict__ part2, int P2, int64_t N, int mode,
+                                     double* __restrict__ D1o, double* __restrict__ D2o) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= M + N) return;
-  const bool second = e >= M;
-  const int64_t i = second ? e - M : e, n = second ? N : M;
-  double* D = second ? D2 : D1;
-  const double* part = second ? part2 : part1;
-  const int P = second ? P2 : P1;
-  double s = part[i];
-  for (int p = 1; p < P; ++p) s = mode == kScaleMax ? fmax(s, part[(size_t)p * n + i]) : s + part[(size_t)p * n + i];
-  const double d = D[i];
-  D[i] = scaled_factor(d, mode == kScaleMax ? d * s : d * d * s, mode);
+  const bool live = e < M + N, second = e >= M;
+  const int i = (int)(second ? e - M : e);
+  const auto inside = [](double v) { return v >= 0x1p-900 && v <= 0x1p900; };
+  double d = 1.0, stat = 0.0;
+  bool again = false;
+  if (live) {
+    const int64_t n = second ? N : M;
+    const double* part = second ? part2 : part1;
+    const int P = second ? P2 : P1;
+    double s = part[i];
+    for (int p = 1; p < P; ++p) s = mode == kScaleMax ? fmax(s, part[(size_t)p * n + i]) : s + part[(size_t)p * n + i];
+    d = (second ? c : a).own[i];
+    const double f = mode == kScaleMax ? d : d * d;
+    stat = f * s;
+    again = !inside(s) || !inside(f) || !inside(stat);
+  }
+  const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll 1
+  for (unsigned long long left = __ballot(again); left; left &= left - 1) {  // by the whole wave
+    const int from = __ffsll(left) - 1;
+    const int j = __shfl(i, from);
+    const ScaleSide& S = __shfl((int)second, from) ? c : a;
+    const double own = __shfl(d, from);
+    double s = 0.0;
+    for (int q = S.ptr[j] + lane; q < S.ptr[j + 1]; q += kWave) {
+      const double x = S.entry(own, S.val[q], S.other[S.idx[q]]);
+      s = mode == kScaleMax ? fmax(s, fabs(x)) : s + x * x;
+    }
+    s = mode == kScaleMax ? wave_max(s) : wave_sum(s);
+    if (lane == from) stat = s;
+  }
+  if (live) (second ? D2o : D1o)[i] = scaled_factor(d, stat, mode);
 }
 
 // Scaled band-entry values from the unscaled ones (in place where src == v64), and
@@ -4321,8 +4350,10 @@ void launch_setup(const KernelCtx& k, const SetupCtx& su, hipStream_t s, int mas
   auto blocks = [&](int64_t n) { return dim3((unsigned)((n + tpb - 1) / tpb)); };
   const int passes = su.precondition ? su.ruiz_iters + (su.l2_pass ? 1 : 0) : 0;
   if (k.use_band) {
-    k_fill<<<blocks(k.M + k.N), tpb, 0, s>>>(k.D1, k.M, k.D2, k.N, 1.0);
     const unsigned slots = (unsigned)(k.band1.nslot + k.band2.nslot);
+    double *d1[2] = {k.D1, su.stat_r}, *d2[2] = {k.D2, su.stat_c};  // the last pass writes D1, D2
+    const int odd = slots > 0 ? passes & 1 : 0;
+    k_fill<<<blocks(k.M + k.N), tpb, 0, s>>>(d1[odd], k.M, d2[odd], k.N, 1.0);
     const size_t lds = (size_t)std::max(k.band1.slots, k.band2.slots) * 8;
     const double *v1 = su.borig64, *v2 = su.borigT64;
     if (!v1) {  // a batch keeps no unscaled values in entry order: they pass through the scaled ones' place
@@ -4333,14 +4364,16 @@ void launch_setup(const KernelCtx& k, const SetupCtx& su, hipStream_t s, int mas
     if (slots > 0) {
       for (int i = 0; i < passes; ++i) {
         const int mode = i < su.ruiz_iters ? kScaleMax : kScaleSquares;
+        const int to = (passes - 1 - i) & 1;
         if (mode == kScaleMax)
-          k_scale_bands<MaxProduct><<<slots, kWave, lds, s>>>(k.band1, v1, k.D2, k.bpart64, k.M, k.band2, v2,
-                                                                           k.D1, k.bpartT64, k.N);
+          k_scale_bands<MaxProduct><<<slots, kWave, lds, s>>>(k.band1, v1, d2[!to], k.bpart64, k.M, k.band2, v2, d1[!to],
+                                                              k.bpartT64, k.N);
         else
-          k_scale_bands<SumSquares><<<slots, kWave, lds, s>>>(k.band1, v1, k.D2, k.bpart64, k.M, k.band2, v2,
-                                                                           k.D1, k.bpartT64, k.N);
-        k_scale_bands_update<<<blocks(k.M + k.N), tpb, 0, s>>>(k.D1, k.bpart64, k.band1.P, k.M, k.D2, k.bpartT64,
-                                                               k.band2.P, k.N, mode);
+          k_scale_bands<SumSquares><<<slots, kWave, lds, s>>>(k.band1, v1, d2[!to], k.bpart64, k.M, k.band2, v2, d1[!to],
+                                                              k.bpartT64, k.N);
+        k_scale_bands_update<<<blocks(k.M + k.N), tpb, 0, s>>>(
+            scale_side(k, su, 0, d1[!to], d2[!to]), scale_side(k, su, 1, d1[!to], d2[!to]), k.bpart64, k.band1.P, k.M,
+            k.bpartT64, k.band2.P, k.N, mode, d1[to], d2[to]);
       }
       k_scale_bands_values<<<slots, kWave, lds, s>>>(k.band1, v1, su.bval64, su.bval32, k.band2, v2,
                                                                   su.bvalT64, su.bvalT32, k.D1, k.D2, su.rec_nm);
