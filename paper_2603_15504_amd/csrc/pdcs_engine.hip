@@ -1253,9 +1253,10 @@ std::vector<pdcs_result> Engine::solve(const pdcs_options& o, const WarmStart& w
       break;
     }
     const int mask = (a32 ? 1 : 0) | (a64 ? 2 : 0);
+    k.idle = mask == 3 || a32 + a64 < (k.use_band ? B : active_built) ? 1 : 0;  // (band tiles are not compacted)
     if (use_graph) {
       // everything that changes the captured launch sequence is in the key
-      const int64_t key = ((int64_t)mask << 48) | ((int64_t)infeas_on << 47) | (period << 8) | probe_passes;
+      const int64_t key = ((int64_t)mask << 48) | ((int64_t)infeas_on << 47) | ((int64_t)k.idle << 46) | (period << 8) | probe_passes;
       auto it = graphs.find(key);
       if (it == graphs.end()) {
         hipGraph_t g;

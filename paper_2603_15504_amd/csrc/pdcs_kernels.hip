@@ -738,6 +738,19 @@ struct FoldIn {  // the instance's records of the two passes before (dual slack:
   Inst* out;
 };
 
+// Whether a folded pass has nothing to do for an instance: one that is done, or iterates
+// in the other precision (the whole workgroup's answer).  IDLE: there are such instances
+// (the host knows when it enqueues a chunk), and every workgroup asks before it requests
+// its operands; without any, the operands do not wait for the record (0.4 us a trial of
+// m = 2e4, n = 4e4, nnz = 3e5).
+// (7 LPs of 4e4 x 8e4, 4.8e5 nonzeros, a trial on row blocks: 81 us with all running, and
+// with one running 51 asked after the operands, 27 before, where it takes 26 alone; on
+// band tiles 83, 54 and 47.)
+template <bool IDLE>
+__device__ __forceinline__ bool fold_idle(const FoldIn& f, int iid, int prec) {
+  return IDLE && (f.in[iid].status != kActive || f.in[iid].precision != prec);
+}
+
 __device__ __forceinline__ void inst_copy_in(Inst* S, const Inst* in) {
   if ((int)threadIdx.x < kInstWords)
     reinterpret_cast<uint64_t*>(S)[threadIdx.x] = reinterpret_cast<const uint64_t*>(in)[threadIdx.x];
@@ -745,6 +758,11 @@ __device__ __forceinline__ void inst_copy_in(Inst* S, const Inst* in) {
 __device__ __forceinline__ void inst_copy_out(Inst* out, const Inst* S) {
   if ((int)threadIdx.x < kInstWords)
     reinterpret_cast<uint64_t*>(out)[threadIdx.x] = reinterpret_cast<const uint64_t*>(S)[threadIdx.x];
+}
+
+// The record of an instance without work here, by the workgroup that writes it.
+__device__ __forceinline__ void fold_pass_on(const FoldIn& f, int iid, int prec, bool first) {
+  if (first && f.in[iid].precision == prec) inst_copy_out(f.out + iid, f.in + iid);
 }
 
 // The line-search decision, in the dual-slack pass.  load() before the pass's own
@@ -899,7 +917,7 @@ __device__ __forceinline__ void primal_body(int b, const Ranges& R, const IterPt
 
 // The primal pass of every trial but the first of a chunk, with the reflection
 // parameter of the trial before folded in.
-template <typename T>
+template <typename T, bool IDLE>
 __global__ __launch_bounds__(kBlock) void k_primal_fold(Ranges R, IterPtrs<T> it, DataPtrs<T> d, FoldIn f, int prec,
                                                         double* __restrict__ rec) {
   __shared__ double lds[kWavesPerBlock * 2];
@@ -907,6 +925,10 @@ __global__ __launch_bounds__(kBlock) void k_primal_fold(Ranges R, IterPtrs<T> it
   const int b = blockIdx.x, iid = R.blk_inst[b];
   const int j1 = R.blk_end[b];
   int j0 = R.blk_start[b] + (int)threadIdx.x;
+  if (fold_idle<IDLE>(f, iid, prec)) {
+    fold_pass_on(f, iid, prec, b == R.inst_blk0[iid]);
+    return;
+  }
   FoldBeta fold;
   fold.load(f, iid, &S);
   PrimalElems<T, kElems> e;
@@ -1257,7 +1279,7 @@ template <typename T>
 __global__ __launch_bounds__(kWave) void k_band_spmv(BandTiles bt, const T* __restrict__ val,
                                                                   const T* __restrict__ x, T* __restrict__ part,
                                                                   int64_t R, const Inst* __restrict__ inst,
-                                                                  int prec, int need_acc) {
+                                                                  int prec, int need_acc, int idle) {
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
   const BandTile t = bt.slot[blockIdx.x];  // (an idle slot has no entries and no rows)
   const auto skip = [&] {
@@ -1266,6 +1288,7 @@ __global__ __launch_bounds__(kWave) void k_band_spmv(BandTiles bt, const T* __re
     const Inst& I = inst[t.inst];
     return I.status != kActive || I.precision != prec || (need_acc && I.last_acc == 0);
   };
+  if (idle && skip()) return;  // (as fold_idle: before the first entries are requested)
   band_tile_product<T, T, T>(bt, t, reinterpret_cast<T*>(dyn), val, x, skip, PutPart<T>(t, part, R));
 }
 
@@ -1284,7 +1307,9 @@ __global__ __launch_bounds__(kWave) void k_band_cand(BandTiles bt, const double*
     return !mode_selects(I, mode) || !prec_selects(I, mode, prec) ||
            (which == 1 && mode == kModeCheck && I.use_avg == 0);
   };
-  band_tile_product<double, TX, double>(bt, t, reinterpret_cast<double*>(dyn), val, x, skip, PutPart<double>(t, part, R));
+  if (skip()) return;  // (once a check: its launches for instances without work cost more than the wait)
+  band_tile_product<double, TX, double>(bt, t, reinterpret_cast<double*>(dyn), val, x, [] { return false; },
+                                        PutPart<double>(t, part, R));
 }
 
 // Window sums of the check / evaluation products (G^T y, then G x), per instance;
@@ -1497,7 +1522,7 @@ __global__ __launch_bounds__(kBlock) void k_fin_beta(const int32_t* __restrict__
 }
 
 // k_lam with the line-search decision folded in.
-template <typename T, typename TM>
+template <typename T, typename TM, bool IDLE>
 __global__ __launch_bounds__(kBlock) void k_lam_fold(RowBlocks rb, MatPtrs<TM> AT, IterPtrs<T> it, DataPtrs<T> d,
                                                      FoldIn f, int prec, double* __restrict__ rec) {
   __shared__ double lds[kRowBlockCap + kWavesPerBlock * 3];
@@ -1505,6 +1530,10 @@ __global__ __launch_bounds__(kBlock) void k_lam_fold(RowBlocks rb, MatPtrs<TM> A
   const int b = blockIdx.x, iid = rb.blk_inst[b];
   __shared__ FoldLds L;
   const bool first = b == rb.inst_blk0[iid];
+  if (fold_idle<IDLE>(f, iid, prec)) {
+    fold_pass_on(f, iid, prec, first);
+    return;
+  }
   FoldLs fold;
   fold.load(f, iid, &S);
   double acc[3] = {0.0, 0.0, 0.0};
@@ -1526,7 +1555,7 @@ __global__ __launch_bounds__(kBlock) void k_lam_fold(RowBlocks rb, MatPtrs<TM> A
 }
 
 // k_lam_epi with the line-search decision folded in.
-template <typename T>
+template <typename T, bool IDLE>
 __global__ __launch_bounds__(kBlock) void k_lam_epi_fold(Ranges R, const T* __restrict__ part, int P, int64_t N,
                                                          IterPtrs<T> it, DataPtrs<T> d, FoldIn f, int prec,
                                                          double* __restrict__ rec) {
@@ -1535,6 +1564,10 @@ __global__ __launch_bounds__(kBlock) void k_lam_epi_fold(Ranges R, const T* __re
   const int b = blockIdx.x, iid = R.blk_inst[b];
   __shared__ FoldLds L;
   const bool first = b == R.inst_blk0[iid];
+  if (fold_idle<IDLE>(f, iid, prec)) {
+    fold_pass_on(f, iid, prec, first);
+    return;
+  }
   FoldLs fold;
   fold.load(f, iid, &S);
   double acc[3] = {0.0, 0.0, 0.0};
@@ -1613,7 +1646,7 @@ __device__ __forceinline__ void wave_decide(const FoldIn& f, int iid, Inst* S, d
 // a tile's end costs about 2 us more, the launch cost 9, and a rejected trial ends before
 // its sweep.  (64 trials with 960 cone blocks 2430 -> 2310 us; 48 LPs of 1e3 to 2e4 rows
 // 6910 -> 6680; m = 2e5, n = 5e5, nnz = 5e6 7450 -> 7310.)
-template <typename T>
+template <typename T, bool IDLE>
 __global__ __launch_bounds__(kWave) void k_band_lam_fold(BandTiles bt, const T* __restrict__ val, IterPtrs<T> it,
                                                          DataPtrs<T> d, FoldIn f, int prec, double* __restrict__ rec) {
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
@@ -1624,7 +1657,7 @@ __global__ __launch_bounds__(kWave) void k_band_lam_fold(BandTiles bt, const T* 
     return;
   }
   const BandTile t = bt.slot[blockIdx.x];
-  if (t.tile < 0) return;
+  if (t.tile < 0 || fold_idle<IDLE>(f, t.inst, prec)) return;
   bool live = false;
   double acc[3] = {0.0, 0.0, 0.0};
   const auto skip = [&] {
@@ -3950,10 +3983,10 @@ const double* band_val<double>(const KernelCtx& k, int which) {
 // Launches of the band-tile kernels, with the LDS of the layout's accumulators.
 template <typename T>
 static void launch_band_spmv(const BandTiles& bt, const T* val, const T* x, T* part, int64_t R, const Inst* inst, int prec,
-                             int need_acc, hipStream_t s) {
+                             int need_acc, int idle, hipStream_t s) {
   if (bt.nslot > 0)
     k_band_spmv<T><<<grid1(bt.nslot), kWave, (size_t)bt.slots * sizeof(T), s>>>(
-        bt, val, x, part, R, inst, prec, need_acc);
+        bt, val, x, part, R, inst, prec, need_acc, idle);
 }
 
 template <typename TX>
@@ -3969,7 +4002,7 @@ static void launch_band_cand(const BandTiles& bt, const double* val, const TX* x
 hipError_t band_raise_lds_limit() {
   const void* const fns[] = {reinterpret_cast<const void*>(&k_band_spmv<float>), reinterpret_cast<const void*>(&k_band_spmv<double>),
                              reinterpret_cast<const void*>(&k_band_cand<float>), reinterpret_cast<const void*>(&k_band_cand<double>),
-                             reinterpret_cast<const void*>(&k_band_lam_fold<float>), reinterpret_cast<const void*>(&k_band_lam_fold<double>),
+                             reinterpret_cast<const void*>(&k_band_lam_fold<float, false>), reinterpret_cast<const void*>(&k_band_lam_fold<float, true>), reinterpret_cast<const void*>(&k_band_lam_fold<double, false>), reinterpret_cast<const void*>(&k_band_lam_fold<double, true>),
                              reinterpret_cast<const void*>(&k_scale_bands<MaxProduct>),
                              reinterpret_cast<const void*>(&k_scale_bands<SumSquares>),
                              reinterpret_cast<const void*>(&k_scale_bands_values)};
@@ -3984,7 +4017,7 @@ template <typename T>
 static void launch_dual_t(const KernelCtx& k, hipStream_t s, int prec, const IterPtrs<T>& it,
                           const DataPtrs<T>& d, const MatPtrs<T>& A, T* part) {
   if (k.use_band) {
-    launch_band_spmv<T>(k.band1, band_val<T>(k, 0), it.xh, part, k.M, k.inst, prec, 0, s);
+    launch_band_spmv<T>(k.band1, band_val<T>(k, 0), it.xh, part, k.M, k.inst, prec, 0, k.idle, s);
   } else if (k.brow.nblk > 0) {
     k_dual<T, T><<<grid1(k.brow.nblk), kBlock, 0, s>>>(k.brow, A, it, d, k.inst, prec, k.rec_dual);
   }
@@ -4002,7 +4035,7 @@ template <typename T>
 static void launch_lam_t(const KernelCtx& k, hipStream_t s, int prec, const IterPtrs<T>& it,
                          const DataPtrs<T>& d, const MatPtrs<T>& AT, T* part) {
   if (k.use_band) {
-    launch_band_spmv<T>(k.band2, band_val<T>(k, 1), it.yh, part, k.N, k.inst, prec, 1, s);
+    launch_band_spmv<T>(k.band2, band_val<T>(k, 1), it.yh, part, k.N, k.inst, prec, 1, k.idle, s);
     if (k.vcol.nblk > 0)
       k_lam_epi<T><<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, part, k.band2.P, k.N, it, d, k.inst, prec,
                                                           k.rec_lam_epi);
@@ -4038,31 +4071,32 @@ void launch_trial_part(const KernelCtx& k, hipStream_t s, int mask, int part) {
 
 // K trials with the finalizers folded into the passes (k.fold): the instance
 // records alternate between inst and inst2 and are back in inst at the end.
-template <typename T>
+template <typename T, bool IDLE>
 static void launch_primal_fold_t(const KernelCtx& k, hipStream_t s, int prec, const IterPtrs<T>& it,
                                  const DataPtrs<T>& d, const FoldIn& f) {
-  if (k.vcol.nblk > 0) k_primal_fold<T><<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, it, d, f, prec, k.rec_primal);
+  if (k.vcol.nblk > 0) k_primal_fold<T, IDLE><<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, it, d, f, prec, k.rec_primal);
 }
 
-template <typename T>
+template <typename T, bool IDLE>
 static void launch_lam_fold_t(const KernelCtx& k, hipStream_t s, int prec, const IterPtrs<T>& it, const DataPtrs<T>& d,
                               const MatPtrs<T>& AT, T* part, const FoldIn& f) {
   if (k.use_band && k.band_lam) {
     if (k.band2.nslot > 0)
-      k_band_lam_fold<T><<<grid1(k.band2.nslot + k.nb), kWave, (size_t)k.band2.slots * sizeof(T), s>>>(
+      k_band_lam_fold<T, IDLE><<<grid1(k.band2.nslot + k.nb), kWave, (size_t)k.band2.slots * sizeof(T), s>>>(
           k.band2, band_val<T>(k, 1), it, d, f, prec, k.rec_lam_epi);
   } else if (k.use_band) {
     // (whether the trial is accepted is not known yet: the product runs either way)
-    launch_band_spmv<T>(k.band2, band_val<T>(k, 1), it.yh, part, k.N, k.inst, prec, 0, s);
+    launch_band_spmv<T>(k.band2, band_val<T>(k, 1), it.yh, part, k.N, k.inst, prec, 0, k.idle, s);
     if (k.vcol.nblk > 0)
-      k_lam_epi_fold<T><<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, part, k.band2.P, k.N, it, d, f, prec,
+      k_lam_epi_fold<T, IDLE><<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, part, k.band2.P, k.N, it, d, f, prec,
                                                                k.rec_lam_epi);
   } else if (k.bcol.nblk > 0) {
-    k_lam_fold<T, T><<<grid1(k.bcol.nblk), kBlock, 0, s>>>(k.bcol, AT, it, d, f, prec, k.rec_lam);
+    k_lam_fold<T, T, IDLE><<<grid1(k.bcol.nblk), kBlock, 0, s>>>(k.bcol, AT, it, d, f, prec, k.rec_lam);
   }
 }
 
-void launch_trials_fold(const KernelCtx& k, hipStream_t s, int mask, int K) {
+template <bool IDLE>
+static void launch_trials_fold_t(const KernelCtx& k, hipStream_t s, int mask, int K) {
   const bool split = k.use_band != 0;
   const FoldIn ls{k.vcol.inst_blk0, split ? k.vrow.inst_blk0 : k.brow.inst_blk0, k.rec_primal,
                   split ? k.rec_dual_epi : k.rec_dual, k.inst, k.inst2};
@@ -4072,16 +4106,21 @@ void launch_trials_fold(const KernelCtx& k, hipStream_t s, int mask, int K) {
     if (t == 0) {
       launch_trial_part(k, s, mask, 0);
     } else {
-      if (mask & 1) launch_primal_fold_t<float>(k, s, kFP32, k.it32, k.d32, beta);
-      if (mask & 2) launch_primal_fold_t<double>(k, s, kFP64, k.it64, k.d64, beta);
+      if (mask & 1) launch_primal_fold_t<float, IDLE>(k, s, kFP32, k.it32, k.d32, beta);
+      if (mask & 2) launch_primal_fold_t<double, IDLE>(k, s, kFP64, k.it64, k.d64, beta);
     }
     launch_trial_part(k, s, mask, 1);
     if (mask & 1) launch_dual_epi_t<float>(k, s, kFP32, k.it32, k.d32, k.bpart32);
     if (mask & 2) launch_dual_epi_t<double>(k, s, kFP64, k.it64, k.d64, k.bpart64);
-    if (mask & 1) launch_lam_fold_t<float>(k, s, kFP32, k.it32, k.d32, k.AT32, k.bpartT32, ls);
-    if (mask & 2) launch_lam_fold_t<double>(k, s, kFP64, k.it64, k.d64, k.AT64, k.bpartT64, ls);
+    if (mask & 1) launch_lam_fold_t<float, IDLE>(k, s, kFP32, k.it32, k.d32, k.AT32, k.bpartT32, ls);
+    if (mask & 2) launch_lam_fold_t<double, IDLE>(k, s, kFP64, k.it64, k.d64, k.AT64, k.bpartT64, ls);
   }
   if (K > 0) k_fold_end<<<grid1(k.nb), kBlock, 0, s>>>(beta);
+}
+
+void launch_trials_fold(const KernelCtx& k, hipStream_t s, int mask, int K) {
+  if (k.idle) launch_trials_fold_t<true>(k, s, mask, K);
+  else launch_trials_fold_t<false>(k, s, mask, K);
 }
 
 // Dynamic LDS the LDS-resident chunk kernel can take: the device's LDS per
@@ -4445,10 +4484,10 @@ void launch_band_plain(const BandTiles& bt, int prec, const void* val, const voi
   if (bt.nslot <= 0 || R <= 0) return;
   const dim3 g((unsigned)((R + 255) / 256));
   if (prec == kFP64) {
-    launch_band_spmv<double>(bt, (const double*)val, (const double*)in, (double*)part, R, nullptr, kFP64, 0, s);
+    launch_band_spmv<double>(bt, (const double*)val, (const double*)in, (double*)part, R, nullptr, kFP64, 0, 0, s);
     k_band_sum<double><<<g, 256, 0, s>>>((const double*)part, bt.P, R, (double*)out);
   } else {
-    launch_band_spmv<float>(bt, (const float*)val, (const float*)in, (float*)part, R, nullptr, kFP32, 0, s);
+    launch_band_spmv<float>(bt, (const float*)val, (const float*)in, (float*)part, R, nullptr, kFP32, 0, 0, s);
     k_band_sum<float><<<g, 256, 0, s>>>((const float*)part, bt.P, R, (float*)out);
   }
 }

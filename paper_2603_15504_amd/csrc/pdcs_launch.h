@@ -116,6 +116,7 @@ struct KernelCtx {
   int wg_trials;
   int lds_trials32, lds_trials64;
   int fold;         // trials run by launch_trials_fold
+  int idle;         // some scheduled instance is done, or both precisions iterate
   int band_lam;     // there, the dual-slack epilogue ends the band tiles (k_band_lam_fold)
   const int32_t* band2_tile0;  // band2: first tile per instance (nb + 1)
   int lds_rowwise;  // every row of G and of G^T has at most kLdsRowMax entries: row-wise passes
