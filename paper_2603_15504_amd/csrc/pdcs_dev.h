@@ -199,6 +199,14 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
+// Between an LDS access of one lane and another lane's of the same wave to the same
+// place.  The hardware executes a wave's LDS instructions in order; the fence keeps the
+// compiler from moving them past each other, and is no instruction itself.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Sum NV values over the workgroup; thread 0..NV-1 of the block write out[i].
 // lds must hold WAVES * NV doubles.  Order is fixed: deterministic.
 template <int NV, int WAVES = kWavesPerBlock>

@@ -1190,6 +1190,7 @@ __device__ __forceinline__ void band_tile_product(const BandTiles& bt, const Ban
   if (skip()) return;
   // the sink slot of the padding is never read and stays uninitialized
   for (int i = lane; i < t.used; i += kWave) a[i] = TA(0);
+  wave_lds_order();
   if (nit > 0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) xA[u] = xs[pA[u] >> kBandSlotBits];
@@ -1207,6 +1208,8 @@ __device__ __forceinline__ void band_tile_product(const BandTiles& bt, const Ban
 #pragma unroll
       for (int u = 0; u < U; ++u) xB[u] = xs[pB[u] >> kBandSlotBits];
     }
+    // (groups of kWave entries may meet in a slot, one lane's and then another's; the slots
+    // are data, so the compiler has to keep these accesses in order for each lane's own sake)
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t sl = pA[u] & kSlotMask;
@@ -1221,6 +1224,7 @@ __device__ __forceinline__ void band_tile_product(const BandTiles& bt, const Ban
       vB[u] = vC[u];
     }
   }
+  wave_lds_order();
   // a row's slot, then its extra slots in order
   for (int r = lane; r - lane < nf; r += F * kWave) {
     uint2 g[F];
@@ -1252,6 +1256,7 @@ __device__ __forceinline__ void band_tile_product(const BandTiles& bt, const Ban
       f[k] = g[k];
     }
   }
+  wave_lds_order();
   for (int r = lane; r - lane < nr; r += F * kWave) {
     TA s[F];
 #pragma unroll
@@ -2402,6 +2407,7 @@ __device__ __forceinline__ void probe_rows_body(int b, int q, const Ranges& R, c
   const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
   if (cones) {
     for (int i = lane; i < kProbeNV; i += kWave) cone_acc[wave][i] = 0.0;
+    wave_lds_order();
     double ld = 0.0, lb = 0.0;  // a lane's own blocks, all at probe lane % kProbes
     for_cone_tasks<kProbes>(R, b, [&](auto who, int r0, int dim, int kind, int p) {
       const double tp = probe_t(C, p) * sigma;
@@ -2432,10 +2438,12 @@ __device__ __forceinline__ void probe_rows_body(int b, int q, const Ranges& R, c
       ld += __shfl_xor(ld, off);
       lb += __shfl_xor(lb, off);
     }
+    wave_lds_order();
     if (lane < kProbes) {
       cone_acc[wave][lane * 2 + 0] += ld * inv_sigma;
       cone_acc[wave][lane * 2 + 1] += lb;
     }
+    wave_lds_order();
   }
   double tq[kProbes];
 #pragma unroll
@@ -2553,7 +2561,7 @@ __device__ __forceinline__ void probe_brackets(ProbeLds& L, int q, int p, CandSt
     L.val[q][p] = L.sums[2 * q][p * 2 + 1] + L.sums[2 * q + 1][p * 2 + 1];
     L.t[q][p] = probe_t(C, p);
   }
-  __builtin_amdgcn_wave_barrier();  // one wave's LDS operations are in order
+  wave_lds_order();
   if (p == 0) probe_update(C, eps, L.dist[q], L.val[q], L.t[q]);
 }
 
@@ -3625,6 +3633,7 @@ __device__ __forceinline__ void band_scale_tile(const BandTiles& bt, const BandT
     for (uint32_t q = f.y; q < f.y + (f.x >> 16); ++q) own[q] = o;
   }
   if (lane == 0) own[bt.slots - 1] = 0.0;  // the padding's sink (its values are 0)
+  wave_lds_order();
   const double* other = D_other + t.col0;
   double big = 0.0;
   constexpr int U = 8;  // the padding makes whole groups of kBandUnroll
