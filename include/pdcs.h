@@ -425,8 +425,10 @@ int  pdcs_batch_solve_device(pdcs_batch b, const pdcs_options* opts, const void*
  * time_budget_ms are skipped (<= 0: 2000 ms); the current schedules are always
  * among those timed. */
 int  pdcs_batch_autotune(pdcs_batch b, double time_budget_ms);
-/* Current schedule: iter_max (row-group iterations per wavefront tile),
- * block_nnz (recorded; a workgroup's row block holds up to 2048 nonzeros), vec_per_block (elements per workgroup). */
+/* Current schedule: iter_max (a row block of several rows reduces each in at most
+ * 4 iter_max passes of its lanes), block_nnz (checked and kept, without effect: a row
+ * block holds up to 2048 nonzeros; autotune leaves it), vec_per_block (elements per
+ * workgroup of the elementwise passes). */
 int  pdcs_batch_schedule(pdcs_batch b, int64_t* iter_max, int64_t* block_nnz,
                          int64_t* vec_per_block);
 int  pdcs_batch_set_schedule(pdcs_batch b, int64_t iter_max, int64_t block_nnz,

@@ -60,8 +60,8 @@ struct HostProblem {
 
 // Tile schedule parameters (chosen by pdcs_batch_autotune or set explicitly).
 struct Schedule {
-  int iter_max = 8;        // passes per lane group in a multi-row wavefront tile
-  int block_nnz = 8192;    // recorded (row blocks hold kRowBlockCap nonzeros)
+  int iter_max = 8;        // a row block of several rows reduces each in at most 4 iter_max passes
+  int block_nnz = 8192;    // the caller's value, without effect (row blocks hold kRowBlockCap nonzeros)
   int vec_per_block = 1024;  // elements per workgroup in elementwise passes
 };
 

@@ -2115,8 +2115,8 @@ void pdcs_batch_destroy(pdcs_batch b) { delete b; }
 
 namespace pdcs {
 
-// Autotuner: time the SpMV-with-dual-step kernel (FP32 and FP64) and the
-// primal pass over a grid of schedules on this batch, keep the fastest.
+// Autotuner: time the SpMV-with-dual-step kernel (FP32 and FP64) on this batch for the
+// current schedule and its alternatives, keep the fastest.
 void Engine::autotune(double budget_ms) {
   if (budget_ms <= 0) budget_ms = 2000.0;
   pdcs_options o;
@@ -2136,11 +2136,9 @@ void Engine::autotune(double budget_ms) {
     I.pending = 0;
   }
   HIP_OK(hipMemcpy(d_inst.p, hi.data(), sizeof(Inst) * B, hipMemcpyHostToDevice));
-  struct Cand {
-    int iter_max, block_nnz;
-  };
-  const Cand cands[] = {{4, 4096}, {8, 4096}, {8, 8192}, {8, 16384}, {16, 8192}, {16, 16384}, {32, 16384},
-                        {32, 32768}};
+  std::vector<int> cands = {sched.iter_max};  // all that the row blocks depend on
+  for (const int c : {4, 8, 16, 32})
+    if (c != sched.iter_max) cands.push_back(c);
   const auto t0 = std::chrono::steady_clock::now();
   auto spent = [&]() { return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count(); };
   // Row blocks: the layout of small batches, and of a band batch's tail once
@@ -2154,9 +2152,8 @@ void Engine::autotune(double budget_ms) {
   }
   Schedule best = sched;
   double best_t = 1e300;
-  for (const Cand& c : cands) {
-    sched.iter_max = c.iter_max;
-    sched.block_nnz = c.block_nnz;
+  for (const int c : cands) {
+    sched.iter_max = c;
     build_schedule();
     const double t = time_dual(kFP32, 5) + time_dual(kFP64, 3);
     if (t < best_t) {
