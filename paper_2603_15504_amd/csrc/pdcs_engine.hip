@@ -833,10 +833,13 @@ void Engine::ensure_iter(int prec) {
 
 // Whether the trials' finalizers are folded into the passes that follow them.
 // Every workgroup of a pass then reads the records of its instance (rec doubles),
-// which pays while that is little: a finalizer launch takes 4 to 5 us and the gap
-// before it, reading 4 KB of records from L2 under a pass's own loads about 1 us.
-// The line: at most kFoldRecords records of a kind per instance (one round of the
-// reduction) and 64 MB of them read by all workgroups of a pass (about 5 us of L2).
+// instead of a launch of its own for one workgroup per instance.
+// The line: at most kFoldRecords records of a kind per instance (what a workgroup reads
+// in one round) and 64 MB of them read by all workgroups of a pass.  It still pays at the
+// line, folded and not, us a trial: row blocks 35.0 and 39.3 at 445 of the 512
+// records (m = 7e4, n = 1.3e5, nnz = 9.1e5), band tiles 89.3 and 96.2 at 508 (m = 2e5, n = 5.2e5,
+// nnz = 4.7e6), with two windows 101.3 and 106.0 (m = 5e5), 48 LPs of 3.7e6 nonzeros on row
+// blocks 70.6 and 75.9; far from it 22.6 and 26.8 (m = 2e4, n = 4e4, nnz = 2.8e5).
 bool Engine::fold_trials(bool band) const {
   const std::vector<int32_t>&p = vcol.h_iblk0, &d = band ? vrow.h_iblk0 : brow.h_iblk0,
                             &l = band ? vcol.h_iblk0 : bcol.h_iblk0;

@@ -1,18 +1,25 @@
 // HIP kernels of the PDCS LP solver for gfx950.
 //
-// One trial of AdaptiveStepPDHG (Function 2) is five launches:
-//   k_primal   : deferred reflected-Halpern commit of x and of G^T y (Algorithm 1:
-//                reflection and averaging), then x_hat = Proj_[l,u](x - tau (c - G^T y))   (eq. PDHG)
-//   k_dual     : CSR SpMV G x_hat with the dual step fused into the row epilogue:
-//                Halpern commit of y and of G x, then
-//                y_hat = Proj_Kd(y + sigma (h - 2 G x_hat + G x))          (eq. PDHG)
-//   k_fin_ls   : step-size test of Function 2 (eta_bar, eta')
-//   k_lam      : transposed SpMV G^T y_hat with the dual-slack epilogue
-//                lam = c - G^T y_hat and its error terms (eq. tolerance-3)
-//   k_fin_beta : reflection parameter (eq. adaptive_reflection)
+// One trial of AdaptiveStepPDHG (Function 2) is three passes and two finalizers:
+//   primal   : deferred reflected-Halpern commit of x and of G^T y (Algorithm 1:
+//              reflection and averaging), then x_hat = Proj_[l,u](x - tau (c - G^T y))   (eq. PDHG)
+//   dual     : SpMV G x_hat and the dual step:
+//              Halpern commit of y and of G x, then
+//              y_hat = Proj_Kd(y + sigma (h - 2 G x_hat + G x))          (eq. PDHG)
+//   fin_ls   : step-size test of Function 2 (eta_bar, eta')
+//   lam      : transposed SpMV G^T y_hat with the dual-slack epilogue
+//              lam = c - G^T y_hat and its error terms (eq. tolerance-3)
+//   fin_beta : reflection parameter (eq. adaptive_reflection)
+// Where an instance has few records, fin_ls runs inside the lam pass and fin_beta inside
+// the next trial's primal pass, by every workgroup (k_lam_fold, k_band_lam_fold,
+// k_lam_epi_fold, k_primal_fold): three launches on row blocks (the dual step ends
+// k_dual's rows), four on band tiles of one window (k_band_spmv and k_dual_epi), five
+// on several.  Else the finalizers are launches of their own (k_fin_ls, k_fin_beta).
+// Instances that fit in LDS run whole chunks of trials in one workgroup (k_trials_lds).
 // G x and G^T y of the Halpern iterate are maintained by the same linear
 // combination as the iterate, so a trial reads the matrix once (G x_hat) and
-// an accepted trial twice (plus G^T y_hat).
+// an accepted trial twice (plus G^T y_hat); k_lam_fold and the product on several
+// windows read it twice for a rejected trial as well.
 //
 // Every K trials a restart check runs (Section 2.3): candidate products with
 // FP64 values, N-norm radii, the bisection of Algorithm 3 as a multisection
@@ -310,16 +317,6 @@ __device__ __forceinline__ bool exp_wave_pick(double bd, double b0, double b1, d
   return true;
 }
 
-// Projection of v onto F K_exp, F = diag(f) > 0, for a point each of whose lanes
-// is its own: v itself if v / f is in K_exp; 0 if -F v is in K_exp* (the
-// polar cone); the clip onto the face {(x, 0, z): x <= 0, z >= 0} if -F times
-// its residual is in K_exp* up to rounding (then the clip is within rounding
-// of the projection: this takes the points whose projection lies on a ray
-// so far out that it meets the face's edge to working precision); otherwise
-// the point of the ray at the root of the slope that carries the projection's
-// certificate (exp_lane), and where a lane finds none, the wave's scan for that
-// lane (exp_scan_wave).
-
 // The projection among the face's clip and the best points of the rays
 // s F a(r), by one wave: the local maxima of the angle along the rays (+ to -
 // sign changes of exp_ray_turn) and, for rays below the scanned range, whose
@@ -427,7 +424,17 @@ __device__ __forceinline__ bool exp_lane(const ExpPoint& P, double (&p)[3]) {
   return cert;
 }
 
-// A projection for each active lane; all lanes of the wave call it together.
+// Projection of v onto F K_exp, F = diag(f) > 0, of each active lane's own point; all
+// lanes of the wave call it together.  v itself if v / f is in K_exp; 0 if -F v is in
+// K_exp* (the polar cone); the clip onto the face {(x, 0, z): x <= 0, z >= 0} if -F times
+// its residual is in K_exp* up to rounding (then the clip is within rounding
+// of the projection: this takes the points whose projection lies on a ray
+// so far out that it meets the face's edge to working precision); otherwise
+// the point of the ray at the root of the slope that carries the projection's
+// certificate (exp_lane), and where a lane finds none, the wave's scan for that
+// lane (exp_scan_wave), one lane after the other: none of 6e6 points of 16 decades
+// and factors of 12, on the cone's boundary, near the apex or in the coordinate planes
+// took it, only points whose squares leave FP64's range.
 __device__ __forceinline__ void exp_proj_lanes(bool active, const double (&v)[3], const double (&f)[3],
                                                double (&p)[3]) {
   bool done = true;
@@ -1526,7 +1533,11 @@ __global__ __launch_bounds__(kBlock) void k_fin_beta(const int32_t* __restrict__
   fin_beta_body(blockIdx.x, iblk_l, rec_l, inst);
 }
 
-// k_lam with the line-search decision folded in.
+// k_lam with the line-search decision folded in.  The decision comes after the gathers, so
+// that neither waits for the other; a rejected trial, which k_lam leaves at once, pays for
+// the product here.  Of the solves measured 1.2% of the trials at most are rejected (m = 1e6
+// power law 15 of 1280, a quarter of it 16 of 3000, 200 x 500 1 of 8832), and a trial saves
+// two launches: 22.6 us for 26.8 at 2.8e5 nonzeros, 35.0 for 39.3 at 9.1e5.
 template <typename T, typename TM, bool IDLE>
 __global__ __launch_bounds__(kBlock) void k_lam_fold(RowBlocks rb, MatPtrs<TM> AT, IterPtrs<T> it, DataPtrs<T> d,
                                                      FoldIn f, int prec, double* __restrict__ rec) {
@@ -4094,7 +4105,8 @@ static void launch_lam_fold_t(const KernelCtx& k, hipStream_t s, int prec, const
       k_band_lam_fold<T, IDLE><<<grid1(k.band2.nslot + k.nb), kWave, (size_t)k.band2.slots * sizeof(T), s>>>(
           k.band2, band_val<T>(k, 1), it, d, f, prec, k.rec_lam_epi);
   } else if (k.use_band) {
-    // (whether the trial is accepted is not known yet: the product runs either way)
+    // (whether the trial is accepted is not known yet: the product runs either way, 30 to
+    // 35 us for a rejected trial of 4.7e6 nonzeros, where every trial saves 4.7 of 106; see k_lam_fold)
     launch_band_spmv<T>(k.band2, band_val<T>(k, 1), it.yh, part, k.N, k.inst, prec, 0, k.idle, s);
     if (k.vcol.nblk > 0)
       k_lam_epi_fold<T, IDLE><<<grid1(k.vcol.nblk), kBlock, 0, s>>>(k.vcol, part, k.band2.P, k.N, it, d, f, prec,

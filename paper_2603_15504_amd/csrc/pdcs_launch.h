@@ -171,8 +171,6 @@ void launch_band_plain(const BandTiles& bt, int prec, const void* val, const voi
 void launch_band_vals(const int32_t* src, int64_t n, const double* v64, double* o64, float* o32, hipStream_t s);
 // out[i] = (float)in[i], i < n
 void launch_to_f32(const double* in, float* out, int64_t n, hipStream_t s);
-// count vectors of dimension dim (contiguous in v, f, out) projected onto
-// diag(f) K, K = K_soc (cone 0), K_exp (1) or K_exp* (2, dim 3).
 // Device-to-device copies of len doubles each, as few launches as they take.
 struct CopyItem {
   const double* src;
@@ -180,6 +178,8 @@ struct CopyItem {
   int64_t len;
 };
 void launch_copies(const CopyItem* items, size_t count, hipStream_t s);
+// count vectors of dimension dim (contiguous in v, f, out) projected onto
+// diag(f) K, K = K_soc (cone 0), K_exp (1) or K_exp* (2, dim 3).
 void launch_proj_cone(int cone, int dim, const double* v, const double* f, double* out, int64_t count,
                       hipStream_t s);
 // Warm starts from device pointers: out[off[b] + e] = src[b][e] (FP64 or FP32
