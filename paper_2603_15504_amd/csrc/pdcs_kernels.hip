@@ -3587,8 +3587,8 @@ __global__ __launch_bounds__(kWave) void k_scale_bands(BandTiles b1, const doubl
 // made d about 1 / (a D_other), the squares without it leave FP64's range for rows of
 // magnitude beyond 1e154 or below 1e-154, whose scaled entries are about 1 all the same
 // (row_scale 1e-157: d^2 infinite, the factor 0).  So whatever is not well inside
-// the range -- empty rows among them -- is taken again from the element's entries, as
-// the row blocks take it; what lies inside lost at most 2^-1043 of a sum of 2^-900.
+// the range is taken again from the element's entries, as the row blocks take it; what
+// lies inside lost at most 2^-1043 of a sum of 2^-900.
 __global__ void k_scale_bands_update(ScaleSide a, ScaleSide c, const double* __restrict__ part1, int P1, int64_t M,
                                      const double* __restrict__ part2, int P2, int64_t N, int mode,
                                      double* __restrict__ D1o, double* __restrict__ D2o) {
@@ -3597,7 +3597,7 @@ __global__ void k_scale_bands_update(ScaleSide a, ScaleSide c, const double* __r
   const int i = (int)(second ? e - M : e);
   const auto inside = [](double v) { return v >= 0x1p-900 && v <= 0x1p900; };
   double d = 1.0, stat = 0.0;
-  bool again = false;
+  int q0 = 0, q1 = 0;  // entries to be taken again
   if (live) {
     const int64_t n = second ? N : M;
     const double* part = second ? part2 : part1;
@@ -3607,17 +3607,20 @@ __global__ void k_scale_bands_update(ScaleSide a, ScaleSide c, const double* __r
     d = (second ? c : a).own[i];
     const double f = mode == kScaleMax ? d : d * d;
     stat = f * s;
-    again = !inside(s) || !inside(f) || !inside(stat);
+    if (!inside(s) || !inside(f) || !inside(stat)) {  // (an empty row has none, and its statistic is 0)
+      q0 = (second ? c : a).ptr[i];
+      q1 = (second ? c : a).ptr[i + 1];
+    }
   }
   const int lane = threadIdx.x & (kWave - 1);
 #pragma unroll 1
-  for (unsigned long long left = __ballot(again); left; left &= left - 1) {  // by the whole wave
+  for (unsigned long long left = __ballot(q1 > q0); left; left &= left - 1) {  // by the whole wave
     const int from = __ffsll(left) - 1;
-    const int j = __shfl(i, from);
+    const int end = __shfl(q1, from);
     const ScaleSide& S = __shfl((int)second, from) ? c : a;
     const double own = __shfl(d, from);
     double s = 0.0;
-    for (int q = S.ptr[j] + lane; q < S.ptr[j + 1]; q += kWave) {
+    for (int q = __shfl(q0, from) + lane; q < end; q += kWave) {
       const double x = S.entry(own, S.val[q], S.other[S.idx[q]]);
       s = mode == kScaleMax ? fmax(s, fabs(x)) : s + x * x;
     }
